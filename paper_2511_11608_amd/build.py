@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -11,7 +13,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -ffp-contract=off: the codec's fp32 steps are single IEEE operations (no fused multiply-add);
 # packed-fp32 instructions are kept out of the generated code.
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
 
 
@@ -20,10 +22,19 @@ def sources():
 
 
 def build(verbose: bool = False) -> str:
-    cmd = [HIPCC, *FLAGS, *sources(), "-o", LIB]
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
+    """One object per translation unit, compiled in parallel (the row kernels are instantiated many times), then one link."""
+    with tempfile.TemporaryDirectory() as tmp:
+        units = [(src, os.path.join(tmp, os.path.basename(src) + ".o")) for src in sources()]
+
+        def run(cmd):
+            if verbose:
+                print(" ".join(cmd))
+            subprocess.run(cmd, check=True)
+
+        with ThreadPoolExecutor(max_workers=int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))) as ex:
+            for job in [ex.submit(run, [HIPCC, *FLAGS, "-c", src, "-o", obj]) for src, obj in units]:
+                job.result()
+        run([HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared", *[obj for _, obj in units], "-o", LIB])
     return LIB
 
 

@@ -9,7 +9,7 @@
 
 #include "slicer_common.hpp"
 #include "slicer_encode_generic.hpp"
-#include "slicer_encode_small.hpp"
+#include "slicer_launch.hpp"
 #include "slicer_encode_wg.hpp"
 #include "slicer_encode_large.hpp"
 #include "slicer_decode.hpp"
@@ -188,84 +188,11 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     return p;
 }
 
-// p.wg_ept: 16-byte chunks per thread (1..16; at most 64 chunk totals for the one-wavefront scan: 4 with 16 wavefronts)
-template <int DT, int NW, int NQ>
-void launch_wg_nw(const SmallArgs& sa, const Plan& p, hipStream_t st)
-{
-    constexpr int EPC = DT == 0 ? 4 : 8;
-    const dim3 g((unsigned)sa.R), b(NW * kWave);
-    const size_t lds = (size_t)p.wg_lds_bytes;
-    if constexpr (NW == 16) {
-        if (p.wg_ept <= 1) hipLaunchKernelGGL((enc_wg_kernel<DT, 16, 1 * EPC, NQ>), g, b, lds, st, sa);
-        else if (p.wg_ept == 2) hipLaunchKernelGGL((enc_wg_kernel<DT, 16, 2 * EPC, NQ>), g, b, lds, st, sa);
-        else hipLaunchKernelGGL((enc_wg_kernel<DT, 16, 4 * EPC, NQ>), g, b, lds, st, sa);
-    } else {
-        if (p.wg_ept <= 4) hipLaunchKernelGGL((enc_wg_kernel<DT, 4, 4 * EPC, NQ>), g, b, lds, st, sa);
-        else if (p.wg_ept == 8) hipLaunchKernelGGL((enc_wg_kernel<DT, 4, 8 * EPC, NQ>), g, b, lds, st, sa);
-        else hipLaunchKernelGGL((enc_wg_kernel<DT, 4, 16 * EPC, NQ>), g, b, lds, st, sa);
-    }
-}
-
 template <int DT>
-int launch_wg(const SmallArgs& sa, const Plan& p, hipStream_t st)
+hipError_t launch_small_any(const SmallArgs& sa, const SmallLaunch& p, bool asym, hipStream_t st)
 {
-    if (p.wg_nw == 16) {
-        if (sa.nq == 7) launch_wg_nw<DT, 16, 7>(sa, p, st); else launch_wg_nw<DT, 16, 0>(sa, p, st);
-    } else {
-        if (sa.nq == 7) launch_wg_nw<DT, 4, 7>(sa, p, st); else launch_wg_nw<DT, 4, 0>(sa, p, st);
-    }
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? SLICER_OK : hip_fail(e);
-}
-
-template <int DT, int EPL, bool ASYM>
-void launch_small_variant(const SmallArgs& sa, dim3 g, dim3 b, size_t lds, int maxs, hipStream_t st)
-{
-    // the paper's bitwidth ladders are short; 7 = {2..8} is the benchmarked one
-    if (sa.nq == 7) {
-        if (maxs == 10) hipLaunchKernelGGL((enc_small_kernel<DT, EPL, 7, 10, ASYM>), g, b, lds, st, sa);
-        else if (maxs == 20) hipLaunchKernelGGL((enc_small_kernel<DT, EPL, 7, 20, ASYM>), g, b, lds, st, sa);
-        else hipLaunchKernelGGL((enc_small_kernel<DT, EPL, 7, 0, ASYM>), g, b, lds, st, sa);
-    } else {
-        if (maxs == 10) hipLaunchKernelGGL((enc_small_kernel<DT, EPL, 0, 10, ASYM>), g, b, lds, st, sa);
-        else if (maxs == 20) hipLaunchKernelGGL((enc_small_kernel<DT, EPL, 0, 20, ASYM>), g, b, lds, st, sa);
-        else hipLaunchKernelGGL((enc_small_kernel<DT, EPL, 0, 0, ASYM>), g, b, lds, st, sa);
-    }
-}
-
-// asym: the asymmetric thresholds of Sec. 3.1 with lambda > 0 (bf16 rows only)
-template <int DT, int EPL>
-void launch_small_epl(const SmallArgs& sa, int lds_bytes, int maxs, hipStream_t st, bool asym)
-{
-    const dim3 g((unsigned)xcd_grid(sa.R)), b(kWave);
-    const size_t lds = (size_t)lds_bytes;
-    if (asym) {
-        launch_small_variant<DT, EPL, true>(sa, g, b, lds, maxs, st);
-        return;
-    }
-    launch_small_variant<DT, EPL, false>(sa, g, b, lds, maxs, st);
-}
-
-template <int DT>
-int launch_small(const SmallArgs& sa, const Plan& p, hipStream_t st, bool asym)
-{
-    constexpr int E0 = DT == 0 ? 4 : 16;      // smallest instantiated elements-per-lane
-    const int lds = p.small_lds_bytes;
-    if constexpr (DT == 0) {
-        if (p.small_epl == 12 || p.small_epl == 20) {
-            if (p.small_epl == 12) launch_small_epl<0, 12>(sa, lds, p.small_maxs, st, asym);
-            else launch_small_epl<0, 20>(sa, lds, p.small_maxs, st, asym);
-            hipError_t e = hipGetLastError();
-            return e == hipSuccess ? SLICER_OK : hip_fail(e);
-        }
-    }
-    if (p.small_epl <= E0) launch_small_epl<DT, E0>(sa, lds, p.small_maxs, st, asym);
-    else if (p.small_epl == E0 * 2) launch_small_epl<DT, E0 * 2>(sa, lds, p.small_maxs, st, asym);
-    else if (p.small_epl == E0 * 4) launch_small_epl<DT, E0 * 4>(sa, lds, p.small_maxs, st, asym);
-    else if (p.small_epl == E0 * 8 || DT != 0) launch_small_epl<DT, E0 * 8>(sa, lds, p.small_maxs, st, asym);
-    else launch_small_epl<DT, DT == 0 ? E0 * 16 : E0 * 8>(sa, lds, p.small_maxs, st, asym);   // fp32 rows of 4096
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? SLICER_OK : hip_fail(e);
+    if (asym) return sa.nq == 7 ? launch_small<DT, true, 7>(sa, p, st) : launch_small<DT, true, 0>(sa, p, st);
+    return sa.nq == 7 ? launch_small<DT, false, 7>(sa, p, st) : launch_small<DT, false, 0>(sa, p, st);
 }
 
 template <int DT>
@@ -437,8 +364,8 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         sa.hint = (u32*)(ws + p.off_hint);
         const bool timed = g_ev_start && g_ev_stop;
         if (timed) SLICER_HIP(hipEventRecord(g_ev_start, st));
-        rc = dt == SLICER_F32 ? launch_wg<0>(sa, p, st) : launch_wg<1>(sa, p, st);
-        if (rc) return rc;
+        const WgLaunch wl = { p.wg_nw, p.wg_ept, p.wg_lds_bytes };
+        SLICER_HIP(dt == SLICER_F32 ? launch_wg<0>(sa, wl, st) : launch_wg<1>(sa, wl, st));
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
         ea.only_flagged = sa.fallback;
     }
@@ -460,8 +387,8 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         sa.hint = (u32*)(ws + p.off_hint);
         const bool timed = g_ev_start && g_ev_stop;
         if (timed) SLICER_HIP(hipEventRecord(g_ev_start, st));
-        rc = dt == SLICER_F32 ? launch_small<0>(sa, p, st, asym) : launch_small<1>(sa, p, st, asym);
-        if (rc) return rc;
+        const SmallLaunch sl = { p.small_epl, p.small_lds_bytes, p.small_maxs };
+        SLICER_HIP(dt == SLICER_F32 ? launch_small_any<0>(sa, sl, asym, st) : launch_small_any<1>(sa, sl, asym, st));
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
         ea.only_flagged = sa.fallback;
     }
