@@ -87,7 +87,9 @@ int count_bits(int64_t k)      // bits that hold any value in 0..k
     return w;
 }
 
-Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_blocks, int n_blocks_neg, uint32_t bit_set)
+// aligned: x starts on a 16-byte boundary (the workspace layout does not depend on it, only the choice of kernel)
+Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_blocks, int n_blocks_neg, uint32_t bit_set,
+               bool aligned = true)
 {
     const int B2_all = n_blocks + n_blocks_neg;          // blocks per row
     Plan p;
@@ -139,21 +141,23 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     p.total = o ? o : 256;
 
     // The one-wave-per-row kernel holds the row in registers (64 * EPL elements) and
-    // its lists in LDS; it needs whole 16-byte chunks, 16-bit indices, one lane per
+    // its lists in LDS; it needs 16-bit indices, one lane per
     // block and a list capacity below 2048 entries (11-bit rank fields).
+    // A row that does not consist of whole aligned chunks may start anywhere in its first one.
     p.small_epl = 0; p.small_cap = 0; p.small_region0 = 0; p.small_lds_bytes = 0; p.small_maxs = 0;
     const int epc = dt == SLICER_F32 ? 4 : 8;
     const int64_t max_n = dt == SLICER_F32 ? 4096 : 8192;
+    const int64_t span = row_len + (row_len % epc == 0 && aligned ? 0 : epc - 1);     // elements of the row's chunks
     int nq = 0;
     for (int q = 1; q <= 16; ++q) nq += (bit_set >> q) & 1u;
-    if (row_len % epc == 0 && row_len <= max_n && B2_all <= kWave) {
+    if (span <= max_n && B2_all <= kWave) {
         const int64_t margin = std::max<int64_t>(64, row_len / (dt == SLICER_F32 ? 16 : 32));  // room for the undecided coarse bin
         int64_t cap = std::min<int64_t>(1984, (p.k + margin + 63) / 64 * 64);   // ranks are 11-bit fields
         int epl = epc;
-        while ((int64_t)epl * kWave < row_len) epl *= 2;
+        while ((int64_t)epl * kWave < span) epl *= 2;
         // fp32 rows of the common transformer widths 768 and 1280: three and five chunks per lane instead of four and eight
-        if (dt == SLICER_F32 && row_len > 512 && row_len <= 768) epl = 12;
-        if (dt == SLICER_F32 && row_len > 1024 && row_len <= 1280) epl = 20;
+        if (dt == SLICER_F32 && span > 512 && span <= 768) epl = 12;
+        if (dt == SLICER_F32 && span > 1024 && span <= 1280) epl = 20;
         const int maxs = cap <= 640 ? 10 : cap <= 1280 ? 20 : 0;             // list held in registers
         const int64_t region0 = small_region0_words(p.k, p.cap_words, B2_all, nq);
         const int64_t lds = 4 * (int64_t)small_lds_words(dt, (int)cap, (int)region0, B2_all, maxs);
@@ -169,7 +173,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     p.wg_ept = 0; p.wg_nw = 0; p.wg_cap = 0; p.wg_region0 = 0; p.wg_lds_bytes = 0;
     {
         const int64_t wg_max = dt == SLICER_F32 ? 16384 : 32768;
-        if (row_len % epc == 0 && row_len > 4096 && row_len <= wg_max && B2_all <= kWave) {
+        if (span > 4096 && span <= wg_max && B2_all <= kWave) {
             const int64_t margin = std::max<int64_t>(64, row_len / (dt == SLICER_F32 ? 16 : 32));
             const int64_t cap = std::min<int64_t>(1984, (p.k + margin + 63) / 64 * 64);
             const int64_t region0 = small_region0_words(p.k, p.cap_words, B2_all, nq);
@@ -179,7 +183,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
                 // latencies: 4 % less latency per call), four otherwise (a 256-row batch on sixteen leaves no room
                 // for a neighbouring stream's kernels: 20 % less throughput when steps overlap)
                 p.wg_nw = rows <= 128 ? 16 : 4;
-                const int64_t chunks = (row_len / epc + 64 * p.wg_nw - 1) / (64 * p.wg_nw);     // 16-byte chunks per thread
+                const int64_t chunks = ((span + epc - 1) / epc + 64 * p.wg_nw - 1) / (64 * p.wg_nw);     // 16-byte chunks per thread
                 p.wg_ept = (int)(chunks <= 1 ? 1 : chunks <= 2 ? 2 : chunks <= 4 ? 4 : chunks <= 8 ? 8 : 16);    // (kept as a chunk count)
                 p.wg_cap = (int)cap; p.wg_region0 = (int)region0; p.wg_lds_bytes = (int)lds;
             }
@@ -249,11 +253,13 @@ int launch_decode(const void* stream, const void* meta, void* y, int dt, int64_t
     if (grid >= (1ull << 31)) return SLICER_EINVAL;
     const bool timed = g_ev_start && g_ev_stop;
     if (timed) SLICER_HIP(hipEventRecord(g_ev_start, st));
-    // short rows: one wavefront per row, the row assembled in LDS (16 KB per wave at most)
-    const int64_t row_bytes = row_len * (dt == SLICER_F32 ? 4 : 2);
-    if (row_bytes % 16 == 0 && row_bytes <= 16 * 1024 && n_blocks + n_blocks_neg <= kWave && ((uintptr_t)y & 15) == 0) {
+    // short rows: one wavefront per row, the row assembled in LDS (16 KB per wave, and up to two more chunks for a
+    // row that starts or ends inside a 16-byte chunk)
+    const int64_t esz = dt == SLICER_F32 ? 4 : 2, row_bytes = row_len * esz;
+    const int64_t image16 = (row_bytes % 16 == 0 && ((uintptr_t)y & 15) == 0) ? row_bytes / 16 : (row_bytes + 2 * (16 - esz)) / 16;
+    if (row_bytes <= 16 * 1024 && n_blocks + n_blocks_neg <= kWave && (uintptr_t)y % (uintptr_t)esz == 0) {
         // one wave per workgroup: the LDS of a row (image + stream segment) is the unit of occupancy
-        const size_t lds = (size_t)row_bytes + 16 * (size_t)((da.stage_words + 4) / 4);
+        const size_t lds = 16 * (size_t)image16 + 16 * (size_t)((da.stage_words + 4) / 4);
         if (dt == SLICER_F32)
             hipLaunchKernelGGL((dec_small_kernel<0>), dim3((unsigned)xcd_grid(rows)), dim3(kWave), lds, st, da);
         else
@@ -316,7 +322,8 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     if (rows >= ((int64_t)1 << 31)) return SLICER_EINVAL;
     if (n_blocks_neg < 1 || n_blocks_neg > SLICER_MAX_BLOCKS) return SLICER_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
-    Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks_neg, bit_set);
+    const bool aligned = ((uintptr_t)x & 15) == 0, on_elements = ((uintptr_t)x & (dt == SLICER_F32 ? 3 : 1)) == 0;
+    Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks_neg, bit_set, aligned);
     char* ws = (char*)workspace;
 
     EncArgs ea;
@@ -345,7 +352,7 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
 
     // asymmetric thresholds need a second selection over a subset of the row: the generic kernel has it for
     // every shape, the row-resident kernel for bf16 rows (rows it flags are redone generically, same rule)
-    const bool use_wg = p.wg_ept && !asym && ((uintptr_t)x & 15) == 0;
+    const bool use_wg = p.wg_ept && !asym && on_elements;
     if (use_wg) {
         // one workgroup per row; rows it cannot hold are flagged and redone by the generic kernel
         SmallArgs sa;
@@ -369,7 +376,7 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
         ea.only_flagged = sa.fallback;
     }
-    if (!use_wg && p.small_epl && ((uintptr_t)x & 15) == 0) {
+    if (!use_wg && p.small_epl && on_elements) {
         // fast path; rows it cannot hold are flagged and redone by the generic kernel
         SmallArgs sa;
         sa.x = x; sa.R = rows; sa.N = row_len; sa.k = p.k;
@@ -392,7 +399,7 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
         ea.only_flagged = sa.fallback;
     }
-    if (!asym && !ea.only_flagged && p.large_C && ((uintptr_t)x & 15) == 0) {
+    if (!asym && !ea.only_flagged && p.large_C && aligned) {
         // long rows: multi-workgroup stages; rows they cannot hold are flagged for the generic kernel
         LargeArgs la;
         la.x = x; la.R = rows; la.N = row_len; la.k = p.k;

@@ -378,18 +378,17 @@ template <int DT>
 __global__ __launch_bounds__(kWave) void dec_small_kernel(DecArgs a)
 {
     typedef typename Elem<DT>::raw_t raw_t;
-    constexpr int ESZ = DT == 0 ? 4 : 2;
     extern __shared__ uint4 dec_smem[];
     const u32 lane = lane_id();
-    const int wid = threadIdx.x / kWave;
     const int64_t r = xcd_row((int64_t)blockIdx.x, a.R);       // one wave per workgroup
     if (r >= a.R) return;
     const int N = (int)a.N, M = a.M, B2 = a.M + a.Mn, w = a.w;
-    const int row_bytes = N * ESZ;                       // multiple of 16
-    const int per_wave16 = row_bytes / 16 + (a.stage_words + 4) / 4;
-    uint4* tile4 = dec_smem + (size_t)wid * per_wave16;
-    raw_t* tile = (raw_t*)tile4;
-    u32* sw = (u32*)(tile4 + row_bytes / 16);            // [stage_words + 1..4]
+    // the image holds the aligned 16-byte chunks of y that the row touches: element i of the row is element head + i
+    const RowChunks<DT> row(a.y, r, a.N);
+    const int image16 = (row.Nh + RowChunks<DT>::EPC - 1) / RowChunks<DT>::EPC;
+    uint4* tile4 = dec_smem;
+    raw_t* tile = (raw_t*)tile4 + row.head;
+    u32* sw = (u32*)(tile4 + image16);                   // [stage_words + 1..4]
 
     const u64 off0 = a.mv.row_off[r];
     const u64 off1 = r + 1 < a.R ? a.mv.row_off[r + 1] : *a.total_words;
@@ -400,7 +399,7 @@ __global__ __launch_bounds__(kWave) void dec_small_kernel(DecArgs a)
     if (staged) {
         for (u32 i = lane; i <= nw; i += kWave) sw[i] = i < nw ? rw[i] : 0u;
     }
-    for (int i = lane; i < row_bytes / 16; i += kWave) tile4[i] = make_uint4(0, 0, 0, 0);
+    for (int i = lane; i < image16; i += kWave) tile4[i] = make_uint4(0, 0, 0, 0);
 
     const u32 lpb = (u32)kWave / (u32)B2;
     const u32 myb = lane / lpb, sub = lane - myb * lpb;
@@ -444,14 +443,22 @@ __global__ __launch_bounds__(kWave) void dec_small_kernel(DecArgs a)
     }
     wave_sync();
 
-    uint4* __restrict__ out = (uint4*)((char*)a.y + (size_t)r * (size_t)row_bytes);
     // the output is written once and not read back by this library: streaming (non-temporal) stores
     typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-    for (int i = lane; i < row_bytes / 16; i += kWave) {
+    u32x4* __restrict__ out = (u32x4*)const_cast<uint4*>(row.base);
+    auto put = [&](int i) {
         const uint4 t = tile4[i];
         u32x4 v4;
         v4.x = t.x; v4.y = t.y; v4.z = t.z; v4.w = t.w;
-        __builtin_nontemporal_store(v4, (u32x4*)(out + i));       // one 16-byte store
+        __builtin_nontemporal_store(v4, out + i);       // one 16-byte store
+    };
+    if (!row.ragged()) {
+        for (int i = lane; i < image16; i += kWave) put(i);
+    } else {
+        for (int i = lane; i < image16; i += kWave) {
+            if (row.whole(i)) put(i);
+            else row.store_partial(i, tile4[i]);
+        }
     }
 }
 

@@ -6,7 +6,7 @@
 // the tie rule of the top-K filter and of the block ranks), and the sign class as the top
 // bit, positive class on top.  Comps are distinct, so a comp is a complete rank threshold.
 //
-//   1. load the row (16-byte coalesced loads); its largest magnitude key; a 2048-bin
+//   1. load the row (16-byte coalesced loads, whatever its length and alignment); its largest magnitude key; a 2048-bin
 //      histogram in LDS over a window that hangs from that key (bf16: one key per bin);
 //      two-level scan from the top -> the bin B1 that holds rank k-1;
 //   2. ordered compaction of everything at or above B1 into a short list L
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     const u32 lane = lane_id();
     const int64_t r = xcd_row((int64_t)blockIdx.x, a.R);        // neighbouring rows stay on one XCD
     if (r >= a.R) return;
-    const int N = (int)a.N, M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq, cap = a.cap;
+    const int M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq, cap = a.cap;
     const int k = (int)a.k;
     const u32 idxmask = (1u << w) - 1u;
     SmallLds L = small_carve(smem, DT, cap, a.region0_words, B2, MAXS);
@@ -208,13 +208,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     };
 
     // ---- 1. load the row, coarse histogram ------------------------------------------
-    const uint4* __restrict__ xr = (const uint4*)((const char*)a.x + (size_t)r * (size_t)N * (DT == 0 ? 4 : 2));
+    const RowChunks<DT> row(a.x, r, a.N);           // element i of the row is element head + i of its chunks
+    const int head = row.head, Nh = row.Nh;
     uint4 v[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int base = (c * kWave + (int)lane) * EPC;
-        v[c] = base < N ? xr[c * kWave + lane] : make_uint4(0, 0, 0, 0);
-    }
+    row.template load<NCH, kWave>(v, (int)lane);
     auto word_of = [&](int c, int d) -> u32 { return d == 0 ? v[c].x : d == 1 ? v[c].y : d == 2 ? v[c].z : v[c].w; };
     constexpr bool kHint = !ASYM && MAXS > 0;       // (the list must be in registers: its largest key is taken from there)
     const u32 hslot = (u32)blockIdx.x & (u32)(kHintSlots - 1);
@@ -272,7 +269,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         const u32 wt2 = wtop * 0x10001u;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            if ((c * kWave + (int)lane) * EPC < N) {
+            if ((c * kWave + (int)lane) * EPC < Nh) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     const u32 wd = word_of(c, d);
@@ -452,7 +449,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         u32 accS = 0, accF = 0;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            if ((c * kWave + (int)lane) * EPC < N) {
+            if ((c * kWave + (int)lane) * EPC < Nh) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     const u32 wd = word_of(c, d);
@@ -493,7 +490,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         u32 accS = 0, accF = 0;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            if ((c * kWave + (int)lane) * EPC < N) {
+            if ((c * kWave + (int)lane) * EPC < Nh) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     const u32 wd = word_of(c, d);
@@ -584,12 +581,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         }
         // (the empty asm statements pin values in registers: the optimiser would otherwise
         //  re-derive each flag and each inverted index with longer instruction sequences)
-        u32 linv = 0xFFFFu - lane * (u32)EPC;
+        u32 linv = 0xFFFFu - lane * (u32)EPC + (u32)head;
         asm volatile("" : "+v"(linv));
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             u32 wa = lent_off + basec[c] * 4u;
-            const u32 idx0 = (u32)((c * kWave + (int)lane) * EPC);
+            const u32 idx0 = (u32)((c * kWave + (int)lane) * EPC - head);
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 const u32 wd = word_of(c, d);

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     const u32 tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
     const int64_t r = (int64_t)blockIdx.x;
     if (r >= a.R) return;
-    const int N = (int)a.N, M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq, cap = a.cap;
+    const int M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq, cap = a.cap;
     const int k = (int)a.k;
     SmallLds L = small_carve(smem, DT, cap, a.region0_words, B2, 0);
     u32* misc = smem + wg_main_words(DT, cap, a.region0_words, B2);      // broadcast words and scan scratch
@@ -84,13 +84,10 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     const u32 lent_off = (u32)(L.Lent - smem) * 4u;
 
     // ---- 1. load the row ---------------------------------------------------------------------
-    const uint4* __restrict__ xr = (const uint4*)((const char*)a.x + (size_t)r * (size_t)N * (DT == 0 ? 4 : 2));
+    const RowChunks<DT> row(a.x, r, a.N);           // element i of the row is element head + i of its chunks
+    const int head = row.head, Nh = row.Nh;
     uint4 v[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int base = (c * kWgThreads + (int)tid) * EPC;
-        v[c] = base < N ? xr[c * kWgThreads + tid] : make_uint4(0, 0, 0, 0);
-    }
+    row.template load<NCH, kWgThreads>(v, (int)tid);
     auto word_of = [&](int c, int d) -> u32 { return d == 0 ? v[c].x : d == 1 ? v[c].y : d == 2 ? v[c].z : v[c].w; };
 
     // List length and positions for a lower key bound t_lo: counts per chunk, positions inside the
@@ -194,7 +191,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         const u32 wt2 = wtop * 0x10001u;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            if ((c * kWgThreads + (int)tid) * EPC < N) {
+            if ((c * kWgThreads + (int)tid) * EPC < Nh) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     if (DT == 0) {
@@ -266,12 +263,12 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
             return;
         }
         const u32 lidx_off = (u32)((u32*)L.Lidx - smem) * 4u;
-        u32 linv = 0xFFFFu - tid * (u32)EPC;
+        u32 linv = 0xFFFFu - tid * (u32)EPC + (u32)head;
         asm volatile("" : "+v"(linv));
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             u32 wa = lent_off + basec[c] * 4u;
-            const u32 idx0 = (u32)((c * kWgThreads + (int)tid) * EPC);
+            const u32 idx0 = (u32)((c * kWgThreads + (int)tid) * EPC - head);
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 const u32 wd = word_of(c, d);
