@@ -63,7 +63,7 @@ int index_bits(int64_t N)
 }
 
 struct Plan {
-    int64_t k;
+    int64_t k, kept_stride;
     int w, qmax;
     u64 cap_words;          // per row
     size_t off_row_words, off_slots, off_kept, off_bo_idx, off_bo_val, off_fallback, off_row_local, off_chunk_tot, off_hint, total;
@@ -71,11 +71,11 @@ struct Plan {
     int small_epl, small_cap, small_region0, small_lds_bytes, small_maxs;
     // workgroup-per-row path for bf16 rows of up to 32768 elements (0 = not eligible)
     int wg_ept, wg_nw, wg_cap, wg_region0, wg_lds_bytes;
-    // long-row path (large_C == 0: not eligible)
-    int large_C, large_LC;
+    // long-row path (large_S == 0: not eligible)
+    int large_S;
     u32 large_capL;
-    size_t lo_ch_cum, lo_ch_off, lo_L, lo_Lblk, lo_Lfine, lo_rowst, lo_thr, lo_blk_start,
-           lo_blkcnt, lo_vminb, lo_vmaxb, lo_sums, lo_qsel, lo_inv_sel, lo_code_off, lo_win_range;
+    size_t lo_tab, lo_cum, lo_seg, lo_Lidx, lo_Lpos, lo_rowst, lo_thr, lo_map, lo_vminb, lo_vmaxb, lo_blk_start, lo_pair, lo_psum,
+           lo_qsel, lo_inv_sel, lo_code_off;
 };
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -85,6 +85,12 @@ int count_bits(int64_t k)      // bits that hold any value in 0..k
     int w = 1;
     while (((int64_t)1 << w) <= k) ++w;
     return w;
+}
+
+// Elements per tile of the long-row stages: short tiles while they do not fill the chip (one tile per CU)
+int large_tile(int64_t rows, int64_t row_len)
+{
+    return rows * ((row_len + 8191) / 8192) <= 256 ? 8192 : 16384;
 }
 
 // aligned: x starts on a 16-byte boundary (the workspace layout does not depend on it, only the choice of kernel)
@@ -102,42 +108,48 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     size_t o = 0;
     p.off_row_words = o; o = align256(o + 8 * (size_t)rows);
     p.off_slots = o;     o = align256(o + 4 * (size_t)rows * (size_t)p.cap_words);
-    p.off_kept = o;      o = align256(o + 8 * (size_t)rows * (size_t)p.k);
+    p.kept_stride = p.k;
     p.off_bo_idx = o;    o = align256(o + 4 * (size_t)rows * (size_t)p.k);
     p.off_bo_val = o;    o = align256(o + 4 * (size_t)rows * (size_t)p.k);
     p.off_fallback = o;  o = align256(o + 4 * (size_t)rows);
     p.off_row_local = o; o = align256(o + 8 * (size_t)rows);
     p.off_chunk_tot = o; o = align256(o + 8 * (size_t)((rows + kScanRows - 1) / kScanRows));
     p.off_hint = o;      o = align256(o + 4 * (size_t)kHintSlots);
-    // Long rows: every pass is spread over many workgroups (slicer_encode_large.hpp).
-    p.large_C = 0; p.large_LC = 0; p.large_capL = 0;
+    // Long rows: every pass is spread over many workgroups (slicer_encode_large.hpp).  A row that starts or ends
+    // inside a 16-byte chunk takes them from 8192 elements on: below, one workgroup of the generic kernel is as fast.
+    p.large_S = 0; p.large_capL = 0;
+    const int epc = dt == SLICER_F32 ? 4 : 8;
+    const bool whole = row_len % epc == 0 && aligned;
+    const int64_t span = row_len + (whole ? 0 : epc - 1);     // elements of the row's 16-byte chunks
     {
-        const int epc_l = dt == SLICER_F32 ? 4 : 8;
-        const int64_t C = (row_len + kLCH - 1) / kLCH;
-        const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;   // whole 16-byte groups of 2-byte entries
+        const int64_t tile = large_tile(rows, row_len);
+        const int64_t S = (row_len + epc - 1 + tile - 1) / tile;
+        const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;
         int nq_l = 0;
         for (int q = 1; q <= 16; ++q) nq_l += (bit_set >> q) & 1u;
-        if (row_len > 4096 && row_len % epc_l == 0 && C <= 1024 && rows <= 65535 && capL < ((int64_t)1 << 27)) {
-            const size_t R = (size_t)rows, B2 = (size_t)B2_all;
-            p.large_C = (int)C; p.large_capL = (u32)capL; p.large_LC = (int)((capL + kLCE - 1) / kLCE);
-            p.lo_ch_cum = o;    o = align256(o + 4 * R * (size_t)C * kLBins);
-            p.lo_ch_off = o;    o = align256(o + 4 * R * (size_t)C);
-            p.lo_L = o;         o = align256(o + 8 * R * (size_t)capL);
-            p.lo_Lblk = o;      o = align256(o + R * (size_t)capL);
-            p.lo_Lfine = o;     o = align256(o + 2 * R * (size_t)capL);
+        if (row_len > 4096 && S <= 512 && rows <= 65535) {
+            const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
+            if (whole || row_len > 8192) p.large_S = (int)S;
+            p.large_capL = (u32)capL;
+            p.kept_stride = capL;
+            p.lo_tab = o;       o = align256(o + 2 * R * kTabSize);
+            p.lo_cum = o;       o = align256(o + 4 * R * Sz * kFB);
+            p.lo_seg = o;       o = align256(o + 8 * R * Sz);
             p.lo_rowst = o;     o = align256(o + 4 * R * 16);
-            p.lo_thr = o;       o = align256(o + 8 * R * (1 + kMaxB2));
-            p.lo_blk_start = o; o = align256(o + 4 * R * (B2 + 1));
-            p.lo_blkcnt = o;    o = align256(o + 4 * R * (size_t)p.large_LC * B2);
+            p.lo_thr = o;       o = align256(o + 8 * R * B2);
+            p.lo_map = o;       o = align256(o + 2 * R * kFB);
             p.lo_vminb = o;     o = align256(o + 4 * R * B2);
             p.lo_vmaxb = o;     o = align256(o + 4 * R * B2);
-            p.lo_sums = o;      o = align256(o + 8 * R * B2 * (size_t)(nq_l + 1));
+            p.lo_blk_start = o; o = align256(o + 4 * R * (B2 + 1));
+            p.lo_pair = o;      o = align256(o + 4 * R * B2 * Sz);
+            p.lo_psum = o;      o = align256(o + 8 * R * Sz * B2 * (size_t)(nq_l + 1));
             p.lo_qsel = o;      o = align256(o + 4 * R * B2);
             p.lo_inv_sel = o;   o = align256(o + 4 * R * B2);
             p.lo_code_off = o;  o = align256(o + 8 * R * (B2 + 1));
-            p.lo_win_range = o; o = align256(o + 8 * R * (size_t)(p.cap_words / 64 + 8));    // pack windows of >= 64 words
         }
     }
+    // the generic kernel's list of a row (8 bytes an entry) and the long-row list (a word and two halves) share their place
+    p.off_kept = o;      o = align256(o + 8 * (size_t)rows * (size_t)p.kept_stride);
     p.total = o ? o : 256;
 
     // The one-wave-per-row kernel holds the row in registers (64 * EPL elements) and
@@ -145,9 +157,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     // block and a list capacity below 2048 entries (11-bit rank fields).
     // A row that does not consist of whole aligned chunks may start anywhere in its first one.
     p.small_epl = 0; p.small_cap = 0; p.small_region0 = 0; p.small_lds_bytes = 0; p.small_maxs = 0;
-    const int epc = dt == SLICER_F32 ? 4 : 8;
     const int64_t max_n = dt == SLICER_F32 ? 4096 : 8192;
-    const int64_t span = row_len + (row_len % epc == 0 && aligned ? 0 : epc - 1);     // elements of the row's chunks
     int nq = 0;
     for (int q = 1; q <= 16; ++q) nq += (bit_set >> q) & 1u;
     if (span <= max_n && B2_all <= kWave) {
@@ -199,22 +209,26 @@ hipError_t launch_small_any(const SmallArgs& sa, const SmallLaunch& p, bool asym
     return sa.nq == 7 ? launch_small<DT, false, 7>(sa, p, st) : launch_small<DT, false, 0>(sa, p, st);
 }
 
-template <int DT>
-int launch_large(const LargeArgs& la, const Plan& p, hipStream_t st)
+template <int DT, int NE>
+void launch_split(const LargeArgs& la, hipStream_t st)
 {
-    const dim3 gC((unsigned)la.C, (unsigned)la.R), gL((unsigned)la.LC, (unsigned)la.R), gR((unsigned)la.R);
-    const dim3 gP((unsigned)std::max<int64_t>(1, (la.k + kPCH - 1) / kPCH), (unsigned)la.R);
-    const dim3 gW((unsigned)la.nwin, (unsigned)la.R);
-    hipLaunchKernelGGL((lr_hist_kernel<DT>), gC, dim3(256), 0, st, la);
-    hipLaunchKernelGGL((lr_select_kernel<DT>), gR, dim3(1024), 0, st, la);
-    hipLaunchKernelGGL((lr_compact_kernel<DT>), gC, dim3(256), 0, st, la);
-    hipLaunchKernelGGL(lr_bounds_kernel, gR, dim3(1024), 0, st, la);
-    hipLaunchKernelGGL(lr_blockcount_kernel, gL, dim3(256), 0, st, la);
-    hipLaunchKernelGGL((lr_scatter_kernel<DT>), gL, dim3(256), 0, st, la);
-    if (la.nq == 7) hipLaunchKernelGGL((lr_abq_kernel<DT, 7>), gP, dim3(256), 0, st, la);   // {2..8}: the benchmarked set
-    else hipLaunchKernelGGL((lr_abq_kernel<DT, 0>), gP, dim3(256), 0, st, la);
-    hipLaunchKernelGGL((lr_choose_kernel<DT>), gR, dim3(128), 0, st, la);
-    hipLaunchKernelGGL((lr_pack_kernel<DT>), gW, dim3(256), 0, st, la);
+    const dim3 g((unsigned)la.S, (unsigned)la.R), b(kTileThreads);
+    const size_t lds = (size_t)lr_split_carve(NE, la.M + la.Mn, la.nq).total;
+    if (la.nq == 7) hipLaunchKernelGGL((lr_split_kernel<DT, NE, 7>), g, b, lds, st, la);   // {2..8}: the benchmarked set
+    else hipLaunchKernelGGL((lr_split_kernel<DT, NE, 0>), g, b, lds, st, la);
+}
+
+template <int DT>
+int launch_large(const LargeArgs& la, const EncArgs& ea, const FinishArgs& fa, hipStream_t st)
+{
+    const dim3 gT((unsigned)la.S, (unsigned)la.R), gR((unsigned)la.R), gW((unsigned)la.nwin, (unsigned)la.R);
+    hipLaunchKernelGGL((lr_sample_kernel<DT>), gR, dim3(1024), 0, st, la);
+    if (la.tile == 8192) hipLaunchKernelGGL((lr_compact_kernel<DT, 2>), gT, dim3(kTileThreads), 0, st, la);
+    else hipLaunchKernelGGL((lr_compact_kernel<DT, 4>), gT, dim3(kTileThreads), 0, st, la);
+    hipLaunchKernelGGL((lr_bounds_kernel<DT>), gR, dim3(1024), 0, st, la, ea);
+    launch_split<DT, 4>(la, st);
+    if (la.n_cols > 0) hipLaunchKernelGGL((lr_pack_kernel<DT, true>), gW, dim3(256), 0, st, la, fa);
+    else hipLaunchKernelGGL((lr_pack_kernel<DT, false>), gW, dim3(256), 0, st, la, fa);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SLICER_OK : hip_fail(e);
 }
@@ -306,12 +320,19 @@ int slicer_encode_path(slicer_dtype dt, int64_t rows, int64_t row_len, double ke
     int rc = check_args((int)dt, rows, row_len, keep_ratio, n_blocks, bit_set);
     if (rc) return rc;
     Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set);
-    return p.wg_ept ? 3 : p.small_epl ? 1 : (p.large_C ? 2 : 0);
+    return p.wg_ept ? 3 : p.small_epl ? 1 : (p.large_S ? 2 : 0);
 }
+
+// two-dimensional instances whose stream the long-row stages write in CSR form themselves
+struct CsrShape {
+    int64_t n_rows, n_cols;
+    int wp, wc;
+    u64 cap_words;
+};
 
 static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row_len, double keep_ratio,
                        int n_blocks, int n_blocks_neg, uint32_t bit_set, double distortion_budget, const Ladder& lad, int guard,
-                       void* stream, void* meta, void* workspace, void* hip_stream, double lambda = 0.0)
+                       void* stream, void* meta, void* workspace, void* hip_stream, double lambda = 0.0, const CsrShape* csr = nullptr)
 {
     if (!(lambda >= 0.0 && lambda < 1.0)) return SLICER_EINVAL;
     const bool asym = (float)lambda > 0.0f;      // lambda = 0 is the plain top-K filter: every fast path applies
@@ -336,6 +357,7 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     for (int t = ea.nq; t < kMaxQ; ++t) ea.qlist[t] = 0;
     ea.beta = distortion_budget;
     ea.cap_words = p.cap_words;
+    ea.kept_stride = p.kept_stride;
     ea.row_words = (u64*)(ws + p.off_row_words);
     ea.slots = (u32*)(ws + p.off_slots);
     ea.kept = (u64*)(ws + p.off_kept);
@@ -399,53 +421,6 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
         ea.only_flagged = sa.fallback;
     }
-    if (!asym && !ea.only_flagged && p.large_C && aligned) {
-        // long rows: multi-workgroup stages; rows they cannot hold are flagged for the generic kernel
-        LargeArgs la;
-        la.x = x; la.R = rows; la.N = row_len; la.k = p.k;
-        la.M = n_blocks; la.Mn = n_blocks_neg; la.w = p.w; la.nq = ea.nq;
-        for (int t = 0; t < kMaxQ; ++t) la.qlist[t] = ea.qlist[t];
-        la.beta = distortion_budget; la.cap_words = p.cap_words;
-        la.C = p.large_C; la.LC = p.large_LC; la.capL = p.large_capL;
-        // pack windows: index fields are w bits, code fields as short as one bit, so the windows
-        // from the first code bit on are a quarter of the others; all are smaller while the launch is small
-        la.pack_words = kPackWords;
-        while (la.pack_words > 128 && (u64)rows * ((p.cap_words + (u64)la.pack_words - 1) / (u64)la.pack_words) < 1024) la.pack_words /= 2;
-        la.pack_words_code = std::max(64, la.pack_words / 4);
-        {
-            const u64 idx_words_max = ((u64)p.k * (u64)p.w) / 32;                              // largest first word with code bits
-            la.nwin_idx = (int)((idx_words_max + (u64)la.pack_words - 1) / (u64)la.pack_words);
-            const u64 code_words_max = ((u64)p.k * (u64)p.qmax + 31) / 32 + 2;                  // words from there to the end
-            la.nwin = la.nwin_idx + (int)((code_words_max + (u64)la.pack_words_code - 1) / (u64)la.pack_words_code);
-        }
-        la.win_range = (u32*)(ws + p.lo_win_range);
-        la.ch_cum = (u32*)(ws + p.lo_ch_cum);     la.ch_off = (u32*)(ws + p.lo_ch_off);
-        la.L = (u64*)(ws + p.lo_L);               la.Lblk = (uint8_t*)(ws + p.lo_Lblk);
-        la.Lfine = (uint16_t*)(ws + p.lo_Lfine);
-        la.rowst = (u32*)(ws + p.lo_rowst);       la.thr = (u64*)(ws + p.lo_thr);
-        la.blk_start = (u32*)(ws + p.lo_blk_start); la.blkcnt = (u32*)(ws + p.lo_blkcnt);
-        la.vminb = (u32*)(ws + p.lo_vminb);       la.vmaxb = (u32*)(ws + p.lo_vmaxb);
-        la.sums = (u64*)(ws + p.lo_sums);         la.qsel = (u32*)(ws + p.lo_qsel);
-        la.inv_sel = (float*)(ws + p.lo_inv_sel); la.code_off = (u64*)(ws + p.lo_code_off);
-        la.bo_idx = ea.bo_idx; la.bo_val = ea.bo_val;
-        la.row_words = ea.row_words; la.slots = ea.slots;
-        la.fallback = (u32*)(ws + p.off_fallback);
-        la.mv = ea.mv;
-        la.lad = lad;
-        la.guard = guard;
-        const bool timed = g_ev_start && g_ev_stop;
-        if (timed) SLICER_HIP(hipEventRecord(g_ev_start, st));
-        rc = dt == SLICER_F32 ? launch_large<0>(la, p, st) : launch_large<1>(la, p, st);
-        if (rc) return rc;
-        if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
-        ea.only_flagged = la.fallback;
-        ea.rows_per_wg = 1;
-    }
-    if (!ea.only_flagged) {
-        rc = dt == SLICER_F32 ? launch_encode<0>(ea, st) : launch_encode<1>(ea, st);
-        if (rc) return rc;
-    }
-
     FinishArgs fa;
     fa.R = rows; fa.N = row_len; fa.k = p.k;
     fa.M = n_blocks; fa.Mn = n_blocks_neg; fa.w = p.w; fa.dt = (int)dt;
@@ -459,6 +434,65 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     fa.stream = (u32*)stream;
     fa.meta = meta;
     fa.mv = ea.mv;
+    bool done = false;                              // every row is in its slot
+    if (!asym && !ea.only_flagged && p.large_S && on_elements) {
+        // long rows: stages of many workgroups per row; rows they cannot hold are redone by the generic encoder inside the third one
+        LargeArgs la;
+        la.x = x; la.R = rows; la.N = row_len; la.k = p.k;
+        la.M = n_blocks; la.Mn = n_blocks_neg; la.w = p.w; la.nq = ea.nq;
+        for (int t = 0; t < kMaxQ; ++t) la.qlist[t] = ea.qlist[t];
+        la.beta = distortion_budget; la.cap_words = csr ? csr->cap_words : p.cap_words;
+        const int epc = dt == SLICER_F32 ? 4 : 8;
+        la.tile = large_tile(rows, row_len);
+        la.S = (int)((row_len + (row_len % epc == 0 && aligned ? 0 : epc - 1) + la.tile - 1) / la.tile);
+        la.capL = p.large_capL;
+        la.n_rows = csr ? csr->n_rows : 0; la.n_cols = csr ? csr->n_cols : 0;
+        la.wp = csr ? csr->wp : 0; la.wc = csr ? csr->wc : 0;
+        // pack windows: index fields are w bits, code fields as short as one bit, so the windows
+        // from the first code bit on are a quarter of the others; all are smaller while the launch is small
+        la.pack_words = kPackWords;
+        while (la.pack_words > 128 && (u64)rows * ((la.cap_words + (u64)la.pack_words - 1) / (u64)la.pack_words) < 1024) la.pack_words /= 2;
+        if (csr) while (la.pack_words * 32 / csr->wp + 2 > kPackPtrs) la.pack_words /= 2;
+        la.pack_words_code = std::max(64, la.pack_words / 4);
+        {
+            // largest first word with code bits; words from there to the end
+            const u64 ptr_bits = csr ? (u64)(n_blocks + n_blocks_neg) * (u64)(csr->n_rows + 1) * (u64)csr->wp : 0;
+            const u64 idx_words_max = (ptr_bits + (u64)p.k * (u64)(csr ? csr->wc : p.w)) / 32;
+            la.nwin_idx = (int)((idx_words_max + (u64)la.pack_words - 1) / (u64)la.pack_words);
+            const u64 code_words_max = ((u64)p.k * (u64)p.qmax + 31) / 32 + 2;
+            la.nwin = la.nwin_idx + (int)((code_words_max + (u64)la.pack_words_code - 1) / (u64)la.pack_words_code);
+        }
+        la.tab = (uint16_t*)(ws + p.lo_tab);      la.cum = (u32*)(ws + p.lo_cum);
+        la.seg = (u32*)(ws + p.lo_seg);
+        la.L = (uint8_t*)(ws + p.off_kept);
+        la.rowst = (u32*)(ws + p.lo_rowst);       la.thr = (u64*)(ws + p.lo_thr);
+        la.map = (uint8_t*)(ws + p.lo_map);
+        la.vminb = (u32*)(ws + p.lo_vminb);       la.vmaxb = (u32*)(ws + p.lo_vmaxb);
+        la.blk_start = (u32*)(ws + p.lo_blk_start); la.pair = (u32*)(ws + p.lo_pair);
+        la.psum = (u64*)(ws + p.lo_psum);
+        la.qsel = (u32*)(ws + p.lo_qsel);         la.inv_sel = (float*)(ws + p.lo_inv_sel);
+        la.code_off = (u64*)(ws + p.lo_code_off);
+        la.bo_idx = ea.bo_idx; la.bo_val = ea.bo_val;
+        la.row_words = ea.row_words; la.slots = ea.slots;
+        la.mv = ea.mv;
+        la.lad = lad;
+        la.guard = guard;
+        la.direct = rows <= kScanRows ? 1 : 0;
+        la.dt = (int)dt; la.bit_set = bit_set; la.stream = (u32*)stream; la.meta = meta;
+        const bool timed = g_ev_start && g_ev_stop;
+        if (timed) SLICER_HIP(hipEventRecord(g_ev_start, st));
+        rc = dt == SLICER_F32 ? launch_large<0>(la, ea, fa, st) : launch_large<1>(la, ea, fa, st);
+        if (rc) return rc;
+        if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
+        if (la.direct) return SLICER_OK;
+        done = true;
+    }
+    if (csr && !done) return SLICER_EINVAL;         // (callers ask for this form only where the long-row stages apply)
+    if (!ea.only_flagged && !done) {
+        rc = dt == SLICER_F32 ? launch_encode<0>(ea, st) : launch_encode<1>(ea, st);
+        if (rc) return rc;
+    }
+
     const u64 grid = (u64)xcd_grid((int64_t)(((u64)rows * (u64)fa.chunks_per_row + 3) / 4));     // four wavefronts per workgroup
     if (grid >= (1ull << 31)) return SLICER_EINVAL;
     if (rows <= kScanRows) {        // small batches: repair, offsets, header and gather in one launch
@@ -604,6 +638,12 @@ int slicer_encode_csr(const void* x, slicer_dtype dt, int64_t instances, int64_t
     Ladder none;
     none.on = 0;
     for (int j = 0; j < kMaxBlocks / 8; ++j) none.nib[j] = 0;
+    // the long-row stages write the CSR form themselves
+    if (c.flat.large_S && !c.flat.wg_ept && !c.flat.small_epl && instances <= kScanRows && c.wp >= 8 && ((uintptr_t)x & 15) == 0) {
+        const CsrShape cs = { n_rows, n_cols, c.wp, c.wc, c.cap_words };
+        return encode_impl(x, dt, instances, n_rows * n_cols, keep_ratio, n_blocks, n_blocks, bit_set, distortion_budget, none, 0,
+                           stream, meta, workspace, hip_stream, 0.0, &cs);
+    }
     // flat encode: kept set, blocks, ranges, bitwidths, codes, flat indices (its stream goes to the workspace)
     rc = encode_impl(x, dt, instances, n_rows * n_cols, keep_ratio, n_blocks, n_blocks, bit_set, distortion_budget, none, 0,
                      ws + c.off_tmp, meta, workspace, hip_stream);

@@ -114,28 +114,6 @@ __device__ inline u32 wave_incl_scan(u32 v)
 }
 
 
-// Exclusive prefix sum over the threads of a block (thread order); `total`
-// receives the block sum.  `scratch` holds BLOCK/64 + 1 words.  Two barriers.
-template <int BLOCK>
-__device__ inline u32 block_excl_scan(u32 v, u32* scratch, u32* total)
-{
-    constexpr int NW = BLOCK / kWave;
-    const u32 lane = lane_id(), wid = threadIdx.x / kWave;
-    u32 inc = wave_incl_scan(v);
-    if (lane == kWave - 1) scratch[wid] = inc;
-    __syncthreads();
-    u32 base = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        u32 s = scratch[i];
-        if ((u32)i < wid) base += s;
-        tot += s;
-    }
-    __syncthreads();
-    *total = tot;
-    return base + inc - v;
-}
-
 // ilogb of a positive finite fp32 given by its bit pattern (subnormals included)
 __device__ inline int ilogb_bits(u32 bits)
 {
@@ -210,6 +188,28 @@ __device__ inline u32 row_scan_dpp(u32 v)
     return r;
 }
 
+// Exclusive prefix sum over the threads of a block (thread order); `total`
+// receives the block sum.  `scratch` holds BLOCK/64 + 1 words.  Two barriers.
+template <int BLOCK>
+__device__ inline u32 block_excl_scan(u32 v, u32* scratch, u32* total)
+{
+    constexpr int NW = BLOCK / kWave;
+    const u32 lane = lane_id(), wid = threadIdx.x / kWave;
+    u32 inc = wave_scan_dpp(v);
+    if (lane == kWave - 1) scratch[wid] = inc;
+    __syncthreads();
+    u32 base = 0, tot = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        u32 s = scratch[i];
+        if ((u32)i < wid) base += s;
+        tot += s;
+    }
+    __syncthreads();
+    *total = tot;
+    return base + inc - v;
+}
+
 // Sum over the 64 lanes, in every lane (data-parallel-primitive moves: no LDS crossbar traffic).
 __device__ inline u32 wave_sum(u32 v) { return bcast(wave_scan_dpp(v), kWave - 1); }
 
@@ -280,7 +280,9 @@ struct RowChunks {
 #pragma unroll
         for (int j = 0; j < EPC; ++j) {
             const int i = q * EPC + j;
-            v[j] = i >= head && i < Nh ? (u32)e[j] : 0u;
+            // (non-temporal: these loads must not be merged with the whole-chunk load of a neighbouring branch; merged,
+            //  the compiler has been seen to leave the address of the lanes with whole chunks undefined)
+            v[j] = i >= head && i < Nh ? (u32)__builtin_nontemporal_load(e + j) : 0u;
         }
         if (DT == 0) return make_uint4(v[0], v[1], v[2], v[3]);
         return make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[EPC - 4] | (v[EPC - 3] << 16), v[EPC - 2] | (v[EPC - 1] << 16));

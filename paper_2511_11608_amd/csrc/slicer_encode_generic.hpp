@@ -26,7 +26,8 @@ struct EncArgs {
     // workspace
     u64* row_words;         // [R]
     u32* slots;             // [R][cap_words]
-    u64* kept;              // [R][k]   class<<63 | key<<32 | idx, ascending idx
+    int64_t kept_stride;    // entries of `kept` per row, at least k
+    u64* kept;              // [R][kept_stride]   class<<63 | key<<32 | idx, ascending idx
     u32* bo_idx;            // [R][k]   block-ordered indices
     u32* bo_val;            // [R][k]   block-ordered |x| (fp32 bits)
     const u32* only_flagged;// if set: rows with a zero flag are skipped (already encoded)
@@ -104,34 +105,44 @@ __device__ inline void stage_or_bits(u32* stage, u64 lo, u64 hi, u64 P, u32 v, i
     if (sh + (u32)nb > 32u) atomicOr(&stage[wi + 1], v >> (32u - sh));
 }
 
+// LDS of the generic encoder
+template <int BLOCK>
+struct GenericLds {
+    static constexpr int NW = BLOCK / kWave;
+    u32 sA[kStageWords];              // histograms / pack staging
+    u32 s_scan[NW + 1];
+    u32 s_out[4];
+    u64 s_thr[2][kMaxBlocks];         // MS thresholds per class
+    u64 tg_prefix[kTgtBatch];
+    u32 tg_rem[kTgtBatch];
+    int tg_cls[kTgtBatch], tg_j[kTgtBatch], tg_done[kTgtBatch], tg_owner[kTgtBatch];
+    u32 blk_start[kMaxB2 + 1];
+    u32 vminb[kMaxB2], vmaxb[kMaxB2];
+    int e_tab[kMaxB2], er_tab[kMaxB2], degen[kMaxB2], qsel[kMaxB2];
+    float inv_sel[kMaxB2];
+    u64 code_off[kMaxB2 + 1];
+    float inv_tab[kMaxB2][kMaxQ];
+    u64 sums[kMaxB2][kMaxQ + 1];
+    u32 cnt_wave[NW][kMaxB2];
+    u32 run_base[kMaxB2];
+    u32 s_range[2];
+    u32 s_asym[4];                    // asymmetric thresholds: smallest kept key, |S_strict|, fill candidates
+};
+
 // Encodes rows [r_begin, r_end) one after the other with the whole workgroup; with
 // a.only_flagged set, only the rows whose flag is non-zero.
 template <int DT, int BLOCK>
-__device__ inline void enc_generic_rows(const EncArgs& a, const int64_t r_begin, const int64_t r_end)
+__device__ inline void enc_generic_rows(const EncArgs& a, const int64_t r_begin, const int64_t r_end, GenericLds<BLOCK>& sh)
 {
     typedef Elem<DT> E;
     typedef typename E::raw_t raw_t;
     constexpr int NW = BLOCK / kWave;
 
-    __shared__ u32 sA[kStageWords];              // histograms / pack staging
-    __shared__ u32 s_scan[NW + 1];
-    __shared__ u32 s_out[4];
-    __shared__ u64 s_thr[2][kMaxBlocks];         // MS thresholds per class
-    __shared__ u64 tg_prefix[kTgtBatch];
-    __shared__ u32 tg_rem[kTgtBatch];
-    __shared__ int tg_cls[kTgtBatch], tg_j[kTgtBatch], tg_done[kTgtBatch], tg_owner[kTgtBatch];
-    __shared__ u32 blk_start[kMaxB2 + 1];
-    __shared__ u32 vminb[kMaxB2], vmaxb[kMaxB2];
-    __shared__ int e_tab[kMaxB2], er_tab[kMaxB2], degen[kMaxB2], qsel[kMaxB2];
-    __shared__ float inv_sel[kMaxB2];
-    __shared__ u64 code_off[kMaxB2 + 1];
-    __shared__ float inv_tab[kMaxB2][kMaxQ];
-    __shared__ u64 sums[kMaxB2][kMaxQ + 1];
-    __shared__ u32 cnt_wave[NW][kMaxB2];
-    __shared__ u32 run_base[kMaxB2];
-    __shared__ u32 s_range[2];
-    __shared__ u32 s_asym[4];                    // asymmetric thresholds: smallest kept key, |S_strict|, fill candidates
-
+    auto& sA = sh.sA; auto& s_scan = sh.s_scan; auto& s_out = sh.s_out; auto& s_thr = sh.s_thr; auto& tg_prefix = sh.tg_prefix;
+    auto& tg_rem = sh.tg_rem; auto& tg_cls = sh.tg_cls; auto& tg_j = sh.tg_j; auto& tg_done = sh.tg_done; auto& tg_owner = sh.tg_owner;
+    auto& blk_start = sh.blk_start; auto& vminb = sh.vminb; auto& vmaxb = sh.vmaxb; auto& e_tab = sh.e_tab; auto& er_tab = sh.er_tab;
+    auto& degen = sh.degen; auto& qsel = sh.qsel; auto& inv_sel = sh.inv_sel; auto& code_off = sh.code_off; auto& inv_tab = sh.inv_tab;
+    auto& sums = sh.sums; auto& cnt_wave = sh.cnt_wave; auto& run_base = sh.run_base; auto& s_range = sh.s_range; auto& s_asym = sh.s_asym;
     const int tid = threadIdx.x;
     const u32 lane = lane_id();
     const int wid = tid / kWave;
@@ -146,7 +157,7 @@ __device__ inline void enc_generic_rows(const EncArgs& a, const int64_t r_begin,
     const int M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn;
     const int Mc[2] = { M, Mn };
     const raw_t* __restrict__ xr = (const raw_t*)a.x + (size_t)r * (size_t)N;
-    u64* __restrict__ kept = a.kept + (size_t)r * (size_t)a.k;
+    u64* __restrict__ kept = a.kept + (size_t)r * (size_t)a.kept_stride;
     u32* __restrict__ bo_idx = a.bo_idx + (size_t)r * (size_t)a.k;
     u32* __restrict__ bo_val = a.bo_val + (size_t)r * (size_t)a.k;
     u32* __restrict__ slot = a.slots + (size_t)r * (size_t)a.cap_words;
@@ -617,8 +628,9 @@ __device__ inline void enc_generic_rows(const EncArgs& a, const int64_t r_begin,
 template <int DT, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void enc_generic_kernel(EncArgs a)
 {
+    __shared__ GenericLds<BLOCK> sh;
     const int64_t r0 = (int64_t)blockIdx.x * a.rows_per_wg;
-    enc_generic_rows<DT, BLOCK>(a, r0, r0 + a.rows_per_wg < a.R ? r0 + a.rows_per_wg : a.R);
+    enc_generic_rows<DT, BLOCK>(a, r0, r0 + a.rows_per_wg < a.R ? r0 + a.rows_per_wg : a.R, sh);
 }
 
 // ---- row offsets (exclusive scan of the row word counts), header, gather ------------------
@@ -681,8 +693,9 @@ __global__ __launch_bounds__(kScanRows) void enc_rowscan_kernel(FinishArgs a)
 template <int DT>
 __global__ __launch_bounds__(kScanRows) void enc_fix_rowscan_kernel(EncArgs ea, FinishArgs a)
 {
+    __shared__ GenericLds<kScanRows> sh;
     const int64_t r0 = (int64_t)blockIdx.x * kScanRows;
-    enc_generic_rows<DT, kScanRows>(ea, r0, r0 + kScanRows < ea.R ? r0 + kScanRows : ea.R);
+    enc_generic_rows<DT, kScanRows>(ea, r0, r0 + kScanRows < ea.R ? r0 + kScanRows : ea.R, sh);
     __syncthreads();
     rowscan_chunk(a);
 }
@@ -751,6 +764,7 @@ __global__ __launch_bounds__(256) void enc_gather_kernel(FinishArgs a)
 template <int DT>
 __global__ __launch_bounds__(kScanRows) void enc_finish_small_kernel(EncArgs ea, FinishArgs a)
 {
+    __shared__ GenericLds<kScanRows> sh;
     __shared__ u64 s_off[kScanRows + 1];
     __shared__ u64 s_wave[kScanRows / kWave];
     const int tid = threadIdx.x, wid = tid / kWave;
@@ -760,7 +774,7 @@ __global__ __launch_bounds__(kScanRows) void enc_finish_small_kernel(EncArgs ea,
         const int any = tid < a.R ? (int)ea.only_flagged[tid] : 0;
         if (__syncthreads_or(any)) {
             if (blockIdx.x != 0) return;             // the whole workgroup
-            enc_generic_rows<DT, kScanRows>(ea, 0, a.R);
+            enc_generic_rows<DT, kScanRows>(ea, 0, a.R, sh);
             __syncthreads();
             alone = true;
         }

@@ -1,27 +1,36 @@
-// Encoder for long rows (tens of thousands of elements and more): every pass over a
-// row is spread over many workgroups, the per-row state lives in the workspace, and
-// the stages are separate launches on the caller's stream:
+// Encoder for long rows (the ones that neither row-resident kernel takes): every pass over a row is spread
+// over many workgroups, the per-row state lives in the workspace, and the stages are five launches on the
+// caller's stream:
 //
-//   hist      per 8192-element chunk: 2048-bin histogram of the key's top 11 bits, stored
-//             as "elements at or above the bin" (so sums over chunks are cumulative too)
-//   select    per row: the bin B1 that holds overall rank k-1, the list offsets of the chunks
-//   compact   per chunk: ordered compaction of everything at or above B1 into the row's
-//             list L (ascending index), plus a 2-byte list of the entries' fine bins
-//   bounds    per row: 8192-bin fine histogram of the list in LDS (three scans of the 2-byte
-//             list; members of the few bins that matter are fetched from L), ranks of the bins; the comp
-//             of overall rank k-1 (ATKF cut, Sec. 3.1) and of class ranks j*K-1 (block boundaries, Sec. 3.2), each resolved
-//             inside its bin by pairwise comparison of the bin's members
-//   blockcount / scatter   per 2048 list entries: block id, per-block counts, block min/max;
-//             then a stable split by block id (ascending index inside a block)
-//   abq / choose / pack    integer ABQ sums (Sec. 3.2.1) with 64-bit atomics, per-block
-//             bitwidth, bit offsets, and the row's stream image, one window of words per workgroup
+//   sample    per row: up to 4096 evenly spread 16-byte chunks.  Their histogram gives a lower bound that a
+//             little more than k elements reach, and a table that maps the elements above it to at
+//             most 4096 "fine bins" of about equal population
+//   compact   per tile of 8192 or 16384 elements: ordered compaction of everything at or above the bound into a list
+//             segment, the tile's histogram over the fine bins (as "entries at or above the bin"), and the
+//             list positions arranged by fine bin
+//   bounds    per row: sums the tiles' histograms; the top-K cut (ATKF, Sec. 3.1) and the first and last
+//             element of every block (MS, Sec. 3.2) are order statistics whose fine bin is found in the sums and
+//             which are resolved among the few members of that bin; rows that do not fit are redone here by the generic encoder
+//   split     per tile: block of every entry, stable split by block (ascending index inside a block), integer
+//             ABQ sums (Sec. 3.2.1); the last workgroup of a row chooses the bitwidths and bit offsets
+//   pack      one window of stream words per workgroup, written straight to its place in the stream when
+//             the batch has at most 256 rows (every workgroup adds up the word counts of the rows before its own)
 //
-// Every stage is bound by the latency of its loads, not by their volume: a thread issues all
-// its loads before it uses the first, and nothing is a chain of dependent global loads.
+// A sample decides only how long the list is and how full the bins are, never the result: the counts are exact.
 //
-// comp = key << w | (2^w - 1 - index): larger comp = larger magnitude, then lower index.
-// Rows that do not fit the lists (heavy ties, more zeros than dropped elements) are
-// flagged and redone by the generic encoder inside the row-scan kernel.
+// What bounds it: launches and the latency of dependent loads, not bandwidth.  Every launch costs 2.5 to 4 us
+// before it does anything and a workgroup lives three to six memory round trips, so the stages were
+// chosen for their number: counting exactly before compacting, separate block counts, sums and choice, and a
+// final gather made ten launches.  One atomic per entry on a table in memory is no way to
+// join the tiles' histograms (29 G atomics/s: 100 us for 3 M of them); the per-tile tables cost 16 KB
+// per tile, written and read once.  Inside a stage the lanes' LDS lookups are written as straight-line code for several
+// entries at once: behind branches they wait for each other (split kernel 68 -> 41 us on 32 maps of 401408, together with four instead of
+// eight entries per thread, which spill nothing, and the choice of the guard taken outside the entry loop).
+// Encode call: fp32 [1 x 200704] 73 -> 53 us, fp32 [32 x 401408] 161 -> 136 us, with CSR blocks 203 -> 173 us.
+//
+// Order: comp = key << w | (2^w - 1 - index): larger comp = larger magnitude, then lower index.  c32 is
+// its leading 31 (fp32: the key) or 32 bits (bf16: the key and the first 17 bits of the inverted
+// index), so that bins can cut through a run of equal bf16 keys.
 #pragma once
 
 #include "slicer_common.hpp"
@@ -29,12 +38,11 @@
 
 namespace slicer {
 
-constexpr int kLCH = 8192;          // elements per hist / compact workgroup
-constexpr int kLBins = 2048;        // coarse bins: top 11 bits of the key
-constexpr int kFB = 8192;           // fine bins of the list (kept in LDS by the bounds stage)
-constexpr int kLCE = 2048;          // list entries per blockcount / scatter workgroup
-constexpr int kPCH = 2048;          // block-ordered positions per abq workgroup
-constexpr int kCutCap = 2048;       // members of the top-K cut bin
+constexpr int kTileThreads = 512;   // a compact / split workgroup handles a tile of 8192 or 16384 elements
+constexpr int kMaxTab = 510, kTabSize = kMaxTab + 2;        // sample bins with fine bins of their own: 16 octaves above the bound
+constexpr int kFB = 4096;           // fine bins per row
+constexpr int kSampleBins = 8192;   // 32 bins per octave
+constexpr int kMemCap = 6144;       // members of the bins that hold order statistics, per row
 constexpr int kPackWords = 1024;    // stream words per pack workgroup
 constexpr u64 kTop = 1ull << 63;
 
@@ -45,25 +53,20 @@ struct LargeArgs {
     int qlist[kMaxQ];
     double beta;
     u64 cap_words;
-    int C, LC;              // chunks per row, list chunks per row
-    int pack_words;         // stream words per pack workgroup in the index section (<= kPackWords)
-    int pack_words_code;    // ... from the first word with code bits on (fields there are short: fewer words per workgroup)
-    int nwin_idx;           // windows that lie in the index section for sure (worst case of its length)
-    int nwin;               // pack workgroups (windows) per row
-    u32* win_range;         // [R][nwin][2] block-ordered entries whose code field meets the window
+    int tile, S;            // elements of a tile, tiles per row
     u32 capL;               // list capacity per row
-    u32* ch_cum;            // [R][C][kLBins]  elements of the chunk at or above the bin
-    u32* ch_off;            // [R][C]
-    u64* L;                 // [R][capL]       class << 63 | key << 32 | index
-    uint16_t* Lfine;        // [R][capL]       fine bin of the entry | class << 15 (capL is a multiple of 8)
-    uint8_t* Lblk;          // [R][capL]       block of the entry, 255 = not kept
-    u32* rowst;             // [R][16]  0 t_lo 1 sh 2 nL 3 n_pos 4 n_neg 5 K0 6 K1 7 ntg 8 nt0
-    u64* thr;               // [R][1 + kMaxB2] thr[0] = cut comp, then boundaries (class on top)
-    u32* blk_start;         // [R][B2 + 1]
-    u32* blkcnt;            // [R][LC][B2]
-    u32* vminb;             // [R][B2]  keys
+    uint16_t* tab;          // [R][kTabSize]  first fine bin of a sample bin | log2 of its number of fine bins << 12; one guard at either end
+    u32* cum;               // [R][S][kFB]    entries of the tile at or above the bin: positive | negative << 16
+    u32* seg;               // [R][S][2]      list position of the tile's segment, positive | negative entries << 16
+    uint8_t* L;             // [R][8 capL]    a row's list, see LrList (the generic encoder's list of the row has the same place)
+    u32* rowst;             // [R][16]        see kSt*
+    u64* thr;               // [R][B2]        comp of the block's last element
+    uint8_t* map;           // [R][2][kFB]    block of a fine bin's first element by class (kMapNone: not kept) | kMapMixed: also of the next | kMapMany: and beyond
+    u32* vminb;             // [R][B2]        keys
     u32* vmaxb;
-    u64* sums;              // [R][B2][nq + 1]
+    u32* blk_start;         // [R][B2 + 1]
+    u32* pair;              // [R][B2][S]     entries of the tile in this block and the blocks of its class before it
+    u64* psum;              // [R][S][B2][nq + 1]  the tiles' ABQ sums
     u32* qsel;              // [R][B2]
     float* inv_sel;         // [R][B2]
     u64* code_off;          // [R][B2 + 1]
@@ -71,827 +74,1182 @@ struct LargeArgs {
     u32* bo_val;            // [R][k]
     u64* row_words;
     u32* slots;
-    u32* fallback;
     MetaView mv;
     Ladder lad;             // fixed multi-level mode
     int guard;              // 0: relative squared-error budget; 1: DS mismatch, greedy descent (beta = delta)
+    // pack
+    int pack_words;         // stream words per pack workgroup in the index section (<= kPackWords)
+    int pack_words_code;    // ... from the first word with code bits on (fields there are short: fewer words per workgroup)
+    int nwin_idx, nwin;     // windows that may lie in the index section; windows per row
+    int direct;             // 1: words go to their place in the stream, 0: to the row's slot
+    int dt;
+    u32 bit_set;
+    u32* stream;
+    void* meta;
+    // two-dimensional instances (n_cols > 0): row pointers and columns instead of flat indices
+    int64_t n_rows, n_cols;
+    int wp, wc;
+};
+
+// coding of `map` (up to 62 blocks; with more of them the split searches the thresholds)
+constexpr u32 kMapMixed = 0x80u, kMapMany = 0x40u, kMapNone = 0x3Fu;
+constexpr int kMapBlocks = 62;
+
+// words of a row's state
+enum { kStT = 0, kStBlo, kStNb, kStCursor, kStTicket, kStFlag, kStNpos, kStNneg };
+
+struct LrList {
+    u32* raw;               // [capL]  fp32: the raw word; bf16: the raw half in the high 16 bits
+    uint16_t* idx;          // [capL]  index relative to the tile
+    uint16_t* pos;          // [capL]  positions inside the segment by fine bin, highest first, positive class first
+    __device__ inline LrList(const LargeArgs& a, int64_t r)
+    {
+        raw = (u32*)(a.L + (size_t)r * 8u * a.capL);
+        idx = (uint16_t*)(raw + a.capL);
+        pos = idx + a.capL;
+    }
+};
+
+template <int DT> struct LrOrder;
+template <> struct LrOrder<0> { static constexpr int kSh = 18; static constexpr u32 kLeast = 1u; };
+template <> struct LrOrder<1> { static constexpr int kSh = 19; static constexpr u32 kLeast = 1u << 17; };
+
+template <int DT>
+__device__ inline u32 lr_c32(u32 key, u32 idx, int w)
+{
+    if (DT == 0) return key;
+    const u32 inv = ((1u << w) - 1u) - idx;
+    return (key << 17) | (w >= 17 ? inv >> (w - 17) : inv << (17 - w));
+}
+
+// fine bin of an element at or above the bound: its sample bin's first one plus the leading bits inside the sample
+// bin (the guards at the table's ends catch elements beyond its reach); no branch, so that the lookups of several entries overlap
+template <int DT>
+__device__ inline u32 lr_fine_bin(u32 cc, const uint16_t* tab, u32 Blo, u32 nb)
+{
+    constexpr int SH = LrOrder<DT>::kSh;
+    const int d = (int)(cc >> SH) - (int)Blo + 1, hi = (int)nb + 1;
+    const u32 t = tab[d < 0 ? 0 : d < hi ? d : hi];
+    return (t & 0xFFFu) + (((cc << (32 - SH)) >> 1) >> (31u - (t >> 12)));
+}
+
+// raw element e of a 16-byte chunk (fp32: 0..3, bf16: 0..7)
+template <int DT>
+__device__ inline u32 chunk_elem(const uint4& v, int e)
+{
+    const int d = DT == 0 ? e : e >> 1;
+    const u32 wd = d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w;
+    return DT == 0 ? wd : ((e & 1) ? wd >> 16 : wd & 0xFFFFu);
+}
+
+__device__ inline u64 lr_comp(u32 key, u32 idx, int w) { return ((u64)key << w) | (u64)(((1u << w) - 1u) - idx); }
+
+// ---- 1. sample ------------------------------------------------------------------------------------
+template <int DT>
+__global__ __launch_bounds__(1024) void lr_sample_kernel(LargeArgs a)
+{
+    typedef Elem<DT> E;
+    constexpr int EPC = RowChunks<DT>::EPC, NU = 4 /* 4096 chunks */, SH = LrOrder<DT>::kSh;
+    __shared__ u32 h[kSampleBins];
+    __shared__ u32 h2[4096];
+    __shared__ u32 scr[1024 / kWave + 1];
+    __shared__ u32 s_v[8];
+    const int tid = threadIdx.x, w = a.w;
+    const int64_t r = blockIdx.x;
+    const RowChunks<DT> row(a.x, r, a.N);
+    const u32 Q = (u32)(row.Nh + EPC - 1) / EPC, G = Q < 1024u * NU ? Q : 1024u * NU;      // chunks of the row, of the sample
+    const bool rg = row.ragged();
+    // one chunk from every G-th of the row, at a hashed place: even spread without a period
+    uint4 v[NU];
+    u32 qs[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const u32 g = (u32)u * 1024u + (u32)tid;
+        v[u] = make_uint4(0, 0, 0, 0);
+        qs[u] = 0;
+        if (g < G) {
+            const u32 lo = G == Q ? g : (u32)(((u64)g * Q) >> 12), len = G == Q ? 1u : (u32)(((u64)(g + 1u) * Q) >> 12) - lo;
+            u32 hs = g * 0x9E3779B1u;
+            hs ^= hs >> 15; hs *= 0x85EBCA77u; hs ^= hs >> 13;
+            qs[u] = lo + __umulhi(hs, len);
+            if (!rg || row.whole((int)qs[u])) v[u] = row.base[qs[u]];       // (a partial chunk at either end is left out)
+        }
+    }
+    {
+        uint4* h4 = (uint4*)h;
+        for (int i = tid; i < kSampleBins / 4; i += 1024) h4[i] = make_uint4(0, 0, 0, 0);
+        ((uint4*)h2)[tid] = make_uint4(0, 0, 0, 0);
+        if (tid < 8) s_v[tid] = tid == 5 ? (u32)kSampleBins - 1u : 0u;
+    }
+    u32* st = a.rowst + (size_t)r * 16;
+    if (tid == 0) { st[kStCursor] = 0; st[kStTicket] = 0; st[kStFlag] = 0; }
+    __syncthreads();
+    auto c32_of = [&](int u, int e) -> u32 {
+        const u32 key = E::key((typename E::raw_t)chunk_elem<DT>(v[u], e));
+        return key ? lr_c32<DT>(key, (u32)((int)qs[u] * EPC + e - row.head), w) : 0u;
+    };
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+            const u32 c = c32_of(u, e);
+            if (c) atomicAdd(&h[c >> SH], 1u);
+        }
+    __syncthreads();
+    // how many of the sample's elements must reach the bound: the expected number of the k kept ones plus four
+    // standard deviations, taken as if the elements of a chunk were all alike; a complete sample needs no margin
+    const bool whole = G == Q && !rg;
+    const double f = (double)a.k / (double)a.N;
+    const double want = whole ? (double)a.k : f * G * EPC + 4.0 * EPC * sqrt((double)G * f * (1.0 - f));
+    const u32 target = (u32)want + (whole && a.k > 0 ? 0u : 1u);
+    const int hi = kSampleBins - tid * 8;           // thread t owns the 8 bins below kSampleBins - 8 t
+    u32 cs[8];
+    {
+        const uint4 t1 = ((const uint4*)h)[hi / 4 - 1], t0 = ((const uint4*)h)[hi / 4 - 2];
+        cs[0] = t1.w; cs[1] = t1.z; cs[2] = t1.y; cs[3] = t1.x; cs[4] = t0.w; cs[5] = t0.z; cs[6] = t0.y; cs[7] = t0.x;
+    }
+    u32 local = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) local += cs[j];
+    u32 tot;
+    {
+        u32 acc = block_excl_scan<1024>(local, scr, &tot);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (acc < target && target <= acc + cs[j]) { s_v[0] = (u32)(hi - 1 - j); s_v[1] = acc; s_v[2] = 1u; }
+            acc += cs[j];
+        }
+        if (local) {
+            int topj = 0, botj = 0;
+#pragma unroll
+            for (int j = 7; j >= 0; --j) if (cs[j]) topj = j;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) if (cs[j]) botj = j;
+            atomicMax(&s_v[3], (u32)(hi - 1 - topj));
+            atomicMin(&s_v[5], (u32)(hi - 1 - botj));
+        }
+    }
+    __syncthreads();
+    u32 T = LrOrder<DT>::kLeast;                    // every non-zero element, unless the sample holds more than wanted
+    if (s_v[2]) {                                    // uniform
+        const u32 B = s_v[0];
+        T = B << SH;
+        if (!whole && h[B] * 16u > target) {         // a full bin: the bound inside it
+            const u32 rem = target - s_v[1];
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) {
+                    const u32 c = c32_of(u, e);
+                    if (c && (c >> SH) == B) atomicAdd(&h2[(c >> (SH - 12)) & 4095u], 1u);
+                }
+            __syncthreads();
+            const int hi2 = 4096 - tid * 4;
+            const uint4 t = ((const uint4*)h2)[hi2 / 4 - 1];
+            const u32 c2[4] = { t.w, t.z, t.y, t.x };
+            u32 tot2;
+            u32 acc = block_excl_scan<1024>(t.x + t.y + t.z + t.w, scr, &tot2);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (acc < rem && rem <= acc + c2[j]) s_v[4] = (u32)(hi2 - 1 - j);
+                acc += c2[j];
+            }
+            __syncthreads();
+            T |= s_v[4] << (SH - 12);
+        }
+        if (T < LrOrder<DT>::kLeast) T = LrOrder<DT>::kLeast;
+    }
+    // fine bins: a sample bin that should hold c list entries is cut into the largest power of two up to c / per, with
+    // `per` such that all of them fit; elements in sample bins above the sample's largest element share the last fine
+    // bin, elements below its smallest one (or below the table's reach, when nearly all non-zeros are wanted) the first
+    u32 Blo = T >> SH;
+    Blo = Blo > s_v[5] ? Blo : s_v[5];
+    u32 Btop = s_v[3] > Blo ? s_v[3] : Blo;
+    if (Btop - Blo > (u32)kMaxTab - 1u) Btop = Blo + (u32)kMaxTab - 1u;
+    const u32 nb = Btop - Blo + 1u;
+    const float scale = (float)((double)a.N / ((double)G * EPC));
+    const u32 room = (u32)kFB - 2u - nb;
+    float per = scale * (float)((tot < target ? tot : target) + h[Blo]) / (float)room + 1.0f;
+    per = per < 8.0f ? 8.0f : per;
+    u32 lg = 0, sub = 0;                             // thread i: sample bin Blo + i
+    if ((u32)tid < nb) {
+        const u32 c = (u32)((float)h[Blo + (u32)tid] * scale / per);
+        lg = c > 1u ? 31u - (u32)__clz((int)c) : 0u;
+        lg = lg < 12u ? lg : 12u;
+        sub = 1u << lg;
+    }
+    u32 nbins;
+    u32 base = block_excl_scan<1024>(sub, scr, &nbins);
+    if (nbins > (u32)kFB - 2u) { lg = 0; nbins = nb; base = (u32)tid; }    // cannot happen by more than rounding: one fine bin each
+    uint16_t* tab = a.tab + (size_t)r * kTabSize;
+    if ((u32)tid < nb) tab[tid + 1] = (uint16_t)((base + 1u) | (lg << 12));
+    if (tid == 0) { tab[0] = 0; tab[nb + 1u] = (uint16_t)(nbins + 1u); }
+    if (tid == 0) { st[kStT] = T; st[kStBlo] = Blo; st[kStNb] = nb; }
+}
+
+// ---- 2. compact -----------------------------------------------------------------------------------
+// A wavefront owns NR * 512 consecutive elements, all of them in registers from the start, and works through them
+// 512 at a time: the entries above the bound are first squeezed into its own piece of LDS (index order), then every
+// lane takes whole entries.  With a fifth of the elements above the bound the work per entry (fine bin, atomic,
+// stores) would otherwise run with a fifth of the lanes; nothing in between is a workgroup barrier.
+template <int DT, int NR>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void lr_compact_kernel(LargeArgs a)
+{
+    typedef Elem<DT> E;
+    constexpr int EPC = RowChunks<DT>::EPC, CPR = 8 / EPC;           // chunks per lane and round: 2 (fp32), 1 (bf16)
+    constexpr int NCH = NR * CPR, NWV = kTileThreads / kWave, RE = 8 * kWave, WCH = NCH * kWave;     // chunks of a wavefront
+    constexpr int kBuf = NWV * RE * 6, kPass = kBuf / 2;     // bytes; list positions arranged at a time
+    __shared__ u32 hist[kFB];                        // positive | negative << 16; later the entries above the bin
+    __shared__ __align__(4) uint16_t tab[kTabSize];
+    __shared__ __align__(16) unsigned char buf[kBuf];
+    __shared__ u32 wtot[NWV];
+    __shared__ u32 scr[NWV + 1];
+    __shared__ u32 s_base;
+    const int tid = threadIdx.x, s = blockIdx.x, w = a.w, wv = tid / kWave;
+    u32* braw = (u32*)buf + wv * RE;                 // a round's entries of this wavefront
+    uint16_t* bidx = (uint16_t*)(buf + NWV * RE * 4) + wv * RE;
+    uint16_t* bpos = (uint16_t*)buf;                 // in the end: list positions by fine bin
+    const u32 lane = lane_id();
+    const int64_t r = blockIdx.y;
+    u32* st = a.rowst + (size_t)r * 16;
+    const RowChunks<DT> row(a.x, r, a.N);
+    const int qt = s * (NWV * WCH), q0 = qt + wv * WCH;          // first chunk of the tile, of the wavefront
+    uint4 v[NCH];
+    {
+        const bool rg = row.ragged();
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int q = q0 + c * kWave + (int)lane;
+            v[c] = q * EPC < row.Nh && (!rg || row.whole(q)) ? row.base[q] : make_uint4(0, 0, 0, 0);
+        }
+        if (rg) {
+            const int ql = (row.Nh - 1) / EPC;
+            if (q0 + (int)lane == 0 && !row.whole(0)) v[0] = row.partial(0);
+            if (ql > 0 && ql >= q0 && ql < q0 + WCH && (ql - q0) % kWave == (int)lane && !row.whole(ql)) {
+                const uint4 e = row.partial(ql);
+                const int cl = (ql - q0) / kWave;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) if (c == cl) v[c] = e;
+            }
+        }
+    }
+    const u32 T = st[kStT], Blo = st[kStBlo], nb = st[kStNb];
+    {
+        uint4* h4 = (uint4*)hist;
+        for (int i = tid; i < kFB / 4; i += kTileThreads) h4[i] = make_uint4(0, 0, 0, 0);
+        const u32* tg = (const u32*)(a.tab + (size_t)r * kTabSize);
+        if (tid < kTabSize / 2) ((u32*)tab)[tid] = tg[tid];
+    }
+    const int e_base = qt * EPC - row.head, le0 = (wv * WCH + (int)lane) * EPC;      // index of the tile's first element; this lane's first one in the tile
+    auto above = [&](int c, int e) -> bool {         // at or above the bound
+        const u32 raw = chunk_elem<DT>(v[c], e);
+        if (DT == 0) return (raw & 0x7FFFFFFFu) >= T;
+        const u32 key = raw & 0x7FFFu;
+        return key && lr_c32<DT>(key, (u32)(e_base + le0 + c * (kWave * EPC) + e), w) >= T;
+    };
+    u32 base[NCH], wn = 0;                           // positions inside the wavefront's entries
+#pragma unroll
+    for (int g = 0; g < (NCH + 2) / 3; ++g) {        // counts of three chunks per scan, 10-bit fields
+        u32 pk = 0;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            if (3 * g + j < NCH) {
+                u32 n1 = 0;
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) n1 += above(3 * g + j, e) ? 1u : 0u;
+                pk |= n1 << (10 * j);
+            }
+        }
+        const u32 incl = wave_scan_dpp(pk);
+        const u32 tt = bcast(incl, kWave - 1);
+        const u32 ex = incl - pk;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            if (3 * g + j < NCH) {
+                base[3 * g + j] = wn + ((ex >> (10 * j)) & 0x3FFu);
+                wn += (tt >> (10 * j)) & 0x3FFu;
+            }
+        }
+    }
+    if (lane == 0) wtot[wv] = wn;
+    __syncthreads();
+    u32 wbase = 0, ntile = 0;                        // entries of the wavefronts before this one, of the tile
+#pragma unroll
+    for (int i = 0; i < NWV; ++i) { const u32 t = wtot[i]; if (i < wv) wbase += t; ntile += t; }
+    if (tid == 0) {
+        u32 b = atomicAdd(&st[kStCursor], ntile);
+        if (b > a.capL || ntile > a.capL - b) { b = 0xFFFFFFFFu; st[kStFlag] = 1u; }     // the list is full: the row is redone generically
+        s_base = b;
+    }
+    const u32 we0 = (u32)(wv * WCH * EPC);           // the wavefront's first element in the tile
+    __syncthreads();
+    const u32 seg0 = s_base;
+    const bool full = seg0 == 0xFFFFFFFFu;
+    const LrList list(a, r);
+    u32* __restrict__ Lraw = list.raw + seg0 + wbase;
+    uint16_t* __restrict__ Lidx = list.idx + seg0 + wbase;
+    uint16_t* __restrict__ Lpos = list.pos + seg0;
+    u32 bf[NR][8];                                   // fine bin | entries of the bin before this one << 12 | negative << 31
+    u32 g0 = 0;
+#pragma unroll
+    for (int g = 0; g < NR; ++g) {
+        const u32 g1 = g + 1 < NR ? bcast(base[(g + 1) * CPR < NCH ? (g + 1) * CPR : 0], 0) : wn;
+        const u32 ng = g1 - g0;
+#pragma unroll
+        for (int cc = 0; cc < CPR; ++cc) {
+            const int c = g * CPR + cc;
+            u32 pos = base[c] - g0;
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) {
+                if (above(c, e)) {
+                    const u32 raw = chunk_elem<DT>(v[c], e);
+                    braw[pos] = DT == 0 ? raw : raw << 16;
+                    bidx[pos] = (uint16_t)(c * (kWave * EPC) + (int)lane * EPC + e);
+                    ++pos;
+                }
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {                // two entries per lane at a time, their lookups side by side
+#pragma unroll
+            for (int e = 0; e < 2; ++e) bf[g][2 * h + e] = 0;
+            if ((u32)(2 * h * kWave) >= ng) continue;        // uniform in the wavefront
+            u32 rw[2], ix[2], bin[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const u32 i = (u32)((2 * h + e) * kWave) + lane;
+                rw[e] = braw[i]; ix[e] = we0 + (u32)bidx[i];
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const u32 key = DT == 0 ? rw[e] & 0x7FFFFFFFu : (rw[e] >> 16) & 0x7FFFu;
+                bin[e] = lr_fine_bin<DT>(lr_c32<DT>(key, (u32)e_base + ix[e], w), tab, Blo, nb);
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const u32 i = (u32)((2 * h + e) * kWave) + lane;
+                const bool in = i < ng, neg = rw[e] >> 31;
+                // (lanes without an entry add nothing, each to a bin of its own)
+                const u32 old = atomicAdd(&hist[in ? bin[e] : lane], in ? (neg ? 0x10000u : 1u) : 0u);
+                bf[g][2 * h + e] = bin[e] | ((neg ? old >> 16 : old & 0xFFFFu) << 12) | (rw[e] & 0x80000000u);
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const u32 i = (u32)((2 * h + e) * kWave) + lane;
+                if (i < ng && !full) { Lraw[g0 + i] = rw[e]; Lidx[g0 + i] = (uint16_t)ix[e]; }
+            }
+        }
+        wave_sync();
+        g0 = g1;
+    }
+    __syncthreads();
+    u32* seg = a.seg + ((size_t)r * a.S + s) * 2;
+    {
+        constexpr int BPT = kFB / kTileThreads;      // 8 bins per thread, from the top
+        uint4* h4 = (uint4*)hist + (kFB - tid * BPT) / 4;
+        const uint4 t1 = h4[-1], t0 = h4[-2];
+        const u32 local = t1.x + t1.y + t1.z + t1.w + t0.x + t0.y + t0.z + t0.w;     // the halves add up separately: no sum reaches 2^16
+        u32 tot;
+        const u32 ex = block_excl_scan<kTileThreads>(local, scr, &tot);
+        const u32 a7 = ex + t1.w, a6 = a7 + t1.z, a5 = a6 + t1.y, a4 = a5 + t1.x;    // at or above
+        const u32 a3 = a4 + t0.w, a2 = a3 + t0.z, a1 = a2 + t0.y, a0 = a1 + t0.x;
+        uint4* out = (uint4*)(a.cum + ((size_t)r * a.S + s) * kFB) + (kFB - tid * BPT) / 4;
+        out[-1] = make_uint4(a4, a5, a6, a7);
+        out[-2] = make_uint4(a0, a1, a2, a3);
+        const u32 off = (tot & 0xFFFFu) << 16;       // the negative entries follow the positive ones
+        h4[-1] = make_uint4(a5 + off, a6 + off, a7 + off, ex + off);
+        h4[-2] = make_uint4(a1 + off, a2 + off, a3 + off, a4 + off);
+        if (tid == 0) { seg[0] = seg0; seg[1] = tot; }
+    }
+    if (full || ntile == 0u) return;                 // uniform
+    __syncthreads();
+    for (u32 p0 = 0; p0 < ntile; p0 += kPass) {      // one pass unless more than three quarters of the tile are above the bound
+    g0 = 0;
+#pragma unroll
+    for (int g = 0; g < NR; ++g) {
+        const u32 g1 = g + 1 < NR ? bcast(base[(g + 1) * CPR < NCH ? (g + 1) * CPR : 0], 0) : wn;
+        const u32 ng = g1 - g0;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            if ((u32)(2 * h * kWave) >= ng) continue;
+            u32 hv[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) hv[e] = hist[bf[g][2 * h + e] & 0xFFFu];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const u32 i = (u32)((2 * h + e) * kWave) + lane, t = bf[g][2 * h + e];
+                const u32 at = ((t >> 31) ? hv[e] >> 16 : hv[e] & 0xFFFFu) + ((t >> 12) & 0x7FFFu) - p0;
+                if (i < ng && at < (u32)kPass) bpos[at] = (uint16_t)(wbase + g0 + i);
+            }
+        }
+        g0 = g1;
+    }
+    __syncthreads();
+    for (u32 i = (u32)tid; i < (u32)kPass && p0 + i < ntile; i += kTileThreads) Lpos[p0 + i] = bpos[i];
+    __syncthreads();
+    }
+}
+
+// ---- bitwidths, bit offsets and the row's length ----------------------------------------------------
+// Thread b holds block b's bitwidth q and flag (0x80: none feasible); everything the pack stage and meta need follows.
+template <int DT>
+__device__ inline void lr_finish_row(const LargeArgs& a, int64_t r, u32 n_pos, u32 n_neg, bool on, u32 q, u32 flag, u32 cnt, float vmin, float vmax,
+                                     u64* bits_s)
+{
+    const int b = threadIdx.x, B2 = a.M + a.Mn;
+    if (on) {
+        float inv = 0.f;
+        const float rng = vmax - vmin;
+        if (cnt && rng > 0.f) inv = (float)((1u << q) - 1u) / unit_range(rng, range_exp(rng));
+        a.qsel[r * B2 + b] = q;
+        a.inv_sel[r * B2 + b] = inv;
+        const size_t mi = (size_t)r * (size_t)B2 + b;
+        a.mv.vmin[mi] = vmin; a.mv.vmax[mi] = vmax; a.mv.q[mi] = (uint8_t)(q | flag);
+        bits_s[b] = (u64)cnt * (u64)q;
+    }
+    __syncthreads();
+    if (on) {
+        u64 acc = 0;
+        for (int i = 0; i < b; ++i) acc += bits_s[i];
+        a.code_off[(size_t)r * (B2 + 1) + b] = acc;
+        if (b == B2 - 1) {
+            acc += bits_s[b];
+            a.code_off[(size_t)r * (B2 + 1) + B2] = acc;
+            const u64 n = (u64)n_pos + n_neg;
+            const u64 bits = a.n_cols > 0 ? (u64)B2 * (u64)(a.n_rows + 1) * (u64)a.wp + n * (u64)a.wc + acc : n * (u64)a.w + acc;
+            u64 words = (bits + 31) >> 5;
+            if (words > a.cap_words) words = a.cap_words;            // cannot happen: the capacity is the worst case
+            a.row_words[r] = words;
+            a.mv.n_pos[r] = n_pos;
+            a.mv.n_neg[r] = n_neg;
+        }
+    }
+}
+
+// ---- 3. bounds ------------------------------------------------------------------------------------
+constexpr int kMaxTargets = 2 * kMaxB2;
+
+struct LrBoundsLds {
+    u32 at_p[kFB + 1], at_n[kFB + 1];                // list entries at or above the bin
+    u64 mem[kMemCap];                                // members of the bins that hold a target
+    u32 mem_g[kMemCap];                              // their group | tile << 8
+    u32 tg_bin[kMaxTargets], tg_rem[kMaxTargets];    // target 2 b: first element of block b, 2 b + 1: its last one
+    u64 tg_comp[kMaxTargets];
+    u32 g_bin[kMaxTargets], g_cls[kMaxTargets];      // groups of consecutive targets in one bin; class 2: both
+    u32 g_start[kMaxTargets + 1], g_fill[kMaxTargets], g_t0[kMaxTargets + 1];
+    u32 v[8];
 };
 
 template <int DT>
-__global__ __launch_bounds__(256) void lr_hist_kernel(LargeArgs a)
+__global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea)
 {
-    typedef Elem<DT> E;
-    typedef typename E::raw_t raw_t;
-    constexpr int KS = E::kKeyBits - 11;
-    __shared__ u32 h[kLBins];
-    __shared__ u32 scr[256 / kWave + 1];
-    const int tid = threadIdx.x, c = blockIdx.x;
-    const int64_t r = blockIdx.y;
-    const int B2 = a.M + a.Mn;
-    for (int i = tid; i < kLBins; i += 256) h[i] = 0;
-    // this launch also clears what later stages accumulate into
-    if (c == 0) {
-        for (int b = tid; b < B2; b += 256) { a.vminb[r * B2 + b] = 0xFFFFFFFFu; a.vmaxb[r * B2 + b] = 0; }
-        for (int i = tid; i < B2 * (a.nq + 1); i += 256) a.sums[(size_t)r * B2 * (a.nq + 1) + i] = 0;
-    }
-    __syncthreads();
-    // 16-byte loads (the row length is a multiple of a 16-byte chunk); exact zeros are not
-    // counted: they are never sent, and skipping them keeps the hot bin of post-ReLU
-    // features out of the LDS atomics (a row whose cut falls among them is redone generically)
-    constexpr int EPC = DT == 0 ? 4 : 8;
-    const int64_t i0 = (int64_t)c * kLCH;
-    const uint4* __restrict__ x4 = (const uint4*)((const char*)a.x + ((size_t)r * (size_t)a.N + (size_t)i0) * sizeof(raw_t));
-#pragma unroll
-    for (int j = 0; j < kLCH / (256 * EPC); ++j) {
-        const int q = j * 256 + tid;
-        if (i0 + (int64_t)q * EPC < a.N) {
-            const uint4 v = x4[q];
-            const u32 wd[4] = { v.x, v.y, v.z, v.w };
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                if (DT == 0) {
-                    const u32 key = wd[d] & 0x7FFFFFFFu;
-                    if (key) atomicAdd(&h[key >> KS], 1u);
-                } else {
-                    const u32 k0 = wd[d] & 0x7FFFu, k1 = (wd[d] >> 16) & 0x7FFFu;
-                    if (k0) atomicAdd(&h[k0 >> KS], 1u);
-                    if (k1) atomicAdd(&h[k1 >> KS], 1u);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    // "at or above": running sum from the top bin down; thread t owns the 8 bins below 2048 - 8t
-    const int hi = kLBins - tid * 8;
-    u32 local = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) local += h[hi - 1 - j];
-    u32 tot;
-    u32 acc = block_excl_scan<256>(local, scr, &tot);
-    u32* __restrict__ out = a.ch_cum + ((size_t)r * a.C + c) * kLBins;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) { acc += h[hi - 1 - j]; out[hi - 1 - j] = acc; }
-}
-
-template <int DT>
-__global__ __launch_bounds__(1024) void lr_select_kernel(LargeArgs a)
-{
-    constexpr int KS = Elem<DT>::kKeyBits - 11;
-    __shared__ u32 rc[kLBins + 1];
-    __shared__ u32 scr[1024 / kWave + 1];
-    __shared__ u32 res[2];
-    const int tid = threadIdx.x;
+    constexpr size_t kLds = sizeof(LrBoundsLds) > sizeof(GenericLds<1024>) ? sizeof(LrBoundsLds) : sizeof(GenericLds<1024>);
+    __shared__ __align__(16) unsigned char lds[kLds];
+    LrBoundsLds& L = *(LrBoundsLds*)lds;
+    const int tid = threadIdx.x, w = a.w, M = a.M, Mn = a.Mn, B2 = M + Mn, S = a.S;
     const int64_t r = blockIdx.x;
-    // sum of the chunks' cumulative histograms: a thread takes four bins (one 16-byte load per
-    // chunk) of every second chunk, eight independent loads in flight
-    for (int bin = tid; bin <= kLBins; bin += 1024) rc[bin] = 0;
-    if (tid == 0) { res[0] = 0; res[1] = 0; }
-    __syncthreads();
+    u32* st = a.rowst + (size_t)r * 16;
+    const u32 k = (u32)a.k;
+    const u32* __restrict__ cum = a.cum + (size_t)r * S * kFB;
+    const u32* __restrict__ seg = a.seg + (size_t)r * S * 2;
+    const LrList list(a, r);
+    const u32* __restrict__ Lraw = list.raw;
+    const uint16_t* __restrict__ Lidx = list.idx;
+    const uint16_t* __restrict__ Lpos = list.pos;
+    u32* pair = a.pair + (size_t)r * B2 * S;
+    const int head = RowChunks<DT>(a.x, r, a.N).head;
+    bool bad = st[kStFlag] != 0u;                    // uniform
+    const u32 T = st[kStT];
+
+    // sums of the tiles' tables: a thread takes four bins, eight tiles in flight
     {
-        const int q = tid & (kLBins / 4 - 1), g = tid / (kLBins / 4);          // 512 quads x 2 chunk groups
-        const uint4* __restrict__ src = (const uint4*)(a.ch_cum + (size_t)r * a.C * kLBins) + q;
-        u32 s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-        for (int c0 = g; c0 < a.C; c0 += 16) {
+        u32 p[4] = { 0, 0, 0, 0 }, n[4] = { 0, 0, 0, 0 };
+        for (int s0 = 0; s0 < S; s0 += 8) {
             uint4 t[8];
 #pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = s0 + u < S ? ((const uint4*)(cum + (size_t)(s0 + u) * kFB))[tid] : make_uint4(0, 0, 0, 0);
+#pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int c = c0 + 2 * u;
-                t[u] = c < a.C ? src[(size_t)c * (kLBins / 4)] : make_uint4(0, 0, 0, 0);
+                p[0] += t[u].x & 0xFFFFu; p[1] += t[u].y & 0xFFFFu; p[2] += t[u].z & 0xFFFFu; p[3] += t[u].w & 0xFFFFu;
+                n[0] += t[u].x >> 16; n[1] += t[u].y >> 16; n[2] += t[u].z >> 16; n[3] += t[u].w >> 16;
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) { s0 += t[u].x; s1 += t[u].y; s2 += t[u].z; s3 += t[u].w; }
         }
-        atomicAdd(&rc[4 * q + 0], s0); atomicAdd(&rc[4 * q + 1], s1);
-        atomicAdd(&rc[4 * q + 2], s2); atomicAdd(&rc[4 * q + 3], s3);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { L.at_p[tid * 4 + j] = p[j]; L.at_n[tid * 4 + j] = n[j]; }
+        if (tid == 0) { L.at_p[kFB] = 0; L.at_n[kFB] = 0; }
+        if (tid < 8) L.v[tid] = 0;
     }
     __syncthreads();
-    const u32 km1 = a.k > 0 ? (u32)(a.k - 1) : 0u;
-    for (int bin = tid; bin < kLBins; bin += 1024) {
-        if (rc[bin] > km1 && rc[bin + 1] <= km1) res[0] = (u32)bin;       // holds rank k-1
-        if (rc[bin] > 0 && rc[bin + 1] == 0) res[1] = (u32)bin;           // highest occupied
-    }
-    __syncthreads();
-    const u32 B1 = res[0], top = res[1];
-    const u32 nL = rc[B1];
-    const u32 t_lo = B1 << KS;
-    const u32 range = (((top + 1u) << KS) - 1u) - t_lo;
-    const int sh = range < (u32)kFB ? 0 : (32 - __clz((int)range)) - 13;   // 13 = log2(kFB)
-    // bin 0 holds the exact zeros, which are never sent: such rows go to the generic kernel
-    const bool bad = a.k > 0 && (B1 == 0 || nL > a.capL);
-    const bool live = a.k > 0 && !bad;
-    u32 v = 0;
-    if (live && tid < a.C) v = a.ch_cum[((size_t)r * a.C + tid) * kLBins + B1];
-    u32 tot;
-    const u32 ex = block_excl_scan<1024>(v, scr, &tot);
-    if (tid < a.C) a.ch_off[(size_t)r * a.C + tid] = ex;
-    if (tid == 0) {
-        u32* st = a.rowst + (size_t)r * 16;
-        st[0] = t_lo; st[1] = (u32)sh; st[2] = live ? nL : 0u;
-        a.fallback[r] = bad ? 1u : 0u;
-    }
-}
+    const u32 nL = L.at_p[0] + L.at_n[0];
+    if (nL < k && T > LrOrder<DT>::kLeast) bad = true;       // the sample's bound was too high
 
-template <int DT>
-__global__ __launch_bounds__(256) void lr_compact_kernel(LargeArgs a)
-{
-    typedef Elem<DT> E;
-    constexpr int EPC = DT == 0 ? 4 : 8;
-    constexpr int NJ = kLCH / 4 / (kWave * EPC);          // 16-byte loads per lane
-    __shared__ u32 wtot[4];
-    const int tid = threadIdx.x, c = blockIdx.x, wid = tid / kWave;
-    const u32 lane = lane_id();
-    const int64_t r = blockIdx.y;
-    if (a.fallback[r]) return;
-    const u32* st = a.rowst + (size_t)r * 16;
-    const u32 t_lo = st[0], nL = st[2];
-    const int sh = (int)st[1];
-    if (nL == 0) return;
-    const int64_t seg0 = (int64_t)c * kLCH + (int64_t)wid * (kLCH / 4);
-    const uint4* __restrict__ xr4 = (const uint4*)((const char*)a.x + ((size_t)r * (size_t)a.N + (size_t)seg0) * (DT == 0 ? 4 : 2));
-    uint4 v[NJ];
-    u32 cntj[NJ];
+    auto at_c = [&](u32 cls, u32 b) -> u32 { return cls == 0u ? L.at_p[b] : cls == 1u ? L.at_n[b] : L.at_p[b] + L.at_n[b]; };
+    // members of the bins of groups 0 .. ng - 1 (g_start: room per group), tile by tile
+    auto gather = [&](int ng) {
+        for (int i = tid; i < ng * S; i += 1024) {
+            const int g = i / S, s = i - g * S;
+            const u32 cls = L.g_cls[g], b = L.g_bin[g];
+            const u32 c0 = cum[(size_t)s * kFB + b], c1 = b + 1u < (u32)kFB ? cum[(size_t)s * kFB + b + 1u] : 0u;
+            const u32 seg0 = seg[2 * s], np = seg[2 * s + 1] & 0xFFFFu;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const int64_t e0 = seg0 + (int64_t)(j * kWave + (int)lane) * EPC;
-        v[j] = e0 < a.N ? xr4[j * kWave + lane] : make_uint4(0, 0, 0, 0);
-    }
-    auto raw_of = [&](int j, int e) -> u32 {
-        const u32 wd = (DT == 0) ? (e == 0 ? v[j].x : e == 1 ? v[j].y : e == 2 ? v[j].z : v[j].w)
-                                 : ((e >> 1) == 0 ? v[j].x : (e >> 1) == 1 ? v[j].y : (e >> 1) == 2 ? v[j].z : v[j].w);
-        return (DT == 0) ? wd : ((e & 1) ? wd >> 16 : wd & 0xFFFFu);
-    };
+            for (u32 h = 0; h < 2u; ++h) {
+                if (cls != 2u && cls != h) continue;
+                const u32 n0 = h ? c0 >> 16 : c0 & 0xFFFFu, n1 = h ? c1 >> 16 : c1 & 0xFFFFu, cn = n0 - n1;
+                if (cls != 2u)                       // entries of the tile above the bin: the start of the blocks' counts
+                    for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t) if (t & 1u) pair[(size_t)(t >> 1) * S + s] = n1;
+                if (!cn) continue;
+                const u32 slot = L.g_start[g] + atomicAdd(&L.g_fill[g], cn);
+                for (u32 j0 = 0; j0 < cn; j0 += 4) {
+                    u32 lp[4], rw[4], ix[4];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        u32 n1 = 0;
+                    for (u32 u = 0; u < 4; ++u) lp[u] = seg0 + (j0 + u < cn ? (u32)Lpos[seg0 + (h ? np : 0u) + n1 + j0 + u] : 0u);
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) n1 += E::key((typename E::raw_t)raw_of(j, e)) >= t_lo ? 1u : 0u;   // t_lo > 0: zeros drop out
-        cntj[j] = n1;
-    }
-    u32 basej[NJ];
-    u32 wsum = 0;
+                    for (u32 u = 0; u < 4; ++u) { rw[u] = Lraw[lp[u]]; ix[u] = Lidx[lp[u]]; }
 #pragma unroll
-    for (int g = 0; g < (NJ + 2) / 3; ++g) {              // three counts per scan, 10-bit fields
-        u32 pk = cntj[3 * g];
-        if (3 * g + 1 < NJ) pk |= cntj[3 * g + 1] << 10;
-        if (3 * g + 2 < NJ) pk |= cntj[3 * g + 2] << 20;
-        const u32 incl = wave_scan_dpp(pk);
-        const u32 tot = bcast(incl, kWave - 1);
-        const u32 ex = incl - pk;
-#pragma unroll
-        for (int jj = 0; jj < 3; ++jj) {
-            if (3 * g + jj < NJ) {
-                basej[3 * g + jj] = wsum + ((ex >> (10 * jj)) & 0x3FFu);
-                wsum += (tot >> (10 * jj)) & 0x3FFu;
-            }
-        }
-    }
-    if (lane == 0) wtot[wid] = wsum;
-    __syncthreads();
-    u32 wbase = a.ch_off[(size_t)r * a.C + c];
-    for (int v2 = 0; v2 < wid; ++v2) wbase += wtot[v2];
-    u64* __restrict__ L = a.L + (size_t)r * a.capL;
-    uint16_t* __restrict__ Lfine = a.Lfine + (size_t)r * a.capL;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        u32 pos = wbase + basej[j];
-        const u32 idx0 = (u32)(seg0 + (int64_t)(j * kWave + (int)lane) * EPC);
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const u32 raw = raw_of(j, e);
-            const u32 key = E::key((typename E::raw_t)raw);
-            if (key >= t_lo) {
-                const u32 neg = E::neg((typename E::raw_t)raw);
-                if (pos < a.capL) {
-                    L[pos] = ((u64)neg << 63) | ((u64)key << 32) | (u64)(idx0 + e);
-                    Lfine[pos] = (uint16_t)(((key - t_lo) >> sh) | (neg << 15));     // what the bounds stage scans
+                    for (u32 u = 0; u < 4; ++u) {
+                        if (j0 + u < cn) {
+                            const u32 key = DT == 0 ? rw[u] & 0x7FFFFFFFu : (rw[u] >> 16) & 0x7FFFu;
+                            L.mem[slot + j0 + u] = lr_comp(key, (u32)(s * a.tile - head) + ix[u], w) | (h ? kTop : 0ull);
+                            L.mem_g[slot + j0 + u] = (u32)g | ((u32)s << 8);
+                        }
+                    }
                 }
-                ++pos;
+            }
+        }
+        __syncthreads();
+    };
+
+    u32 n_pos = L.at_p[0], n_neg = L.at_n[0];
+    if (!bad && nL > k) {
+        if (n_neg == 0u || k == 0u) { n_pos = k; n_neg = 0; }
+        else if (n_pos == 0u) n_neg = k;
+        else {                                       // ATKF cut: overall rank k - 1
+#pragma unroll
+            for (u32 j = 0; j < 4; ++j) {
+                const u32 b = (u32)tid * 4u + j;
+                if (at_c(2, b) > k - 1u && at_c(2, b + 1u) <= k - 1u) {
+                    L.g_bin[0] = b; L.g_cls[0] = 2; L.g_start[0] = 0; L.g_start[1] = at_c(2, b) - at_c(2, b + 1u);
+                    L.g_fill[0] = 0;
+                }
+            }
+            __syncthreads();
+            const u32 cn = L.g_start[1], cb = L.g_bin[0];
+            if (cn > (u32)kMemCap) bad = true;
+            else {
+                gather(1);
+                const u32 rem = k - 1u - at_c(2, cb + 1u);
+                for (u32 i = (u32)tid; i < cn; i += 1024) {
+                    const u64 me = L.mem[i] & ~kTop;
+                    u32 gt = 0;
+                    for (u32 j = 0; j < cn; ++j) gt += (L.mem[j] & ~kTop) > me ? 1u : 0u;
+                    if (gt <= rem) atomicAdd(&L.v[(L.mem[i] & kTop) ? 1 : 0], 1u);
+                }
+                __syncthreads();
+                n_pos = L.at_p[cb + 1u] + L.v[0];
+                n_neg = L.at_n[cb + 1u] + L.v[1];
+                __syncthreads();
             }
         }
     }
-}
-
-__device__ inline u64 lr_comp(u64 e, int w)       // key << w | inverted index
-{
-    return (((e >> 32) & 0x7FFFFFFFull) << w) | (((1ull << w) - 1ull) - (e & 0xFFFFFFFFull));
-}
-
-// Visit the row's 2-byte list in groups of eight entries (one 16-byte load), four independent
-// loads in flight per thread: f(first position, the eight entries, number of valid ones).
-template <typename F>
-__device__ inline void lr_for_each_fine(const uint16_t* __restrict__ Lfine, u32 nL, F f)
-{
-    const uint4* __restrict__ q4 = (const uint4*)Lfine;
-    const u32 ng = (nL + 7u) / 8u;
-    for (u32 g0 = 0; g0 < ng; g0 += 4 * 1024) {
-        uint4 t[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) { const u32 g = g0 + (u32)u * 1024 + threadIdx.x; t[u] = g < ng ? q4[g] : make_uint4(0, 0, 0, 0); }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const u32 g = g0 + (u32)u * 1024 + threadIdx.x;
-            if (g < ng) {
-                const u32 v[8] = { t[u].x & 0xFFFFu, t[u].x >> 16, t[u].y & 0xFFFFu, t[u].y >> 16,
-                                   t[u].z & 0xFFFFu, t[u].z >> 16, t[u].w & 0xFFFFu, t[u].w >> 16 };
-                const u32 left = nL - g * 8u;
-                f(g * 8u, v, left < 8u ? left : 8u);
-            }
-        }
-    }
-}
-
-__global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a)
-{
-    // fine histogram of the list in LDS: kFB bins, positive count | negative count << 16
-    __shared__ u32 fh[kFB];                      // later: members of the boundary bins
-    __shared__ u64 cutmem[kCutCap];              // members of the cut bin
-    __shared__ u32 tpre_p[1024], tpre_n[1024];   // first class rank of each thread's group of bins
-    __shared__ u32 bitmap[kFB / 32];
-    __shared__ u32 scr[1024 / kWave + 1];
-    __shared__ u32 tgbin[kMaxB2], tgrem[kMaxB2], tcnt[kMaxB2];
-    __shared__ u32 s_cut[3], s_n[4];
-    __shared__ u64 s_thrK;
-    constexpr int BPT = kFB / 1024;              // bins per thread
-    const int tid = threadIdx.x;
-    const int64_t r = blockIdx.x;
-    if (a.fallback[r]) return;
-    const int M = a.M, Mn = a.Mn, B2 = a.M + a.Mn, w = a.w;
-    u32* st = a.rowst + (size_t)r * 16;
-    const u32 nL = st[2];
-    const u64* __restrict__ L = a.L + (size_t)r * a.capL;
-    const uint16_t* __restrict__ Lfine = a.Lfine + (size_t)r * a.capL;
-    const u32 k = (u32)a.k;
-
-    for (int i = tid; i < kFB; i += 1024) fh[i] = 0;
-    for (int i = tid; i < kFB / 32; i += 1024) bitmap[i] = 0;
-    if (tid < kMaxB2) tcnt[tid] = 0;
-    if (tid == 0) { s_cut[0] = 0xFFFFFFFFu; s_n[0] = 0; s_n[1] = 0; s_n[2] = 0; s_n[3] = 0; s_thrK = 0; }
-    __syncthreads();
-    lr_for_each_fine(Lfine, nL, [&](u32, const u32 (&v)[8], u32 nv) {
-#pragma unroll
-        for (int d = 0; d < 8; ++d)
-            if ((u32)d < nv) atomicAdd(&fh[v[d] & 0x7FFFu], (v[d] >> 15) ? 0x10000u : 1u);
-    });
-    __syncthreads();
-
-    // (a) class ranks from the top: thread t owns the BPT bins below kFB - BPT * t
-    const int hi = kFB - tid * BPT;
-    u32 cp[BPT], cn[BPT];
-    u32 lp = 0, ln = 0;
-#pragma unroll
-    for (int j = 0; j < BPT; ++j) { const u32 c = fh[hi - 1 - j]; cp[j] = c & 0xFFFFu; cn[j] = c >> 16; lp += cp[j]; ln += cn[j]; }
-    u32 tp, tn;
-    const u32 ep = block_excl_scan<1024>(lp, scr, &tp);
-    const u32 en = block_excl_scan<1024>(ln, scr, &tn);
-    tpre_p[tid] = ep; tpre_n[tid] = en;
-    // a 16-bit count that wrapped shows up as a wrong total: such rows are redone generically
-    if (tp + tn != nL) { if (tid == 0) a.fallback[r] = 1u; return; }
-    {
-        u32 ap = ep, an = en;
-#pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            const u32 cnt = cp[j] + cn[j];
-            if (nL > k && cnt && ap + an <= k - 1 && k - 1 < ap + an + cnt) { s_cut[0] = (u32)(hi - 1 - j); s_cut[1] = ap; s_cut[2] = an; }
-            ap += cp[j]; an += cn[j];
-        }
-    }
-    __syncthreads();
-
-    // (b) ATKF cut: the comp of overall rank k-1 inside the cut bin
-    u32 n_pos = tp, n_neg = tn;
-    u64 thrK = 0;
-    if (nL > k) {
-        const u32 cut = s_cut[0];
-        // positions first, then the members themselves with all loads in flight together
-        lr_for_each_fine(Lfine, nL, [&](u32 p, const u32 (&v)[8], u32 nv) {
-            u32 hits = 0;
-#pragma unroll
-            for (int d = 0; d < 8; ++d) hits |= ((u32)d < nv && (v[d] & 0x7FFFu) == cut) ? 1u << d : 0u;
-            while (hits) {
-                const u32 d = (u32)__builtin_ctz(hits);
-                hits &= hits - 1u;
-                const u32 slot = atomicAdd(&s_n[0], 1u);
-                if (slot < (u32)kCutCap) cutmem[slot] = (u64)(p + d);
-            }
-        });
-        __syncthreads();
-        const u32 nm = s_n[0];
-        if (nm > (u32)kCutCap) { if (tid == 0) a.fallback[r] = 1u; return; }
-        for (u32 i = tid; i < nm; i += 1024) {
-            const u64 e = L[(u32)cutmem[i]];
-            cutmem[i] = (e & kTop) | lr_comp(e, w);
-        }
-        __syncthreads();
-        const u32 rem = (k - 1) - (s_cut[1] + s_cut[2]);
-        for (u32 i = tid; i < nm; i += 1024) {
-            const u64 me = cutmem[i] & ~kTop;
-            u32 gt = 0;
-            for (u32 j = 0; j < nm; ++j) gt += (cutmem[j] & ~kTop) > me ? 1u : 0u;
-            if (gt == rem) s_thrK = me;
-            if (gt <= rem) atomicAdd((cutmem[i] & kTop) ? &s_n[2] : &s_n[1], 1u);
-        }
-        __syncthreads();
-        thrK = s_thrK;
-        n_pos = s_cut[1] + s_n[1];
-        n_neg = s_cut[2] + s_n[2];
-    }
-
-    // (c) block boundaries: class ranks j*K-1, one thread per boundary: first the group of
-    //     bins (binary search over the threads' first ranks), then the bin inside the group
     const u32 Kc0 = n_pos / (u32)M, Kc1 = n_neg / (u32)Mn;
-    const int nt0 = Kc0 ? M - 1 : 0, nt1 = Kc1 ? Mn - 1 : 0, ntg = nt0 + nt1;
-    if (tid < ntg) {
-        const int cls = tid >= nt0 ? 1 : 0;
-        const int j = (cls ? tid - nt0 : tid) + 1;
-        const u32 Rk = (u32)j * (cls ? Kc1 : Kc0) - 1u;
-        const u32* tpre = cls ? tpre_n : tpre_p;
-        int lo = 0, hi2 = 1023;                      // last group whose first rank is <= Rk
-        while (lo < hi2) {
-            const int mid = (lo + hi2 + 1) >> 1;
-            if (tpre[mid] <= Rk) lo = mid; else hi2 = mid - 1;
+    if (!bad) {
+        if (tid < 2 * B2) {
+            const int b = tid >> 1, c = b >= M ? 1 : 0, m = b - c * M, Ms = c ? Mn : M;
+            const u32 K = c ? Kc1 : Kc0, cnt = m < Ms - 1 ? K : (c ? n_neg : n_pos) - K * (u32)(Ms - 1);
+            u32 bin = 0xFFFFFFFFu, rem = 0;          // an empty block has no elements
+            if (cnt) {
+                const u32 rank = (u32)m * K + ((tid & 1) ? cnt - 1u : 0u);
+                const u32* at = c ? L.at_n : L.at_p;
+                int lo = 0, hi = kFB - 1;            // the last bin with more than `rank` entries at or above it
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (at[mid] > rank) lo = mid; else hi = mid - 1;
+                }
+                bin = (u32)lo;
+                rem = rank - at[lo + 1];
+            }
+            L.tg_bin[tid] = bin; L.tg_rem[tid] = rem; L.tg_comp[tid] = ~0ull;
         }
-        u32 acc = tpre[lo];
-        const int top = kFB - lo * BPT;
-        u32 bin = (u32)(top - 1);
-        for (int jj = 0; jj < BPT; ++jj) {           // the bin of the group that holds rank Rk
-            const u32 c = fh[top - 1 - jj];
-            const u32 cc = cls ? c >> 16 : c & 0xFFFFu;
-            if (Rk < acc + cc) { bin = (u32)(top - 1 - jj); break; }
-            acc += cc;
-        }
-        tgbin[tid] = bin;
-        tgrem[tid] = Rk - acc;
-        atomicOr(&bitmap[bin >> 5], 1u << (bin & 31));
-    }
-    __syncthreads();                                 // the histogram is dead from here on
-    u64* tmem = (u64*)fh;                            // [ntg][tcap]
-    const u32 tcap = ntg ? (u32)(kFB / 2) / (u32)ntg : 1u;
-    // members of the boundary bins: their positions go to a flat list first (the cut's storage is
-    // free now), then one thread per hit finds its boundaries and fetches the member
-    u32* hitpos = (u32*)cutmem;
-    constexpr u32 kHitCap = 2 * kCutCap;
-    if (tid == 0) s_n[3] = 0;
-    __syncthreads();
-    lr_for_each_fine(Lfine, nL, [&](u32 p, const u32 (&v)[8], u32 nv) {
-        u32 hits = 0;
+        __syncthreads();
+        if (tid < kWave) {                           // groups: a target opens one unless the target before it lies in the same bin
+            u32 lead = 0, room = 0;
 #pragma unroll
-        for (int d = 0; d < 8; ++d) {
-            const u32 b = v[d] & 0x7FFFu;
-            hits |= ((u32)d < nv && ((bitmap[b >> 5] >> (b & 31u)) & 1u)) ? 1u << d : 0u;
+            for (int j = 0; j < 4; ++j) {
+                const int t = tid * 4 + j;
+                if (t >= 2 * B2) continue;
+                const u32 b = L.tg_bin[t], c = (t >> 1) >= M ? 1u : 0u;
+                const bool same = t > 0 && L.tg_bin[t - 1] == b && (((t - 1) >> 1) >= M ? 1u : 0u) == c;
+                if (b != 0xFFFFFFFFu && !same) { lead |= 1u << j; room += at_c(c, b) - at_c(c, b + 1u); }
+            }
+            const u32 nl = (u32)__popc(lead);
+            const u32 incl = wave_scan_dpp(nl), incr = wave_scan_dpp(room);
+            u32 g = incl - nl, at = incr - room;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int t = tid * 4 + j;
+                if (!((lead >> j) & 1u)) continue;
+                const u32 b = L.tg_bin[t], c = (t >> 1) >= M ? 1u : 0u;
+                L.g_bin[g] = b; L.g_cls[g] = c; L.g_start[g] = at; L.g_fill[g] = 0; L.g_t0[g] = (u32)t;
+                at += at_c(c, b) - at_c(c, b + 1u);
+                ++g;
+            }
+            if (tid == kWave - 1) { L.g_start[incl] = incr; L.g_t0[incl] = (u32)(2 * B2); L.v[2] = incl; }
         }
-        while (hits) {
-            const u32 d = (u32)__builtin_ctz(hits);
-            hits &= hits - 1u;
-            const u32 slot = atomicAdd(&s_n[3], 1u);
-            if (slot < kHitCap) hitpos[slot] = p + d;
-        }
-    });
-    __syncthreads();
-    const u32 nhits = s_n[3];
-    if (nhits > kHitCap) { if (tid == 0) a.fallback[r] = 1u; return; }
-    for (u32 i = tid; i < nhits; i += 1024) {
-        const u32 p = hitpos[i];
-        const u64 e = L[p];
-        const u32 v = Lfine[p], d = v & 0x7FFFu;
-        const int cls = (int)(v >> 15);
-        const int t0 = cls ? nt0 : 0, t1 = cls ? ntg : nt0;
-        for (int t = t0; t < t1; ++t) {
-            if (tgbin[t] == d) {
-                const u32 slot = atomicAdd(&tcnt[t], 1u);
-                if (slot < tcap) tmem[(u32)t * tcap + slot] = lr_comp(e, w);
+        __syncthreads();
+        const int ng = (int)L.v[2];
+        const u32 nm = L.g_start[ng];
+        if (nm > (u32)kMemCap) bad = true;
+        else {
+            gather(ng);
+            for (u32 i = (u32)tid; i < nm; i += 1024) {
+                const u32 g = L.mem_g[i] & 0xFFu, m1 = L.g_start[g + 1];
+                const u64 me = L.mem[i];
+                u32 gt = 0;
+                for (u32 j = L.g_start[g]; j < m1; ++j) gt += L.mem[j] > me ? 1u : 0u;
+                for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t)
+                    if (L.tg_bin[t] == L.g_bin[g] && L.tg_rem[t] == gt) L.tg_comp[t] = me & ~kTop;
+            }
+            __syncthreads();
+            // per tile: entries of the class from the block's last element up
+            for (u32 i = (u32)tid; i < nm; i += 1024) {
+                const u32 g = L.mem_g[i] & 0xFFu;
+                const u64 me = L.mem[i] & ~kTop;
+                for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t)
+                    if ((t & 1u) && me >= L.tg_comp[t]) atomicAdd(&pair[(size_t)(t >> 1) * S + (L.mem_g[i] >> 8)], 1u);
+            }
+            for (int b = tid; b < B2; b += 1024) {
+                const u64 first = L.tg_comp[2 * b], last = L.tg_comp[2 * b + 1];
+                a.thr[(size_t)r * B2 + b] = last;
+                a.vminb[(size_t)r * B2 + b] = last == ~0ull ? 0u : (u32)(last >> w);
+                a.vmaxb[(size_t)r * B2 + b] = last == ~0ull ? 0u : (u32)(first >> w);
+            }
+            for (int b = tid; b <= B2; b += 1024) {  // K, ..., K, K + remainder per class
+                const int c = b >= M ? 1 : 0, m = b - c * M;
+                a.blk_start[(size_t)r * (B2 + 1) + b] = b == B2 ? n_pos + n_neg : (c ? n_pos : 0u) + (u32)m * (c ? Kc1 : Kc0);
+            }
+            if (tid == 0) { st[kStNpos] = n_pos; st[kStNneg] = n_neg; }
+            // block of every fine bin, for the split: only the bins that hold a boundary need a look at the element
+#pragma unroll
+            for (u32 c = 0; c < 2u; ++c) {
+                if (B2 > kMapBlocks) break;
+                const u32* at = c ? L.at_n : L.at_p;
+                const u32 nc = c ? n_neg : n_pos, K = c ? Kc1 : Kc0, Ms = (u32)(c ? Mn : M), b0 = c ? (u32)M : 0u;
+                const float rK = 1.0f / (float)(K ? K : 1u);
+                auto block_of = [&](u32 rank) -> u32 {
+                    if (rank >= nc) return kMapNone;
+                    u32 q = K ? (u32)((float)rank * rK) : Ms - 1u;
+                    if (K) { if (q * K > rank) --q; if ((q + 1u) * K <= rank) ++q; }        // (the product is off by less than one)
+                    return b0 + (q < Ms ? q : Ms - 1u);
+                };
+                u32 wd = 0;
+#pragma unroll
+                for (u32 j = 0; j < 4u; ++j) {
+                    const u32 hi = at[tid * 4 + j], lo = at[tid * 4 + j + 1];
+                    u32 v = kMapNone;
+                    if (hi > lo) {
+                        const u32 v0 = block_of(lo), v1 = block_of(hi - 1u);
+                        const u32 next = v0 == b0 + Ms - 1u ? kMapNone : v0 + 1u;
+                        v = v0 | (v1 != v0 ? kMapMixed : 0u) | (v1 != v0 && v1 != next ? kMapMany : 0u);
+                    }
+                    wd |= v << (8u * j);
+                }
+                ((u32*)(a.map + ((size_t)r * 2 + c) * kFB))[tid] = wd;
             }
         }
     }
-    __syncthreads();
-    int over = 0;
-    if (tid < ntg && tcnt[tid] > tcap) over = 1;
-    if (__syncthreads_or(over)) { if (tid == 0) a.fallback[r] = 1u; return; }
-    const u32 nslots = (u32)ntg * tcap;              // <= kFB / 2
-    u64* __restrict__ thr = a.thr + (size_t)r * (1 + kMaxB2);
-    for (u32 i = tid; i < nslots; i += 1024) {       // the member with exactly `rem` class-mates above it
-        const u32 t = i / tcap, sl = i - t * tcap, cnt = tcnt[t];
-        if (sl < cnt) {
-            const u64 me = tmem[i];
-            u32 gt = 0;
-            for (u32 j = 0; j < cnt; ++j) gt += tmem[t * tcap + j] > me ? 1u : 0u;
-            if (gt == tgrem[t]) thr[1 + t] = me | ((int)t >= nt0 ? 0ull : kTop);
-        }
-    }
-    if (tid == 0) {
-        thr[0] = thrK;
-        st[3] = n_pos; st[4] = n_neg; st[5] = Kc0; st[6] = Kc1; st[7] = (u32)ntg; st[8] = (u32)nt0;
-    }
-    for (int b = tid; b <= B2; b += 1024) {          // K, ..., K, K + remainder per class
-        u32 v;
-        if (b == B2) v = n_pos + n_neg;
-        else { const int s2 = b >= M ? 1 : 0, m = b - s2 * M; v = (s2 ? n_pos : 0u) + (u32)m * (s2 ? Kc1 : Kc0); }
-        a.blk_start[(size_t)r * (B2 + 1) + b] = v;
-    }
-}
-
-__global__ __launch_bounds__(256) void lr_blockcount_kernel(LargeArgs a)
-{
-    __shared__ u64 thr_s[1 + kMaxB2];
-    __shared__ u32 cnt[kMaxB2], kmin[kMaxB2], kmax[kMaxB2];
-    const int tid = threadIdx.x, lc = blockIdx.x;
-    const int64_t r = blockIdx.y;
-    if (a.fallback[r]) return;
-    const int M = a.M, Mn = a.Mn, B2 = a.M + a.Mn, w = a.w;
-    const u32* st = a.rowst + (size_t)r * 16;
-    const u32 nL = st[2];
-    const u32 Kc[2] = { st[5], st[6] };
-    const int ntg = (int)st[7], nt0 = (int)st[8];
-    const u64* __restrict__ L = a.L + (size_t)r * a.capL;
-    uint8_t* __restrict__ Lblk = a.Lblk + (size_t)r * a.capL;
-    const u32 p0 = (u32)lc * kLCE, p1 = p0 + kLCE < nL ? p0 + kLCE : nL;
-    constexpr int NJ = kLCE / 256;
-    u64 ev[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) { const u32 p = p0 + (u32)j * 256 + (u32)tid; ev[j] = p < p1 ? L[p] : 0ull; }   // all loads in flight at once
-    for (int i = tid; i <= ntg; i += 256) thr_s[i] = a.thr[(size_t)r * (1 + kMaxB2) + i];
-    for (int b = tid; b < B2; b += 256) { cnt[b] = 0; kmin[b] = 0xFFFFFFFFu; kmax[b] = 0; }
-    __syncthreads();
-    const u64 thrK = thr_s[0];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const u32 p = p0 + (u32)j * 256 + (u32)tid;
-        if (p >= p1) break;
-        const u64 e = ev[j];
-        const u64 comp = lr_comp(e, w);
-        u32 b = 255u;
-        if (comp >= thrK) {
-            const u32 cls = (u32)(e >> 63);
-            const u64 cx = comp | (cls ? 0ull : kTop);
-            int lo = 0, hi = ntg;                   // boundaries above cx (they are sorted, largest first)
-            while (lo < hi) { const int mid = (lo + hi) >> 1; if (thr_s[1 + mid] > cx) lo = mid + 1; else hi = mid; }
-            const u32 m = Kc[cls] ? (u32)lo - (cls ? (u32)nt0 : 0u) : (u32)((cls ? Mn : M) - 1);
-            b = cls * (u32)M + m;
-            const u32 key = (u32)(e >> 32) & 0x7FFFFFFFu;
-            atomicAdd(&cnt[b], 1u);
-            atomicMin(&kmin[b], key);
-            atomicMax(&kmax[b], key);
-        }
-        Lblk[p] = (uint8_t)b;
-    }
-    __syncthreads();
-    for (int b = tid; b < B2; b += 256) {
-        a.blkcnt[((size_t)r * a.LC + lc) * B2 + b] = cnt[b];
-        if (cnt[b]) { atomicMin(&a.vminb[r * B2 + b], kmin[b]); atomicMax(&a.vmaxb[r * B2 + b], kmax[b]); }
-    }
-}
-
-template <int DT>
-__global__ __launch_bounds__(256) void lr_scatter_kernel(LargeArgs a)
-{
-    __shared__ u32 base[kMaxB2];
-    __shared__ u32 cw[4][kMaxB2];
-    const int tid = threadIdx.x, lc = blockIdx.x, wid = tid / kWave;
-    const int64_t r = blockIdx.y;
-    if (a.fallback[r]) return;
-    const int B2 = a.M + a.Mn;
-    const u32 nL = a.rowst[(size_t)r * 16 + 2];
-    if ((u32)lc * kLCE >= nL) return;
-    const u64* __restrict__ L = a.L + (size_t)r * a.capL;
-    const uint8_t* __restrict__ Lblk = a.Lblk + (size_t)r * a.capL;
-    // this thread's entries, all loads in flight at once
-    constexpr int NJ = kLCE / 256;
-    u32 bl[NJ];
-    u64 ev[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const u32 p = (u32)lc * kLCE + (u32)j * 256 + (u32)tid;
-        bl[j] = p < nL ? (u32)Lblk[p] : 255u;
-        ev[j] = p < nL ? L[p] : 0ull;
-    }
-    for (int b = tid; b < B2; b += 256) {
-        base[b] = a.blk_start[(size_t)r * (B2 + 1) + b];
-        for (int v2 = 0; v2 < 4; ++v2) cw[v2][b] = 0;
-    }
-    __syncthreads();
-    {   // plus the block counts of the list chunks before this one (contiguous: [chunk][block])
-        const u32* __restrict__ bc = a.blkcnt + (size_t)r * a.LC * B2;
-        const u32 tot = (u32)lc * (u32)B2;
-        for (u32 i0 = (u32)tid; i0 < tot; i0 += 256 * 8) {
-            u32 t[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) { const u32 i = i0 + (u32)u * 256; t[u] = i < tot ? bc[i] : 0u; }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) { const u32 i = i0 + (u32)u * 256; if (t[u]) atomicAdd(&base[i % (u32)B2], t[u]); }
-        }
-    }
-    __syncthreads();
-    int nbits = 0;
-    while ((1 << nbits) < B2) ++nbits;
-    u32* __restrict__ bo_idx = a.bo_idx + (size_t)r * (size_t)a.k;
-    u32* __restrict__ bo_val = a.bo_val + (size_t)r * (size_t)a.k;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const bool kept = bl[j] != 255u;
-        const u32 b = kept ? bl[j] : 0u;
-        const u64 e = ev[j];
-        const u64 km = __ballot(kept);
-        u32 plo = (u32)km, phi = (u32)(km >> 32);
-        for (int bit = 0; bit < nbits; ++bit) {
-            const u32 onm = (u32)__builtin_amdgcn_sbfe((int)b, (u32)bit, 1u);
-            const u64 bal = __ballot(onm != 0u);
-            plo &= ~((u32)bal ^ onm);
-            phi &= ~((u32)(bal >> 32) ^ onm);
-        }
-        const u32 before = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
-        if (kept && before == 0) cw[wid][b] = (u32)__popc(plo) + (u32)__popc(phi);
+    if (bad) {                                       // rare: the row goes to its slot by the generic encoder
         __syncthreads();
-        if (kept) {
-            u32 pos = base[b] + before;
-            for (int v2 = 0; v2 < wid; ++v2) pos += cw[v2][b];
-            if ((int64_t)pos < a.k) {
-                bo_idx[pos] = (u32)e;
-                bo_val[pos] = DT == 0 ? ((u32)(e >> 32) & 0x7FFFFFFFu) : (((u32)(e >> 32) & 0x7FFFu) << 16);
+        if (tid == 0) st[kStFlag] = 1u;
+        enc_generic_rows<DT, 1024>(ea, r, r + 1, *(GenericLds<1024>*)lds);
+        __syncthreads();
+        // its block-ordered arrays, counts, ranges and bitwidths are what the pack stage reads
+        const u32 gp = a.mv.n_pos[r], gn = a.mv.n_neg[r], K0 = gp / (u32)M, K1 = gn / (u32)Mn;
+        const bool on = tid < B2;
+        u32 q = 0, cnt = 0;
+        float vmin = 0.f, vmax = 0.f;
+        if (on) {
+            const int c = tid >= M ? 1 : 0, m = tid - c * M, Ms = c ? Mn : M;
+            const u32 K = c ? K1 : K0;
+            cnt = m < Ms - 1 ? K : (c ? gn : gp) - K * (u32)(Ms - 1);
+            a.blk_start[(size_t)r * (B2 + 1) + tid] = (c ? gp : 0u) + (u32)m * K;
+            if (tid == B2 - 1) a.blk_start[(size_t)r * (B2 + 1) + B2] = gp + gn;
+            const size_t mi = (size_t)r * B2 + tid;
+            q = a.mv.q[mi];
+            vmin = a.mv.vmin[mi]; vmax = a.mv.vmax[mi];
+        }
+        __syncthreads();
+        lr_finish_row<DT>(a, r, gp, gn, on, q & 0x7Fu, q & 0x80u, cnt, vmin, vmax, L.mem);
+    }
+}
+
+// ---- 4. split -------------------------------------------------------------------------------------
+// LDS carve-up (bytes); NE: entries per thread and step
+struct LrSplitLds { int thr, sums, place, val, map, gbase, lstart, cnt, inv, vmin, e, er, tab, lidx, wcnt, blk, total; };
+// room for a step's entries with every block padded to whole groups of NE
+__host__ __device__ inline int lr_split_room(int NE, int B2) { return kTileThreads * NE + NE * (B2 + 1); }     // (and one group for what is not kept)
+__host__ __device__ inline LrSplitLds lr_split_carve(int NE, int B2, int nq)
+{
+    LrSplitLds o;
+    const int EC = lr_split_room(NE, B2);
+    int p = 0;
+    o.thr = p;    p += 8 * (B2 > (int)kMapNone + 1 ? B2 : (int)kMapNone + 1);
+    o.sums = p;   p += 8 * B2 * (nq + 1);
+    o.place = p;  p += 8 * B2;
+    o.val = (p + 15) & ~15; p = o.val + 4 * EC;
+    o.map = p;    p += 2 * kFB;
+    o.gbase = p;  p += 4 * B2;
+    o.lstart = p; p += 4 * (B2 + 1);
+    o.cnt = p;    p += 4 * B2;
+    o.inv = p;    p += 4 * B2 * nq;
+    o.vmin = p;   p += 4 * B2;
+    o.e = p;      p += 4 * B2;
+    o.er = p;     p += 4 * B2;
+    o.tab = p;    p += 2 * kTabSize;
+    o.lidx = p;   p += 2 * EC;
+    o.wcnt = p;   p += 2 * (kTileThreads / kWave) * B2;
+    o.blk = p;    p += EC / NE;
+    o.total = (p + 15) & ~15;
+    return o;
+}
+
+// stores and loads between workgroups of one launch, past the caches of one XCD
+__device__ inline void agent_store(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline u64 agent_load(const u64* p) { return __hip_atomic_load(const_cast<u64*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// ABQ sums of the first `left` of NE values of one block (keys as fp32 patterns): acc[t] += squared residual (or DS mismatch) at the
+// t-th bitwidth; returns the energy.  inv15: 2^15 L / (range brought to [1, 2)) per bitwidth, 0 for a block of range 0.
+// MODE 0: squared error, bitwidths up to 8; 1: squared error, any bitwidth; 2: Eq. "DS"
+template <int DT, int NE, int NQ, int MODE>
+__device__ inline u64 lr_abq_entries(const LargeArgs& a, int nq, const u32 (&vv)[NE], u32 left, float vmin, int e, int er, const float* inv15,
+                                     u32 (&acc)[NQ ? NQ : kMaxQ])
+{
+    constexpr int QN = NQ ? NQ : kMaxQ;
+    float inv[QN];
+#pragma unroll
+    for (int t = 0; t < QN; ++t) inv[t] = (NQ || t < nq) ? inv15[t] : 0.f;
+    float inv_top = 0.f;
+    const int top = nq - 1, qtop = a.qlist[top];
+    if (MODE == 2) inv_top = inv15[top] * 0x1p-15f;
+    u64 accE = 0;
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+        const bool in = (u32)j < left;
+        const float av = in ? __uint_as_float(vv[j]) : vmin;   // (an offset of zero adds nothing to any residual)
+        const u64 A = in ? (u64)(u32)rintf(ldexpf(av, 20 - e)) : 0ull;     // 20-bit energy grid scaled to vmax
+        accE += A * A;
+        const float d = to_unit(av - vmin, er);                // (range 0: every offset is zero)
+        if (MODE == 2) {
+            // | (code at q_bit >> (q_bit - q)) - code at q | for every lower bitwidth
+            const u32 c0 = (u32)rintf(d * inv_top);               // within [0, 2^q - 1]: no clamp needed
+#pragma unroll
+            for (int t = 0; t < QN; ++t) {
+                if ((NQ || t < nq) && t < top) {
+                    const u32 c = (u32)rintf(d * (inv[t] * 0x1p-15f));
+                    const u32 ref = c0 >> (u32)(qtop - a.qlist[t]);
+                    acc[t] += ref > c ? ref - c : c - ref;
+                }
+            }
+        } else {
+            // residual on the 2^-15 grid: rint(y * 2^15) reduced to 15 signed bits (Sec. 3.2.1 metric
+            // in the code domain); bitwidths up to 8 keep y * 2^15 below 2^23, where adding 2^23
+            // rounds to the integer grid with the same round-half-even
+#pragma unroll
+            for (int t = 0; t < QN; ++t) {
+                if (NQ || t < nq) {
+                    const u32 zi = MODE == 0 ? __float_as_uint(d * inv[t] + 8388608.0f) : (u32)rintf(d * inv[t]);
+                    const int rho = __builtin_amdgcn_sbfe((int)zi, 0u, 15u);
+                    acc[t] += (u32)(rho * rho);
+                }
             }
         }
-        __syncthreads();
-        for (int bb = tid; bb < B2; bb += 256) {
-            u32 s = 0;
-            for (int v2 = 0; v2 < 4; ++v2) { s += cw[v2][bb]; cw[v2][bb] = 0; }
-            base[bb] += s;
-        }
-        __syncthreads();
     }
+    return accE;
 }
 
 // NQ > 0: the number of allowed bitwidths is known at compile time; NQ == 0: any number up to 16.
-template <int DT, int NQ>
-__global__ __launch_bounds__(256) void lr_abq_kernel(LargeArgs a)
+template <int DT, int NE, int NQ>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void lr_split_kernel(LargeArgs a)
 {
     typedef Elem<DT> E;
-    constexpr int QN = NQ ? NQ : kMaxQ;
-    constexpr int NJ = kPCH / 256;               // entries per thread: u32 partial sums hold 8 residuals of 2^28
-    static_assert(NJ <= 8, "u32 partial sums");
-    __shared__ u32 bs[kMaxB2 + 1];
-    __shared__ float vminf[kMaxB2];
-    __shared__ int e_tab[kMaxB2], er_tab[kMaxB2], degen[kMaxB2];
-    __shared__ float inv_tab[kMaxB2][kMaxQ];
-    __shared__ u64 sums[kMaxB2][kMaxQ + 1];
-    const int tid = threadIdx.x, pc = blockIdx.x;
+    constexpr int QN = NQ ? NQ : kMaxQ, NWV = kTileThreads / kWave, EC = kTileThreads * NE;
+    static_assert(NE <= 8, "u32 partial sums hold 8 residuals of 2^28");
+    extern __shared__ __align__(16) unsigned char smem8[];
+    const int tid_in = threadIdx.x, tid = tid_in, s = blockIdx.x, wv = tid / kWave, w = a.w, M = a.M, Mn = a.Mn, B2 = M + Mn, S = a.S;
+    const int nq = NQ ? NQ : a.nq;
+    const u32 lane = lane_id();
     const int64_t r = blockIdx.y;
-    // the values first: their loads need nothing but the launch geometry (positions beyond the
-    // row's count hold leftovers and are never used) and are the longest wait of the kernel
-    const u32 p0 = (u32)pc * kPCH;
-    const u32* __restrict__ bo_val = a.bo_val + (size_t)r * (size_t)a.k;
-    u32 vb[NJ];
+    u32* st = a.rowst + (size_t)r * 16;
+    const u32 seg0 = a.seg[((size_t)r * S + s) * 2], ntp = a.seg[((size_t)r * S + s) * 2 + 1];
+    if (st[kStFlag]) return;                         // encoded by the bounds stage
+    const u32 nt = (ntp & 0xFFFFu) + (ntp >> 16);
+    const LrSplitLds o = lr_split_carve(NE, B2, nq);
+    u64* thr = (u64*)(smem8 + o.thr);
+    u64* sums = (u64*)(smem8 + o.sums);
+    u32* val = (u32*)(smem8 + o.val);
+    u32* gbase = (u32*)(smem8 + o.gbase);
+    u32* lstart = (u32*)(smem8 + o.lstart);
+    float* invt = (float*)(smem8 + o.inv);
+    float* vminf = (float*)(smem8 + o.vmin);
+    int* e_tab = (int*)(smem8 + o.e);
+    int* er_tab = (int*)(smem8 + o.er);
+    uint16_t* lidx = (uint16_t*)(smem8 + o.lidx);
+    uint16_t* wcnt = (uint16_t*)(smem8 + o.wcnt);
+    uint8_t* blk = (uint8_t*)(smem8 + o.blk);        // block of every group of NE places
+    u32* cntb = (u32*)(smem8 + o.cnt);
+    uint2* place = (uint2*)(smem8 + o.place);        // position of a block's entry in the row minus its place here; end of its places
+    constexpr u32 kNone = 0xFFu;                     // not kept
+    constexpr int kMaskBlocks = 32;
+    const int room = lr_split_room(NE, B2);
+    static_assert(8 * (kTileThreads / kWave) * (kMaskBlocks + 1) <= 4 * kTileThreads + 4 * kMaskBlocks, "the masks fit the sorted entries");
+    uint8_t* map = (uint8_t*)(smem8 + o.map);
+    uint16_t* tab = (uint16_t*)(smem8 + o.tab);
+    const u32 Blo = st[kStBlo], nb = st[kStNb];
+    const LrList list(a, r);
+    const u32* __restrict__ Lraw = list.raw + seg0;
+    const uint16_t* __restrict__ Lidx = list.idx + seg0;
+    const int head = RowChunks<DT>(a.x, r, a.N).head;
+    const u32 tile0 = (u32)(s * a.tile - head);       // index of the tile's element 0 (modulo 2^32)
+    const bool want_sums = !a.lad.on;
+
+    u32 rw[NE], ix[NE];
+    auto fetch = [&](u32 e0) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) { const u32 p = p0 + (u32)j * 256 + (u32)tid; vb[j] = (int64_t)p < a.k ? bo_val[p] : 0u; }
-    if (a.fallback[r]) return;
-    const int B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq;
-    const u32* st = a.rowst + (size_t)r * 16;
-    const u32 n = st[3] + st[4];
-    const u32 p1 = p0 + kPCH < n ? p0 + kPCH : n;
-    if (p0 >= n) return;
-    for (int b = tid; b <= B2; b += 256) bs[b] = a.blk_start[(size_t)r * (B2 + 1) + b];
-    __syncthreads();
-    for (int b = tid; b < B2; b += 256) {
-        const u32 cnt = bs[b + 1] - bs[b];
-        int dg = 1, e = 0, er = 0;
-        float rng1 = 1.f, vmin = 0.f;
-        if (cnt) {
-            const u32 lo = E::value_bits(a.vminb[r * B2 + b]), hi = E::value_bits(a.vmaxb[r * B2 + b]);
-            vmin = __uint_as_float(lo);
-            const float rng = __uint_as_float(hi) - vmin;
-            dg = !(rng > 0.f);                       // only a range of exactly 0 is degenerate
-            if (!dg) { er = range_exp(rng); rng1 = unit_range(rng, er); }
-            e = ilogb_bits(hi) + 1;
+        for (int j = 0; j < NE; ++j) {
+            const u32 p = e0 + (u32)(wv * NE + j) * kWave + lane;
+            rw[j] = p < nt ? Lraw[p] : 0u;
+            ix[j] = p < nt ? (u32)Lidx[p] : 0u;
         }
-        vminf[b] = vmin; degen[b] = dg; e_tab[b] = e; er_tab[b] = er;
-        for (int t = 0; t < nq; ++t) {
-            inv_tab[b][t] = dg ? 0.f : (float)((1u << a.qlist[t]) - 1u) / rng1;
-            sums[b][t] = 0;
-        }
-        sums[b][kMaxQ] = 0;
+    };
+    fetch(0);
+    if (tid < B2) {
+        const size_t rb = (size_t)r * B2 + tid;
+        const u64 t = a.thr[rb];
+        thr[tid] = t;
+        gbase[tid] = a.blk_start[(size_t)r * (B2 + 1) + tid];
+        const u32 lo = E::value_bits(a.vminb[rb]), hi = E::value_bits(a.vmaxb[rb]);
+        const float vmin = __uint_as_float(lo), rng = __uint_as_float(hi) - vmin;
+        vminf[tid] = vmin;
+        er_tab[tid] = rng > 0.f ? range_exp(rng) : 0;                // only a range of exactly 0 is degenerate
+        e_tab[tid] = t != ~0ull ? ilogb_bits(hi) + 1 : 0;
     }
-    bool small_q = true;
-#pragma unroll
-    for (int t = 0; t < QN; ++t)
-        if ((NQ || t < nq) && a.qlist[t] > 8) small_q = false;
-    __syncthreads();
+    for (int i = tid; i < B2 * (nq + 1); i += kTileThreads) sums[i] = 0;
     {
-        int cur = -1;
-        u32 acc[QN];
-        u64 accE = 0;
-        float inv[QN], inv15[QN];
+        const u32* tg = (const u32*)(a.tab + (size_t)r * kTabSize);
+        if (tid < kTabSize / 2) ((u32*)tab)[tid] = tg[tid];
+        const uint4* mg = (const uint4*)(a.map + (size_t)r * 2 * kFB);
+        for (int i = tid; i < 2 * kFB / 16; i += kTileThreads) ((uint4*)map)[i] = mg[i];
+    }
+    __syncthreads();
+    for (int i = tid; i < B2 * nq; i += kTileThreads) {              // quantiser scales 2^15 L / (range brought to [1, 2))
+        const int b = i / nq, t = i - b * nq;
+        const size_t rb = (size_t)r * B2 + b;
+        const float rng = __uint_as_float(E::value_bits(a.vmaxb[rb])) - vminf[b];
+        invt[i] = rng > 0.f ? (float)((1u << a.qlist[t]) - 1u) / unit_range(rng, er_tab[b]) * 32768.0f : 0.f;      // (times 2^15: exact)
+    }
+    // the tile's place in every block: the entries of the tiles before it
+    for (int i = tid; i < B2 * s; i += kTileThreads) {
+        const int b = i / s, t = i - b * s;
+        if (thr[b] == ~0ull) continue;               // an empty block
+        const u32* pr = a.pair + ((size_t)r * B2 + b) * S + t;
+        const bool first = b == 0 || b == M || thr[b - 1] == ~0ull;
+        const u32 d = pr[0] - (first ? 0u : *(pr - S));
+        if (d) atomicAdd(&gbase[b], d);
+    }
+    int nbits = 0;
+    while ((1 << nbits) < B2) ++nbits;
+    const int mode = a.guard == 1 ? 2 : a.qlist[nq - 1] > 8 ? 1 : 0;      // (the bitwidths ascend)
+    u32* __restrict__ bo_idx = a.bo_idx + (size_t)r * (size_t)a.k;
+    u32* __restrict__ bo_val = a.bo_val + (size_t)r * (size_t)a.k;
+
+    for (u32 e0 = 0; e0 < nt; e0 += EC) {
+        // (an opaque copy: the addresses below are cheap, and hoisting all of them out of this loop, which runs once or
+        //  twice, spilled up to 50 registers: 68 against 64 us on a batch of 32 maps)
+        int tid = tid_in;
+        asm volatile("" : "+v"(tid));
+        const u32 lane = (u32)tid & (u32)(kWave - 1);
+        const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+        for (int i = tid; i < NWV * B2 / 2; i += kTileThreads) ((u32*)wcnt)[i] = 0;      // (16 * B2 counters)
+        __syncthreads();
+        // (a) block of every entry: that of the first element of its fine bin, or in the few bins that hold a boundary the
+        // next one if the threshold lies above it.  Straight-line code: the lookups of a lane's entries overlap.
+        u32 bk[NE], rank[NE];
+        if (B2 <= kMapBlocks) {
+            u32 many = 0;
 #pragma unroll
-        for (int t = 0; t < QN; ++t) { acc[t] = 0; inv[t] = 0.f; inv15[t] = 0.f; }
-        float vmin = 0.f;
-        int e = 0, dg = 1, er = 0;
-        auto flush = [&]() {
-            if (cur < 0) return;
-#pragma unroll
-            for (int t = 0; t < QN; ++t)
-                if ((NQ || t < nq) && acc[t]) { atomicAdd(&sums[cur][t], (u64)acc[t]); acc[t] = 0; }
-            if (accE) { atomicAdd(&sums[cur][kMaxQ], accE); accE = 0; }
-        };
-        const int top = nq - 1, qtop = a.qlist[top];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const u32 p = p0 + (u32)j * 256 + (u32)tid;
-            if (p >= p1) break;
-            int b = cur < 0 ? 0 : cur;
-            while (b < B2 - 1 && p >= bs[b + 1]) ++b;
-            if (b != cur) {
-                flush();
-                cur = b; vmin = vminf[b]; e = e_tab[b]; dg = degen[b]; er = er_tab[b];
-#pragma unroll
-                for (int t = 0; t < QN; ++t) {
-                    inv[t] = (NQ || t < nq) ? inv_tab[b][t] : 0.f;
-                    inv15[t] = inv[t] * 32768.0f;        // the scale is at most 2^16 - 1
-                }
+            for (int j = 0; j < NE; ++j) {
+                const u32 neg = rw[j] >> 31;
+                const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
+                bk[j] = map[neg * kFB + lr_fine_bin<DT>(lr_c32<DT>(key, tile0 + ix[j], w), tab, Blo, nb)];
             }
-            const float av = __uint_as_float(vb[j]);
-            const u64 A = (u64)(u32)rintf(ldexpf(av, 20 - e));     // 20-bit energy grid scaled to vmax
-            accE += A * A;
-            if (dg) continue;
-            const float d = to_unit(av - vmin, er);
-            if (a.guard == 1) {
-                // Eq. "DS": | (code at q_bit >> (q_bit - q)) - code at q | for every lower bitwidth
-                float inv_top = 0.f;
 #pragma unroll
-                for (int t = 0; t < QN; ++t) inv_top = t == top ? inv[t] : inv_top;
-                const u32 c0 = (u32)rintf(d * inv_top);               // within [0, 2^q - 1]: no clamp needed
-#pragma unroll
-                for (int t = 0; t < QN; ++t) {
-                    if ((NQ || t < nq) && t < top) {
-                        const u32 c = (u32)rintf(d * inv[t]);
-                        const u32 ref = c0 >> (u32)(qtop - a.qlist[t]);
-                        acc[t] += ref > c ? ref - c : c - ref;
-                    }
-                }
-            } else {
-                // residual on the 2^-15 grid: rint(y * 2^15) reduced to 15 signed bits (Sec. 3.2.1 metric
-                // in the code domain); bitwidths up to 8 keep y * 2^15 below 2^23, where adding 2^23
-                // rounds to the integer grid with the same round-half-even
-#pragma unroll
-                for (int t = 0; t < QN; ++t) {
-                    if (NQ || t < nq) {
-                        const u32 zi = small_q ? __float_as_uint(d * inv15[t] + 8388608.0f)
-                                               : (u32)rintf((d * inv[t]) * 32768.0f);
-                        const int rho = __builtin_amdgcn_sbfe((int)zi, 0u, 15u);
-                        acc[t] += (u32)(rho * rho);
-                    }
-                }
+            for (int j = 0; j < NE; ++j) {
+                const u32 p = e0 + (u32)(wv * NE + j) * kWave + lane;
+                const u32 neg = rw[j] >> 31, c1 = neg ? (u32)B2 : (u32)M;
+                const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
+                const u32 v = bk[j];
+                u32 b = v & kMapNone;
+                const bool step = (v & kMapMixed) && thr[b] > lr_comp(key, tile0 + ix[j], w);        // (thr has kMapNone + 1 readable words)
+                b = step ? b + 1u : b;
+                many |= v & kMapMany;
+                bk[j] = p < nt && (v & kMapNone) != kMapNone && b < c1 ? b : kNone;
             }
-        }
-        // The positions of a wavefront are consecutive, so its lanes are nearly always in one
-        // block: the sums are then added up across the wavefront first (16-bit and 22-bit
-        // pieces, so that the lane sums fit 32 bits) and one lane adds them to the table.
-        const int cur0 = __builtin_amdgcn_readfirstlane(cur);
-        if (__all(cur == cur0)) {
-            if (cur0 >= 0) {
+            if (__any(many != 0u)) {                 // a fine bin of more than two blocks
 #pragma unroll
-                for (int t = 0; t < QN; ++t) {
-                    if (NQ || t < nq) {
-                        const u32 lo16 = wave_sum(acc[t] & 0xFFFFu), hi16 = wave_sum(acc[t] >> 16);
-                        if ((tid & (kWave - 1)) == 0 && (lo16 | hi16)) atomicAdd(&sums[cur0][t], (u64)lo16 + ((u64)hi16 << 16));
-                    }
+                for (int j = 0; j < NE; ++j) {
+                    const u32 neg = rw[j] >> 31, c1 = neg ? (u32)B2 : (u32)M;
+                    const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
+                    const u64 cx = lr_comp(key, tile0 + ix[j], w);
+                    while (bk[j] != kNone && thr[bk[j]] > cx) bk[j] = bk[j] + 1u < c1 ? bk[j] + 1u : kNone;
                 }
-                const u32 e0 = wave_sum((u32)accE & 0x3FFFFFu), e1 = wave_sum((u32)(accE >> 22) & 0x3FFFFFu), e2 = wave_sum((u32)(accE >> 44));
-                if ((tid & (kWave - 1)) == 0 && (e0 | e1 | e2)) atomicAdd(&sums[cur0][kMaxQ], (u64)e0 + ((u64)e1 << 22) + ((u64)e2 << 44));
             }
         } else {
-            flush();
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                const u32 p = e0 + (u32)(wv * NE + j) * kWave + lane;
+                const u32 neg = rw[j] >> 31;
+                const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
+                const u64 cx = lr_comp(key, tile0 + ix[j], w);
+                int lo = neg ? M : 0, hi = neg ? B2 : M;
+                const int c1 = hi;
+                // (empty blocks have the largest threshold and sit before the class's last block)
+                while (lo < hi) { const int mid = (lo + hi) >> 1; if (thr[mid] > cx) lo = mid + 1; else hi = mid; }
+                bk[j] = p < nt && lo < c1 ? (u32)lo : kNone;
+            }
+        }
+        // (b) stable rank inside the wavefront's 64 * NE consecutive entries: a bit mask of the lanes per block and slot
+        // (in the storage of the sorted entries; row B2 takes what is not kept), or with many blocks one ballot per bit of
+        // the block number
+        if (B2 <= kMaskBlocks) {
+            const int MB = B2 + 1;
+            u64* mk = (u64*)val + wv * NE * MB;
+            uint16_t* pf = lidx + wv * NE * MB;
+            for (int i = (int)lane; i < NE * MB; i += kWave) mk[i] = 0;
+            wave_sync();
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                const int b = bk[j] != kNone ? (int)bk[j] : B2;
+                atomicOr((u32*)(mk + j * MB + b) + (lane >> 5), 1u << (lane & 31u));
+            }
+            wave_sync();
+            if ((int)lane < B2) {
+                u64 m[NE];
+                u32 run = 0;
+#pragma unroll
+                for (int j = 0; j < NE; ++j) m[j] = mk[j * MB + (int)lane];
+#pragma unroll
+                for (int j = 0; j < NE; ++j) { pf[j * MB + (int)lane] = (uint16_t)run; run += (u32)__popcll(m[j]); }
+                wcnt[wv * B2 + (int)lane] = (uint16_t)run;
+            }
+            wave_sync();
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                const int b = bk[j] != kNone ? (int)bk[j] : B2;
+                rank[j] = (u32)pf[j * MB + b] + mask_rank(mk[j * MB + b]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                const bool kept = bk[j] != kNone;
+                const u32 b = kept ? bk[j] : 0u;
+                const u64 km = __ballot(kept);
+                u32 plo = (u32)km, phi = (u32)(km >> 32);
+                for (int bit = 0; bit < nbits; ++bit) {
+                    const u32 onm = (u32)__builtin_amdgcn_sbfe((int)b, (u32)bit, 1u);
+                    const u64 bal = __ballot(onm != 0u);
+                    plo &= ~((u32)bal ^ onm);
+                    phi &= ~((u32)(bal >> 32) ^ onm);
+                }
+                const u32 before = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
+                u32 run = 0;
+                if (kept) run = wcnt[wv * B2 + (int)b];
+                wave_sync();
+                if (kept && before == 0) wcnt[wv * B2 + (int)b] = (uint16_t)(run + (u32)__popc(plo) + (u32)__popc(phi));
+                wave_sync();
+                rank[j] = run + before;
+            }
+        }
+        __syncthreads();
+        if (wv == 0) {                               // per block: the wavefronts' places, then the blocks' places (two blocks per lane)
+            u32 tot[2] = { 0, 0 };
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int b = 2 * (int)lane + h;
+                if (b < B2) {
+                    u32 c[NWV];
+#pragma unroll
+                    for (int v = 0; v < NWV; ++v) c[v] = wcnt[v * B2 + b];
+#pragma unroll
+                    for (int v = 0; v < NWV; ++v) { wcnt[v * B2 + b] = (uint16_t)tot[h]; tot[h] += c[v]; }
+                }
+            }
+            constexpr u32 PM = (u32)NE - 1u;         // every block starts on a whole group of NE places
+            const u32 pad[2] = { (tot[0] + PM) & ~PM, (tot[1] + PM) & ~PM };
+            const u32 incl = wave_scan_dpp(pad[0] + pad[1]);
+            const u32 ex = incl - pad[0] - pad[1];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int b = 2 * (int)lane + h;
+                if (b < B2) {
+                    const u32 at = ex + (h ? pad[0] : 0u);
+                    lstart[b] = at; cntb[b] = tot[h];
+                    for (u32 g = at / NE; g < (at + pad[h]) / NE; ++g) blk[g] = (uint8_t)b;
+                }
+            }
+            if (lane == kWave - 1) lstart[B2] = incl;
+        }
+        __syncthreads();
+        const u32 n_it = lstart[B2];
+        if (tid < B2) place[tid] = make_uint2(gbase[tid] - lstart[tid], lstart[tid] + cntb[tid]);
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            const bool kept = bk[j] != kNone;
+            const u32 b = kept ? bk[j] : 0u;
+            const u32 at = kept ? lstart[b] + (u32)wcnt[wv * B2 + (int)b] + rank[j] : (u32)(room - 1);
+            val[at] = DT == 0 ? rw[j] & 0x7FFFFFFFu : rw[j] & 0x7FFF0000u;
+            lidx[at] = (uint16_t)ix[j];
+        }
+        __syncthreads();
+        if (e0 + EC < nt) fetch(e0 + EC);
+        // (c) to the block-ordered arrays, in runs
+        for (u32 i1 = 0; i1 < n_it; i1 += 4 * kTileThreads) {
+#pragma unroll
+            for (u32 u = 0; u < 4; ++u) {
+                const u32 i = i1 + u * kTileThreads + (u32)tid, ic = i < n_it ? i : 0u;
+                const uint2 pl = place[blk[ic / NE]];
+                const u32 g = pl.x + ic, ixv = tile0 + (u32)lidx[ic], vv = val[ic];
+                if (i < n_it && i < pl.y && (int64_t)g < a.k) {      // (the last test always holds)
+                    bo_idx[g] = ixv;
+                    bo_val[g] = vv;
+                }
+            }
+        }
+        // (d) ABQ sums: a thread takes a group of NE places, all of one block; the lanes of one block inside each
+        // row of sixteen are added up by a segmented scan, and the last lane of a segment adds to the table
+        if (want_sums) {
+            for (u32 i0 = (u32)tid * NE; i0 < n_it + (u32)(kWave * NE); i0 += kTileThreads * NE) {
+                if ((i0 & ~(u32)(kWave * NE - 1)) >= n_it) break;        // uniform in the wavefront
+                const bool on = i0 < n_it;
+                const u32 b = on ? (u32)blk[i0 / NE] : 0xFFFFu, bb = on ? b : 0u;
+                const u32 left = on ? cntb[bb] - (i0 - lstart[bb]) : 0u;
+                u32 vv[NE];
+#pragma unroll
+                for (int j = 0; j < NE; j += 4) {
+                    uint4 t = make_uint4(0, 0, 0, 0);
+                    if (on) t = *(const uint4*)(val + i0 + j);
+                    vv[j] = t.x; vv[j + 1] = t.y; vv[j + 2] = t.z; vv[j + 3] = t.w;
+                }
+                u32 acc[QN];
+#pragma unroll
+                for (int t = 0; t < QN; ++t) acc[t] = 0;
+                u64 accE;
+                if (mode == 0) accE = lr_abq_entries<DT, NE, NQ, 0>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
+                else if (mode == 1) accE = lr_abq_entries<DT, NE, NQ, 1>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
+                else accE = lr_abq_entries<DT, NE, NQ, 2>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
+                // low 28 bits of every sum, and what is above them four to a word (at most 16 * 8 each)
+                u32 hi4[(QN + 3) / 4];
+#pragma unroll
+                for (int t = 0; t < (QN + 3) / 4; ++t) hi4[t] = 0;
+#pragma unroll
+                for (int t = 0; t < QN; ++t) { hi4[t / 4] |= (acc[t] >> 28) << (8 * (t & 3)); acc[t] &= 0xFFFFFFFu; }
+                u32 e0 = (u32)accE & 0xFFFFFFFu, e1 = (u32)(accE >> 28);
+                u32 m[4];                                // all ones where the lane 1, 2, 4, 8 below is of the same block
+                m[0] = dpp_get<0x111, 0xf, 0xf>(b + 1u) == b + 1u ? ~0u : 0u;
+                m[1] = dpp_get<0x112, 0xf, 0xf>(b + 1u) == b + 1u ? ~0u : 0u;
+                m[2] = dpp_get<0x114, 0xf, 0xf>(b + 1u) == b + 1u ? ~0u : 0u;
+                m[3] = dpp_get<0x118, 0xf, 0xf>(b + 1u) == b + 1u ? ~0u : 0u;
+                auto seg_scan = [&](u32 v) -> u32 {      // (lanes outside the row read zero)
+                    v += dpp_get<0x111, 0xf, 0xf>(v) & m[0];
+                    v += dpp_get<0x112, 0xf, 0xf>(v) & m[1];
+                    v += dpp_get<0x114, 0xf, 0xf>(v) & m[2];
+                    v += dpp_get<0x118, 0xf, 0xf>(v) & m[3];
+                    return v;
+                };
+                const u32 nxt = dpp_get<0x101, 0xf, 0xf>(b + 1u);        // row_shl:1 (zero for a row's last lane)
+                const bool last = on && nxt != b + 1u;
+#pragma unroll
+                for (int t = 0; t < (QN + 3) / 4; ++t) hi4[t] = seg_scan(hi4[t]);
+#pragma unroll
+                for (int t = 0; t < QN; ++t) {
+                    if (NQ || t < nq) {
+                        const u32 lo = seg_scan(acc[t]);
+                        if (last) atomicAdd(&sums[bb * (u32)(nq + 1) + (u32)t], (u64)lo + ((u64)((hi4[t / 4] >> (8 * (t & 3))) & 0xFFu) << 28));
+                    }
+                }
+                e0 = seg_scan(e0); e1 = seg_scan(e1);
+                if (last) atomicAdd(&sums[bb * (u32)(nq + 1) + (u32)nq], (u64)e0 + ((u64)e1 << 28));
+            }
+        }
+        __syncthreads();
+        if (tid < B2) gbase[tid] += cntb[tid];
+    }
+    // the tile's sums leave the workgroup; the row's last workgroup adds them up and chooses
+    __syncthreads();
+    const int ns = B2 * (nq + 1);
+    u64* ps = a.psum + (size_t)r * S * ns;
+    if (want_sums && S > 1) for (int i = tid; i < ns; i += kTileThreads) agent_store(&ps[(size_t)s * ns + i], sums[i]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the stores have reached the point all XCDs see ...
+    __syncthreads();
+    if (tid == 0) lstart[0] = S > 1 ? __hip_atomic_fetch_add(&st[kStTicket], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;   // ... before the ticket
+    __syncthreads();
+    if (lstart[0] != (u32)S - 1u) return;
+    if (want_sums && S > 1) {
+        // several threads share a sum, so that all its loads are in flight at once
+        int gr = 1;
+        while (gr * 2 * ns <= kTileThreads && gr * 16 < S) gr *= 2;
+        for (int i = tid; i < ns; i += kTileThreads) sums[i] = 0;
+        __syncthreads();
+        for (int i = tid; i < ns * gr; i += kTileThreads) {
+            const int j = i % ns;
+            u64 t = 0;
+            for (int s0 = i / ns; s0 < S; s0 += 16 * gr) {
+                u64 p[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) p[u] = s0 + u * gr < S ? agent_load(&ps[(size_t)(s0 + u * gr) * ns + j]) : 0ull;
+#pragma unroll
+                for (int u = 0; u < 16; ++u) t += p[u];
+            }
+            if (t) atomicAdd(&sums[j], t);
         }
     }
     __syncthreads();
-    for (int i = tid; i < B2 * (nq + 1); i += 256) {
-        const int b = i / (nq + 1), t = i - b * (nq + 1);
-        const u64 v = sums[b][t == nq ? kMaxQ : t];
-        if (v) atomicAdd(&a.sums[((size_t)r * B2 + b) * (nq + 1) + t], v);
-    }
-}
-
-// Window x of a row's slot for the pack stage: windows of pack_words words up to the first word
-// that holds code bits (word wb), windows of pack_words_code words from there on.  Returns the
-// first word and the number of words (0: nothing to do).
-__device__ inline void lr_pack_window(const LargeArgs& a, int x, u64 wb, u64 row_words, u64* c0, u64* cw)
-{
-    u64 lo, hi;
-    if (x < a.nwin_idx) {
-        lo = (u64)x * (u64)a.pack_words;
-        hi = lo + (u64)a.pack_words;
-        hi = hi < wb ? hi : wb;
-    } else {
-        lo = wb + (u64)(x - a.nwin_idx) * (u64)a.pack_words_code;
-        hi = lo + (u64)a.pack_words_code;
-    }
-    hi = hi < row_words ? hi : row_words;
-    *c0 = lo;
-    *cw = hi > lo ? hi - lo : 0;
-}
-
-template <int DT>
-__global__ __launch_bounds__(128) void lr_choose_kernel(LargeArgs a)
-{
-    typedef Elem<DT> E;
-    __shared__ u32 bits_s[kMaxB2], q_s[kMaxB2], bs_s[kMaxB2 + 1];
-    __shared__ u64 co_s[kMaxB2 + 1];
-    __shared__ u64 s_words;
-    const int b = threadIdx.x;
-    const int64_t r = blockIdx.x;
-    if (a.fallback[r]) return;
-    const int B2 = a.M + a.Mn, nq = a.nq;
-    const u32* st = a.rowst + (size_t)r * 16;
-    const u32 n = st[3] + st[4];
-    if (b < B2) {
-        const u32 cnt = a.blk_start[(size_t)r * (B2 + 1) + b + 1] - a.blk_start[(size_t)r * (B2 + 1) + b];
-        float vmin = 0.f, vmax = 0.f, inv = 0.f;
-        int q = a.qlist[0];
-        u32 flag = 0;
+    const int b = tid;
+    const bool on = b < B2;
+    u32 q = 0, flag = 0, cnt = 0;
+    float vmin = 0.f, vmax = 0.f;
+    if (on) {
+        cnt = a.blk_start[(size_t)r * (B2 + 1) + b + 1] - a.blk_start[(size_t)r * (B2 + 1) + b];
+        int chosen = 0;
         if (cnt) {
             const u32 hi = E::value_bits(a.vmaxb[r * B2 + b]);
-            vmin = __uint_as_float(E::value_bits(a.vminb[r * B2 + b]));
+            vmin = vminf[b];
             vmax = __uint_as_float(hi);
             const float rng = vmax - vmin;
-            if (rng > 0.f) {
-                const float rng1 = unit_range(rng, range_exp(rng));
-                const int e = ilogb_bits(hi) + 1;
-                const u64* sm = a.sums + ((size_t)r * B2 + b) * (nq + 1);
-                const double rhs = a.beta * ldexp((double)sm[nq], 2 * e - 40);
-                flag = 0x80u;
-                for (int t = 0; t < nq && flag; ++t) {
-                    const float Lq = (float)((1u << a.qlist[t]) - 1u);
-                    const float o = rng / Lq;
-                    const double lhs = ((double)o * (double)o) * (double)sm[t] * 0x1p-30;
-                    q = a.qlist[t]; inv = Lq / rng1;
-                    if (lhs <= rhs) flag = 0;
+            if (rng > 0.f && a.guard == 0 && !a.lad.on) {
+                const double rhs = a.beta * ldexp((double)sums[b * (nq + 1) + nq], 2 * e_tab[b] - 40);
+                chosen = -1;
+                for (int t = 0; t < nq && chosen < 0; ++t) {
+                    const float ostep = rng / (float)((1u << a.qlist[t]) - 1u);
+                    const double lhs = ((double)ostep * (double)ostep) * (double)sums[b * (nq + 1) + t] * 0x1p-30;
+                    if (lhs <= rhs) chosen = t;
+                }
+                if (chosen < 0) { chosen = nq - 1; flag = 0x80u; }
+            }
+            if (a.guard == 1) {                      // greedy descent from q_bit while the mismatch stays within delta
+                chosen = nq - 1;
+                for (int t = nq - 2; t >= 0; --t) {
+                    if ((double)sums[b * (nq + 1) + t] <= a.beta * (double)cnt) chosen = t; else break;
                 }
             }
         }
-        if (a.guard == 1) {         // greedy descent from q_bit while the mismatch stays within delta
-            int chosen = cnt ? nq - 1 : 0;
-            const u64* sm = a.sums + ((size_t)r * B2 + b) * (nq + 1);
-            for (int t = nq - 2; t >= 0 && cnt; --t) {
-                if ((double)sm[t] <= a.beta * (double)cnt) chosen = t; else break;
-            }
-            q = a.qlist[chosen]; flag = 0; inv = 0.f;
-            if (cnt && vmax - vmin > 0.f) inv = (float)((1u << q) - 1u) / unit_range(vmax - vmin, range_exp(vmax - vmin));
-        }
-        if (a.lad.on) {             // the bitwidth is given, also for empty and degenerate blocks
-            q = a.qlist[ladder_index(a.lad, b < a.M ? b : b - a.M)];
-            flag = 0; inv = 0.f;
-            if (cnt && vmax - vmin > 0.f) inv = (float)((1u << q) - 1u) / unit_range(vmax - vmin, range_exp(vmax - vmin));
-        }
-        a.qsel[r * B2 + b] = (u32)q;
-        a.inv_sel[r * B2 + b] = inv;
-        q_s[b] = (u32)q;
-        bs_s[b] = a.blk_start[(size_t)r * (B2 + 1) + b];
-        if (b == B2 - 1) bs_s[B2] = bs_s[b] + cnt;
-        bits_s[b] = cnt * (u32)q;             // < 2^31 * 16 would overflow: the list capacity keeps cnt small
-        const size_t mi = (size_t)r * (size_t)B2 + b;
-        a.mv.vmin[mi] = vmin; a.mv.vmax[mi] = vmax; a.mv.q[mi] = (uint8_t)((u32)q | flag);
+        if (a.lad.on) chosen = (int)ladder_index(a.lad, b < M ? b : b - M);      // given, also for empty and degenerate blocks
+        q = (u32)a.qlist[chosen];
     }
-    __syncthreads();
-    if (b == 0) {
-        u64 acc = 0;
-        u64* co = a.code_off + (size_t)r * (B2 + 1);
-        for (int i = 0; i < B2; ++i) { co[i] = acc; co_s[i] = acc; acc += bits_s[i]; }
-        co[B2] = acc; co_s[B2] = acc;
-        const u64 bits = (u64)n * (u64)a.w + acc;
-        u64 words = (bits + 31) >> 5;
-        if (words > a.cap_words) words = a.cap_words;
-        a.row_words[r] = words;
-        s_words = words;
-        a.mv.n_pos[r] = st[3];
-        a.mv.n_neg[r] = st[4];
-    }
-    __syncthreads();
-    // for every window of the pack stage: the block-ordered entries whose code field meets it.
-    // Code fields lie at or after word wb, i.e. in the short windows only: every block's thread
-    // walks the few windows its code section meets.
-    {
-        const u64 idx_bits = (u64)n * (u64)a.w, wb = idx_bits >> 5;
-        u32* __restrict__ wr = a.win_range + (size_t)r * a.nwin * 2;
-        for (int wi = b; wi < a.nwin; wi += 128) { wr[2 * wi] = n; wr[2 * wi + 1] = 0; }
-        __syncthreads();
-        const int csh = 31 - __clz(a.pack_words_code);          // pack_words_code is a power of two
-        const int tpb = 128 / B2 > 0 ? 128 / B2 : 1;           // threads per block (B2 <= 128)
-        const int bb = b / tpb, sub = b - bb * tpb;
-        if (bb < B2) {
-            const u32 cnt = bs_s[bb + 1] - bs_s[bb];
-            const u64 cs = idx_bits + co_s[bb], ce = idx_bits + co_s[bb + 1];
-            if (cnt && ce > cs) {
-                const u32 q = q_s[bb];
-                const int w0 = a.nwin_idx + (int)(((cs >> 5) - wb) >> csh), w1 = a.nwin_idx + (int)((((ce - 1) >> 5) - wb) >> csh);
-                for (int wi = w0 + sub; wi <= w1 && wi < a.nwin; wi += tpb) {
-                    u64 c0, cw;
-                    lr_pack_window(a, wi, wb, s_words, &c0, &cw);
-                    const u64 lo = c0 << 5, hi = (c0 + cw) << 5;
-                    if (cw == 0 || ce <= lo || cs >= hi) continue;
-                    const u32 dlo = (u32)((lo > cs ? lo : cs) - cs), dhi = (u32)((hi < ce ? hi : ce) - cs);   // < 2^31: one block's bits
-                    atomicMin(&wr[2 * wi], bs_s[bb] + dlo / q);
-                    atomicMax(&wr[2 * wi + 1], bs_s[bb] + (dhi + q - 1) / q);
-                }
-            }
-        }
-    }
+    __syncthreads();                                 // the sums have been read: their storage takes the blocks' code bits
+    lr_finish_row<DT>(a, r, st[kStNpos], st[kStNneg], on, q, flag, cnt, vmin, vmax, sums);
 }
 
+// ---- 5. pack --------------------------------------------------------------------------------------
 // A thread packs a run of consecutive fields into whole words in registers and writes each
 // word of the window image once: the first and the last word of a run may be shared with the
 // neighbouring runs (atomic OR), the words between belong to this run alone (plain store).
@@ -925,8 +1283,11 @@ struct RunPacker {
     __device__ inline void finish() { if (fill > 0) put((u32)acc, true); }
 };
 
-template <int DT>
-__global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a)
+constexpr int kPackPtrs = 4096;                   // row pointers of one window
+
+// CSR: row pointers and columns instead of flat indices (Sec. 3.2 step 3)
+template <int DT, bool CSR>
+__global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa)
 {
     typedef Elem<DT> E;
     constexpr int RUN = 8;                        // consecutive entries per thread and run
@@ -935,71 +1296,154 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a)
     __shared__ u32 crel[kMaxB2];                  // first code bit of the block relative to the window, modulo 2^32
     __shared__ float vminf[kMaxB2], invs[kMaxB2];
     __shared__ int ers[kMaxB2];
+    __shared__ u32 s_rng[2];
+    __shared__ u64 s_off[2];
+    __shared__ u32 ptrs[CSR ? kPackPtrs : 1];
     const int tid = threadIdx.x;
     const int64_t r = blockIdx.y;
-    const int B2 = a.M + a.Mn, w = a.w;
-    // everything the workgroup needs to know its work, in one round of loads
-    const u32 fb = a.fallback[r];
-    const u64 row_words = a.row_words[r];
-    const u32 n = a.rowst[(size_t)r * 16 + 3] + a.rowst[(size_t)r * 16 + 4];
+    const int B2 = a.M + a.Mn, wi = CSR ? a.wc : a.w;
     // the windows with code fields hold the most entries: they are started first
     const int nwc = a.nwin - a.nwin_idx;
     const int win = (int)blockIdx.x < nwc ? a.nwin_idx + (int)blockIdx.x : (int)blockIdx.x - nwc;
-    const u32 cq0 = a.win_range[((size_t)r * a.nwin + win) * 2 + 0];
-    const u32 cq1 = a.win_range[((size_t)r * a.nwin + win) * 2 + 1];
-    if (fb) return;
-    const u64 idx_bits = (u64)n * (u64)w;
-    u64 c0, cw;
-    lr_pack_window(a, win, idx_bits >> 5, row_words, &c0, &cw);
-    if (cw == 0) return;
-    const u64 lo = c0 << 5, hi = (c0 + cw) << 5;
+    const u64 row_words = a.row_words[r];
+    const u32 n = a.blk_start[(size_t)r * (B2 + 1) + B2];
+    const u64 ptr_bits = CSR ? (u64)B2 * (u64)(a.n_rows + 1) * (u64)a.wp : 0ull;
+    const u64 idx_bits = ptr_bits + (u64)n * (u64)wi;       // first code bit
+    // windows of pack_words words up to the first word that holds code bits, then of pack_words_code words
+    u64 c0, c1;
+    {
+        const u64 wb = idx_bits >> 5;
+        if (win < a.nwin_idx) {
+            c0 = (u64)win * (u64)a.pack_words;
+            c1 = c0 + (u64)a.pack_words < wb ? c0 + (u64)a.pack_words : wb;
+        } else {
+            c0 = wb + (u64)(win - a.nwin_idx) * (u64)a.pack_words_code;
+            c1 = c0 + (u64)a.pack_words_code;
+        }
+        c1 = c1 < row_words ? c1 : row_words;
+    }
+    const bool lead = win == 0;                      // also the row's offset; of row 0 also the header
+    if (c1 <= c0 && !lead) return;
+    const int cw = c1 > c0 ? (int)(c1 - c0) : 0;
+    const u64 lo = c0 << 5, hi = lo + ((u64)cw << 5);
     const u32* __restrict__ bo_idx = a.bo_idx + (size_t)r * (size_t)a.k;
     const u32* __restrict__ bo_val = a.bo_val + (size_t)r * (size_t)a.k;
-    // index fields that meet the window
+    // index fields that meet the window; their first run is in flight while the tables arrive
     u32 iq0 = 0, iq1 = 0;
-    if (lo < idx_bits) {
-        iq0 = (u32)(lo / (u64)w);
-        const u64 t1 = (hi + (u64)w - 1) / (u64)w;
+    if (cw && lo < idx_bits && hi > ptr_bits) {
+        iq0 = lo > ptr_bits ? (u32)((lo - ptr_bits) / (u64)wi) : 0u;
+        const u64 t1 = (hi - ptr_bits + (u64)wi - 1) / (u64)wi;
         iq1 = t1 > (u64)n ? n : (u32)t1;
     }
-    // first run of both sections: the loads are in flight while the block tables arrive
-    u32 vi[RUN], vc[RUN];
+    u32 vi[RUN];
 #pragma unroll
     for (int u = 0; u < RUN; ++u) { const u32 p = iq0 + (u32)tid * RUN + (u32)u; vi[u] = p < iq1 ? bo_idx[p] : 0u; }
+    if (a.direct && tid < kWave) {                   // words of the rows before this one (at most 256 rows)
+        u64 before = 0, total = 0;
+#pragma unroll
+        for (int j = 0; j < kScanRows / kWave; ++j) {
+            const int64_t i = (int64_t)j * kWave + tid;
+            const u64 t = i < a.R ? a.row_words[i] : 0ull;
+            total += t;
+            if (i < r) before += t;
+        }
+#pragma unroll
+        for (int d = kWave / 2; d > 0; d >>= 1) { before += __shfl_xor(before, d); total += __shfl_xor(total, d); }
+        if (tid == 0) { s_off[0] = before; s_off[1] = total; }
+    }
+    if (tid == 0) { s_rng[0] = n; s_rng[1] = 0; }
+    __syncthreads();
+    for (int b = tid; b < B2; b += 256) {
+        const size_t rb = (size_t)r * B2 + b;
+        const u32 b0 = a.blk_start[(size_t)r * (B2 + 1) + b], q = a.qsel[rb];
+        bs[b] = b0;
+        if (b == B2 - 1) bs[B2] = n;
+        qsel[b] = q;
+        invs[b] = a.inv_sel[rb];
+        vminf[b] = a.mv.vmin[rb];
+        const float rng = a.mv.vmax[rb] - vminf[b];
+        ers[b] = rng > 0.f ? range_exp(rng) : 0;          // blocks of range 0 have inv = 0 and are not scaled
+        const u64 cs = idx_bits + a.code_off[(size_t)r * (B2 + 1) + b], ce = idx_bits + a.code_off[(size_t)r * (B2 + 1) + b + 1];
+        crel[b] = (u32)(cs - lo);
+        if (ce > cs && ce > lo && cs < hi) {              // the block's entries whose code field meets the window (fewer than 2^31 bits)
+            const u32 dlo = (u32)((lo > cs ? lo : cs) - cs), dhi = (u32)((hi < ce ? hi : ce) - cs);
+            atomicMin(&s_rng[0], b0 + dlo / q);
+            atomicMax(&s_rng[1], b0 + (dhi + q - 1) / q);
+        }
+    }
+    for (int i = tid; i < cw; i += 256) sA[i] = 0;
+    __syncthreads();
+    if (a.direct && lead && tid == 0) {
+        a.mv.row_off[r] = s_off[0];
+        if (r == 0) {
+            write_header(fa, s_off[1]);
+            if (CSR) { u32* h32 = (u32*)a.meta; h32[11] = (u32)a.wc; h32[15] = (u32)a.n_cols; }
+        }
+    }
+    if (!cw) return;
+    const u32 cq0 = s_rng[0], cq1 = s_rng[1];
+    u32 vc[RUN];
 #pragma unroll
     for (int u = 0; u < RUN; ++u) { const u32 p = cq0 + (u32)tid * RUN + (u32)u; vc[u] = p < cq1 ? bo_val[p] : 0u; }
-    for (int b = tid; b < B2; b += 256) {
-        const u32 b0 = a.blk_start[(size_t)r * (B2 + 1) + b];
-        bs[b] = b0;
-        if (b == B2 - 1) bs[B2] = a.blk_start[(size_t)r * (B2 + 1) + B2];
-        qsel[b] = a.qsel[r * B2 + b];
-        invs[b] = a.inv_sel[r * B2 + b];
-        vminf[b] = __uint_as_float(E::value_bits(a.vminb[r * B2 + b]));
-        {
-            const float rng = __uint_as_float(E::value_bits(a.vmaxb[r * B2 + b])) - vminf[b];
-            ers[b] = rng > 0.f ? range_exp(rng) : 0;      // blocks of range 0 have inv = 0 and are not scaled
-        }
-        crel[b] = (u32)(idx_bits + a.code_off[(size_t)r * (B2 + 1) + b] - lo);
-    }
-    for (int i = tid; i < (int)cw; i += 256) sA[i] = 0;
-    __syncthreads();
+    const u32 ncols = (u32)a.n_cols, rcp = CSR ? (ncols > 1u ? (u32)((1ull << 32) / ncols) : 0xFFFFFFFFu) : 0u;
+    auto tensor_row = [&](u32 idx) -> u32 {          // idx / n_cols: the scaled reciprocal is at most one too low for idx < 2^31
+        u32 q = __umulhi(idx, rcp);
+        if (idx - q * ncols >= ncols) ++q;
+        return q;
+    };
+    RunPacker rp;
     // Bit positions are taken relative to the window in 32-bit arithmetic: the true value of
     // every position handled here lies within a few bits of the window, so the wrapped
     // difference is exact.
-    RunPacker rp;
-    {
-        const u32 lo32 = (u32)lo;
-        for (u32 p0 = iq0 + (u32)tid * RUN; p0 < iq1; p0 += 256 * RUN) {
-            if (p0 != iq0 + (u32)tid * RUN) {
-#pragma unroll
-                for (int u = 0; u < RUN; ++u) { const u32 p = p0 + (u32)u; vi[u] = p < iq1 ? bo_idx[p] : 0u; }
+    const u32 lo32 = (u32)lo;
+    if (CSR && lo < ptr_bits) {
+        // pointer j of a block = number of its entries in tensor rows before j.  An entry settles the
+        // pointers from the row after its predecessor's to its own; the last one also those behind it.  Blocks with few
+        // entries per tensor row are searched instead, pointer by pointer.
+        const u32 np1 = (u32)a.n_rows + 1u;
+        const u64 n_ptr = (u64)B2 * np1;
+        const u64 f0 = lo / (u64)a.wp, fe = (hi + (u64)a.wp - 1) / (u64)a.wp, f1 = fe < n_ptr ? fe : n_ptr;
+        for (u32 b = (u32)(f0 / np1); b <= (u32)((f1 - 1) / np1); ++b) {
+            const u64 fb = (u64)b * np1;
+            const u32 j0 = f0 > fb ? (u32)(f0 - fb) : 0u, j1 = f1 < fb + np1 ? (u32)(f1 - fb) : np1;     // pointers [j0, j1)
+            u32* out = ptrs + (fb + j0 - f0);        // pointer j0
+            const u32 p0 = bs[b], cnt = bs[b + 1] - p0;
+            if (cnt * 8u < np1) {
+                for (u32 j = j0 + (u32)tid; j < j1; j += 256) {
+                    const u64 target = (u64)j * ncols;
+                    u32 l = 0, h = cnt;
+                    while (l < h) { const u32 mid = (l + h) >> 1; if ((u64)bo_idx[p0 + mid] < target) l = mid + 1; else h = mid; }
+                    out[j - j0] = l;
+                }
+            } else {
+                for (u32 i = (u32)tid; i < cnt; i += 256) {
+                    const u32 row = tensor_row(bo_idx[p0 + i]), prev = i ? tensor_row(bo_idx[p0 + i - 1u]) + 1u : 0u;
+                    const u32 x1 = row + 1u < j1 ? row + 1u : j1;
+                    for (u32 j = prev > j0 ? prev : j0; j < x1; ++j) out[j - j0] = i;
+                    if (i == cnt - 1u) for (u32 j = row + 1u > j0 ? row + 1u : j0; j < j1; ++j) out[j - j0] = cnt;
+                }
             }
-            rp.begin(sA, (int)cw, (int)(p0 * (u32)w - lo32));
+        }
+        __syncthreads();
+        const u32 nf = (u32)(f1 - f0);
+        for (u32 p0 = (u32)tid * RUN; p0 < nf; p0 += 256 * RUN) {
+            rp.begin(sA, cw, (int)((u32)f0 * (u32)a.wp + p0 * (u32)a.wp - lo32));
 #pragma unroll
             for (int u = 0; u < RUN; ++u)
-                if (p0 + (u32)u < iq1) rp.append(vi[u], w);
+                if (p0 + (u32)u < nf) rp.append(ptrs[p0 + (u32)u], a.wp);
             rp.finish();
         }
+    }
+    for (u32 p0 = iq0 + (u32)tid * RUN; p0 < iq1; p0 += 256 * RUN) {
+        if (p0 != iq0 + (u32)tid * RUN) {
+#pragma unroll
+            for (int u = 0; u < RUN; ++u) { const u32 p = p0 + (u32)u; vi[u] = p < iq1 ? bo_idx[p] : 0u; }
+        }
+        rp.begin(sA, cw, (int)((u32)ptr_bits + p0 * (u32)wi - lo32));
+#pragma unroll
+        for (int u = 0; u < RUN; ++u)
+            if (p0 + (u32)u < iq1) rp.append(CSR ? vi[u] - tensor_row(vi[u]) * ncols : vi[u], wi);
+        rp.finish();
     }
     {
         // the block's constants stay in registers until the position leaves the block; the code
@@ -1015,7 +1459,7 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a)
             int q = (int)qsel[b];
             float inv = invs[b], vmin = vminf[b], qmaxf = (float)((1u << q) - 1u);
             int er = ers[b];
-            rp.begin(sA, (int)cw, (int)(crel[b] + (p0 - bs[b]) * (u32)q));
+            rp.begin(sA, cw, (int)(crel[b] + (p0 - bs[b]) * (u32)q));
 #pragma unroll
             for (int u = 0; u < RUN; ++u) {
                 const u32 p = p0 + (u32)u;
@@ -1036,8 +1480,8 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a)
         }
     }
     __syncthreads();
-    u32* __restrict__ slot = a.slots + (size_t)r * (size_t)a.cap_words;
-    for (int i = tid; i < (int)cw; i += 256) slot[c0 + i] = sA[i];
+    u32* __restrict__ dst = a.direct ? a.stream + s_off[0] : a.slots + (size_t)r * (size_t)a.cap_words;
+    for (int i = tid; i < cw; i += 256) dst[c0 + i] = sA[i];
 }
 
 }  // namespace slicer

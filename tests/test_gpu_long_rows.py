@@ -1,0 +1,47 @@
+"""Long-row stages at the edges of their tiles, tables and launch rules, byte-exact against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2511_11608_amd import synth
+from tests.test_gpu_parity import B28, check, check_csr, check_ds, check_ladder
+
+pytestmark = pytest.mark.gpu
+
+
+def features(dtype, rows, N, seed, kind="normal"):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((rows, N)).astype(np.float32)
+    if kind == "relu":
+        x = np.abs(x) * (rng.random((rows, N)) < 0.5)
+    elif kind == "sparse":                              # fewer non-zeros than kept elements, over thirty octaves
+        x = x * (rng.random((rows, N)) < 0.03) * np.exp2(rng.uniform(-15, 15, (rows, N)))
+    elif kind == "ties":                                # a few dozen distinct values
+        x = np.round(x * 8) / 8
+    elif kind == "outliers":
+        x[:, :: N // 7] *= 3000
+    elif kind == "patches":                             # constant stretches: one key fills whole tiles
+        x = np.repeat(x[:, : (N + 999) // 1000], 1000, axis=1)[:, :N] + (rng.random((rows, N)) < 0.2)
+    x = x.astype(np.float32)
+    return synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+
+
+@pytest.mark.parametrize("dtype,rows,N", [("f32", 3, 16388), ("f32", 2, 32768), ("f32", 1, 81919), ("f32", 2, 81921), ("bf16", 2, 65544), ("bf16", 3, 40961),
+                                          ("f32", 40, 65536), ("f32", 41, 65533), ("f32", 300, 16640), ("bf16", 270, 33001)])
+def test_tiles_and_batches(oracle, dtype, rows, N):
+    check(oracle, features(dtype, rows, N, N), dtype, 0.12, 8, B28, 1e-3, use_header=bool(rows & 1))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["relu", "sparse", "ties", "outliers", "patches"])
+def test_value_structures(oracle, dtype, kind):
+    x = features(dtype, 3, 50_000, 11, kind)
+    for keep, M in ((0.05, 4), (0.2, 16), (0.6, 31), (0.2, 33), (0.3, 64), (1.0, 5)):
+        check(oracle, x, dtype, keep, M, B28, 1e-3)
+    check_ds(oracle, x, dtype, 0.2, 16, (1 << 2) | (1 << 5) | (1 << 12), 0.3)
+    check_ladder(oracle, x, dtype, 0.2, [8, 7, 6, 5, 4, 3, 2, 2])
+
+
+@pytest.mark.parametrize("dtype,inst,n_rows,n_cols", [("f32", 2, 1, 60_000), ("f32", 2, 60_000, 1), ("f32", 3, 197, 301), ("bf16", 2, 128, 513), ("f32", 260, 40, 512)])
+def test_csr_blocks(oracle, dtype, inst, n_rows, n_cols):
+    for kind in ("normal", "sparse"):
+        check_csr(oracle, features(dtype, inst, n_rows * n_cols, 5, kind), dtype, n_rows, n_cols, 0.1, 8, B28, 1e-3)
