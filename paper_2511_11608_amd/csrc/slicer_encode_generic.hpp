@@ -725,7 +725,14 @@ __device__ inline void gather_item(const FinishArgs& a, int64_t r, u64 c, u64 of
     const u64 j1 = j0 + (u64)kGatherWords < nw ? j0 + (u64)kGatherWords : nw;
     const u32* __restrict__ src = a.slots + (size_t)r * a.cap_words;
     u32* __restrict__ dst = a.stream + off;
-    for (u64 j = j0 + lane; j < j1; j += kWave) dst[j] = src[j];
+    // eight words per lane in flight: one at a time, every word waits a memory round trip
+    for (u64 j = j0 + lane; j < j1; j += 8 * kWave) {
+        u32 t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = j + (u64)(u * kWave) < j1 ? src[j + (u64)(u * kWave)] : 0u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) if (j + (u64)(u * kWave) < j1) dst[j + (u64)(u * kWave)] = t[u];
+    }
 }
 
 __global__ __launch_bounds__(256) void enc_gather_kernel(FinishArgs a)
