@@ -29,7 +29,7 @@
 namespace slicer {
 
 constexpr int kWgMaxSlots = 32;        // list slots (64 entries): lists of up to 2048 entries
-constexpr int kWgMisc = 64;            // broadcast words (0..15), per-wavefront maxima (16..31), scan scratch (32..)
+constexpr int kWgMisc = 64;            // broadcast words (0..15), per-wavefront maxima (16..31), scan scratch (32..47), bounds tried (48..)
 
 // words of LDS: the one-wavefront layout (list in LDS) followed by the workgroup's own tables
 __host__ __device__ inline int wg_main_words(int dt, int cap, int region0, int B2)
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     static_assert(NCH * kWgWaves <= kWave, "chunk totals are scanned by one wavefront");
     extern __shared__ u32 smem[];
 
-    const u32 tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const u32 tid = threadIdx.x, lane = lane_id(), wv = (u32)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
     const int64_t r = (int64_t)blockIdx.x;
     if (r >= a.R) return;
     const int M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq, cap = a.cap;
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
 
     // List length and positions for a lower key bound t_lo: counts per chunk, positions inside the
     // wavefront (three chunk counts share a scan: 10-bit fields, at most 512 keys per wavefront and
-    // chunk), then the wavefronts' chunk totals are scanned in chunk order by wavefront 0.
+    // chunk), then the wavefronts' chunk totals are scanned in chunk order.
     u32 t_lo = 1u, nL = 0;
     u32 cntc[NCH], basec[NCH];
     auto count_pass = [&]() {
@@ -124,34 +124,33 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
             }
         }
         __syncthreads();
-        if (wv == 0) {
+        {   // every wavefront scans the (at most 64) totals itself
             const u32 t = (int)lane < NCH * kWgWaves ? ctab[lane] : 0u;
-            const u32 incl = wave_scan_dpp(t);
-            ctab[64 + lane] = incl - t;
-            if (lane == kWave - 1) misc[4] = incl;
-        }
-        __syncthreads();
-        nL = misc[4];
+            const u32 incl = wave_scan_dpp(t), ex = incl - t;
+            nL = bcast(incl, kWave - 1);
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) basec[c] += ctab[64 + c * kWgWaves + (int)wv];
-        __syncthreads();                             // the tables are free for the next use
+            for (int c = 0; c < NCH; ++c) basec[c] += bcast(ex, c * kWgWaves + (int)wv);
+        }
     };
 
     // Threshold hint (see slicer_encode_small.hpp): the cut key an earlier row left in the workspace,
     // lowered a few steps; accepted when it keeps at least k keys and not many more.  The count decides.
+    // A row that ends meanwhile may change the slot between two wavefronts' reads: the bound is taken only when
+    // all of them tried the same one.
     const u32 hslot = (u32)blockIdx.x & (u32)(kHintSlots - 1);
     bool hinted = false;
     if (k > 0) {
-        const u32 hint_key = a.hint[hslot] & kKeyMask;
+        const u32 hint_key = (u32)__builtin_amdgcn_readfirstlane((int)a.hint[hslot]) & kKeyMask;
         const u32 dlt = kHintDelta << (DT == 0 ? 16 : 0);
         t_lo = hint_key > dlt ? hint_key - dlt : 1u;
+        if (lane == 0) misc[48 + wv] = t_lo;
         count_pass();
-        hinted = nL >= (u32)k && nL <= (u32)k + 2u * kHintSlack && (int)nL <= cap;
+        const bool same = __ballot(misc[48 + (lane & (u32)(NW - 1))] != t_lo) == 0;
+        hinted = same && nL >= (u32)k && nL <= (u32)k + 2u * kHintSlack && (int)nL <= cap;
     }
 
+    // largest magnitude key of the row: per wavefront now, of the row behind the next barrier
     u32 kmax = 0;
-    if (!hinted) {
-    // largest magnitude key of the row
     {
         u32 mx = 0;
 #pragma unroll
@@ -165,12 +164,15 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         if (DT == 1) mx = max(mx & 0xFFFFu, mx >> 16);
         mx = wave_max_dpp(mx);
         if (lane == 0) misc[16 + wv] = mx;
-        __syncthreads();
+    }
+    auto row_kmax = [&]() {
         kmax = 0;
 #pragma unroll
         for (int i = 0; i < NW; ++i) kmax = max(kmax, misc[16 + i]);
-        __syncthreads();
-    }
+    };
+    if (!hinted) {
+    __syncthreads();
+    row_kmax();
 
     // ---- coarse histogram: 2048 bins hanging from wtop, bin = (wtop - key) >> S ---------------
     constexpr int S1 = DT == 0 ? 16 : 0;             // fp32: 65536 keys per bin (the same 128 bins per octave as bf16)
@@ -295,9 +297,17 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
             }
         }
     }
-    __syncthreads();
-    // wavefront v takes list slots v, v + 4, ...: entries into registers (sign, key, inverted index in one word)
     const int nslots = (int)((nL + kWave - 1) / kWave);
+    {   // (the fine bins and the tables below share no storage with the list)
+        uint4* h4 = (uint4*)L.hist;
+        for (int i = (int)tid; i < kFineBins / 4; i += kWgThreads) h4[i] = make_uint4(0, 0, 0, 0);
+        if (tid < 16) misc[tid] = 0;
+        if ((int)tid < QN && (NQ || (int)tid < nq)) L.qtab[tid] = (u32)a.qlist[tid];
+        for (int i = (int)tid; i < (nslots * B2 + 1) / 2; i += kWgThreads) ((u32*)stab)[i] = 0;
+    }
+    __syncthreads();
+    row_kmax();
+    // wavefront v takes list slots v, v + 4, ...: entries into registers (sign, key, inverted index in one word)
     u32 ent[kWgSlots], eix[DT == 0 ? kWgSlots : 1];           // fp32: the entry's index beside its raw word
 #pragma unroll
     for (int j = 0; j < kWgSlots; ++j) {
@@ -307,27 +317,6 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     }
     auto ent_key = [&](int j) -> u32 { return DT == 0 ? ent[j] & 0x7FFFFFFFu : (ent[j] >> 16) & 0x7FFFu; };
     auto ent_idx = [&](int j) -> u32 { return DT == 0 ? eix[DT == 0 ? j : 0] : 0xFFFFu - (ent[j] & 0xFFFFu); };
-    if (hinted) {                                                 // the row's largest key is the list's largest
-        u32 mx = 0;
-#pragma unroll
-        for (int j = 0; j < kWgSlots; ++j) mx = max(mx, ent[j] & 0x7FFFFFFFu);
-        mx = wave_max_dpp(mx) >> (DT == 0 ? 0 : 16);
-        if (lane == 0) misc[16 + wv] = mx;
-    }
-    __syncthreads();                                              // (the histogram region overlays the list's neighbours)
-    if (hinted) {
-        kmax = 0;
-#pragma unroll
-        for (int i = 0; i < NW; ++i) kmax = max(kmax, misc[16 + i]);
-    }
-    {
-        uint4* h4 = (uint4*)L.hist;
-        for (int i = (int)tid; i < kFineBins / 4; i += kWgThreads) h4[i] = make_uint4(0, 0, 0, 0);
-        if (tid < 16) misc[tid] = 0;
-        if ((int)tid < QN && (NQ || (int)tid < nq)) L.qtab[tid] = (u32)a.qlist[tid];
-        for (int i = (int)tid; i < (nslots * B2 + 1) / 2; i += kWgThreads) ((u32*)stab)[i] = 0;
-    }
-    __syncthreads();
 
     // ---- 3. fine bins: 1024 bins linear in (key - t_lo) >> sh, both classes packed 11 + 11 bits --------
     const u32 range = kmax > t_lo ? kmax - t_lo : 0u;
@@ -354,13 +343,16 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
 #pragma unroll
         for (int j = 0; j < FPT; ++j) { local += cs[j]; big |= ((cs[j] & 0x7FFu) + (cs[j] >> 11)) >> 10; }
         if (nL >= 1024u && big != 0u) misc[10] = 1u;        // a fine bin with 1024+ members overflows its 10-bit fill field
-        __syncthreads();                                    // (no library reduction here: it would bring static LDS)
+        const u32 inc_w = wave_scan_dpp(local);             // (the wavefronts' totals meet in misc: the block scan has a barrier more)
+        if (lane == kWave - 1) misc[32 + wv] = inc_w;
+        __syncthreads();
         if (misc[10]) {
             give_up();
             return;
         }
-        u32 tot;
-        const u32 excl = block_excl_scan<kWgThreads>(local, misc + 32, &tot);
+        u32 tot = 0, excl = inc_w - local;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) { const u32 t = misc[32 + i]; tot += t; if (i < (int)wv) excl += t; }
         n_pos = tot & 0x7FFu; n_neg = tot >> 11;
         const u32 incl = excl + local;
         const u32 ov_ex = (excl & 0x7FFu) + (excl >> 11), ov_in = (incl & 0x7FFu) + (incl >> 11);
@@ -397,43 +389,56 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         return (comp_t)(s ^ 0x80000000u);
     };
 
-    // ---- top-K cut and block boundaries: wavefront 0 ------------------------------------------------
+    // ---- top-K cut and block boundaries ----------------------------------------------------------------
+    // Every wavefront finds the cut and locates the boundaries itself (the same broadcast reads, no barrier in
+    // between); the members of the boundary bins are then dealt to the wavefronts.  Members are read four at a time: one
+    // by one, each read waits for the one before (cut + boundaries were 8 100 of an 8192-element row's 39 600 cycles).
     const int ntg = B2 - 2;
     comp_t* thr = (comp_t*)L.thr;
-    if (wv == 0) {
-        comp_t thrK = 0;                                // plain comp; every entry of the list is kept when nL <= k
-        if (nL > (u32)k) {
-            constexpr int FPT = kFineBins / kWgThreads;
-            const int hi = kFineBins - (int)misc[5] * FPT;
-            const u32 wj = lane < (u32)FPT ? L.hist[hi - 1 - (int)lane] : 0xFFFFFFFFu;
-            const u64 mj = __ballot(lane < (u32)FPT && (wj & 0x7FFu) + ((wj >> 11) & 0x7FFu) <= (u32)(k - 1));
-            const int lo = hi - (int)__popcll(mj);
-            const u32 wd = L.hist[lo];
-            const u32 pe = wd & 0x7FFu, ne = (wd >> 11) & 0x7FFu, cnt = wd >> 22, base = pe + ne;
-            const u32 rem = (u32)(k - 1) - base;
-            u32 kp = 0, kn = 0;
-            for (u32 g = 0; g < cnt; g += kWave) {
-                const u32 i = g + lane;
-                u32 me = 0, gt = 0;
-                if (i < cnt) {
-                    me = L.S[base + i];
-                    for (u32 j = 0; j < cnt; ++j) gt += s_plain(L.S[base + j]) > s_plain(me) ? 1u : 0u;
-                }
-                const bool in = i < cnt && gt <= rem;
-                kp += (u32)__popcll(__ballot(in && !s_neg(me)));
-                kn += (u32)__popcll(__ballot(in && s_neg(me)));
-                const u64 hit = __ballot(i < cnt && gt == rem);
-                if (hit) {
-                    const int hl = (int)__builtin_ctzll(hit);
-                    const comp_t cx = s_cx(me, (u32)lo) & ~kClsBit;
-                    if (DT == 0) thrK = ((comp_t)bcast((u32)((u64)cx >> kHiShift), hl) << kHiShift) | (comp_t)bcast((u32)cx, hl);
-                    else thrK = (comp_t)bcast((u32)cx, hl);
-                }
+    comp_t thrK = 0;                                // plain comp; every entry of the list is kept when nL <= k
+    if (nL > (u32)k) {
+        constexpr int FPT = kFineBins / kWgThreads;
+        const int hi = kFineBins - (int)misc[5] * FPT;
+        const u32 wj = lane < (u32)FPT ? L.hist[hi - 1 - (int)lane] : 0xFFFFFFFFu;
+        const u64 mj = __ballot(lane < (u32)FPT && (wj & 0x7FFu) + ((wj >> 11) & 0x7FFu) <= (u32)(k - 1));
+        const int fj = (int)__popcll(mj) - 1, lo = hi - 1 - fj;         // the last bin whose first rank is <= k - 1
+        const u32 wd = bcast(wj, fj);
+        const u32 pe = wd & 0x7FFu, ne = (wd >> 11) & 0x7FFu, cnt = wd >> 22, base = pe + ne;
+        const u32 rem = (u32)(k - 1) - base;
+        u32 kp = 0, kn = 0;
+        for (u32 g = 0; g < cnt; g += kWave) {
+            const u32 i = g + lane;
+            const u32 me = L.S[base + (i < cnt ? i : 0u)];
+            u32 gt = 0;
+            for (u32 j = 0; j < cnt; j += 4) {
+                u32 t[4];
+#pragma unroll
+                for (u32 u = 0; u < 4; ++u) t[u] = L.S[base + (j + u < cnt ? j + u : 0u)];
+#pragma unroll
+                for (u32 u = 0; u < 4; ++u) gt += j + u < cnt && s_plain(t[u]) > s_plain(me) ? 1u : 0u;
             }
-            n_pos = pe + kp; n_neg = ne + kn;
+            const bool in = i < cnt && gt <= rem;
+            kp += (u32)__popcll(__ballot(in && !s_neg(me)));
+            kn += (u32)__popcll(__ballot(in && s_neg(me)));
+            const u64 hit = __ballot(i < cnt && gt == rem);
+            if (hit) {
+                const int hl = (int)__builtin_ctzll(hit);
+                const comp_t cx = s_cx(me, (u32)lo) & ~kClsBit;
+                if (DT == 0) thrK = ((comp_t)bcast((u32)((u64)cx >> kHiShift), hl) << kHiShift) | (comp_t)bcast((u32)cx, hl);
+                else thrK = (comp_t)bcast((u32)cx, hl);
+            }
         }
-        const u32 Kc[2] = { n_pos / (u32)M, n_neg / (u32)Mn };
-        if (lane == 0) { misc[6] = (u32)thrK; misc[11] = (u32)((u64)thrK >> kHiShift); misc[7] = n_pos; misc[8] = n_neg; }
+        n_pos = pe + kp; n_neg = ne + kn;
+    }
+    const u32 n = n_pos + n_neg;
+    const u32 Kc[2] = { n_pos / (u32)M, n_neg / (u32)Mn };
+    if ((int)tid < B2) {
+        const int s = (int)tid >= M ? 1 : 0, m = (int)tid - s * M;
+        L.blk_start[tid] = (s ? n_pos : 0u) + (u32)m * Kc[s];
+        L.vminb[tid] = 0xFFFFFFFFu; L.vmaxb[tid] = 0;
+    }
+    if (tid == 0) L.blk_start[B2] = n;
+    {
         // boundaries: comps of class ranks j*K-1, one lane per boundary
         const int ntp = ntg > 0 ? ntg : 1;
         u32* tg_bin = L.tg; u32* tg_base = L.tg + ntp; u32* tg_cnt = L.tg + 2 * ntp; u32* tg_rem = L.tg + 3 * ntp; u32* tg_pre = L.tg + 4 * ntp;
@@ -442,18 +447,22 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         const int jb = (cls ? (int)lane - (M - 1) : (int)lane) + 1;
         const bool act = mine && Kc[cls] > 0;
         const u32 Rk = act ? (u32)jb * Kc[cls] - 1u : 0u;
-        int lo = 0, hi = kFineBins - 1;                 // smallest bin whose first class rank is <= Rk
-        for (int it = 0; it < 10; ++it) {
-            const int mid = (lo + hi) >> 1;
-            const u32 wd = L.hist[mid];
-            const u32 pc = cls ? (wd >> 11) & 0x7FFu : wd & 0x7FFu;
-            if (pc <= Rk) hi = mid; else lo = mid + 1;
+        // smallest bin whose first class rank is <= Rk: three probes a step, so five dependent reads instead of ten
+        int lo = 0, len = kFineBins;
+        const u32 csh = cls ? 11u : 0u;
+#pragma unroll
+        for (int it = 0; it < 5; ++it) {
+            const int q = len >> 2;
+            const u32 w0 = L.hist[lo + q - 1], w1 = L.hist[lo + 2 * q - 1], w2 = L.hist[lo + 3 * q - 1];
+            const u32 f0 = ((w0 >> csh) & 0x7FFu) > Rk ? 1u : 0u, f1 = ((w1 >> csh) & 0x7FFu) > Rk ? 1u : 0u, f2 = ((w2 >> csh) & 0x7FFu) > Rk ? 1u : 0u;
+            lo += q * (int)(f0 + f1 + f2);           // (first ranks fall as the bins rise)
+            len = q;
         }
         const u32 wd = L.hist[lo];
         const u32 pe = wd & 0x7FFu, ne = (wd >> 11) & 0x7FFu;
         const u32 cnt = act ? wd >> 22 : 0u;
         const u32 incl = wave_scan_dpp(cnt);
-        if (mine) {
+        if (mine) {                                  // (all wavefronts write the same words)
             tg_bin[lane] = (u32)lo; tg_base[lane] = pe + ne; tg_cnt[lane] = cnt;
             tg_rem[lane] = Rk - (cls ? ne : pe);
             tg_pre[lane] = incl - cnt;
@@ -461,7 +470,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         }
         const u32 npairs = bcast(incl, kWave - 1);
         wave_sync();
-        for (u32 g = 0; g < npairs; g += kWave) {
+        for (u32 g = wv * kWave; g < npairs; g += kWgThreads) {
             const u32 pr = g + lane;
             if (pr < npairs) {
                 int tl = 0, th = ntg - 1;
@@ -471,35 +480,29 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
                 }
                 const int t = tl;
                 const u32 tc = (u32)(t >= M - 1 ? 1 : 0);
-                const u32 bs = tg_base[t], cn = tg_cnt[t];
+                const u32 bs = tg_base[t], cn = tg_cnt[t], rem = tg_rem[t], bin = tg_bin[t];
                 const u32 me = L.S[bs + (pr - tg_pre[t])];
-                if (s_neg(me) == tc) {
-                    // one compare per member: with the class bit moved to the top and set for the boundary's
-                    // class, "same class and larger comp" is a plain unsigned "larger"
-                    const u32 fm = DT == 0 ? (tc ^ 1u) : (tc ? 0u : 0x80000000u);
-                    auto key_of = [&](u32 sv) -> u32 {
-                        const u32 xv = sv ^ fm;
-                        return DT == 0 ? __builtin_amdgcn_alignbit(xv, xv, 1) : xv;     // fp32: rotate the class bit up
-                    };
-                    const u32 mk = key_of(me);
-                    u32 gt = 0;
-                    for (u32 jj = 0; jj < cn; ++jj) gt += key_of(L.S[bs + jj]) > mk ? 1u : 0u;
-                    if (gt == tg_rem[t]) thr[t] = s_cx(me, tg_bin[t]);
+                // one compare per member: with the class bit moved to the top and set for the boundary's
+                // class, "same class and larger comp" is a plain unsigned "larger"
+                const u32 fm = DT == 0 ? (tc ^ 1u) : (tc ? 0u : 0x80000000u);
+                auto key_of = [&](u32 sv) -> u32 {
+                    const u32 xv = sv ^ fm;
+                    return DT == 0 ? __builtin_amdgcn_alignbit(xv, xv, 1) : xv;     // fp32: rotate the class bit up
+                };
+                const u32 mk = key_of(me);
+                u32 gt = 0;
+                for (u32 jj = 0; jj < cn; jj += 4) {
+                    u32 t4[4];
+#pragma unroll
+                    for (u32 u = 0; u < 4; ++u) t4[u] = L.S[bs + (jj + u < cn ? jj + u : 0u)];
+#pragma unroll
+                    for (u32 u = 0; u < 4; ++u) gt += jj + u < cn && key_of(t4[u]) > mk ? 1u : 0u;
                 }
+                if (s_neg(me) == tc && gt == rem) thr[t] = s_cx(me, bin);
             }
         }
     }
     __syncthreads();
-    const comp_t thrK = DT == 0 ? (comp_t)(((u64)misc[11] << kHiShift) | (u64)misc[6]) : (comp_t)misc[6];
-    n_pos = misc[7]; n_neg = misc[8];
-    const u32 n = n_pos + n_neg;
-    const u32 Kc[2] = { n_pos / (u32)M, n_neg / (u32)Mn };
-    if ((int)tid < B2) {
-        const int s = (int)tid >= M ? 1 : 0, m = (int)tid - s * M;
-        L.blk_start[tid] = (s ? n_pos : 0u) + (u32)m * Kc[s];
-        L.vminb[tid] = 0xFFFFFFFFu; L.vmaxb[tid] = 0;
-    }
-    if (tid == 0) L.blk_start[B2] = n;
 
     // ---- 4. blocks and stable split -----------------------------------------------------------------
     u32* bo_val = L.S;
@@ -511,7 +514,6 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
 #pragma unroll
     for (int j = 0; j < kRegThr; ++j) tx[j] = j < ntg ? thr[j] : (comp_t)0;
     const bool tree8 = DT == 1 && M == 8 && Mn == 8;      // (one-word comps: a select is one instruction)
-    __syncthreads();                                 // S, the fine bins and the boundaries have been read: their storage is reused
     u32 info[kWgSlots];                              // kept << 31 | block << 16 | entries of the same block before this one in the slot
 #pragma unroll
     for (int j = 0; j < kWgSlots; ++j) {
@@ -565,14 +567,21 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         }
     }
     __syncthreads();
-    if ((int)tid < B2) {                             // per block: entries in earlier slots
+    if ((int)tid < B2) {                             // per block: entries in earlier slots (eight reads in flight)
         u32 acc = 0;
-        for (int s = 0; s < nslots; ++s) {
-            const u32 c = stab[s * B2 + (int)tid];
-            stab[s * B2 + (int)tid] = (uint16_t)acc;
-            acc += c;
+        for (int s0 = 0; s0 < nslots; s0 += 8) {
+            u32 c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = s0 + u < nslots ? (u32)stab[(s0 + u) * B2 + (int)tid] : 0u;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (s0 + u < nslots) stab[(s0 + u) * B2 + (int)tid] = (uint16_t)acc;
+                acc += c[u];
+            }
         }
     }
+    // the words of the stream image (the fine bins, which it overlays, are dead)
+    for (u32 i = tid; i < (u32)a.cap_words; i += kWgThreads) stage[i] = 0;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kWgSlots; ++j) {
@@ -677,57 +686,69 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     } else if (!a.lad.on) {
         // residual on the 2^-15 grid: rint(y * 2^15) reduced to 15 signed bits; bitwidths up to 8 keep
         // y * 2^15 below 2^23, where adding 2^23 rounds to the integer grid with the same round-half-even
-        float inv15[QN];
+        // (the choice stays outside the loops: inside, it was a branch per bitwidth and value)
+        auto abq_sums = [&](auto fast) {
+            constexpr bool kFast = decltype(fast)::value;
+            float inv15[QN];
 #pragma unroll
-        for (int t = 0; t < QN; ++t) inv15[t] = inv[t] * 32768.0f;
-        u64 accE = 0;
-        for (u32 i0 = 0; i0 < T; i0 += 8) {             // u32 partial sums hold 8 residuals of 2^28
-            u32 acc[QN];
+            for (int t = 0; t < QN; ++t) inv15[t] = inv[t] * 32768.0f;
+            u64 accE = 0;
+            u32 nxt = r0 < r1 ? bo_val[r0] : 0u;            // (one value ahead)
+            for (u32 i0 = 0; i0 < T; i0 += 8) {             // u32 partial sums hold 8 residuals of 2^28
+                u32 acc[QN];
 #pragma unroll
-            for (int t = 0; t < QN; ++t) acc[t] = 0;
-            const u32 i1 = i0 + 8 < T ? i0 + 8 : T;
-            for (u32 i = i0; i < i1; ++i) {
-                const u32 p = r0 + i;
-                if (p < r1) {
-                    const float av = __uint_as_float(bo_val[p]);
-                    const u64 A = (u64)(u32)rintf(ldexpf(av, 20 - e));   // 20-bit energy grid scaled to vmax
-                    accE += A * A;
-                    const float d = to_unit(av - vmin, er);
+                for (int t = 0; t < QN; ++t) acc[t] = 0;
+                const u32 i1 = i0 + 8 < T ? i0 + 8 : T;
+                for (u32 i = i0; i < i1; ++i) {
+                    const u32 p = r0 + i;
+                    const float av = __uint_as_float(nxt);
+                    nxt = bo_val[p + 1u < r1 ? p + 1u : r0];
+                    if (p < r1) {
+                        const u64 A = (u64)(u32)rintf(ldexpf(av, 20 - e));   // 20-bit energy grid scaled to vmax
+                        accE += A * A;
+                        const float d = to_unit(av - vmin, er);
 #pragma unroll
-                    for (int t = 0; t < QN; ++t) {
-                        if (NQ || t < nq) {
-                            const u32 zi = small_q ? __float_as_uint(d * inv15[t] + 8388608.0f)
-                                                   : (u32)rintf((d * inv[t]) * 32768.0f);
-                            const int rho = __builtin_amdgcn_sbfe((int)zi, 0u, 15u);
-                            acc[t] += (u32)(rho * rho);
+                        for (int t = 0; t < QN; ++t) {
+                            if (NQ || t < nq) {
+                                const u32 zi = kFast ? __float_as_uint(d * inv15[t] + 8388608.0f) : (u32)rintf((d * inv[t]) * 32768.0f);
+                                const int rho = __builtin_amdgcn_sbfe((int)zi, 0u, 15u);
+                                acc[t] += (u32)(rho * rho);
+                            }
                         }
                     }
                 }
+                if (row_one_block) {
+                    // low 28 bits of a sum, and what is above them four to a word: the sums over a row fit 32 bits
+                    u32 hi4[(QN + 3) / 4];
+#pragma unroll
+                    for (int t = 0; t < (QN + 3) / 4; ++t) hi4[t] = 0;
+#pragma unroll
+                    for (int t = 0; t < QN; ++t) { hi4[t / 4] |= (acc[t] >> 28) << (8 * (t & 3)); acc[t] &= 0xFFFFFFFu; }
+#pragma unroll
+                    for (int t = 0; t < (QN + 3) / 4; ++t) hi4[t] = row_scan_dpp(hi4[t]);
+#pragma unroll
+                    for (int t = 0; t < QN; ++t) {
+                        if (NQ || t < nq) {
+                            const u32 lo = row_scan_dpp(acc[t]);
+                            if (row_last) atomicAdd(&sums[myb * (nq + 1) + t], (u64)lo + ((u64)((hi4[t / 4] >> (8 * (t & 3))) & 0xFFu) << 28));
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int t = 0; t < QN; ++t)
+                        if ((NQ || t < nq) && acc[t]) atomicAdd(&sums[myb * (nq + 1) + t], (u64)acc[t]);
+                }
             }
             if (row_one_block) {
-                // 16-bit pieces, so that the sums over a row fit 32 bits
-#pragma unroll
-                for (int t = 0; t < QN; ++t) {
-                    if (NQ || t < nq) {
-                        const u32 lo16 = row_scan_dpp(acc[t] & 0xFFFFu);
-                        const u32 hi16 = row_scan_dpp(acc[t] >> 16);
-                        if (row_last && (lo16 | hi16)) atomicAdd(&sums[myb * (nq + 1) + t], (u64)lo16 + ((u64)hi16 << 16));
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int t = 0; t < QN; ++t)
-                    if ((NQ || t < nq) && acc[t]) atomicAdd(&sums[myb * (nq + 1) + t], (u64)acc[t]);
+                const u32 e0 = row_scan_dpp((u32)accE & 0x3FFFFFu);
+                const u32 e1 = row_scan_dpp((u32)(accE >> 22) & 0x3FFFFFu);
+                const u32 e2 = row_scan_dpp((u32)(accE >> 44));
+                if (row_last) atomicAdd(&sums[myb * (nq + 1) + nq], (u64)e0 + ((u64)e1 << 22) + ((u64)e2 << 44));
+            } else if (accE) {
+                atomicAdd(&sums[myb * (nq + 1) + nq], accE);
             }
-        }
-        if (row_one_block) {
-            const u32 e0 = row_scan_dpp((u32)accE & 0x3FFFFFu);
-            const u32 e1 = row_scan_dpp((u32)(accE >> 22) & 0x3FFFFFu);
-            const u32 e2 = row_scan_dpp((u32)(accE >> 44));
-            if (row_last && (e0 | e1 | e2)) atomicAdd(&sums[myb * (nq + 1) + nq], (u64)e0 + ((u64)e1 << 22) + ((u64)e2 << 44));
-        } else if (accE) {
-            atomicAdd(&sums[myb * (nq + 1) + nq], accE);
-        }
+        };
+        if (small_q) abq_sums(std::true_type()); else abq_sums(std::false_type());
     }
     __syncthreads();
     if (a.lad.on) {
@@ -769,31 +790,29 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         L.thr[myb] = mycnt * myq;                    // code bits of the block (the boundaries are dead)
     }
     __syncthreads();
-    if (wv == 0) {                                   // bit offsets of the blocks' code sections
+    u32 code_bits, coff;
+    {   // bit offsets of the blocks' code sections: every wavefront scans them itself
         const u32 bits = (int)lane < B2 ? L.thr[lane] : 0u;
         const u32 incl = wave_scan_dpp(bits);
-        if ((int)lane < B2) L.tg[lane] = incl - bits;
-        if (lane == kWave - 1) misc[9] = incl;
+        code_bits = bcast(incl, kWave - 1);
+        coff = (u32)__shfl((int)(incl - bits), (int)(on ? myb : 0u));
     }
-    __syncthreads();
-    const u32 code_bits = misc[9];
-    const u32 coff = on ? L.tg[myb] : 0u;
     const u32 idx_bits = n * (u32)w;
     const u32 row_bits = idx_bits + code_bits;
     u32 row_words = (row_bits + 31u) >> 5;
     if ((u64)row_words > a.cap_words) row_words = (u32)a.cap_words;   // cannot happen (worst-case capacity)
-    __syncthreads();                                 // sums and scales have been read: the stage image overlays nothing live
-    for (u32 i = tid; i < row_words; i += kWgThreads) stage[i] = 0;
-    __syncthreads();
 
     // ---- packing ---------------------------------------------------------------------------------
+    u32 nval = r0 < r1 ? bo_val[r0] : 0u, nidx = r0 < r1 ? (u32)bo_idx[r0] : 0u;     // (one entry ahead)
     for (u32 i = 0; i < T; ++i) {
         const u32 p = r0 + i;
+        const u32 cval = nval, val = nidx, pn = p + 1u < r1 ? p + 1u : r0;
+        nval = bo_val[pn]; nidx = bo_idx[pn];
         if (p < r1) {
             u32 c = 0;
-            if (!dg) c = (u32)rintf(to_unit(__uint_as_float(bo_val[p]) - vmin, er) * my_inv);   // already within [0, 2^q - 1]
+            if (!dg) c = (u32)rintf(to_unit(__uint_as_float(cval) - vmin, er) * my_inv);   // already within [0, 2^q - 1]
             {
-                const u32 P = __umul24(p, (u32)w), wi = P >> 5, sft = P & 31u, val = bo_idx[p];
+                const u32 P = __umul24(p, (u32)w), wi = P >> 5, sft = P & 31u;
                 atomicOr(&stage[wi], val << sft);
                 if (sft + (u32)w > 32u) atomicOr(&stage[wi + 1], val >> (32u - sft));
             }
