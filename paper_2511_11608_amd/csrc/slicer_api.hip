@@ -74,7 +74,7 @@ struct Plan {
     // long-row path (large_S == 0: not eligible)
     int large_S;
     u32 large_capL;
-    size_t lo_tab, lo_cum, lo_seg, lo_Lidx, lo_Lpos, lo_rowst, lo_thr, lo_map, lo_vminb, lo_vmaxb, lo_blk_start, lo_pair, lo_psum,
+    size_t lo_tab, lo_cum, lo_seg, lo_rowst, lo_thr, lo_map, lo_vminb, lo_vmaxb, lo_blk_start, lo_pair, lo_psum,
            lo_qsel, lo_inv_sel, lo_code_off;
 };
 
@@ -94,8 +94,9 @@ int large_tile(int64_t rows, int64_t row_len)
 }
 
 // aligned: x starts on a 16-byte boundary (the workspace layout does not depend on it, only the choice of kernel)
+// long_ragged: rows of odd length may take the long-row stages; without them (the generic kernel) they need less workspace
 Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_blocks, int n_blocks_neg, uint32_t bit_set,
-               bool aligned = true)
+               bool aligned = true, bool long_ragged = true)
 {
     const int B2_all = n_blocks + n_blocks_neg;          // blocks per row
     Plan p;
@@ -115,42 +116,9 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     p.off_row_local = o; o = align256(o + 8 * (size_t)rows);
     p.off_chunk_tot = o; o = align256(o + 8 * (size_t)((rows + kScanRows - 1) / kScanRows));
     p.off_hint = o;      o = align256(o + 4 * (size_t)kHintSlots);
-    // Long rows: every pass is spread over many workgroups (slicer_encode_large.hpp).  A row that starts or ends
-    // inside a 16-byte chunk takes them from 8192 elements on: below, one workgroup of the generic kernel is as fast.
-    p.large_S = 0; p.large_capL = 0;
     const int epc = dt == SLICER_F32 ? 4 : 8;
-    const bool whole = row_len % epc == 0 && aligned;
+    const bool whole_len = row_len % epc == 0, whole = whole_len && aligned;
     const int64_t span = row_len + (whole ? 0 : epc - 1);     // elements of the row's 16-byte chunks
-    {
-        const int64_t tile = large_tile(rows, row_len);
-        const int64_t S = (row_len + epc - 1 + tile - 1) / tile;
-        const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;
-        int nq_l = 0;
-        for (int q = 1; q <= 16; ++q) nq_l += (bit_set >> q) & 1u;
-        if (row_len > 4096 && S <= 512 && rows <= 65535) {
-            const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
-            if (whole || row_len > 8192) p.large_S = (int)S;
-            p.large_capL = (u32)capL;
-            p.kept_stride = capL;
-            p.lo_tab = o;       o = align256(o + 2 * R * kTabSize);
-            p.lo_cum = o;       o = align256(o + 4 * R * Sz * kFB);
-            p.lo_seg = o;       o = align256(o + 8 * R * Sz);
-            p.lo_rowst = o;     o = align256(o + 4 * R * 16);
-            p.lo_thr = o;       o = align256(o + 8 * R * B2);
-            p.lo_map = o;       o = align256(o + 2 * R * kFB);
-            p.lo_vminb = o;     o = align256(o + 4 * R * B2);
-            p.lo_vmaxb = o;     o = align256(o + 4 * R * B2);
-            p.lo_blk_start = o; o = align256(o + 4 * R * (B2 + 1));
-            p.lo_pair = o;      o = align256(o + 4 * R * B2 * Sz);
-            p.lo_psum = o;      o = align256(o + 8 * R * Sz * B2 * (size_t)(nq_l + 1));
-            p.lo_qsel = o;      o = align256(o + 4 * R * B2);
-            p.lo_inv_sel = o;   o = align256(o + 4 * R * B2);
-            p.lo_code_off = o;  o = align256(o + 8 * R * (B2 + 1));
-        }
-    }
-    // the generic kernel's list of a row (8 bytes an entry) and the long-row list (a word and two halves) share their place
-    p.off_kept = o;      o = align256(o + 8 * (size_t)rows * (size_t)p.kept_stride);
-    p.total = o ? o : 256;
 
     // The one-wave-per-row kernel holds the row in registers (64 * EPL elements) and
     // its lists in LDS; it needs 16-bit indices, one lane per
@@ -199,6 +167,43 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
             }
         }
     }
+
+    // Long rows: every pass is spread over many workgroups (slicer_encode_large.hpp).  A row that starts or ends
+    // inside a 16-byte chunk takes them from 8192 elements on: below, one workgroup of the generic kernel is as fast.
+    // Rows of odd length get the stages' tables (16 KB a tile) only where they can reach the stages, so that
+    // the others' workspace stays small enough for slicer_encode_static.
+    p.large_S = 0; p.large_capL = 0;
+    {
+        const int64_t tile = large_tile(rows, row_len);
+        const int64_t S = (row_len + epc - 1 + tile - 1) / tile;
+        const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;
+        int nq_l = 0;
+        for (int q = 1; q <= 16; ++q) nq_l += (bit_set >> q) & 1u;
+        const bool ragged_too = long_ragged && row_len > 8192 && !p.wg_ept && !p.small_epl;
+        if (row_len > 4096 && S <= 512 && rows <= 65535 && (whole_len || ragged_too)) {
+            const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
+            if (whole || row_len > 8192) p.large_S = (int)S;
+            p.large_capL = (u32)capL;
+            p.kept_stride = capL;
+            p.lo_tab = o;       o = align256(o + 2 * R * kTabSize);
+            p.lo_cum = o;       o = align256(o + 4 * R * Sz * kFB);
+            p.lo_seg = o;       o = align256(o + 8 * R * Sz);
+            p.lo_rowst = o;     o = align256(o + 4 * R * 16);
+            p.lo_thr = o;       o = align256(o + 8 * R * B2);
+            p.lo_map = o;       o = align256(o + 2 * R * kFB);
+            p.lo_vminb = o;     o = align256(o + 4 * R * B2);
+            p.lo_vmaxb = o;     o = align256(o + 4 * R * B2);
+            p.lo_blk_start = o; o = align256(o + 4 * R * (B2 + 1));
+            p.lo_pair = o;      o = align256(o + 4 * R * B2 * Sz);
+            p.lo_psum = o;      o = align256(o + 8 * R * Sz * B2 * (size_t)(nq_l + 1));
+            p.lo_qsel = o;      o = align256(o + 4 * R * B2);
+            p.lo_inv_sel = o;   o = align256(o + 4 * R * B2);
+            p.lo_code_off = o;  o = align256(o + 8 * R * (B2 + 1));
+        }
+    }
+    // the generic kernel's list of a row (8 bytes an entry) and the long-row list (a word and two halves) share their place
+    p.off_kept = o;      o = align256(o + 8 * (size_t)rows * (size_t)p.kept_stride);
+    p.total = o ? o : 256;
     return p;
 }
 
@@ -332,7 +337,8 @@ struct CsrShape {
 
 static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row_len, double keep_ratio,
                        int n_blocks, int n_blocks_neg, uint32_t bit_set, double distortion_budget, const Ladder& lad, int guard,
-                       void* stream, void* meta, void* workspace, void* hip_stream, double lambda = 0.0, const CsrShape* csr = nullptr)
+                       void* stream, void* meta, void* workspace, void* hip_stream, double lambda = 0.0, const CsrShape* csr = nullptr,
+                       bool long_ragged = true)
 {
     if (!(lambda >= 0.0 && lambda < 1.0)) return SLICER_EINVAL;
     const bool asym = (float)lambda > 0.0f;      // lambda = 0 is the plain top-K filter: every fast path applies
@@ -344,7 +350,7 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     if (n_blocks_neg < 1 || n_blocks_neg > SLICER_MAX_BLOCKS) return SLICER_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
     const bool aligned = ((uintptr_t)x & 15) == 0, on_elements = ((uintptr_t)x & (dt == SLICER_F32 ? 3 : 1)) == 0;
-    Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks_neg, bit_set, aligned);
+    Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks_neg, bit_set, aligned, long_ragged);
     char* ws = (char*)workspace;
 
     EncArgs ea;
@@ -554,8 +560,13 @@ int slicer_encode_static(const void* x, slicer_dtype dt, int64_t rows, int64_t r
 {
     int rc = check_args((int)dt, rows, row_len, keep_ratio, n_blocks, bit_set);
     if (rc) return rc;
-    const Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set);
-    if (p.total > (size_t)SLICER_STATIC_SCRATCH_BYTES) return SLICER_ETOOBIG;
+    // rows of odd length whose long-row tables do not fit the array go to the generic kernel, which needs none
+    bool long_ragged = true;
+    if (make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set).total > (size_t)SLICER_STATIC_SCRATCH_BYTES) {
+        long_ragged = false;
+        const Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set, true, false);
+        if (p.total > (size_t)SLICER_STATIC_SCRATCH_BYTES) return SLICER_ETOOBIG;
+    }
     if (!x || !stream || !meta) return SLICER_EINVAL;
     void* ws = nullptr;
     rc = static_scratch(&ws);
@@ -564,7 +575,7 @@ int slicer_encode_static(const void* x, slicer_dtype dt, int64_t rows, int64_t r
     none.on = 0;
     for (int j = 0; j < kMaxBlocks / 8; ++j) none.nib[j] = 0;
     return encode_impl(x, dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set, distortion_budget, none, 0,
-                       stream, meta, ws, hip_stream);
+                       stream, meta, ws, hip_stream, 0.0, nullptr, long_ragged);
 }
 
 int slicer_encode_pn(const void* x, slicer_dtype dt, int64_t rows, int64_t row_len, double keep_ratio,

@@ -65,6 +65,9 @@ def test_argument_errors_and_strings(lib):
     # the entry point without a workspace: shapes beyond its static scratch are refused before anything else
     assert lib.slicer_encode_static(None, 1, 16384, 4096, 0.1, 8, 0x1FC, 1e-3, None, None, None) == -5
     assert lib.slicer_encode_static(None, 1, 16, 4096, 0.1, 8, 0x1FC, 1e-3, None, None, None) == -1
+    # rows of odd length: the long-row tables do not count where another kernel serves the row, or can
+    for dt, rows, N, keep, M in ((1, 1621, 4163, 0.05, 16), (0, 1152, 4813, 0.05, 64), (1, 900, 16383, 0.05, 8), (0, 900, 16399, 0.02, 8)):
+        assert lib.slicer_encode_static(None, dt, rows, N, keep, M, 0x1FC, 1e-3, None, None, None) == -1, (dt, rows, N)
 
 
 def test_encode_path_by_shape(lib):

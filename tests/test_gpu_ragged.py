@@ -54,3 +54,20 @@ def test_tensors_that_start_anywhere(oracle, dtype, rows, N, shift):
     torch.cuda.synchronize()
     assert np.array_equal(to_host(view.clone()), y_ref)
     assert bool((big[:shift] == 3).all()) and bool((big[shift + rows * N:] == 3).all())     # nothing beside y is written
+
+
+def test_static_scratch_serves_odd_rows_without_the_long_row_tables(oracle):
+    import torch
+    from paper_2511_11608_amd import binding
+    from paper_2511_11608_amd.devmem import to_device
+    rows, N, keep = 900, 16399, 0.02                    # 72 MiB with the tables of the long-row stages, 5 MiB without
+    assert binding.slicer_sizes(binding.SLICER_F32, rows, N, keep, 8, B28)[2] > 64 << 20
+    x = features("f32", rows, N, 3)
+    s_ref, m_ref = oracle.encode(x, "f32", keep, 8, B28, 1e-3, n_threads=8)
+    xd = to_device(x, "f32")
+    sb, meta, _ = binding.alloc_buffers(xd, keep, 8, B28)
+    binding.slicer_encode_static(xd, keep, 8, B28, 1e-3, sb, meta)
+    words = binding.slicer_stream_words(meta)
+    torch.cuda.synchronize()
+    assert np.array_equal(meta.cpu().numpy(), m_ref)
+    assert np.array_equal(sb[:words].cpu().numpy().view(np.uint32), s_ref)
