@@ -16,8 +16,12 @@
 // split by block, integer ABQ sums (Sec. 3.2.1), bitwidth choice, packing through an LDS image.
 // What changes is who does what: per-element passes and per-entry passes are dealt to the NW
 // wavefronts (thread t owns 16-byte chunks t, t + 64 NW, ...; wavefront v owns list slots v, v + NW,
-// ...), scans run over the workgroup, the two short serial steps (cut, boundaries) run on
-// wavefront 0, and workgroup barriers separate the stages.
+// ...), scans run over the workgroup, and workgroup barriers separate the stages.  What is short and serial (the
+// scan of the chunk totals, the top-K cut, the blocks' boundary bins) every wavefront computes for itself:
+// a repeated computation costs less than one wavefront's result behind a barrier.
+//
+// What bounds it: the chain of barriers and dependent LDS reads, not the arithmetic (bf16 [256 x 8192]: 26.0 us
+// when wavefront 0 did the serial steps for all and members of a bin were read one by one, 20.9 us now).
 //
 // Either guard or a fixed ladder, lambda = 0; rows it cannot hold are flagged for the generic kernel.  bf16 entries
 // are one word (sign, key, inverted index); fp32 entries keep the raw word in the list and the index
