@@ -715,23 +715,36 @@ __device__ inline void write_header(const FinishArgs& a, u64 total)
     for (size_t o = kHeaderBytes + 16 * (size_t)a.R + 9 * (size_t)a.R * (a.M + a.Mn); o < meta_bytes(a.R, a.M + a.Mn); ++o) m8[o] = 0;
 }
 
-// one wavefront copies words [c * kGatherWords, (c + 1) * kGatherWords) of row r's slot to the stream
-__device__ inline void gather_item(const FinishArgs& a, int64_t r, u64 c, u64 off)
+// One wavefront copies words [c * kGatherWords, (c + 1) * kGatherWords) of row r's slot to the stream.  Bound by the
+// latency of dependent loads: eight words per lane are in flight (one at a time, bf16 [16384 x 4096] took 12.6 instead of 8.9 us),
+// and the first ones are on their way while offset() finds where they go.  Segments of up to 128 words, which short
+// rows have, skip the rest of the eight (fp32 [12608 x 768], 84 words a row: 6.6 us with all eight tests).
+template <class F>
+__device__ inline void gather_item(const FinishArgs& a, int64_t r, u64 c, F offset)
 {
     const u32 lane = lane_id();
-    const u64 nw = a.row_words[r];
-    const u64 j0 = c * (u64)kGatherWords;
-    if (j0 >= nw) return;
-    const u64 j1 = j0 + (u64)kGatherWords < nw ? j0 + (u64)kGatherWords : nw;
-    const u32* __restrict__ src = a.slots + (size_t)r * a.cap_words;
-    u32* __restrict__ dst = a.stream + off;
-    // eight words per lane in flight: one at a time, every word waits a memory round trip
-    for (u64 j = j0 + lane; j < j1; j += 8 * kWave) {
-        u32 t[8];
+    const u64 nw = a.row_words[r], j0 = c * (u64)kGatherWords;
+    const u32 n = j0 >= nw ? 0u : nw - j0 < (u64)kGatherWords ? (u32)(nw - j0) : (u32)kGatherWords;
+    const u32* __restrict__ src = a.slots + (size_t)r * a.cap_words + j0;
+    u32 t[8];
+    auto load = [&](u32 j) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = j + (u64)(u * kWave) < j1 ? src[j + (u64)(u * kWave)] : 0u;
+        for (int u = 0; u < 2; ++u) t[u] = j + (u32)(u * kWave) < n ? src[j + (u32)(u * kWave)] : 0u;
+        if (n > 2 * kWave) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) if (j + (u64)(u * kWave) < j1) dst[j + (u64)(u * kWave)] = t[u];
+            for (int u = 2; u < 8; ++u) t[u] = j + (u32)(u * kWave) < n ? src[j + (u32)(u * kWave)] : 0u;
+        }
+    };
+    load(lane);
+    u32* __restrict__ dst = a.stream + offset() + j0;
+    for (u32 j = lane; j < n; j += 8 * kWave) {
+        if (j >= 8 * kWave) load(j);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) if (j + (u32)(u * kWave) < n) dst[j + (u32)(u * kWave)] = t[u];
+        if (n > 2 * kWave) {
+#pragma unroll
+            for (int u = 2; u < 8; ++u) if (j + (u32)(u * kWave) < n) dst[j + (u32)(u * kWave)] = t[u];
+        }
     }
 }
 
@@ -741,27 +754,36 @@ __global__ __launch_bounds__(256) void enc_gather_kernel(FinishArgs a)
     const u32 lane = lane_id();
     const int64_t n_items = a.R * a.chunks_per_row;
     const int64_t wg = xcd_row((int64_t)blockIdx.x, (n_items + 3) / 4);   // neighbouring rows stay on one XCD
-    const int64_t item = wg * (256 / kWave) + threadIdx.x / kWave;
-    const int64_t r = item / a.chunks_per_row;
-    const u64 c = (u64)(item % a.chunks_per_row);
-    if (r >= a.R) return;
-    const int64_t my_chunk = r / kScanRows;
-    const int64_t n_chunks = (a.R + kScanRows - 1) / kScanRows;
-    const bool want_total = item == 0;               // this wave also writes the header
-    const int64_t upto = want_total ? n_chunks : my_chunk;
-    u64 before = 0, total = 0;
-    for (int64_t j = lane; j < upto; j += kWave) {
-        const u64 t = a.chunk_tot[j];
-        total += t;
-        if (j < my_chunk) before += t;
+    const int64_t item = wg * (256 / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    int64_t r = item;
+    u64 c = 0;
+    if (a.chunks_per_row > 1) {                      // (a 64-bit division costs more than the copy of a short row)
+        r = item / a.chunks_per_row;
+        c = (u64)(item % a.chunks_per_row);
     }
+    if (r >= a.R) return;
+    gather_item(a, r, c, [&]() -> u64 {
+        const int64_t my_chunk = r / kScanRows;
+        const int64_t n_chunks = (a.R + kScanRows - 1) / kScanRows;
+        const bool want_total = item == 0;           // this wave also writes the header
+        const int64_t upto = want_total ? n_chunks : my_chunk;
+        u64 before = 0, total = 0;
+        for (int64_t j = lane; j < upto; j += kWave) {
+            const u64 t = a.chunk_tot[j];
+            total += t;
+            if (j < my_chunk) before += t;
+        }
 #pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) { before += __shfl_xor(before, d); total += __shfl_xor(total, d); }
-
-    const u64 off = before + a.row_off_local[r];
-    if (c == 0 && lane == 0) a.mv.row_off[r] = off;
-    if (want_total && lane == 0) write_header(a, total);
-    gather_item(a, r, c, off);
+        for (int d = kWave / 2; d > 0; d >>= 1) before += __shfl_xor(before, d);
+        const u64 off = before + a.row_off_local[r];
+        if (c == 0 && lane == 0) a.mv.row_off[r] = off;
+        if (want_total) {
+#pragma unroll
+            for (int d = kWave / 2; d > 0; d >>= 1) total += __shfl_xor(total, d);
+            if (lane == 0) write_header(a, total);
+        }
+        return off;
+    });
 }
 
 // Batches of up to kScanRows rows (one decode step, one feature map, a batch of long rows): repair, row
@@ -815,7 +837,7 @@ __global__ __launch_bounds__(kScanRows) void enc_finish_small_kernel(EncArgs ea,
         const u64 off = s_off[r];
         if (c == 0 && lane == 0) a.mv.row_off[r] = off;
         if (item == 0 && lane == 0) write_header(a, s_off[kScanRows]);
-        gather_item(a, r, c, off);
+        gather_item(a, r, c, [&]() { return off; });
     }
 }
 
