@@ -175,12 +175,13 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     p.large_S = 0; p.large_capL = 0;
     {
         const int64_t tile = large_tile(rows, row_len);
-        const int64_t S = (row_len + epc - 1 + tile - 1) / tile;
+        // rows of up to 2^23 elements; the workspace has room for the tile more that such a row takes when it starts inside a chunk
+        const int64_t S_whole = (row_len + tile - 1) / tile, S = (row_len + epc - 1 + tile - 1) / tile;
         const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;
         int nq_l = 0;
         for (int q = 1; q <= 16; ++q) nq_l += (bit_set >> q) & 1u;
         const bool ragged_too = long_ragged && row_len > 8192 && !p.wg_ept && !p.small_epl;
-        if (row_len > 4096 && S <= 512 && rows <= 65535 && (whole_len || ragged_too)) {
+        if (row_len > 4096 && S_whole <= 512 && rows <= 65535 && (whole_len || ragged_too)) {
             const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
             if (whole || row_len > 8192) p.large_S = (int)S;
             p.large_capL = (u32)capL;

@@ -83,6 +83,15 @@ def test_encode_path_by_shape(lib):
     assert binding.slicer_encode_path(binding.SLICER_F32, 3, 4097, 0.5, 3, B) == 0           # odd length
 
 
+@pytest.mark.parametrize("dt", [0, 1])
+def test_long_rows_up_to_two_to_the_23(lib, dt):
+    """The stages of many workgroups per row take rows of up to 2^23 elements, in every batch size."""
+    for rows in (1, 2, 64):
+        for N in (8388592, 8388600, 8388607, 8388608):
+            assert lib.slicer_encode_path(dt, rows, N, 0.1, 8, 0x1FC) == 2, (rows, N)
+        assert lib.slicer_encode_path(dt, rows, 8388609, 0.1, 8, 0x1FC) == 0
+
+
 def test_bound_matches_the_oracle_and_the_buffer_sizes(lib, oracle):
     """slicer_bound is host arithmetic: it must agree with the oracle's statement of Sec. 3.3 and
     with the worst-case buffer sizes, on the five workload shapes and a few odd ones."""

@@ -31,6 +31,27 @@ def test_tiles_and_batches(oracle, dtype, rows, N):
     check(oracle, features(dtype, rows, N, N), dtype, 0.12, 8, B28, 1e-3, use_header=bool(rows & 1))
 
 
+@pytest.mark.parametrize("dtype,shift", [("f32", 0), ("f32", 1), ("bf16", 0), ("bf16", 7)])
+def test_longest_rows(oracle, dtype, shift):
+    """2^23 elements: 512 tiles, 513 when the row starts inside a 16-byte chunk."""
+    import torch
+    from paper_2511_11608_amd import binding
+    from paper_2511_11608_amd.devmem import to_device
+    N = 1 << 23
+    x = features(dtype, 1, N, 23)
+    s_ref, m_ref = oracle.encode(x, dtype, 0.01, 8, B28, 1e-3)
+    xd = to_device(x, dtype)
+    big = torch.zeros(N + 16, dtype=xd.dtype, device="cuda")
+    view = big[shift:shift + N].view(1, N)
+    view.copy_(xd)
+    sb, meta, ws = binding.alloc_buffers(view, 0.01, 8, B28)
+    ws.fill_(0xA5)
+    binding.slicer_encode(view, 0.01, 8, B28, 1e-3, sb, meta, ws)
+    words = binding.slicer_stream_words(meta)
+    assert np.array_equal(meta.cpu().numpy(), m_ref)
+    assert np.array_equal(sb[:words].cpu().numpy().view(np.uint32), s_ref)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("kind", ["relu", "sparse", "ties", "outliers", "patches"])
 def test_value_structures(oracle, dtype, kind):
