@@ -120,68 +120,63 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     const bool whole_len = row_len % epc == 0, whole = whole_len && aligned;
     const int64_t span = row_len + (whole ? 0 : epc - 1);     // elements of the row's 16-byte chunks
 
+    int nq = 0;
+    for (int q = 1; q <= 16; ++q) nq += (bit_set >> q) & 1u;
+
     // The one-wave-per-row kernel holds the row in registers (64 * EPL elements) and
     // its lists in LDS; it needs 16-bit indices, one lane per
     // block and a list capacity below 2048 entries (11-bit rank fields).
     // A row that does not consist of whole aligned chunks may start anywhere in its first one.
     p.small_epl = 0; p.small_cap = 0; p.small_region0 = 0; p.small_lds_bytes = 0; p.small_maxs = 0;
-    const int64_t max_n = dt == SLICER_F32 ? 4096 : 8192;
-    int nq = 0;
-    for (int q = 1; q <= 16; ++q) nq += (bit_set >> q) & 1u;
-    if (span <= max_n && B2_all <= kWave) {
-        const int64_t margin = std::max<int64_t>(64, row_len / (dt == SLICER_F32 ? 16 : 32));  // room for the undecided coarse bin
-        int64_t cap = std::min<int64_t>(1984, (p.k + margin + 63) / 64 * 64);   // ranks are 11-bit fields
+    const int64_t margin = std::max<int64_t>(64, row_len / (dt == SLICER_F32 ? 16 : 32));  // room for the undecided coarse bin
+    const int64_t cap = std::min<int64_t>(1984, (p.k + margin + 63) / 64 * 64);   // ranks are 11-bit fields
+    const bool lists_fit = B2_all <= kWave && p.k + 64 <= cap;
+    const int64_t region0 = lists_fit ? small_region0_words(p.k, p.cap_words, B2_all, nq) : 0;
+    const int maxs = cap <= 640 ? 10 : cap <= 1280 ? 20 : 0;             // list held in registers
+    const int64_t small_lds = lists_fit ? 4 * (int64_t)small_lds_words(dt, (int)cap, (int)region0, B2_all, maxs) : 0;
+    auto small_holds = [&](int64_t elements) { return lists_fit && elements <= (dt == SLICER_F32 ? 4096 : 8192) && small_lds <= 64 * 1024; };
+    if (small_holds(span)) {
         int epl = epc;
         while ((int64_t)epl * kWave < span) epl *= 2;
         // fp32 rows of the common transformer widths 768 and 1280: three and five chunks per lane instead of four and eight
         if (dt == SLICER_F32 && span > 512 && span <= 768) epl = 12;
         if (dt == SLICER_F32 && span > 1024 && span <= 1280) epl = 20;
-        const int maxs = cap <= 640 ? 10 : cap <= 1280 ? 20 : 0;             // list held in registers
-        const int64_t region0 = small_region0_words(p.k, p.cap_words, B2_all, nq);
-        const int64_t lds = 4 * (int64_t)small_lds_words(dt, (int)cap, (int)region0, B2_all, maxs);
-        if (p.k + 64 <= cap && lds <= 64 * 1024) {
-            p.small_epl = epl; p.small_cap = (int)cap; p.small_region0 = (int)region0; p.small_lds_bytes = (int)lds;
-            p.small_maxs = maxs;
-        }
+        p.small_epl = epl; p.small_cap = (int)cap; p.small_region0 = (int)region0; p.small_lds_bytes = (int)small_lds;
+        p.small_maxs = maxs;
     }
     // One workgroup per row (the wavefronts of a workgroup share the row): every row of more than 4096 and up to
     // 32768 bf16 / 16384 fp32 elements.  For bf16 rows of 4097..8192 elements, which one wavefront could hold,
     // it is the faster kernel at every batch size (16384 rows of 8192: 238 against 293 us; 4096 rows of 6144:
     // 68 against 74 us); at 4096 elements and below one wavefront per row wins (115 against 189 us).
     p.wg_ept = 0; p.wg_nw = 0; p.wg_cap = 0; p.wg_region0 = 0; p.wg_lds_bytes = 0;
-    {
-        const int64_t wg_max = dt == SLICER_F32 ? 16384 : 32768;
-        if (span > 4096 && span <= wg_max && B2_all <= kWave) {
-            const int64_t margin = std::max<int64_t>(64, row_len / (dt == SLICER_F32 ? 16 : 32));
-            const int64_t cap = std::min<int64_t>(1984, (p.k + margin + 63) / 64 * 64);
-            const int64_t region0 = small_region0_words(p.k, p.cap_words, B2_all, nq);
-            const int64_t lds = 4 * (int64_t)wg_lds_words(dt, (int)cap, (int)region0, B2_all);
-            if (p.k + 64 <= cap && lds <= 64 * 1024) {
-                // wavefronts per row: sixteen for the smallest batches (more wavefronts per SIMD hide each other's
-                // latencies: 4 % less latency per call), four otherwise (a 256-row batch on sixteen leaves no room
-                // for a neighbouring stream's kernels: 20 % less throughput when steps overlap)
-                p.wg_nw = rows <= 128 ? 16 : 4;
-                const int64_t chunks = ((span + epc - 1) / epc + 64 * p.wg_nw - 1) / (64 * p.wg_nw);     // 16-byte chunks per thread
-                p.wg_ept = (int)(chunks <= 1 ? 1 : chunks <= 2 ? 2 : chunks <= 4 ? 4 : chunks <= 8 ? 8 : 16);    // (kept as a chunk count)
-                p.wg_cap = (int)cap; p.wg_region0 = (int)region0; p.wg_lds_bytes = (int)lds;
-            }
-        }
+    const int64_t wg_lds = lists_fit ? 4 * (int64_t)wg_lds_words(dt, (int)cap, (int)region0, B2_all) : 0;
+    auto wg_holds = [&](int64_t elements) {
+        return lists_fit && elements > 4096 && elements <= (dt == SLICER_F32 ? 16384 : 32768) && wg_lds <= 64 * 1024;
+    };
+    if (wg_holds(span)) {
+        // wavefronts per row: sixteen for the smallest batches (more wavefronts per SIMD hide each other's
+        // latencies: 4 % less latency per call), four otherwise (a 256-row batch on sixteen leaves no room
+        // for a neighbouring stream's kernels: 20 % less throughput when steps overlap)
+        p.wg_nw = rows <= 128 ? 16 : 4;
+        const int64_t chunks = ((span + epc - 1) / epc + 64 * p.wg_nw - 1) / (64 * p.wg_nw);     // 16-byte chunks per thread
+        p.wg_ept = (int)(chunks <= 1 ? 1 : chunks <= 2 ? 2 : chunks <= 4 ? 4 : chunks <= 8 ? 8 : 16);    // (kept as a chunk count)
+        p.wg_cap = (int)cap; p.wg_region0 = (int)region0; p.wg_lds_bytes = (int)wg_lds;
     }
 
     // Long rows: every pass is spread over many workgroups (slicer_encode_large.hpp).  A row that starts or ends
     // inside a 16-byte chunk takes them from 8192 elements on: below, one workgroup of the generic kernel is as fast.
-    // Rows of odd length get the stages' tables (16 KB a tile) only where they can reach the stages, so that
-    // the others' workspace stays small enough for slicer_encode_static.
+    // The workspace holds the stages' tables (16 KB a tile and more) only where some row of this length can reach the
+    // stages: not where a row-resident kernel holds the row wherever it starts.
     p.large_S = 0; p.large_capL = 0;
     {
         const int64_t tile = large_tile(rows, row_len);
         // rows of up to 2^23 elements; the workspace has room for the tile more that such a row takes when it starts inside a chunk
         const int64_t S_whole = (row_len + tile - 1) / tile, S = (row_len + epc - 1 + tile - 1) / tile;
         const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;
-        int nq_l = 0;
-        for (int q = 1; q <= 16; ++q) nq_l += (bit_set >> q) & 1u;
-        const bool ragged_too = long_ragged && row_len > 8192 && !p.wg_ept && !p.small_epl;
-        if (row_len > 4096 && S_whole <= 512 && rows <= 65535 && (whole_len || ragged_too)) {
+        auto row_kernel_holds = [&](int64_t elements) { return small_holds(elements) || wg_holds(elements); };
+        const bool held = (!whole_len || row_kernel_holds(row_len)) && row_kernel_holds(row_len + epc - 1);
+        const bool ragged_too = long_ragged && row_len > 8192;
+        if (row_len > 4096 && S_whole <= 512 && rows <= 65535 && !held && (whole_len || ragged_too)) {
             const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
             if (whole || row_len > 8192) p.large_S = (int)S;
             p.large_capL = (u32)capL;
@@ -196,7 +191,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
             p.lo_vmaxb = o;     o = align256(o + 4 * R * B2);
             p.lo_blk_start = o; o = align256(o + 4 * R * (B2 + 1));
             p.lo_pair = o;      o = align256(o + 4 * R * B2 * Sz);
-            p.lo_psum = o;      o = align256(o + 8 * R * Sz * B2 * (size_t)(nq_l + 1));
+            p.lo_psum = o;      o = align256(o + 8 * R * Sz * B2 * (size_t)(nq + 1));
             p.lo_qsel = o;      o = align256(o + 4 * R * B2);
             p.lo_inv_sel = o;   o = align256(o + 4 * R * B2);
             p.lo_code_off = o;  o = align256(o + 8 * R * (B2 + 1));

@@ -92,6 +92,20 @@ def test_long_rows_up_to_two_to_the_23(lib, dt):
         assert lib.slicer_encode_path(dt, rows, 8388609, 0.1, 8, 0x1FC) == 0
 
 
+def test_workspace_without_tables_that_nothing_reaches(lib):
+    """Rows that a row-resident kernel holds wherever they start: slots, lists and offsets only."""
+    from paper_2511_11608_amd import binding
+    held = ((1, 16384, 8192, 0.1, 8), (1, 851, 18400, 0.01, 4), (1, 256, 32760, 0.05, 8), (0, 900, 16380, 0.05, 8), (1, 2000, 8193, 0.1, 8))
+    reach = ((1, 16, 32768, 0.05, 8), (0, 16, 16384, 0.05, 8),     # a shifted row is too long for the row kernel
+             (1, 16, 8192, 0.25, 8), (0, 16, 8192, 0.05, 33))       # list or blocks too many for it
+    for shapes, tables in ((held, False), (reach, True)):
+        for dt, rows, N, keep, M in shapes:
+            cap, _, ws = binding.slicer_sizes(dt, rows, N, keep, M, 0x1FC)
+            k = int(keep * N)
+            plain = cap + rows * (8 + 8 * k + 8 * k + 4 + 8) + 64 * 1024
+            assert (ws > plain + 16384 * rows) == tables and (ws > plain) == tables, (dt, rows, N, keep, M)
+
+
 def test_bound_matches_the_oracle_and_the_buffer_sizes(lib, oracle):
     """slicer_bound is host arithmetic: it must agree with the oracle's statement of Sec. 3.3 and
     with the worst-case buffer sizes, on the five workload shapes and a few odd ones."""

@@ -31,7 +31,9 @@ def test_lengths_around_the_layouts(oracle, dtype, N):
 
 
 @pytest.mark.parametrize("dtype,rows,N,shift", [("f32", 9, 768, 1), ("f32", 300, 1024, 3), ("f32", 5, 4096, 2), ("bf16", 9, 4096, 1),
-                                                ("bf16", 400, 512, 5), ("bf16", 4, 8192, 7), ("bf16", 3, 1001, 3)])
+                                                ("bf16", 400, 512, 5), ("bf16", 4, 8192, 7), ("bf16", 3, 1001, 3),
+                                                # aligned they are the longest rows of the workgroup-per-row kernel
+                                                ("f32", 6, 16384, 1), ("bf16", 3, 32768, 7)])
 def test_tensors_that_start_anywhere(oracle, dtype, rows, N, shift):
     import torch
     from paper_2511_11608_amd import binding
