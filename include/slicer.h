@@ -56,7 +56,7 @@ enum {
     SLICER_EUNSUPPORTED = -2, /* unknown dtype */
     SLICER_EHIP = -3,         /* a HIP call failed; see slicer_last_hip_error() */
     SLICER_EFORMAT = -4,      /* meta header is not a version-1 header */
-    SLICER_ETOOBIG = -5       /* slicer_encode_static: the shape needs more scratch than the library holds */
+    SLICER_ETOOBIG = -5       /* slicer_encode_static: every kernel needs more scratch for the shape than the library holds */
 };
 
 #define SLICER_MAX_BLOCKS 64  /* n_blocks (per sign class) accepted by the library */
@@ -100,8 +100,10 @@ int slicer_encode(const void* x, slicer_dtype dt, int64_t rows, int64_t row_len,
  * allocates nothing (no hipMalloc, hipFree or allocating library routine); its workspace is a
  * static device array of SLICER_STATIC_SCRATCH_BYTES inside the library, of which every GPU the
  * library runs on holds a copy until the process ends.  Arguments, output and errors as
- * slicer_encode (same kernels, byte-identical stream and meta), plus SLICER_ETOOBIG when the
- * shape's workspace_bytes (slicer_sizes) exceed SLICER_STATIC_SCRATCH_BYTES.  All calls on one
+ * slicer_encode (byte-identical stream and meta).  A shape whose workspace_bytes (slicer_sizes)
+ * exceed SLICER_STATIC_SCRATCH_BYTES is served by a kernel that needs less scratch, where there is
+ * one (long rows by the generic kernel, whatever slicer_encode_path says), and is refused with
+ * SLICER_ETOOBIG otherwise.  All calls on one
  * GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two host
  * threads) race and give undefined output; calls on one stream are ordered and safe.  The
  * array keeps the last call's contents; the kernels write every word before they read it.

@@ -94,9 +94,9 @@ int large_tile(int64_t rows, int64_t row_len)
 }
 
 // aligned: x starts on a 16-byte boundary (the workspace layout does not depend on it, only the choice of kernel)
-// long_ragged: rows of odd length may take the long-row stages; without them (the generic kernel) they need less workspace
+// long_rows: the long-row stages may serve the call; without them (the generic kernel) it needs less workspace
 Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_blocks, int n_blocks_neg, uint32_t bit_set,
-               bool aligned = true, bool long_ragged = true)
+               bool aligned = true, bool long_rows = true)
 {
     const int B2_all = n_blocks + n_blocks_neg;          // blocks per row
     Plan p;
@@ -175,8 +175,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
         const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;
         auto row_kernel_holds = [&](int64_t elements) { return small_holds(elements) || wg_holds(elements); };
         const bool held = (!whole_len || row_kernel_holds(row_len)) && row_kernel_holds(row_len + epc - 1);
-        const bool ragged_too = long_ragged && row_len > 8192;
-        if (row_len > 4096 && S_whole <= 512 && rows <= 65535 && !held && (whole_len || ragged_too)) {
+        if (long_rows && row_len > 4096 && S_whole <= 512 && rows <= 65535 && !held && (whole_len || row_len > 8192)) {
             const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
             if (whole || row_len > 8192) p.large_S = (int)S;
             p.large_capL = (u32)capL;
@@ -334,7 +333,7 @@ struct CsrShape {
 static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row_len, double keep_ratio,
                        int n_blocks, int n_blocks_neg, uint32_t bit_set, double distortion_budget, const Ladder& lad, int guard,
                        void* stream, void* meta, void* workspace, void* hip_stream, double lambda = 0.0, const CsrShape* csr = nullptr,
-                       bool long_ragged = true)
+                       bool long_rows = true)
 {
     if (!(lambda >= 0.0 && lambda < 1.0)) return SLICER_EINVAL;
     const bool asym = (float)lambda > 0.0f;      // lambda = 0 is the plain top-K filter: every fast path applies
@@ -346,7 +345,7 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     if (n_blocks_neg < 1 || n_blocks_neg > SLICER_MAX_BLOCKS) return SLICER_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
     const bool aligned = ((uintptr_t)x & 15) == 0, on_elements = ((uintptr_t)x & (dt == SLICER_F32 ? 3 : 1)) == 0;
-    Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks_neg, bit_set, aligned, long_ragged);
+    Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks_neg, bit_set, aligned, long_rows);
     char* ws = (char*)workspace;
 
     EncArgs ea;
@@ -556,10 +555,10 @@ int slicer_encode_static(const void* x, slicer_dtype dt, int64_t rows, int64_t r
 {
     int rc = check_args((int)dt, rows, row_len, keep_ratio, n_blocks, bit_set);
     if (rc) return rc;
-    // rows of odd length whose long-row tables do not fit the array go to the generic kernel, which needs none
-    bool long_ragged = true;
+    // rows whose long-row tables do not fit the array go to the generic kernel, which needs none
+    bool long_rows = true;
     if (make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set).total > (size_t)SLICER_STATIC_SCRATCH_BYTES) {
-        long_ragged = false;
+        long_rows = false;
         const Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set, true, false);
         if (p.total > (size_t)SLICER_STATIC_SCRATCH_BYTES) return SLICER_ETOOBIG;
     }
@@ -571,7 +570,7 @@ int slicer_encode_static(const void* x, slicer_dtype dt, int64_t rows, int64_t r
     none.on = 0;
     for (int j = 0; j < kMaxBlocks / 8; ++j) none.nib[j] = 0;
     return encode_impl(x, dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set, distortion_budget, none, 0,
-                       stream, meta, ws, hip_stream, 0.0, nullptr, long_ragged);
+                       stream, meta, ws, hip_stream, 0.0, nullptr, long_rows);
 }
 
 int slicer_encode_pn(const void* x, slicer_dtype dt, int64_t rows, int64_t row_len, double keep_ratio,

@@ -106,6 +106,16 @@ def test_workspace_without_tables_that_nothing_reaches(lib):
             assert (ws > plain + 16384 * rows) == tables and (ws > plain) == tables, (dt, rows, N, keep, M)
 
 
+def test_static_scratch_serves_whole_rows_without_the_long_row_tables(lib):
+    """Shapes near 64 MiB whose tables do not fit go to the generic kernel; what no kernel can serve is refused."""
+    from paper_2511_11608_amd import binding
+    for dt, rows, N, keep, M, bits in ((0, 1064, 4928, 0.02, 33, 0x24), (1, 777, 16384, 0.01, 33, 0x1FC), (1, 391, 75776, 0.001, 32, 0x1FFFE),
+                                       (0, 337, 74780, 0.02, 64, 0x1FC), (0, 403, 65536, 0.02, 31, 0x1FC), (0, 4, 8388608, 0.05, 1, 0x24)):
+        assert binding.slicer_sizes(dt, rows, N, keep, M, bits)[2] > 64 << 20
+        assert lib.slicer_encode_static(None, dt, rows, N, keep, M, bits, 1e-3, None, None, None) == -1, (dt, rows, N)
+    assert lib.slicer_encode_static(None, 0, 4, 8388608, 0.5, 1, 0x24, 1e-3, None, None, None) == -5
+
+
 def test_bound_matches_the_oracle_and_the_buffer_sizes(lib, oracle):
     """slicer_bound is host arithmetic: it must agree with the oracle's statement of Sec. 3.3 and
     with the worst-case buffer sizes, on the five workload shapes and a few odd ones."""

@@ -73,3 +73,19 @@ def test_static_scratch_serves_odd_rows_without_the_long_row_tables(oracle):
     torch.cuda.synchronize()
     assert np.array_equal(meta.cpu().numpy(), m_ref)
     assert np.array_equal(sb[:words].cpu().numpy().view(np.uint32), s_ref)
+
+
+def test_static_scratch_serves_whole_rows_without_the_long_row_tables(oracle):
+    import torch
+    from paper_2511_11608_amd import binding
+    from paper_2511_11608_amd.devmem import to_device
+    rows, N, keep, M, bits = 1064, 4928, 0.02, 33, 0x24     # 65 MiB with the tables of the long-row stages, 3 MiB without
+    x = features("f32", rows, N, 4)
+    s_ref, m_ref = oracle.encode(x, "f32", keep, M, bits, 1e-3, n_threads=8)
+    xd = to_device(x, "f32")
+    sb, meta, _ = binding.alloc_buffers(xd, keep, M, bits)
+    binding.slicer_encode_static(xd, keep, M, bits, 1e-3, sb, meta)
+    words = binding.slicer_stream_words(meta)
+    torch.cuda.synchronize()
+    assert np.array_equal(meta.cpu().numpy(), m_ref)
+    assert np.array_equal(sb[:words].cpu().numpy().view(np.uint32), s_ref)
