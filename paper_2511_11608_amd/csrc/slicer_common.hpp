@@ -272,17 +272,24 @@ struct RowChunks {
     }
     __device__ inline bool ragged() const { return head != 0 || (Nh & (EPC - 1)) != 0; }     // the same for a whole row
     __device__ inline bool whole(int q) const { return q * EPC >= head && q * EPC + EPC <= Nh; }
-    __device__ inline uint4 partial(int q) const     // chunk q, only the row's own elements
+    // Chunk q, only the row's own elements, zeros elsewhere.  Every element load takes place, at the nearest place inside
+    // the row (which has at least one element), and callers keep the call out of branches on whole(): no load here
+    // stands under the opposite condition of the whole-chunk load, so the two cannot be made one with an address
+    // that only some lanes set.
+    __device__ inline uint4 partial(int q) const
     {
         typedef typename Elem<DT>::raw_t raw_t;
-        const raw_t* e = (const raw_t*)(base + q);
+        const raw_t* e = (const raw_t*)base;
         u32 v[EPC];
 #pragma unroll
         for (int j = 0; j < EPC; ++j) {
+            const int i = q * EPC + j, at = i < head ? head : i < Nh ? i : Nh - 1;
+            v[j] = (u32)e[at];
+        }
+#pragma unroll
+        for (int j = 0; j < EPC; ++j) {
             const int i = q * EPC + j;
-            // (non-temporal: these loads must not be merged with the whole-chunk load of a neighbouring branch; merged,
-            //  the compiler has been seen to leave the address of the lanes with whole chunks undefined)
-            v[j] = i >= head && i < Nh ? (u32)__builtin_nontemporal_load(e + j) : 0u;
+            v[j] = i >= head && i < Nh ? v[j] : 0u;
         }
         if (DT == 0) return make_uint4(v[0], v[1], v[2], v[3]);
         return make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[EPC - 4] | (v[EPC - 3] << 16), v[EPC - 2] | (v[EPC - 1] << 16));
@@ -309,19 +316,15 @@ struct RowChunks {
                 v[c] = q * EPC < Nh ? base[q] : make_uint4(0, 0, 0, 0);
             }
         } else {
+            const int ql = (Nh - 1) / EPC;           // the row's last chunk
+            const uint4 first = partial(0), last = partial(ql);
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
                 const int q = c * STEP + t;
                 v[c] = whole(q) ? base[q] : make_uint4(0, 0, 0, 0);
+                if (q == ql) v[c] = last;
             }
-            const int ql = (Nh - 1) / EPC;           // the row's last chunk
-            if (t == 0 && !whole(0)) v[0] = partial(0);
-            if (ql > 0 && t == ql % STEP && !whole(ql)) {
-                const uint4 e = partial(ql);
-                const int cl = ql / STEP;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) if (c == cl) v[c] = e;
-            }
+            if (t == 0) v[0] = first;
         }
     }
 };

@@ -324,12 +324,14 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
         }
         if (rg) {
             const int ql = (row.Nh - 1) / EPC;
-            if (q0 + (int)lane == 0 && !row.whole(0)) v[0] = row.partial(0);
-            if (ql > 0 && ql >= q0 && ql < q0 + WCH && (ql - q0) % kWave == (int)lane && !row.whole(ql)) {
+            if (ql >= q0 && ql < q0 + WCH) {         // (uniform in the wavefront, as the next one)
                 const uint4 e = row.partial(ql);
-                const int cl = (ql - q0) / kWave;
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) if (c == cl) v[c] = e;
+                for (int c = 0; c < NCH; ++c) if (q0 + c * kWave + (int)lane == ql) v[c] = e;
+            }
+            if (q0 == 0) {
+                const uint4 e = row.partial(0);
+                if (lane == 0) v[0] = e;
             }
         }
     }
