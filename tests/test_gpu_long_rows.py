@@ -66,3 +66,33 @@ def test_value_structures(oracle, dtype, kind):
 def test_csr_blocks(oracle, dtype, inst, n_rows, n_cols):
     for kind in ("normal", "sparse"):
         check_csr(oracle, features(dtype, inst, n_rows * n_cols, 5, kind), dtype, n_rows, n_cols, 0.1, 8, B28, 1e-3)
+
+
+@pytest.mark.parametrize("inst,n_rows,n_cols,M,keep", [(2, 40_000, 1, 1, 0.3), (3, 9_000, 7, 1, 0.2), (2, 1, 50_000, 16, 0.3), (2, 7, 9_001, 16, 0.3),
+                                                       (1, 2_049, 33, 2, 0.5)])
+def test_csr_pointers_searched_and_walked(oracle, inst, n_rows, n_cols, M, keep):
+    """Windows that hold a part of a block's row pointers, blocks with far more entries than pointers, and the reverse."""
+    for kind in ("relu", "normal", "patches"):
+        check_csr(oracle, features("f32", inst, n_rows * n_cols, 6, kind), "f32", n_rows, n_cols, keep, M, B28, 1e-3)
+
+
+@pytest.mark.parametrize("dtype,shift", [("f32", 3), ("bf16", 5)])
+def test_csr_of_long_rows_through_the_flat_stream(oracle, dtype, shift):
+    """The stages write CSR themselves only for aligned tensors and pointers of eight bits and more."""
+    import torch
+    from paper_2511_11608_amd import binding
+    from paper_2511_11608_amd.devmem import to_device
+    n_rows, n_cols = 120, 400
+    x = features(dtype, 2, n_rows * n_cols, 8)
+    for keep in (0.0, 0.5 / (n_rows * n_cols), 100.5 / (n_rows * n_cols), 127.5 / (n_rows * n_cols), 128.5 / (n_rows * n_cols)):    # k = 0, 0, 100, 127, 128
+        check_csr(oracle, x, dtype, n_rows, n_cols, keep, 4, B28, 1e-3)
+    s_ref, m_ref = oracle.encode_csr(x, dtype, n_rows, n_cols, 0.1, 8, B28, 1e-3, n_threads=8)
+    xd = to_device(x, dtype)
+    view = torch.zeros(x.size + 16, dtype=xd.dtype, device="cuda")[shift:shift + x.size].view(x.shape)
+    view.copy_(xd)
+    sb, meta, ws = binding.alloc_buffers_csr(view, n_rows, n_cols, 0.1, 8, B28)
+    ws.fill_(0xA5)
+    binding.slicer_encode_csr(view, n_rows, n_cols, 0.1, 8, B28, 1e-3, sb, meta, ws)
+    words = binding.slicer_stream_words(meta)
+    assert np.array_equal(meta.cpu().numpy(), m_ref)
+    assert np.array_equal(sb[:words].cpu().numpy().view(np.uint32), s_ref)
