@@ -72,7 +72,7 @@ struct Plan {
     // workgroup-per-row path for bf16 rows of up to 32768 elements (0 = not eligible)
     int wg_ept, wg_nw, wg_cap, wg_region0, wg_lds_bytes;
     // long-row path (large_S == 0: not eligible)
-    int large_S;
+    int large_S, large_fb;  // tiles per row, fine bins
     u32 large_capL;
     size_t lo_tab, lo_cum, lo_seg, lo_rowst, lo_thr, lo_map, lo_vminb, lo_vmaxb, lo_blk_start, lo_pair, lo_psum,
            lo_qsel, lo_inv_sel, lo_code_off;
@@ -87,10 +87,24 @@ int count_bits(int64_t k)      // bits that hold any value in 0..k
     return w;
 }
 
-// Elements per tile of the long-row stages: short tiles while they do not fill the chip (one tile per CU)
+// Elements per tile of the long-row stages: short tiles while they do not fill the chip (one tile per CU), and in large
+// batches where they leave out a quarter or more of what long tiles would cover (bf16 [4096 x 8192] 461 -> 428 us, fp32
+// [4096 x 20480] 529 -> 510; with a sixth left out the added tiles cost more: bf16 [4096 x 33001] 758 -> 826)
 int large_tile(int64_t rows, int64_t row_len)
 {
-    return rows * ((row_len + 8191) / 8192) <= 256 ? 8192 : 16384;
+    const int64_t n8 = (row_len + 8191) / 8192;
+    return rows * n8 <= 256 || (rows > kScanRows && (n8 == 1 || n8 == 3)) ? 8192 : 16384;
+}
+
+// Fine bins per row of the long-row stages.  Few of them in large batches (encode with 4096 and with 1024: fp32 [4096 x 20480]
+// 821 and 529 us, bf16 [9494 x 8738] keep 0.01 M 64 2367 and 1146, bf16 [512 x 8193] M 40 113 and 108), where the bins
+// that hold a block's first or last element (two per block, most of them shared) should fit a row's room of 1536 members: a bin
+// is filled with 8 to 16 entries, or with k / 700 and up to twice as many, and all of them together cannot
+// hold more than the list, about 1.4 k.
+int large_fine_bins(int64_t rows, int64_t k, int B2)
+{
+    const int64_t members = std::min<int64_t>((B2 + 2) * std::max<int64_t>(12, k * 3 / 1400), k * 14 / 10 + 100);
+    return rows > kScanRows && members <= 1200 ? kFBNarrow : kFBWide;
 }
 
 // aligned: x starts on a 16-byte boundary (the workspace layout does not depend on it, only the choice of kernel)
@@ -167,7 +181,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     // inside a 16-byte chunk takes them from 8192 elements on: below, one workgroup of the generic kernel is as fast.
     // The workspace holds the stages' tables (16 KB a tile and more) only where some row of this length can reach the
     // stages: not where a row-resident kernel holds the row wherever it starts.
-    p.large_S = 0; p.large_capL = 0;
+    p.large_S = 0; p.large_capL = 0; p.large_fb = 0;
     {
         const int64_t tile = large_tile(rows, row_len);
         // rows of up to 2^23 elements; the workspace has room for the tile more that such a row takes when it starts inside a chunk
@@ -179,13 +193,14 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
             const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
             if (whole || row_len > 8192) p.large_S = (int)S;
             p.large_capL = (u32)capL;
+            p.large_fb = large_fine_bins(rows, p.k, B2_all);
             p.kept_stride = capL;
             p.lo_tab = o;       o = align256(o + 2 * R * kTabSize);
-            p.lo_cum = o;       o = align256(o + 4 * R * Sz * kFB);
+            p.lo_cum = o;       o = align256(o + 4 * R * Sz * (size_t)p.large_fb);
             p.lo_seg = o;       o = align256(o + 8 * R * Sz);
             p.lo_rowst = o;     o = align256(o + 4 * R * 16);
             p.lo_thr = o;       o = align256(o + 8 * R * B2);
-            p.lo_map = o;       o = align256(o + 2 * R * kFB);
+            p.lo_map = o;       o = align256(o + 2 * R * (size_t)p.large_fb);
             p.lo_vminb = o;     o = align256(o + 4 * R * B2);
             p.lo_vmaxb = o;     o = align256(o + 4 * R * B2);
             p.lo_blk_start = o; o = align256(o + 4 * R * (B2 + 1));
@@ -209,26 +224,26 @@ hipError_t launch_small_any(const SmallArgs& sa, const SmallLaunch& p, bool asym
     return sa.nq == 7 ? launch_small<DT, false, 7>(sa, p, st) : launch_small<DT, false, 0>(sa, p, st);
 }
 
-template <int DT, int NE>
-void launch_split(const LargeArgs& la, hipStream_t st)
+template <int DT, int FB>
+void launch_large_stages(const LargeArgs& la, const EncArgs& ea, const FinishArgs& fa, hipStream_t st)
 {
-    const dim3 g((unsigned)la.S, (unsigned)la.R), b(kTileThreads);
-    const size_t lds = (size_t)lr_split_carve(NE, la.M + la.Mn, la.nq).total;
-    if (la.nq == 7) hipLaunchKernelGGL((lr_split_kernel<DT, NE, 7>), g, b, lds, st, la);   // {2..8}: the benchmarked set
-    else hipLaunchKernelGGL((lr_split_kernel<DT, NE, 0>), g, b, lds, st, la);
+    const dim3 gT((unsigned)la.S, (unsigned)la.R), gR((unsigned)la.R), gW((unsigned)la.nwin, (unsigned)la.R), bT(kTileThreads);
+    hipLaunchKernelGGL((lr_sample_kernel<DT, FB>), gR, dim3(FB / 4), 0, st, la);
+    if (la.tile == 8192) hipLaunchKernelGGL((lr_compact_kernel<DT, 2, FB>), gT, bT, 0, st, la);
+    else hipLaunchKernelGGL((lr_compact_kernel<DT, 4, FB>), gT, bT, 0, st, la);
+    hipLaunchKernelGGL((lr_bounds_kernel<DT, FB>), gR, dim3(FB / 4), 0, st, la, ea);
+    const size_t lds = (size_t)lr_split_carve(FB, la.M + la.Mn, la.nq).total;
+    if (la.nq == 7) hipLaunchKernelGGL((lr_split_kernel<DT, 7, FB>), gT, bT, lds, st, la);   // {2..8}: the benchmarked set
+    else hipLaunchKernelGGL((lr_split_kernel<DT, 0, FB>), gT, bT, lds, st, la);
+    if (la.n_cols > 0) hipLaunchKernelGGL((lr_pack_kernel<DT, true>), gW, dim3(256), 0, st, la, fa);
+    else hipLaunchKernelGGL((lr_pack_kernel<DT, false>), gW, dim3(256), 0, st, la, fa);
 }
 
 template <int DT>
-int launch_large(const LargeArgs& la, const EncArgs& ea, const FinishArgs& fa, hipStream_t st)
+int launch_large(const LargeArgs& la, int fine_bins, const EncArgs& ea, const FinishArgs& fa, hipStream_t st)
 {
-    const dim3 gT((unsigned)la.S, (unsigned)la.R), gR((unsigned)la.R), gW((unsigned)la.nwin, (unsigned)la.R);
-    hipLaunchKernelGGL((lr_sample_kernel<DT>), gR, dim3(1024), 0, st, la);
-    if (la.tile == 8192) hipLaunchKernelGGL((lr_compact_kernel<DT, 2>), gT, dim3(kTileThreads), 0, st, la);
-    else hipLaunchKernelGGL((lr_compact_kernel<DT, 4>), gT, dim3(kTileThreads), 0, st, la);
-    hipLaunchKernelGGL((lr_bounds_kernel<DT>), gR, dim3(1024), 0, st, la, ea);
-    launch_split<DT, 4>(la, st);
-    if (la.n_cols > 0) hipLaunchKernelGGL((lr_pack_kernel<DT, true>), gW, dim3(256), 0, st, la, fa);
-    else hipLaunchKernelGGL((lr_pack_kernel<DT, false>), gW, dim3(256), 0, st, la, fa);
+    if (fine_bins == kFBNarrow) launch_large_stages<DT, kFBNarrow>(la, ea, fa, st);
+    else launch_large_stages<DT, kFBWide>(la, ea, fa, st);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SLICER_OK : hip_fail(e);
 }
@@ -479,13 +494,21 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         la.lad = lad;
         la.guard = guard;
         la.direct = rows <= kScanRows ? 1 : 0;
-        la.dt = (int)dt; la.bit_set = bit_set; la.stream = (u32*)stream; la.meta = meta;
+        la.stream = (u32*)stream; la.meta = meta;
+        la.redo = p.large_fb == kFBNarrow ? (u32*)(ws + p.off_fallback) : nullptr;
         const bool timed = g_ev_start && g_ev_stop;
         if (timed) SLICER_HIP(hipEventRecord(g_ev_start, st));
-        rc = dt == SLICER_F32 ? launch_large<0>(la, ea, fa, st) : launch_large<1>(la, ea, fa, st);
+        rc = dt == SLICER_F32 ? launch_large<0>(la, p.large_fb, ea, fa, st) : launch_large<1>(la, p.large_fb, ea, fa, st);
         if (rc) return rc;
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
         if (la.direct) return SLICER_OK;
+        if (la.redo) {                              // flagged rows, spread over the chip (data with many equal values flags all of them)
+            EncArgs ra = ea;
+            ra.only_flagged = la.redo;
+            ra.rows_per_wg = (int)((rows + 1023) / 1024);
+            rc = dt == SLICER_F32 ? launch_encode<0>(ra, st) : launch_encode<1>(ra, st);
+            if (rc) return rc;
+        }
         done = true;
     }
     if (csr && !done) return SLICER_EINVAL;         // (callers ask for this form only where the long-row stages apply)

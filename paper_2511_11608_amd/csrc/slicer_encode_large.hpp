@@ -40,9 +40,13 @@ namespace slicer {
 
 constexpr int kTileThreads = 512;   // a compact / split workgroup handles a tile of 8192 or 16384 elements
 constexpr int kMaxTab = 510, kTabSize = kMaxTab + 2;        // sample bins with fine bins of their own: 16 octaves above the bound
-constexpr int kFB = 4096;           // fine bins per row
+// Fine bins per row, a template parameter (FB) of the stages.  A batch of up to 256 rows has a CU for every row and takes the
+// many bins, few members each, and FB / 4 = 1024 threads per row where a stage works on whole rows; there a row's latency counts.
+// In a larger batch the rows wait for each other and what counts is a row's cost: tables of 16 KB a tile to write and
+// sum, and one row per CU at a time (the bounds stage's LDS), made fp32 [4096 x 20480] 821 us.
+constexpr int kFBWide = 4096, kFBNarrow = 1024;
 constexpr int kSampleBins = 8192;   // 32 bins per octave
-constexpr int kMemCap = 6144;       // members of the bins that hold order statistics, per row
+constexpr int lr_mem_cap(int FB) { return FB == kFBWide ? 6144 : 1536; }       // members of the bins that hold order statistics, per row
 constexpr int kPackWords = 1024;    // stream words per pack workgroup
 constexpr u64 kTop = 1ull << 63;
 
@@ -56,12 +60,13 @@ struct LargeArgs {
     int tile, S;            // elements of a tile, tiles per row
     u32 capL;               // list capacity per row
     uint16_t* tab;          // [R][kTabSize]  first fine bin of a sample bin | log2 of its number of fine bins << 12; one guard at either end
-    u32* cum;               // [R][S][kFB]    entries of the tile at or above the bin: positive | negative << 16
+    u32* cum;               // [R][S][FB]     entries of the tile at or above the bin: positive | negative << 16
     u32* seg;               // [R][S][2]      list position of the tile's segment, positive | negative entries << 16
     uint8_t* L;             // [R][8 capL]    a row's list, see LrList (the generic encoder's list of the row has the same place)
     u32* rowst;             // [R][16]        see kSt*
+    u32* redo;              // [R]            the row is left to the generic encoder (narrow tables only)
     u64* thr;               // [R][B2]        comp of the block's last element
-    uint8_t* map;           // [R][2][kFB]    block of a fine bin's first element by class (kMapNone: not kept) | kMapMixed: also of the next | kMapMany: and beyond
+    uint8_t* map;           // [R][2][FB]     block of a fine bin's first element by class (kMapNone: not kept) | kMapMixed: also of the next | kMapMany: and beyond
     u32* vminb;             // [R][B2]        keys
     u32* vmaxb;
     u32* blk_start;         // [R][B2 + 1]
@@ -82,8 +87,6 @@ struct LargeArgs {
     int pack_words_code;    // ... from the first word with code bits on (fields there are short: fewer words per workgroup)
     int nwin_idx, nwin;     // windows that may lie in the index section; windows per row
     int direct;             // 1: words go to their place in the stream, 0: to the row's slot
-    int dt;
-    u32 bit_set;
     u32* stream;
     void* meta;
     // two-dimensional instances (n_cols > 0): row pointers and columns instead of flat indices
@@ -145,30 +148,33 @@ __device__ inline u32 chunk_elem(const uint4& v, int e)
 __device__ inline u64 lr_comp(u32 key, u32 idx, int w) { return ((u64)key << w) | (u64)(((1u << w) - 1u) - idx); }
 
 // ---- 1. sample ------------------------------------------------------------------------------------
-template <int DT>
-__global__ __launch_bounds__(1024) void lr_sample_kernel(LargeArgs a)
+template <int DT, int FB>
+__global__ __launch_bounds__(FB / 4) __attribute__((amdgpu_waves_per_eu(FB == kFBWide ? 4 : DT == 0 ? 6 : 5))) void lr_sample_kernel(LargeArgs a)
 {
     typedef Elem<DT> E;
-    constexpr int EPC = RowChunks<DT>::EPC, NU = 4 /* 4096 chunks */, SH = LrOrder<DT>::kSh;
-    __shared__ u32 h[kSampleBins];
-    __shared__ u32 h2[4096];
-    __shared__ u32 scr[1024 / kWave + 1];
+    constexpr int TH = FB / 4, NU = FB == kFBWide ? 4 : 8, LG = FB == kFBWide ? 12 : 11;     // 4096 or 2048 chunks
+    constexpr int EPC = RowChunks<DT>::EPC, SH = LrOrder<DT>::kSh, SUB = FB == kFBWide ? 12 : 10;
+    static_assert(TH * NU == 1 << LG && FB == 1 << SUB && TH * NU * EPC < 65536, "16-bit counters");
+    constexpr bool kHalf = FB != kFBWide;            // two counters per word (more rows per CU; a single row is 0.4 us faster with words)
+    __shared__ u32 h[kHalf ? kSampleBins / 2 : kSampleBins];
+    __shared__ u32 h2[FB];
+    __shared__ u32 scr[TH / kWave + 1];
     __shared__ u32 s_v[8];
     const int tid = threadIdx.x, w = a.w;
     const int64_t r = blockIdx.x;
     const RowChunks<DT> row(a.x, r, a.N);
-    const u32 Q = (u32)(row.Nh + EPC - 1) / EPC, G = Q < 1024u * NU ? Q : 1024u * NU;      // chunks of the row, of the sample
+    const u32 Q = (u32)(row.Nh + EPC - 1) / EPC, G = Q < (u32)(TH * NU) ? Q : (u32)(TH * NU);      // chunks of the row, of the sample
     const bool rg = row.ragged();
     // one chunk from every G-th of the row, at a hashed place: even spread without a period
     uint4 v[NU];
     u32 qs[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        const u32 g = (u32)u * 1024u + (u32)tid;
+        const u32 g = (u32)u * (u32)TH + (u32)tid;
         v[u] = make_uint4(0, 0, 0, 0);
         qs[u] = 0;
         if (g < G) {
-            const u32 lo = G == Q ? g : (u32)(((u64)g * Q) >> 12), len = G == Q ? 1u : (u32)(((u64)(g + 1u) * Q) >> 12) - lo;
+            const u32 lo = G == Q ? g : (u32)(((u64)g * Q) >> LG), len = G == Q ? 1u : (u32)(((u64)(g + 1u) * Q) >> LG) - lo;
             u32 hs = g * 0x9E3779B1u;
             hs ^= hs >> 15; hs *= 0x85EBCA77u; hs ^= hs >> 13;
             qs[u] = lo + __umulhi(hs, len);
@@ -177,10 +183,11 @@ __global__ __launch_bounds__(1024) void lr_sample_kernel(LargeArgs a)
     }
     {
         uint4* h4 = (uint4*)h;
-        for (int i = tid; i < kSampleBins / 4; i += 1024) h4[i] = make_uint4(0, 0, 0, 0);
+        for (int i = tid; i < (kHalf ? kSampleBins / 8 : kSampleBins / 4); i += TH) h4[i] = make_uint4(0, 0, 0, 0);
         ((uint4*)h2)[tid] = make_uint4(0, 0, 0, 0);
         if (tid < 8) s_v[tid] = tid == 5 ? (u32)kSampleBins - 1u : 0u;
     }
+    auto count_of = [&](u32 bin) -> u32 { return kHalf ? (h[bin >> 1] >> (16u * (bin & 1u))) & 0xFFFFu : h[bin]; };
     u32* st = a.rowst + (size_t)r * 16;
     if (tid == 0) { st[kStCursor] = 0; st[kStTicket] = 0; st[kStFlag] = 0; }
     __syncthreads();
@@ -192,8 +199,8 @@ __global__ __launch_bounds__(1024) void lr_sample_kernel(LargeArgs a)
     for (int u = 0; u < NU; ++u)
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
-            const u32 c = c32_of(u, e);
-            if (c) atomicAdd(&h[c >> SH], 1u);
+            const u32 c = c32_of(u, e), bin = c >> SH;
+            if (c) atomicAdd(&h[kHalf ? bin >> 1 : bin], kHalf ? 1u << (16u * (bin & 1u)) : 1u);
         }
     __syncthreads();
     // how many of the sample's elements must reach the bound: the expected number of the k kept ones plus four
@@ -202,29 +209,37 @@ __global__ __launch_bounds__(1024) void lr_sample_kernel(LargeArgs a)
     const double f = (double)a.k / (double)a.N;
     const double want = whole ? (double)a.k : f * G * EPC + 4.0 * EPC * sqrt((double)G * f * (1.0 - f));
     const u32 target = (u32)want + (whole && a.k > 0 ? 0u : 1u);
-    const int hi = kSampleBins - tid * 8;           // thread t owns the 8 bins below kSampleBins - 8 t
-    u32 cs[8];
-    {
-        const uint4 t1 = ((const uint4*)h)[hi / 4 - 1], t0 = ((const uint4*)h)[hi / 4 - 2];
-        cs[0] = t1.w; cs[1] = t1.z; cs[2] = t1.y; cs[3] = t1.x; cs[4] = t0.w; cs[5] = t0.z; cs[6] = t0.y; cs[7] = t0.x;
+    constexpr int BPT = kSampleBins / TH;
+    const int hi = kSampleBins - tid * BPT;         // thread t owns the BPT bins below kSampleBins - BPT t
+    u32 cs[BPT];
+    constexpr int PER = kHalf ? 8 : 4;              // bins per 16 bytes
+#pragma unroll
+    for (int j = 0; j < BPT / PER; ++j) {
+        const uint4 t = ((const uint4*)h)[hi / PER - 1 - j];
+        const u32 wd[4] = { t.w, t.z, t.y, t.x };
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (kHalf) { cs[PER * j + 2 * i] = wd[i] >> 16; cs[PER * j + 2 * i + 1] = wd[i] & 0xFFFFu; }
+            else cs[PER * j + i] = wd[i];
+        }
     }
     u32 local = 0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) local += cs[j];
+    for (int j = 0; j < BPT; ++j) local += cs[j];
     u32 tot;
     {
-        u32 acc = block_excl_scan<1024>(local, scr, &tot);
+        u32 acc = block_excl_scan<TH>(local, scr, &tot);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < BPT; ++j) {
             if (acc < target && target <= acc + cs[j]) { s_v[0] = (u32)(hi - 1 - j); s_v[1] = acc; s_v[2] = 1u; }
             acc += cs[j];
         }
         if (local) {
             int topj = 0, botj = 0;
 #pragma unroll
-            for (int j = 7; j >= 0; --j) if (cs[j]) topj = j;
+            for (int j = BPT - 1; j >= 0; --j) if (cs[j]) topj = j;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) if (cs[j]) botj = j;
+            for (int j = 0; j < BPT; ++j) if (cs[j]) botj = j;
             atomicMax(&s_v[3], (u32)(hi - 1 - topj));
             atomicMin(&s_v[5], (u32)(hi - 1 - botj));
         }
@@ -234,28 +249,28 @@ __global__ __launch_bounds__(1024) void lr_sample_kernel(LargeArgs a)
     if (s_v[2]) {                                    // uniform
         const u32 B = s_v[0];
         T = B << SH;
-        if (!whole && h[B] * 16u > target) {         // a full bin: the bound inside it
+        if (!whole && count_of(B) * 16u > target) {  // a full bin: the bound inside it
             const u32 rem = target - s_v[1];
 #pragma unroll
             for (int u = 0; u < NU; ++u)
 #pragma unroll
                 for (int e = 0; e < EPC; ++e) {
                     const u32 c = c32_of(u, e);
-                    if (c && (c >> SH) == B) atomicAdd(&h2[(c >> (SH - 12)) & 4095u], 1u);
+                    if (c && (c >> SH) == B) atomicAdd(&h2[(c >> (SH - SUB)) & (u32)(FB - 1)], 1u);
                 }
             __syncthreads();
-            const int hi2 = 4096 - tid * 4;
+            const int hi2 = FB - tid * 4;
             const uint4 t = ((const uint4*)h2)[hi2 / 4 - 1];
             const u32 c2[4] = { t.w, t.z, t.y, t.x };
             u32 tot2;
-            u32 acc = block_excl_scan<1024>(t.x + t.y + t.z + t.w, scr, &tot2);
+            u32 acc = block_excl_scan<TH>(t.x + t.y + t.z + t.w, scr, &tot2);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (acc < rem && rem <= acc + c2[j]) s_v[4] = (u32)(hi2 - 1 - j);
                 acc += c2[j];
             }
             __syncthreads();
-            T |= s_v[4] << (SH - 12);
+            T |= s_v[4] << (SH - SUB);
         }
         if (T < LrOrder<DT>::kLeast) T = LrOrder<DT>::kLeast;
     }
@@ -268,21 +283,33 @@ __global__ __launch_bounds__(1024) void lr_sample_kernel(LargeArgs a)
     if (Btop - Blo > (u32)kMaxTab - 1u) Btop = Blo + (u32)kMaxTab - 1u;
     const u32 nb = Btop - Blo + 1u;
     const float scale = (float)((double)a.N / ((double)G * EPC));
-    const u32 room = (u32)kFB - 2u - nb;
-    float per = scale * (float)((tot < target ? tot : target) + h[Blo]) / (float)room + 1.0f;
+    const u32 room = (u32)FB - 2u - nb;
+    float per = scale * (float)((tot < target ? tot : target) + count_of(Blo)) / (float)room + 1.0f;
     per = per < 8.0f ? 8.0f : per;
-    u32 lg = 0, sub = 0;                             // thread i: sample bin Blo + i
-    if ((u32)tid < nb) {
-        const u32 c = (u32)((float)h[Blo + (u32)tid] * scale / per);
-        lg = c > 1u ? 31u - (u32)__clz((int)c) : 0u;
-        lg = lg < 12u ? lg : 12u;
-        sub = 1u << lg;
+    constexpr int VPT = TH >= 512 ? 1 : 512 / TH;    // thread i: sample bins Blo + VPT i, ...
+    u32 lg[VPT], sub = 0;
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        const u32 i = (u32)(tid * VPT + j);
+        lg[j] = 0;
+        if (i < nb) {
+            const u32 c = (u32)((float)count_of(Blo + i) * scale / per);
+            lg[j] = c > 1u ? 31u - (u32)__clz((int)c) : 0u;
+            lg[j] = lg[j] < (u32)SUB ? lg[j] : (u32)SUB;
+            sub += 1u << lg[j];
+        }
     }
     u32 nbins;
-    u32 base = block_excl_scan<1024>(sub, scr, &nbins);
-    if (nbins > (u32)kFB - 2u) { lg = 0; nbins = nb; base = (u32)tid; }    // cannot happen by more than rounding: one fine bin each
+    u32 base = block_excl_scan<TH>(sub, scr, &nbins);
+    const bool over = nbins > (u32)FB - 2u;          // cannot happen by more than rounding: one fine bin each
+    if (over) { nbins = nb; base = (u32)(tid * VPT); }
     uint16_t* tab = a.tab + (size_t)r * kTabSize;
-    if ((u32)tid < nb) tab[tid + 1] = (uint16_t)((base + 1u) | (lg << 12));
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        const u32 i = (u32)(tid * VPT + j), l = over ? 0u : lg[j];
+        if (i < nb) tab[i + 1u] = (uint16_t)((base + 1u) | (l << 12));
+        base += 1u << l;
+    }
     if (tid == 0) { tab[0] = 0; tab[nb + 1u] = (uint16_t)(nbins + 1u); }
     if (tid == 0) { st[kStT] = T; st[kStBlo] = Blo; st[kStNb] = nb; }
 }
@@ -292,14 +319,13 @@ __global__ __launch_bounds__(1024) void lr_sample_kernel(LargeArgs a)
 // 512 at a time: the entries above the bound are first squeezed into its own piece of LDS (index order), then every
 // lane takes whole entries.  With a fifth of the elements above the bound the work per entry (fine bin, atomic,
 // stores) would otherwise run with a fifth of the lanes; nothing in between is a workgroup barrier.
-template <int DT, int NR>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void lr_compact_kernel(LargeArgs a)
+template <int DT, int NR, int FB>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(FB == kFBWide ? 8 : 6))) void lr_compact_kernel(LargeArgs a)
 {
-    typedef Elem<DT> E;
     constexpr int EPC = RowChunks<DT>::EPC, CPR = 8 / EPC;           // chunks per lane and round: 2 (fp32), 1 (bf16)
     constexpr int NCH = NR * CPR, NWV = kTileThreads / kWave, RE = 8 * kWave, WCH = NCH * kWave;     // chunks of a wavefront
     constexpr int kBuf = NWV * RE * 6, kPass = kBuf / 2;     // bytes; list positions arranged at a time
-    __shared__ u32 hist[kFB];                        // positive | negative << 16; later the entries above the bin
+    __shared__ u32 hist[FB];                         // positive | negative << 16; later the entries above the bin
     __shared__ __align__(4) uint16_t tab[kTabSize];
     __shared__ __align__(16) unsigned char buf[kBuf];
     __shared__ u32 wtot[NWV];
@@ -338,7 +364,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     const u32 T = st[kStT], Blo = st[kStBlo], nb = st[kStNb];
     {
         uint4* h4 = (uint4*)hist;
-        for (int i = tid; i < kFB / 4; i += kTileThreads) h4[i] = make_uint4(0, 0, 0, 0);
+        for (int i = tid; i < FB / 4; i += kTileThreads) h4[i] = make_uint4(0, 0, 0, 0);
         const u32* tg = (const u32*)(a.tab + (size_t)r * kTabSize);
         if (tid < kTabSize / 2) ((u32*)tab)[tid] = tg[tid];
     }
@@ -448,20 +474,31 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     __syncthreads();
     u32* seg = a.seg + ((size_t)r * a.S + s) * 2;
     {
-        constexpr int BPT = kFB / kTileThreads;      // 8 bins per thread, from the top
-        uint4* h4 = (uint4*)hist + (kFB - tid * BPT) / 4;
-        const uint4 t1 = h4[-1], t0 = h4[-2];
-        const u32 local = t1.x + t1.y + t1.z + t1.w + t0.x + t0.y + t0.z + t0.w;     // the halves add up separately: no sum reaches 2^16
+        // bins per thread from the top, 8 or 2; the halves add up separately: no sum reaches 2^16
+        constexpr int BPT = FB / kTileThreads;
+        typedef u32 bins_t __attribute__((ext_vector_type(BPT < 4 ? BPT : 4)));
+        constexpr int VW = BPT < 4 ? BPT : 4, NV = BPT / VW;
+        bins_t* h4 = (bins_t*)hist + (FB - tid * BPT) / VW;
+        bins_t t[NV];
+        u32 local = 0;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            t[i] = h4[-1 - i];
+#pragma unroll
+            for (int j = 0; j < VW; ++j) local += t[i][j];
+        }
         u32 tot;
-        const u32 ex = block_excl_scan<kTileThreads>(local, scr, &tot);
-        const u32 a7 = ex + t1.w, a6 = a7 + t1.z, a5 = a6 + t1.y, a4 = a5 + t1.x;    // at or above
-        const u32 a3 = a4 + t0.w, a2 = a3 + t0.z, a1 = a2 + t0.y, a0 = a1 + t0.x;
-        uint4* out = (uint4*)(a.cum + ((size_t)r * a.S + s) * kFB) + (kFB - tid * BPT) / 4;
-        out[-1] = make_uint4(a4, a5, a6, a7);
-        out[-2] = make_uint4(a0, a1, a2, a3);
+        u32 at = block_excl_scan<kTileThreads>(local, scr, &tot);
         const u32 off = (tot & 0xFFFFu) << 16;       // the negative entries follow the positive ones
-        h4[-1] = make_uint4(a5 + off, a6 + off, a7 + off, ex + off);
-        h4[-2] = make_uint4(a1 + off, a2 + off, a3 + off, a4 + off);
+        bins_t* out = (bins_t*)(a.cum + ((size_t)r * a.S + s) * FB) + (FB - tid * BPT) / VW;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            bins_t up, st0;                          // entries at or above the bin; place of the bin's first one
+#pragma unroll
+            for (int j = VW - 1; j >= 0; --j) { st0[j] = at + off; at += t[i][j]; up[j] = at; }
+            out[-1 - i] = up;
+            h4[-1 - i] = st0;
+        }
         if (tid == 0) { seg[0] = seg0; seg[1] = tot; }
     }
     if (full || ntile == 0u) return;                 // uniform
@@ -532,8 +569,10 @@ __device__ inline void lr_finish_row(const LargeArgs& a, int64_t r, u32 n_pos, u
 // ---- 3. bounds ------------------------------------------------------------------------------------
 constexpr int kMaxTargets = 2 * kMaxB2;
 
+template <int FB>
 struct LrBoundsLds {
-    u32 at_p[kFB + 1], at_n[kFB + 1];                // list entries at or above the bin
+    static constexpr int kMemCap = lr_mem_cap(FB);
+    u32 at_p[FB + 1], at_n[FB + 1];                // list entries at or above the bin
     u64 mem[kMemCap];                                // members of the bins that hold a target
     u32 mem_g[kMemCap];                              // their group | tile << 8
     u32 tg_bin[kMaxTargets], tg_rem[kMaxTargets];    // target 2 b: first element of block b, 2 b + 1: its last one
@@ -543,17 +582,19 @@ struct LrBoundsLds {
     u32 v[8];
 };
 
-template <int DT>
-__global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea)
+template <int DT, int FB>
+__global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs ea)
 {
-    constexpr size_t kLds = sizeof(LrBoundsLds) > sizeof(GenericLds<1024>) ? sizeof(LrBoundsLds) : sizeof(GenericLds<1024>);
-    __shared__ __align__(16) unsigned char lds[kLds];
-    LrBoundsLds& L = *(LrBoundsLds*)lds;
+    constexpr int TH = FB / 4, kMemCap = lr_mem_cap(FB);
+    constexpr bool kRedo = FB == kFBWide;            // rows that do not fit are redone here (else: after the pack stage)
+    constexpr size_t kOwn = sizeof(LrBoundsLds<FB>), kRedoLds = kRedo ? sizeof(GenericLds<1024>) : 0;
+    __shared__ __align__(16) unsigned char lds[kOwn > kRedoLds ? kOwn : kRedoLds];
+    LrBoundsLds<FB>& L = *(LrBoundsLds<FB>*)lds;
     const int tid = threadIdx.x, w = a.w, M = a.M, Mn = a.Mn, B2 = M + Mn, S = a.S;
     const int64_t r = blockIdx.x;
     u32* st = a.rowst + (size_t)r * 16;
     const u32 k = (u32)a.k;
-    const u32* __restrict__ cum = a.cum + (size_t)r * S * kFB;
+    const u32* __restrict__ cum = a.cum + (size_t)r * S * FB;
     const u32* __restrict__ seg = a.seg + (size_t)r * S * 2;
     const LrList list(a, r);
     const u32* __restrict__ Lraw = list.raw;
@@ -570,7 +611,7 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
         for (int s0 = 0; s0 < S; s0 += 8) {
             uint4 t[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = s0 + u < S ? ((const uint4*)(cum + (size_t)(s0 + u) * kFB))[tid] : make_uint4(0, 0, 0, 0);
+            for (int u = 0; u < 8; ++u) t[u] = s0 + u < S ? ((const uint4*)(cum + (size_t)(s0 + u) * FB))[tid] : make_uint4(0, 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 p[0] += t[u].x & 0xFFFFu; p[1] += t[u].y & 0xFFFFu; p[2] += t[u].z & 0xFFFFu; p[3] += t[u].w & 0xFFFFu;
@@ -579,7 +620,7 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) { L.at_p[tid * 4 + j] = p[j]; L.at_n[tid * 4 + j] = n[j]; }
-        if (tid == 0) { L.at_p[kFB] = 0; L.at_n[kFB] = 0; }
+        if (tid == 0) { L.at_p[FB] = 0; L.at_n[FB] = 0; }
         if (tid < 8) L.v[tid] = 0;
     }
     __syncthreads();
@@ -589,10 +630,10 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
     auto at_c = [&](u32 cls, u32 b) -> u32 { return cls == 0u ? L.at_p[b] : cls == 1u ? L.at_n[b] : L.at_p[b] + L.at_n[b]; };
     // members of the bins of groups 0 .. ng - 1 (g_start: room per group), tile by tile
     auto gather = [&](int ng) {
-        for (int i = tid; i < ng * S; i += 1024) {
+        for (int i = tid; i < ng * S; i += TH) {
             const int g = i / S, s = i - g * S;
             const u32 cls = L.g_cls[g], b = L.g_bin[g];
-            const u32 c0 = cum[(size_t)s * kFB + b], c1 = b + 1u < (u32)kFB ? cum[(size_t)s * kFB + b + 1u] : 0u;
+            const u32 c0 = cum[(size_t)s * FB + b], c1 = b + 1u < (u32)FB ? cum[(size_t)s * FB + b + 1u] : 0u;
             const u32 seg0 = seg[2 * s], np = seg[2 * s + 1] & 0xFFFFu;
 #pragma unroll
             for (u32 h = 0; h < 2u; ++h) {
@@ -641,7 +682,7 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
             else {
                 gather(1);
                 const u32 rem = k - 1u - at_c(2, cb + 1u);
-                for (u32 i = (u32)tid; i < cn; i += 1024) {
+                for (u32 i = (u32)tid; i < cn; i += TH) {
                     const u64 me = L.mem[i] & ~kTop;
                     u32 gt = 0;
                     for (u32 j = 0; j < cn; ++j) gt += (L.mem[j] & ~kTop) > me ? 1u : 0u;
@@ -663,7 +704,7 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
             if (cnt) {
                 const u32 rank = (u32)m * K + ((tid & 1) ? cnt - 1u : 0u);
                 const u32* at = c ? L.at_n : L.at_p;
-                int lo = 0, hi = kFB - 1;            // the last bin with more than `rank` entries at or above it
+                int lo = 0, hi = FB - 1;            // the last bin with more than `rank` entries at or above it
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
                     if (at[mid] > rank) lo = mid; else hi = mid - 1;
@@ -704,7 +745,7 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
         if (nm > (u32)kMemCap) bad = true;
         else {
             gather(ng);
-            for (u32 i = (u32)tid; i < nm; i += 1024) {
+            for (u32 i = (u32)tid; i < nm; i += TH) {
                 const u32 g = L.mem_g[i] & 0xFFu, m1 = L.g_start[g + 1];
                 const u64 me = L.mem[i];
                 u32 gt = 0;
@@ -714,19 +755,19 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
             }
             __syncthreads();
             // per tile: entries of the class from the block's last element up
-            for (u32 i = (u32)tid; i < nm; i += 1024) {
+            for (u32 i = (u32)tid; i < nm; i += TH) {
                 const u32 g = L.mem_g[i] & 0xFFu;
                 const u64 me = L.mem[i] & ~kTop;
                 for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t)
                     if ((t & 1u) && me >= L.tg_comp[t]) atomicAdd(&pair[(size_t)(t >> 1) * S + (L.mem_g[i] >> 8)], 1u);
             }
-            for (int b = tid; b < B2; b += 1024) {
+            for (int b = tid; b < B2; b += TH) {
                 const u64 first = L.tg_comp[2 * b], last = L.tg_comp[2 * b + 1];
                 a.thr[(size_t)r * B2 + b] = last;
                 a.vminb[(size_t)r * B2 + b] = last == ~0ull ? 0u : (u32)(last >> w);
                 a.vmaxb[(size_t)r * B2 + b] = last == ~0ull ? 0u : (u32)(first >> w);
             }
-            for (int b = tid; b <= B2; b += 1024) {  // K, ..., K, K + remainder per class
+            for (int b = tid; b <= B2; b += TH) {  // K, ..., K, K + remainder per class
                 const int c = b >= M ? 1 : 0, m = b - c * M;
                 a.blk_start[(size_t)r * (B2 + 1) + b] = b == B2 ? n_pos + n_neg : (c ? n_pos : 0u) + (u32)m * (c ? Kc1 : Kc0);
             }
@@ -756,11 +797,16 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
                     }
                     wd |= v << (8u * j);
                 }
-                ((u32*)(a.map + ((size_t)r * 2 + c) * kFB))[tid] = wd;
+                ((u32*)(a.map + ((size_t)r * 2 + c) * FB))[tid] = wd;
             }
         }
     }
-    if (bad) {                                       // rare: the row goes to its slot by the generic encoder
+    if constexpr (!kRedo) {
+        if (tid == 0) {
+            a.redo[r] = bad ? 1u : 0u;
+            if (bad) { st[kStFlag] = 1u; a.row_words[r] = 0; a.blk_start[(size_t)r * (B2 + 1) + B2] = 0; }     // (nothing for the pack stage)
+        }
+    } else if (bad) {                                // rare: the row goes to its slot by the generic encoder
         __syncthreads();
         if (tid == 0) st[kStFlag] = 1u;
         enc_generic_rows<DT, 1024>(ea, r, r + 1, *(GenericLds<1024>*)lds);
@@ -786,20 +832,21 @@ __global__ __launch_bounds__(1024) void lr_bounds_kernel(LargeArgs a, EncArgs ea
 }
 
 // ---- 4. split -------------------------------------------------------------------------------------
-// LDS carve-up (bytes); NE: entries per thread and step
+constexpr int kSplitNE = 4;          // entries per thread and step (eight spill)
+// LDS carve-up (bytes)
 struct LrSplitLds { int thr, sums, place, val, map, gbase, lstart, cnt, inv, vmin, e, er, tab, lidx, wcnt, blk, total; };
-// room for a step's entries with every block padded to whole groups of NE
-__host__ __device__ inline int lr_split_room(int NE, int B2) { return kTileThreads * NE + NE * (B2 + 1); }     // (and one group for what is not kept)
-__host__ __device__ inline LrSplitLds lr_split_carve(int NE, int B2, int nq)
+// room for a step's entries with every block padded to whole groups of kSplitNE
+__host__ __device__ inline int lr_split_room(int B2) { return (kTileThreads + B2 + 1) * kSplitNE; }     // (and one group for what is not kept)
+__host__ __device__ inline LrSplitLds lr_split_carve(int FB, int B2, int nq)
 {
     LrSplitLds o;
-    const int EC = lr_split_room(NE, B2);
+    const int EC = lr_split_room(B2);
     int p = 0;
     o.thr = p;    p += 8 * (B2 > (int)kMapNone + 1 ? B2 : (int)kMapNone + 1);
     o.sums = p;   p += 8 * B2 * (nq + 1);
     o.place = p;  p += 8 * B2;
     o.val = (p + 15) & ~15; p = o.val + 4 * EC;
-    o.map = p;    p += 2 * kFB;
+    o.map = p;    p += 2 * FB;
     o.gbase = p;  p += 4 * B2;
     o.lstart = p; p += 4 * (B2 + 1);
     o.cnt = p;    p += 4 * B2;
@@ -810,7 +857,7 @@ __host__ __device__ inline LrSplitLds lr_split_carve(int NE, int B2, int nq)
     o.tab = p;    p += 2 * kTabSize;
     o.lidx = p;   p += 2 * EC;
     o.wcnt = p;   p += 2 * (kTileThreads / kWave) * B2;
-    o.blk = p;    p += EC / NE;
+    o.blk = p;    p += EC / kSplitNE;
     o.total = (p + 15) & ~15;
     return o;
 }
@@ -819,11 +866,11 @@ __host__ __device__ inline LrSplitLds lr_split_carve(int NE, int B2, int nq)
 __device__ inline void agent_store(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline u64 agent_load(const u64* p) { return __hip_atomic_load(const_cast<u64*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// ABQ sums of the first `left` of NE values of one block (keys as fp32 patterns): acc[t] += squared residual (or DS mismatch) at the
+// ABQ sums of the first `left` of kSplitNE values of one block (keys as fp32 patterns): acc[t] += squared residual (or DS mismatch) at the
 // t-th bitwidth; returns the energy.  inv15: 2^15 L / (range brought to [1, 2)) per bitwidth, 0 for a block of range 0.
 // MODE 0: squared error, bitwidths up to 8; 1: squared error, any bitwidth; 2: Eq. "DS"
-template <int DT, int NE, int NQ, int MODE>
-__device__ inline u64 lr_abq_entries(const LargeArgs& a, int nq, const u32 (&vv)[NE], u32 left, float vmin, int e, int er, const float* inv15,
+template <int DT, int NQ, int MODE>
+__device__ inline u64 lr_abq_entries(const LargeArgs& a, int nq, const u32 (&vv)[kSplitNE], u32 left, float vmin, int e, int er, const float* inv15,
                                      u32 (&acc)[NQ ? NQ : kMaxQ])
 {
     constexpr int QN = NQ ? NQ : kMaxQ;
@@ -835,7 +882,7 @@ __device__ inline u64 lr_abq_entries(const LargeArgs& a, int nq, const u32 (&vv)
     if (MODE == 2) inv_top = inv15[top] * 0x1p-15f;
     u64 accE = 0;
 #pragma unroll
-    for (int j = 0; j < NE; ++j) {
+    for (int j = 0; j < kSplitNE; ++j) {
         const bool in = (u32)j < left;
         const float av = in ? __uint_as_float(vv[j]) : vmin;   // (an offset of zero adds nothing to any residual)
         const u64 A = in ? (u64)(u32)rintf(ldexpf(av, 20 - e)) : 0ull;     // 20-bit energy grid scaled to vmax
@@ -870,11 +917,11 @@ __device__ inline u64 lr_abq_entries(const LargeArgs& a, int nq, const u32 (&vv)
 }
 
 // NQ > 0: the number of allowed bitwidths is known at compile time; NQ == 0: any number up to 16.
-template <int DT, int NE, int NQ>
+template <int DT, int NQ, int FB>
 __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void lr_split_kernel(LargeArgs a)
 {
     typedef Elem<DT> E;
-    constexpr int QN = NQ ? NQ : kMaxQ, NWV = kTileThreads / kWave, EC = kTileThreads * NE;
+    constexpr int QN = NQ ? NQ : kMaxQ, NWV = kTileThreads / kWave, NE = kSplitNE, EC = kTileThreads * NE;
     static_assert(NE <= 8, "u32 partial sums hold 8 residuals of 2^28");
     extern __shared__ __align__(16) unsigned char smem8[];
     const int tid_in = threadIdx.x, tid = tid_in, s = blockIdx.x, wv = tid / kWave, w = a.w, M = a.M, Mn = a.Mn, B2 = M + Mn, S = a.S;
@@ -885,7 +932,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     const u32 seg0 = a.seg[((size_t)r * S + s) * 2], ntp = a.seg[((size_t)r * S + s) * 2 + 1];
     if (st[kStFlag]) return;                         // encoded by the bounds stage
     const u32 nt = (ntp & 0xFFFFu) + (ntp >> 16);
-    const LrSplitLds o = lr_split_carve(NE, B2, nq);
+    const LrSplitLds o = lr_split_carve(FB, B2, nq);
     u64* thr = (u64*)(smem8 + o.thr);
     u64* sums = (u64*)(smem8 + o.sums);
     u32* val = (u32*)(smem8 + o.val);
@@ -902,7 +949,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     uint2* place = (uint2*)(smem8 + o.place);        // position of a block's entry in the row minus its place here; end of its places
     constexpr u32 kNone = 0xFFu;                     // not kept
     constexpr int kMaskBlocks = 32;
-    const int room = lr_split_room(NE, B2);
+    const int room = lr_split_room(B2);
     static_assert(8 * (kTileThreads / kWave) * (kMaskBlocks + 1) <= 4 * kTileThreads + 4 * kMaskBlocks, "the masks fit the sorted entries");
     uint8_t* map = (uint8_t*)(smem8 + o.map);
     uint16_t* tab = (uint16_t*)(smem8 + o.tab);
@@ -939,8 +986,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     {
         const u32* tg = (const u32*)(a.tab + (size_t)r * kTabSize);
         if (tid < kTabSize / 2) ((u32*)tab)[tid] = tg[tid];
-        const uint4* mg = (const uint4*)(a.map + (size_t)r * 2 * kFB);
-        for (int i = tid; i < 2 * kFB / 16; i += kTileThreads) ((uint4*)map)[i] = mg[i];
+        const uint4* mg = (const uint4*)(a.map + (size_t)r * 2 * FB);
+        for (int i = tid; i < 2 * FB / 16; i += kTileThreads) ((uint4*)map)[i] = mg[i];
     }
     __syncthreads();
     for (int i = tid; i < B2 * nq; i += kTileThreads) {              // quantiser scales 2^15 L / (range brought to [1, 2))
@@ -982,7 +1029,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
             for (int j = 0; j < NE; ++j) {
                 const u32 neg = rw[j] >> 31;
                 const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
-                bk[j] = map[neg * kFB + lr_fine_bin<DT>(lr_c32<DT>(key, tile0 + ix[j], w), tab, Blo, nb)];
+                bk[j] = map[neg * FB + lr_fine_bin<DT>(lr_c32<DT>(key, tile0 + ix[j], w), tab, Blo, nb)];
             }
 #pragma unroll
             for (int j = 0; j < NE; ++j) {
@@ -1145,9 +1192,9 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
 #pragma unroll
                 for (int t = 0; t < QN; ++t) acc[t] = 0;
                 u64 accE;
-                if (mode == 0) accE = lr_abq_entries<DT, NE, NQ, 0>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
-                else if (mode == 1) accE = lr_abq_entries<DT, NE, NQ, 1>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
-                else accE = lr_abq_entries<DT, NE, NQ, 2>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
+                if (mode == 0) accE = lr_abq_entries<DT, NQ, 0>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
+                else if (mode == 1) accE = lr_abq_entries<DT, NQ, 1>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
+                else accE = lr_abq_entries<DT, NQ, 2>(a, nq, vv, left, vminf[bb], e_tab[bb], er_tab[bb], invt + bb * nq, acc);
                 // low 28 bits of every sum, and what is above them four to a word (at most 16 * 8 each)
                 u32 hi4[(QN + 3) / 4];
 #pragma unroll
@@ -1291,7 +1338,6 @@ constexpr int kPackPtrs = 4096;                   // row pointers of one window
 template <int DT, bool CSR>
 __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa)
 {
-    typedef Elem<DT> E;
     constexpr int RUN = 8;                        // consecutive entries per thread and run
     __shared__ u32 sA[kPackWords];
     __shared__ u32 bs[kMaxB2 + 1], qsel[kMaxB2];

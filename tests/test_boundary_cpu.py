@@ -111,6 +111,9 @@ def test_static_scratch_serves_whole_rows_without_the_long_row_tables(lib):
     from paper_2511_11608_amd import binding
     for dt, rows, N, keep, M, bits in ((0, 1064, 4928, 0.02, 33, 0x24), (1, 777, 16384, 0.01, 33, 0x1FC), (1, 391, 75776, 0.001, 32, 0x1FFFE),
                                        (0, 337, 74780, 0.02, 64, 0x1FC), (0, 403, 65536, 0.02, 31, 0x1FC), (0, 4, 8388608, 0.05, 1, 0x24)):
+        assert lib.slicer_encode_static(None, dt, rows, N, keep, M, bits, 1e-3, None, None, None) == -1, (dt, rows, N)
+    for dt, rows, N, keep, M, bits in ((0, 1560, 4928, 0.02, 33, 0x24), (1, 1255, 16384, 0.01, 33, 0x1FC), (1, 634, 75776, 0.001, 32, 0x1FFFE),
+                                       (0, 337, 74780, 0.02, 64, 0x1FC), (0, 652, 65536, 0.02, 31, 0x1FC), (0, 1322, 16399, 0.02, 8, 0x1FC)):
         assert binding.slicer_sizes(dt, rows, N, keep, M, bits)[2] > 64 << 20
         assert lib.slicer_encode_static(None, dt, rows, N, keep, M, bits, 1e-3, None, None, None) == -1, (dt, rows, N)
     assert lib.slicer_encode_static(None, 0, 4, 8388608, 0.5, 1, 0x24, 1e-3, None, None, None) == -5

@@ -31,6 +31,19 @@ def test_tiles_and_batches(oracle, dtype, rows, N):
     check(oracle, features(dtype, rows, N, N), dtype, 0.12, 8, B28, 1e-3, use_header=bool(rows & 1))
 
 
+@pytest.mark.parametrize("dtype,rows,N,keep,M", [("f32", 257, 20480, 0.05, 8), ("bf16", 257, 33001, 0.05, 8), ("bf16", 300, 8192, 0.25, 8),
+                                                 ("f32", 258, 4100, 0.1, 40), ("bf16", 258, 8193, 0.1, 40), ("f32", 257, 16388, 0.9, 1),
+                                                 ("f32", 260, 16640, 0.0005, 16), ("f32", 257, 70001, 0.4, 2)])
+def test_large_batches(oracle, dtype, rows, N, keep, M):
+    """More than 256 rows: the stages with 1024 fine bins; rows of equal values are left to the generic kernel."""
+    x = features(dtype, rows, N, N)
+    for i, kind in enumerate(("sparse", "ties", "patches", "relu")):       # a few rows of every structure
+        x[7 + i::41] = features(dtype, rows, N, i, kind)[7 + i::41]
+    x[3] = 0
+    check(oracle, x, dtype, keep, M, B28, 1e-3)
+    check_ds(oracle, x[:, : N - 3].copy(), dtype, keep, M, (1 << 2) | (1 << 5) | (1 << 12), 0.3)
+
+
 @pytest.mark.parametrize("dtype,shift", [("f32", 0), ("f32", 1), ("bf16", 0), ("bf16", 7)])
 def test_longest_rows(oracle, dtype, shift):
     """2^23 elements: 512 tiles, 513 when the row starts inside a 16-byte chunk."""

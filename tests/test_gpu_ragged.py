@@ -62,7 +62,7 @@ def test_static_scratch_serves_odd_rows_without_the_long_row_tables(oracle):
     import torch
     from paper_2511_11608_amd import binding
     from paper_2511_11608_amd.devmem import to_device
-    rows, N, keep = 900, 16399, 0.02                    # 72 MiB with the tables of the long-row stages, 5 MiB without
+    rows, N, keep = 1322, 16399, 0.02                   # 67 MiB with the tables of the long-row stages, 8 MiB without
     assert binding.slicer_sizes(binding.SLICER_F32, rows, N, keep, 8, B28)[2] > 64 << 20
     x = features("f32", rows, N, 3)
     s_ref, m_ref = oracle.encode(x, "f32", keep, 8, B28, 1e-3, n_threads=8)
@@ -79,7 +79,7 @@ def test_static_scratch_serves_whole_rows_without_the_long_row_tables(oracle):
     import torch
     from paper_2511_11608_amd import binding
     from paper_2511_11608_amd.devmem import to_device
-    rows, N, keep, M, bits = 1064, 4928, 0.02, 33, 0x24     # 65 MiB with the tables of the long-row stages, 3 MiB without
+    rows, N, keep, M, bits = 1560, 4928, 0.02, 33, 0x24     # 69 MiB with the tables of the long-row stages, 4 MiB without
     x = features("f32", rows, N, 4)
     s_ref, m_ref = oracle.encode(x, "f32", keep, M, bits, 1e-3, n_threads=8)
     xd = to_device(x, "f32")
