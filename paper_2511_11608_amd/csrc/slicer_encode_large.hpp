@@ -1466,14 +1466,14 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa
         };
         if (bl1 > bl0) {                             // pointers of several blocks, at most 128
             const u32 bt = bl0 + (u32)tid;
-            if (__syncthreads_or(bt <= bl1 && !walked(bs[bt + 1] - bs[bt]))) {
+            if (__syncthreads_or(bt <= bl1 && bs[bt + 1] > bs[bt] && !walked(bs[bt + 1] - bs[bt]))) {
                 for (u32 i = (u32)tid; i < (u32)(f1 - f0); i += 256) {
                     const u32 f = first + i;
                     u32 db = (u32)((float)f * rnp);  // f / np1, less than 4096: the float quotient is off by at most one
                     if (db * np1 > f) --db;
                     if ((db + 1u) * np1 <= f) ++db;
                     const u32 p0 = bs[bl0 + db], cnt = bs[bl0 + db + 1] - p0;
-                    if (!walked(cnt)) ptrs[i] = search(p0, cnt, f - db * np1);
+                    if (cnt && !walked(cnt)) ptrs[i] = search(p0, cnt, f - db * np1);
                 }
             }
         }
@@ -1483,7 +1483,7 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa
             u32* out = ptrs + (fb + j0 - f0);        // pointer j0
             const u32 p0 = bs[b], cnt = bs[b + 1] - p0;
             if (!walked(cnt)) {                      // (uniform)
-                if (bl1 == bl0) for (u32 j = j0 + (u32)tid; j < j1; j += 256) out[j - j0] = search(p0, cnt, j);
+                if (bl1 == bl0 || !cnt) for (u32 j = j0 + (u32)tid; j < j1; j += 256) out[j - j0] = search(p0, cnt, j);      // (empty: zeros)
                 continue;
             }
             // entries in tensor rows before j: 256 probes at once
