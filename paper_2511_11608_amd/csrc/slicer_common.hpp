@@ -255,10 +255,10 @@ __device__ inline u32 udiv16(u32 x, u32 d)
 // a neighbour's elements or lie partly outside the tensor, are loaded element by element, zeros elsewhere
 // (a zero key is never sent and ranks below every other, so the selection needs no further guard).
 // Ragged rows ran on the one-workgroup-per-row generic kernel before, which reads the row some six times from
-// L2: bf16 [2048 x 3001] encode + decode 231 -> 36 us.  Whole rows run through the same
-// loads, which test one end of the row per chunk (with both ends tested per chunk the headline row kernel lost 1 %), and never
-// jump: what ragged rows add has no branch inside and lies behind the kernel's end.  A single wavefront pays for every jump
-// with an instruction-cache miss (fp32 [1 x 768] encode 13.9 us before rows could be ragged, 14.8 with two loops).
+// L2: bf16 [2048 x 3001] encode + decode 231 -> 36 us.  Whole rows keep a loop without any
+// of the tests.  One loop for both, with the ragged ends behind the kernel's end, saves a single wavefront the instruction-cache
+// miss of the jump (bf16 [1 x 4096] 20.0 -> 19.85 us) but costs the headline kernel four registers and two
+// spilled words (107.1 -> 108.7 us).
 template <int DT>
 struct RowChunks {
     static constexpr int EPC = DT == 0 ? 4 : 8;     // elements per chunk
@@ -311,17 +311,20 @@ struct RowChunks {
     template <int NCH, int STEP>
     __device__ inline void load(uint4 (&v)[NCH], int t) const
     {
+        if (!ragged()) {                             // uniform in the workgroup
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int q = c * STEP + t;
-            v[c] = q * EPC + EPC <= Nh && (c > 0 || q * EPC >= head) ? base[q] : make_uint4(0, 0, 0, 0);     // whole(q)
-        }
-        if (__builtin_expect(ragged(), 0)) {         // uniform in the workgroup; no branches inside
+            for (int c = 0; c < NCH; ++c) {
+                const int q = c * STEP + t;
+                v[c] = q * EPC < Nh ? base[q] : make_uint4(0, 0, 0, 0);
+            }
+        } else {
             const int ql = (Nh - 1) / EPC;           // the row's last chunk
             const uint4 first = partial(0), last = partial(ql);
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
-                const bool is = c * STEP + t == ql;
+                const int q = c * STEP + t;
+                v[c] = whole(q) ? base[q] : make_uint4(0, 0, 0, 0);
+                const bool is = q == ql;
                 v[c].x = is ? last.x : v[c].x; v[c].y = is ? last.y : v[c].y; v[c].z = is ? last.z : v[c].z; v[c].w = is ? last.w : v[c].w;
             }
             v[0].x = t == 0 ? first.x : v[0].x; v[0].y = t == 0 ? first.y : v[0].y;
