@@ -274,10 +274,9 @@ struct RowChunks {
     }
     __device__ inline bool ragged() const { return head != 0 || (Nh & (EPC - 1)) != 0; }     // the same for a whole row
     __device__ inline bool whole(int q) const { return q * EPC >= head && q * EPC + EPC <= Nh; }
-    // Chunk q, only the row's own elements, zeros elsewhere.  Every element load takes place, at the nearest place inside
-    // the row (which has at least one element), and callers keep the call out of branches on whole(): no load here
-    // stands under the opposite condition of the whole-chunk load, so the two cannot be made one with an address
-    // that only some lanes set.
+    // Chunk q, only the row's own elements, zeros elsewhere.  Every element load takes place, at the nearest place inside the row
+    // (which has at least one element): with conditional element loads beside the whole-chunk load, the compiler made one
+    // load of the two whose address only some lanes set.
     __device__ inline uint4 partial(int q) const
     {
         typedef typename Elem<DT>::raw_t raw_t;
@@ -318,17 +317,19 @@ struct RowChunks {
                 v[c] = q * EPC < Nh ? base[q] : make_uint4(0, 0, 0, 0);
             }
         } else {
-            const int ql = (Nh - 1) / EPC;           // the row's last chunk
-            const uint4 first = partial(0), last = partial(ql);
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
                 const int q = c * STEP + t;
                 v[c] = whole(q) ? base[q] : make_uint4(0, 0, 0, 0);
-                const bool is = q == ql;
-                v[c].x = is ? last.x : v[c].x; v[c].y = is ? last.y : v[c].y; v[c].z = is ? last.z : v[c].z; v[c].w = is ? last.w : v[c].w;
             }
-            v[0].x = t == 0 ? first.x : v[0].x; v[0].y = t == 0 ? first.y : v[0].y;
-            v[0].z = t == 0 ? first.z : v[0].z; v[0].w = t == 0 ? first.w : v[0].w;
+            const int ql = (Nh - 1) / EPC;           // the row's last chunk
+            if (t == 0 && !whole(0)) v[0] = partial(0);
+            if (ql > 0 && t == ql % STEP && !whole(ql)) {
+                const uint4 e = partial(ql);
+                const int cl = ql / STEP;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) if (c == cl) v[c] = e;
+            }
         }
     }
 };
