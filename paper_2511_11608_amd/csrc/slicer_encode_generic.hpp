@@ -799,6 +799,7 @@ __global__ __launch_bounds__(kScanRows) void enc_finish_small_kernel(EncArgs ea,
     const int tid = threadIdx.x, wid = tid / kWave;
     const u32 lane = lane_id();
     bool alone = false;
+    u64 v = tid < a.R ? a.row_words[tid] : 0ull;      // (on its way while the flags are looked at)
     if (ea.only_flagged) {
         const int any = tid < a.R ? (int)ea.only_flagged[tid] : 0;
         if (__syncthreads_or(any)) {
@@ -806,10 +807,10 @@ __global__ __launch_bounds__(kScanRows) void enc_finish_small_kernel(EncArgs ea,
             enc_generic_rows<DT, kScanRows>(ea, 0, a.R, sh);
             __syncthreads();
             alone = true;
+            v = tid < a.R ? a.row_words[tid] : 0ull;
         }
     }
     {   // exclusive scan of the word counts
-        const u64 v = tid < a.R ? a.row_words[tid] : 0ull;
         u64 inc = v;
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) {
@@ -832,8 +833,11 @@ __global__ __launch_bounds__(kScanRows) void enc_finish_small_kernel(EncArgs ea,
     const int64_t first = alone ? wid : xcd_row((int64_t)blockIdx.x, (n_items + 3) / 4) * (kScanRows / kWave) + wid;
     const int64_t step = alone ? kScanRows / kWave : n_items;      // (not alone: one item per wavefront)
     for (int64_t item = first; item < n_items; item += step) {
-        const int64_t r = item / a.chunks_per_row;
-        const u64 c = (u64)(item % a.chunks_per_row);
+        u32 r = (u32)item, c = 0;
+        if (a.chunks_per_row > 1) {                  // (no division for short rows)
+            r = (u32)item / (u32)a.chunks_per_row;   // at most 2^31 items
+            c = (u32)item - r * (u32)a.chunks_per_row;
+        }
         const u64 off = s_off[r];
         if (c == 0 && lane == 0) a.mv.row_off[r] = off;
         if (item == 0 && lane == 0) write_header(a, s_off[kScanRows]);
