@@ -122,7 +122,7 @@ def slicer_sizes(dt: int, rows: int, row_len: int, keep_ratio: float, n_blocks: 
 
 
 def slicer_encode_path(dt: int, rows: int, row_len: int, keep_ratio: float, n_blocks: int, bit_set: int) -> int:
-    """0 generic, 1 row-resident, 2 long-row kernel family for this shape."""
+    """0 generic, 1 one wavefront per row, 2 long-row stages, 3 one workgroup per row: what slicer_encode runs for this shape."""
     rc = load().slicer_encode_path(dt, rows, row_len, keep_ratio, n_blocks, bit_set)
     if rc < 0:
         raise SlicerError("slicer_encode_path", rc)

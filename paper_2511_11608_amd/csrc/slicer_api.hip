@@ -69,7 +69,7 @@ struct Plan {
     size_t off_row_words, off_slots, off_kept, off_bo_idx, off_bo_val, off_fallback, off_row_local, off_chunk_tot, off_hint, total;
     // row-resident fast path (0 = not eligible)
     int small_epl, small_cap, small_region0, small_lds_bytes, small_maxs;
-    // workgroup-per-row path for bf16 rows of up to 32768 elements (0 = not eligible)
+    // workgroup-per-row path for rows of up to 32768 bf16 or 16384 fp32 elements (0 = not eligible)
     int wg_ept, wg_nw, wg_cap, wg_region0, wg_lds_bytes;
     // long-row path (large_S == 0: not eligible)
     int large_S, large_fb;  // tiles per row, fine bins
@@ -613,8 +613,8 @@ static int check_csr_shape(int64_t n_rows, int64_t n_cols)
     return SLICER_OK;
 }
 
-// Two-dimensional instances: the flat encode (any kernel family) writes its stream into the workspace, the
-// repack kernels turn it into the CSR form.  Workspace: the flat plan's, then the flat stream, then its offsets.
+// Two-dimensional instances: the long-row stages write the CSR form themselves; elsewhere the flat encode (any kernel
+// family) writes its stream into the workspace and the repack kernels turn it into the CSR form.  Workspace: the flat plan's, then the flat stream, then its offsets.
 struct CsrPlan {
     Plan flat;
     int wc, wp;

@@ -1,5 +1,8 @@
 // Two-dimensional instances (Sec. 3.2: an IF X of shape N x K; step 3: CSR(X_m) = (v_m, c_m, r_m)).
 //
+// The long-row stages write this form themselves (slicer_encode_large.hpp) for up to 256 aligned instances whose row
+// pointers take eight bits or more.  What follows serves all other shapes.
+//
 // ATKF and MS work on the flattened tensor, so the encoder proper is the flat one (whichever kernel
 // family serves the shape); only the index encoding of the stream differs.  The flat encode writes its
 // stream into the workspace, and two short kernels turn it into the CSR form:

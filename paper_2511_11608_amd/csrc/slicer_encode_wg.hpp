@@ -42,8 +42,8 @@ __host__ __device__ inline int wg_main_words(int dt, int cap, int region0, int B
 }
 __host__ __device__ inline int wg_lds_words(int dt, int cap, int region0, int B2)
 {
-    // misc, chunk totals and their prefix (2 x 64), per-slot per-block counts as 16-bit (cap / 64 slots)
-    return wg_main_words(dt, cap, region0, B2) + kWgMisc + 128 + ((cap / kWave) * B2 + 1) / 2 + 2;
+    // misc, chunk totals (64), per-slot per-block counts as 16-bit (cap / 64 slots)
+    return wg_main_words(dt, cap, region0, B2) + kWgMisc + 64 + ((cap / kWave) * B2 + 1) / 2 + 2;
 }
 
 // wavefronts per SIMD the register allocator must leave room for (same rule as the one-wavefront kernel)
@@ -78,8 +78,8 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     const int k = (int)a.k;
     SmallLds L = small_carve(smem, DT, cap, a.region0_words, B2, 0);
     u32* misc = smem + wg_main_words(DT, cap, a.region0_words, B2);      // broadcast words and scan scratch
-    u32* ctab = misc + kWgMisc;                                           // [NCH][4] chunk totals per wavefront, then their prefixes
-    uint16_t* stab = (uint16_t*)(ctab + 128);                        // [slot][B2] entries of block b in slot s
+    u32* ctab = misc + kWgMisc;                                           // [NCH][NW] chunk totals per wavefront
+    uint16_t* stab = (uint16_t*)(ctab + 64);                         // [slot][B2] entries of block b in slot s
     auto give_up = [&]() { if (tid == 0) a.fallback[r] = 1u; };      // callers return right after, all threads alike
     if (__builtin_amdgcn_groupstaticsize() != 0u) {                  // integer LDS addresses assume offset 0
         give_up();
