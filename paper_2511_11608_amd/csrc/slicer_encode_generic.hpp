@@ -716,7 +716,7 @@ __device__ inline void write_header(const FinishArgs& a, u64 total)
 }
 
 // One wavefront copies words [c * kGatherWords, (c + 1) * kGatherWords) of row r's slot to the stream.  Bound by the
-// latency of dependent loads: eight words per lane are in flight,
+// latency of dependent loads: eight words per lane are in flight (bf16 [16384 x 4096]: 9.5 -> 8.1 us),
 // and the first ones are on their way while offset() finds where they go.  Segments of up to 128 words, which short
 // rows have, skip the rest of the eight (fp32 [12608 x 768], 84 words a row: 6.6 us with all eight tests).
 template <class F>

@@ -629,13 +629,13 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
 
     auto at_c = [&](u32 cls, u32 b) -> u32 { return cls == 0u ? L.at_p[b] : cls == 1u ? L.at_n[b] : L.at_p[b] + L.at_n[b]; };
     // members of the bins of groups 0 .. ng - 1 (g_start: room per group), tile by tile; up to eight threads share a tile's
-    // members while there are threads to spare (equal values fill a bin: fp32 [1 x 200704] quantised to 256 levels 119 -> 115 us, bf16
+    // members while there are threads to spare (equal values fill a bin: fp32 [1 x 200704] quantised to 256 levels 119 -> 113 us, bf16
     // to 16 levels 84 -> 70; what remains there is the comparison of all members of a bin with each other)
     auto gather = [&](int ng) {
-        int parts = 1;
-        while (parts < 8 && ng * S * parts * 2 <= TH) parts *= 2;
-        for (int i = tid; i < ng * S * parts; i += TH) {
-            const int gs = i / parts, part = i - gs * parts, g = gs / S, s = gs - g * S;
+        int lp = 0;                                  // log2 of the threads that share
+        while (lp < 3 && (ng * S << (lp + 1)) <= TH) ++lp;
+        for (int i = tid; i < ng * S << lp; i += TH) {
+            const int gs = i >> lp, part = i - (gs << lp), g = gs / S, s = gs - g * S;
             const u32 cls = L.g_cls[g], b = L.g_bin[g];
             const u32 c0 = cum[(size_t)s * FB + b], c1 = b + 1u < (u32)FB ? cum[(size_t)s * FB + b + 1u] : 0u;
             const u32 seg0 = seg[2 * s], np = seg[2 * s + 1] & 0xFFFFu;
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
                 const u32 n0 = h ? c0 >> 16 : c0 & 0xFFFFu, n1 = h ? c1 >> 16 : c1 & 0xFFFFu, cn = n0 - n1;
                 if (cls != 2u && part == 0)          // entries of the tile above the bin: the start of the blocks' counts
                     for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t) if (t & 1u) pair[(size_t)(t >> 1) * S + s] = n1;
-                const u32 share = (cn + (u32)parts - 1u) / (u32)parts, p0 = (u32)part * share, p1 = p0 + share < cn ? p0 + share : cn;
+                const u32 share = (cn + (1u << lp) - 1u) >> lp, p0 = (u32)part * share, p1 = p0 + share < cn ? p0 + share : cn;
                 if (p0 >= p1) continue;
                 const u32 slot = L.g_start[g] + atomicAdd(&L.g_fill[g], p1 - p0) - p0;
                 for (u32 j0 = p0; j0 < p1; j0 += 4) {
@@ -1242,6 +1242,9 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     const int ns = B2 * (nq + 1);
     u64* ps = a.psum + (size_t)r * S * ns;
     if (want_sums && S > 1) for (int i = tid; i < ns; i += kTileThreads) agent_store(&ps[(size_t)s * ns + i], sums[i]);
+    // The sums alone must be seen by the row's last workgroup: they are stored past the XCD's L2 and waited for before the
+    // ticket is drawn, and are loaded the same way.  A ticket with release and acquire order writes back the whole L2, dirty with the
+    // block-ordered entries, once per workgroup: encode of 32 maps of 401408 with a ladder 113 -> 133 us, DS guard 123 -> 138.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the stores have reached the point all XCDs see ...
     __syncthreads();
     if (tid == 0) lstart[0] = S > 1 ? __hip_atomic_fetch_add(&st[kStTicket], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;   // ... before the ticket
