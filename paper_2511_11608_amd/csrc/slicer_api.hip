@@ -145,7 +145,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     const int64_t margin = std::max<int64_t>(64, row_len / (dt == SLICER_F32 ? 16 : 32));  // room for the undecided coarse bin
     const int64_t cap = std::min<int64_t>(1984, (p.k + margin + 63) / 64 * 64);   // ranks are 11-bit fields
     const bool lists_fit = B2_all <= kWave && p.k + 64 <= cap;
-    const int64_t region0 = lists_fit ? small_region0_words(p.k, p.cap_words, B2_all, nq) : 0;
+    const int64_t region0 = lists_fit ? small_region0_words(p.k, p.cap_words, B2_all, nq, (int)cap) : 0;
     const int maxs = cap <= 640 ? 10 : cap <= 1280 ? 20 : 0;             // list held in registers
     const int64_t small_lds = lists_fit ? 4 * (int64_t)small_lds_words(dt, (int)cap, (int)region0, B2_all, maxs) : 0;
     auto small_holds = [&](int64_t elements) { return lists_fit && elements <= (dt == SLICER_F32 ? 4096 : 8192) && small_lds <= 64 * 1024; };

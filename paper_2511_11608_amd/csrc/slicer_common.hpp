@@ -255,10 +255,7 @@ __device__ inline u32 udiv16(u32 x, u32 d)
 // a neighbour's elements or lie partly outside the tensor, are loaded element by element, zeros elsewhere
 // (a zero key is never sent and ranks below every other, so the selection needs no further guard).
 // Ragged rows ran on the one-workgroup-per-row generic kernel before, which reads the row some six times from
-// L2: bf16 [2048 x 3001] encode + decode 231 -> 36 us.  Whole rows keep a loop without any
-// of the tests.  One loop for both, with the ragged ends behind the kernel's end, saves a single wavefront the instruction-cache
-// miss of the jump (bf16 [1 x 4096] 20.0 -> 19.85 us) but costs the headline kernel four registers and two
-// spilled words (107.1 -> 108.7 us).
+// L2: bf16 [2048 x 3001] encode + decode 231 -> 36 us.  Whole rows have loads of their own, without any of the tests.
 template <int DT>
 struct RowChunks {
     static constexpr int EPC = DT == 0 ? 4 : 8;     // elements per chunk
@@ -311,10 +308,14 @@ struct RowChunks {
     __device__ inline void load(uint4 (&v)[NCH], int t) const
     {
         if (!ragged()) {                             // uniform in the workgroup
+            // buffer loads: what lies behind the row's end reads as zeros, with no test and no zeroed registers (the whole offset is in
+            // the part that the bounds check looks at)
+            typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+            __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(base), 0, Nh * (16 / EPC), 0x00020000);
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
-                const int q = c * STEP + t;
-                v[c] = q * EPC < Nh ? base[q] : make_uint4(0, 0, 0, 0);
+                const u32x4 l = __builtin_amdgcn_raw_buffer_load_b128(rs, (c * STEP + t) * 16, 0, 0);
+                v[c] = make_uint4(l.x, l.y, l.z, l.w);
             }
         } else {
 #pragma unroll

@@ -93,11 +93,14 @@ __host__ __device__ inline int small_tg_words(int B2)
     return (5 * ntg + 1) & ~1;
 }
 
-// words of region 0: fine histogram, or indices + stream image + sums + scales
-__host__ __device__ inline int small_region0_words(int64_t k, u64 cap_words, int B2, int nq)
+// words of region 0: the row's bit mask (at most 2 * 128 words) and list positions, then the fine histogram, then indices +
+// stream image + sums + scales
+__host__ __device__ inline int small_region0_words(int64_t k, u64 cap_words, int B2, int nq, int cap)
 {
     const int64_t late = (((k + 1) / 2 + (int64_t)cap_words + 1) & ~(int64_t)1) + 2 * B2 * (nq + 1) + B2 * nq;
-    const int64_t r0 = late > kFineBins ? late : kFineBins;
+    const int64_t early = 2 * 128 + 4 + cap / 2;
+    int64_t r0 = late > kFineBins ? late : kFineBins;
+    r0 = r0 > early ? r0 : early;
     return (int)((r0 + 1) & ~(int64_t)1);
 }
 
@@ -326,51 +329,63 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         }
         wave_sync();
     };
-    // List length and positions for a lower key bound t_lo: per 16-byte chunk the number of keys at or
-    // above it, then exclusive positions (three chunk counts share one scan: 10-bit fields, a chunk
-    // holds at most 512 keys).
-    u32 t_lo = 1u, nL = 0;
-    u32 cntc[NCH], basec[NCH];
-    auto scan_counts = [&]() {
-        nL = 0;
-#pragma unroll
-        for (int g = 0; g < (NCH + 2) / 3; ++g) {
-            u32 pk = cntc[3 * g];
-            if (3 * g + 1 < NCH) pk |= cntc[3 * g + 1] << 10;
-            if (3 * g + 2 < NCH) pk |= cntc[3 * g + 2] << 20;
-            const u32 incl = wave_scan_dpp(pk);
-            const u32 tot = bcast(incl, kWave - 1);
-            const u32 ex = incl - pk;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                if (3 * g + j < NCH) {
-                    basec[3 * g + j] = nL + ((ex >> (10 * j)) & 0x3FFu);
-                    nL += (tot >> (10 * j)) & 0x3FFu;
-                }
-            }
-        }
-    };
-    auto count_plain = [&]() {
-        const u32 C16 = (0x8000u - t_lo) * 0x10001u;            // bf16: bit 15 / 31 of (key + C16) <=> key >= t_lo
+    // Which elements go to the list: a bit mask of the row.  Every lane flags the elements of its own chunks (8 or 4 bits a
+    // chunk: the flags are the words' sign bits, gathered by one byte permutation and one dot product per four of them), the
+    // chunks' bits meet in LDS, and every lane takes the bits of EPL consecutive elements: one prefix sum over the lanes then
+    // gives the list positions in index order.
+    constexpr int NM = EPL >= 32 ? EPL / 32 : 1;    // words of a lane's mask
+    uint16_t* plist = (MAXS || DT == 1) ? (uint16_t*)(smem + 2 * EPL + 4) : L.Lidx;      // row positions of the list's entries
+    u32 t_lo = 1u, nL = 0, mk[NM], pos0 = 0;        // pos0: entries of the lanes below
+    // flag(word): bf16: bits 15 and 31 set where the word's elements are taken; fp32: bit 31
+    auto row_mask = [&](auto flag) {
+        unsigned char* mb = (unsigned char*)smem;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            u32 n1 = 0;
+            u32 f[4];
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const u32 wd = word_of(c, d);
-                if (DT == 0) n1 += ((wd & 0x7FFFFFFFu) >= t_lo) ? 1u : 0u;
-                else n1 += (u32)__popc(((wd & 0x7FFF7FFFu) + C16) & 0x80008000u);
+            for (int d = 0; d < 4; ++d) f[d] = flag(word_of(c, d));
+            // selectors 8 to 11 of the byte permutation: the sign of a 16-bit half as a byte of ones or zeros; 12: zero
+            const u32 p0 = __builtin_amdgcn_perm(f[1], f[0], DT == 0 ? 0x0C0C0B09u : 0x0B0A0908u);
+            const u32 p1 = __builtin_amdgcn_perm(f[3], f[2], DT == 0 ? 0x0B090C0Cu : 0x0B0A0908u);
+            // -1 times weights -1, -2, -4, ...
+            int m = __builtin_amdgcn_sdot4((int)p0, DT == 0 ? 0x0000FEFF : (int)0xF8FCFEFFu, 0, false);
+            m = __builtin_amdgcn_sdot4((int)p1, DT == 0 ? (int)0xF8FC0000u : (int)0x80C0E0F0u, m, false);
+            if (DT == 0) {                          // two lanes share a byte
+                const u32 up = (u32)__builtin_amdgcn_update_dpp(0, m, 0xF5, 0xf, 0xf, true);      // quad_perm 1 1 3 3
+                if (!(lane & 1u)) mb[(c * kWave + (int)lane) >> 1] = (unsigned char)((u32)m | (up << 4));
+            } else {
+                mb[c * kWave + (int)lane] = (unsigned char)m;
             }
-            cntc[c] = n1;
         }
-        scan_counts();
+        wave_sync();
+        if (EPL >= 32) {
+#pragma unroll
+            for (int i = 0; i < NM; ++i) mk[i] = smem[(int)lane * NM + i];
+        } else {                                    // (the word after the mask is readable; its bits are masked off)
+            const u32 at = lane * (u32)EPL;
+            mk[0] = __builtin_amdgcn_alignbit(smem[(at >> 5) + 1], smem[at >> 5], at & 31u) & ((1u << (EPL & 31)) - 1u);
+        }
+        wave_sync();
+    };
+    auto scan_mask = [&]() {
+        u32 n1 = 0;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) n1 += (u32)__popc(mk[i]);
+        const u32 incl = wave_scan_dpp(n1);
+        nL = bcast(incl, kWave - 1);
+        pos0 = incl - n1;
+    };
+    auto mask_plain = [&]() {                       // every key at or above t_lo
+        const u32 C = DT == 0 ? 0x80000000u - t_lo : (0x8000u - t_lo) * 0x10001u;      // the sign bit of (key + C) <=> key >= t_lo
+        row_mask([&](u32 wd) -> u32 { return (wd & (DT == 0 ? 0x7FFFFFFFu : 0x7FFF7FFFu)) + C; });
+        scan_mask();
     };
     // the hinted bound: accepted when it keeps at least k keys and not many more
     bool hinted = false;
     if (kHint && k > 0) {
         const u32 dlt = kHintDelta << (DT == 0 ? 16 : 0);
         t_lo = hint_key > dlt ? hint_key - dlt : 1u;
-        count_plain();
+        mask_plain();
         hinted = nL >= (u32)k && nL <= (u32)k + kHintSlack && (int)nL <= cap;
     }
     if (!hinted && ASYM && DT == 0) row_kmax();      // (its selections run further down)
@@ -539,126 +554,98 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     }
 
     // ---- 2. ordered compaction into L -------------------------------------------------
+    // The list's row positions first (a lane writes its set bits one after the other), then its values, fetched again from
+    // the row: consecutive entries lie close together, so these loads touch a few cache lines each, and they hit the L2.
+    // Storing from registers instead costs 12 instructions per pair of elements, flagged or not.  Up to the list in registers a
+    // row of 4096 bf16 elements took 757 vector instructions and takes 352 (kernel, 16384 rows: 95.1 -> 87.2 us); fp32
+    // [12608 x 768]: 281 and 213 (44.2 -> 43.6 us).
     if (k == 0) nL = 0;
     if (k > 0) {
-        const u32 C16 = (0x8000u - t_lo) * 0x10001u;            // bf16: bit 15 / 31 of (key + C16) <=> key >= t_lo
-        // bits 15 and 31: the element goes to the list
-        auto list_flags = [&](u32 wd) -> u32 {
-            if (!ASYM) return (wd & 0x7FFF7FFFu) + C16;
-            const u32 st = strict01(wd);
-            u32 wk = wd;
-            asm volatile("" : "+v"(wk));
-            const u32 ge = gt01(t2_2, wk & 0x7FFF7FFFu) ^ kOne2;              // key >= last key taken
-            return (trim ? (st & ge) : (st | (fill01(wd, st) & ge))) << 15;
-        };
-        // fp32: the element goes to the list
-        auto flag32 = [&](u32 wd) -> u32 {
-            const u32 key = wd & 0x7FFFFFFFu;
-            if (!ASYM) return key >= t_lo ? 1u : 0u;
-            const bool st = strict32(wd), ge = key >= t2_key;
-            return (trim ? (st && ge) : (st || (fill32(wd) && ge))) ? 1u : 0u;
-        };
         if (ASYM) {
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                u32 n1 = 0;
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    if (DT == 0) n1 += flag32(word_of(c, d));
-                    else n1 += (u32)__popc(list_flags(word_of(c, d)) & 0x80008000u);
+            // taken: the strict set or its largest part, and the fill candidates down to the last key taken; of several
+            // elements with that key the first need_ties stay
+            auto taken = [&](u32 wd, bool ties) -> u32 {         // ties: only the candidates with the last key taken
+                if (DT == 1) {
+                    const u32 st = strict01(wd);
+                    u32 wk = wd;
+                    asm volatile("" : "+v"(wk));
+                    const u32 ge = gt01(t2_2, wk & 0x7FFF7FFFu) ^ kOne2;              // key >= last key taken
+                    if (ties) return ((trim ? st : fill01(wd, st)) & ge & (gt01(wk & 0x7FFF7FFFu, t2_2) ^ kOne2)) << 15;
+                    return (trim ? (st & ge) : (st | (fill01(wd, st) & ge))) << 15;
                 }
-                cntc[c] = n1;
+                const u32 key = wd & 0x7FFFFFFFu;
+                const bool st = strict32(wd), ge = key >= t2_key;
+                if (ties) return (trim ? st : fill32(wd)) && key == t2_key ? 0x80000000u : 0u;
+                return (trim ? (st && ge) : (st || (fill32(wd) && ge))) ? 0x80000000u : 0u;
+            };
+            row_mask([&](u32 wd) -> u32 { return taken(wd, false); });
+            if (need_ties < cnt_ties) {              // uniform
+                u32 all[NM];
+#pragma unroll
+                for (int i = 0; i < NM; ++i) all[i] = mk[i];
+                row_mask([&](u32 wd) -> u32 { return taken(wd, true); });
+                scan_mask();
+                u32 left = need_ties > pos0 ? need_ties - pos0 : 0u;
+#pragma unroll
+                for (int i = 0; i < NM; ++i) {
+                    u32 e = mk[i], stay = 0;
+                    for (; e && left; --left) { stay |= e & (0u - e); e &= e - 1u; }
+                    mk[i] = (all[i] & ~mk[i]) | stay;
+                }
             }
-            scan_counts();
+            scan_mask();
         } else if (!hinted) {
-            count_plain();
+            mask_plain();
         }
-        // every flagged element is stored at a running byte address that advances by its flag
-        const u32 lidx_off = (u32)((u32*)L.Lidx - smem) * 4u;
         if ((int)nL > cap) {                                      // uniform
             if (lane == 0) a.fallback[r] = 1u;
             return;
         }
-        // (the empty asm statements pin values in registers: the optimiser would otherwise
-        //  re-derive each flag and each inverted index with longer instruction sequences)
-        u32 linv = 0xFFFFu - lane * (u32)EPC + (u32)head;
-        asm volatile("" : "+v"(linv));
+        const u32 pl_off = (u32)((u32*)plist - smem) * 4u;
+        typedef __attribute__((address_space(3))) uint16_t lds_u16;
+        u32 wa = pl_off + 2u * pos0;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            u32 wa = lent_off + basec[c] * 4u;
-            const u32 idx0 = (u32)((c * kWave + (int)lane) * EPC - head);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const u32 wd = word_of(c, d);
-                if (DT == 0) {
-                    const u32 fl = flag32(wd);
-                    if (fl) {
-                        *lds_at(wa) = wd;
-                        *(__attribute__((address_space(3))) uint16_t*)(uintptr_t)(lidx_off + ((wa - lent_off) >> 1)) = (uint16_t)(idx0 + d);
-                    }
-                    wa += fl << 2;
-                } else {
-                    const u32 f = list_flags(wd);
-                    u32 f0 = (f >> 15) & 1u, f1 = f >> 31;
-                    asm volatile("" : "+v"(f0));
-                    asm volatile("" : "+v"(f1));
-                    const u32 i0 = linv - (u32)(c * kWave * EPC + 2 * d), i1 = linv - (u32)(c * kWave * EPC + 2 * d + 1);
-                    if (f0) *lds_at(wa) = (wd << 16) | i0;
-                    wa += f0 << 2;
-                    asm volatile("" : "+v"(wa));
-                    if (f1) *lds_at(wa) = __builtin_amdgcn_perm(wd, i1, 0x07060100u);   // wd's high half : i1's low half
-                    wa += f1 << 2;
-                    asm volatile("" : "+v"(wa));
-                }
+        for (int i = 0; i < NM; ++i) {
+            const u32 i0 = lane * (u32)EPL + 32u * (u32)i - (u32)head;
+            u32 m = mk[i];
+            while (m) {
+                *(lds_u16*)(uintptr_t)wa = (uint16_t)(i0 + (u32)__builtin_ctz(m));
+                wa += 2u;
+                m &= m - 1u;
             }
         }
-    }
-    if (ASYM && k > 0 && need_ties < cnt_ties) {
-        // The list holds every candidate with the last key taken; only the first need_ties of them
-        // in index order stay.  The list is in index order: the others are squeezed out in place.
         wave_sync();
-        u32 seen = 0, dead = 0;
-        for (u32 p0 = 0; p0 < nL; p0 += kWave) {
-            const u32 p = p0 + lane;
-            u32 e = 0, ei = 0;
-            bool tie = false;
-            if (p < nL) {
-                e = L.Lent[p];
-                if (DT == 0) {
-                    ei = L.Lidx[p];
-                    const bool cand = trim ? strict32(e) : fill32(e);
-                    tie = cand && (e & 0x7FFFFFFFu) == t2_key;
-                } else {
-                    const u32 wd = e >> 16;                              // sign and key in the low half, as in the row
-                    const u32 st = strict01(wd) & 1u;
-                    const u32 cand = trim ? st : (fill01(wd, st) & 1u);
-                    tie = cand && (wd & 0x7FFFu) == t2_key;
-                }
-            }
-            const u64 mt = __ballot(tie);
-            const bool drop = tie && seen + mask_rank(mt) >= need_ties;
-            const u64 md = __ballot(drop);
-            wave_sync();
-            if (p < nL && !drop) {
-                L.Lent[p - dead - mask_rank(md)] = e;
-                if (DT == 0) L.Lidx[p - dead - mask_rank(md)] = (uint16_t)ei;
-            }
-            wave_sync();
-            seen += (u32)__popcll(mt);
-            dead += (u32)__popcll(md);
-        }
-        nL -= dead;
     }
+    const typename E::raw_t* __restrict__ xr = (const typename E::raw_t*)a.x + (size_t)r * (size_t)a.N;
     if (MAXS) {
-        // the list moves into registers: its LDS storage is free for the bin-ordered list
-        wave_sync();
+        // the list moves straight into registers, four slots at a time with all their loads in flight
+        u32 ix[MAXS ? MAXS : 1];
+#pragma unroll
+        for (int s = 0; s < SLN; ++s) { ix[MAXS ? s : 0] = 0; ent[MAXS ? s : 0] = 0; }
+#pragma unroll
+        for (int g = 0; g < SLN; g += 4) {
+            if ((u32)(g * kWave) >= nL) continue;   // uniform
+#pragma unroll
+            for (int s = g; s < g + 4 && s < SLN; ++s) ix[MAXS ? s : 0] = (u32)plist[s * kWave + lane];
+#pragma unroll
+            for (int s = g; s < g + 4 && s < SLN; ++s)      // (element 0 exists; its copies behind the list's end are not looked at)
+                ent[MAXS ? s : 0] = (u32)xr[ix[MAXS ? s : 0] = (int)lane < (int)nL - s * kWave ? ix[MAXS ? s : 0] : 0u];
+        }
 #pragma unroll
         for (int s = 0; s < SLN; ++s) {
-            const u32 p = s * kWave + lane;
-            if (MAXS) ent[MAXS ? s : 0] = p < nL ? L.Lent[p] : 0u;
-            if (MAXS && DT == 0) eix[(MAXS && DT == 0) ? s : 0] = p < nL ? (u32)L.Lidx[p] : 0u;
+            asm volatile("" : "+v"(ent[MAXS ? s : 0]));     // (the shift stays behind all of the loads)
+            if (DT == 1) ent[MAXS ? s : 0] = (ent[MAXS ? s : 0] << 16) | (ix[MAXS ? s : 0] ^ 0xFFFFu);
+            else eix[(MAXS && DT == 0) ? s : 0] = ix[MAXS ? s : 0];
         }
         wave_sync();
+    } else {
+        for (u32 p = lane; p < nL; p += kWave) {    // fp32: the row positions stay where they are
+            const u32 i = plist[p], raw = (u32)xr[i];
+            L.Lent[p] = DT == 1 ? (raw << 16) | (i ^ 0xFFFFu) : raw;
+        }
+        wave_sync();
+    }
+    if (MAXS) {
         if (kHint && hinted) {                        // the row's largest key is the list's largest
             u32 mx = 0;
 #pragma unroll
