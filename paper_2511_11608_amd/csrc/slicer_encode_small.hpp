@@ -13,11 +13,11 @@
 //      (ascending index: the kept set plus the undecided bin);
 //   3. L is bucketed into 1024 fine bins, linear in the key from the list's lower
 //      bound, both sign classes counted in one packed table; an exclusive scan from
-//      the top gives every bin's first rank, overall and per class.  Order
-//      statistics (rank k-1 overall for the top-K cut of Sec. 3.1; ranks j*K-1 per
-//      class for the block boundaries of Sec. 3.2) are located over the bins, one lane
-//      per boundary, and resolved inside their bin by comparing the bin's few members
-//      pairwise;
+//      the top gives every bin's places in the list S, which holds the positive class
+//      and then the negative one, each arranged by bin.  Order statistics (rank k-1
+//      overall for the top-K cut of Sec. 3.1; ranks j*K-1 per class for the block
+//      boundaries of Sec. 3.2) are resolved among the members of their bin, and the bin
+//      of a class rank is that of the entry of S at this place;
 //   4. an entry's block is the number of boundaries above it (plus one for the negative
 //      class); a stable split by block id (wave ballots) restores ascending index inside
 //      each block;
@@ -71,15 +71,14 @@ constexpr int kFineBins = 1024;
 // The coarse histogram (2048 16-bit counters) overlays everything: nothing else is live before the
 // compaction.  Region 0 is the fine histogram first; once the boundaries are known it holds
 // the block-ordered indices, the stream image, the ABQ sums and the quantiser scales.
-// MAXS > 0: the list is copied into registers after the compaction, so the bin-ordered
-// list S reuses the storage of L.
 struct SmallLds {
-    u32* hist;      // [region0]   fine histogram; later bo_idx, stream image, sums, invt
-    u32* Lent;      // [cap]       list entries, ascending index: bf16 raw << 16 | ~idx; fp32 raw
-    u32* S;         // [cap]       entries arranged by fine bin; later bo_val
-    uint16_t* Lidx; // [cap]       fp32 only: index of the entry (inside region 0 when MAXS > 0)
-    u32* thr;       // [2 * B2]    block boundaries (class-extended comps), positive class first
-    u32* tg;        // [5][ntg]    boundary work table: bin, base, count, rank in bin, pair prefix
+    u32* hist;      // [region0]   fine histogram and a word for the bin above it; later bo_idx, stream image, sums, invt
+    u32* S;         // [cap + 4]   entries arranged by class and fine bin (bf16: comp; fp32: its key word), then zeros; later bo_val
+    uint16_t* Sp;   // [cap + 4]   fp32 only: the entry's list position
+    u32* thr;       // [B2]        block boundaries (class-extended comps; fp32: their key words), positive class first
+    u32* thr_lo;    // [B2]        fp32 only: the low words
+    u32* Lent;      // [cap]       MAXS = 0 only: list entries, ascending index (as `ent` in the kernel)
+    uint16_t* Lidx; // [cap]       MAXS = 0 and fp32 only: index of the entry
     u32* qtab;      // [16]        allowed bitwidths
     u32* blk_start; // [B2 + 1]
     u32* vminb;     // [B2] key of the block's smallest / largest element
@@ -87,31 +86,24 @@ struct SmallLds {
     u32* run;       // [B2]        next free position of the block; later the chosen bitwidth index
 };
 
-__host__ __device__ inline int small_tg_words(int B2)
-{
-    const int ntg = B2 > 2 ? B2 - 2 : 1;
-    return (5 * ntg + 1) & ~1;
-}
-
 // words of region 0: the row's bit mask (at most 2 * 128 words) and list positions, then the fine histogram, then indices +
 // stream image + sums + scales
 __host__ __device__ inline int small_region0_words(int64_t k, u64 cap_words, int B2, int nq, int cap)
 {
     const int64_t late = (((k + 1) / 2 + (int64_t)cap_words + 1) & ~(int64_t)1) + 2 * B2 * (nq + 1) + B2 * nq;
     const int64_t early = 2 * 128 + 4 + cap / 2;
-    int64_t r0 = late > kFineBins ? late : kFineBins;
+    int64_t r0 = late > kFineBins + 1 ? late : kFineBins + 1;
     r0 = r0 > early ? r0 : early;
-    return (int)((r0 + 1) & ~(int64_t)1);
+    return (int)((r0 + 3) & ~(int64_t)3);
 }
 
-// floor: words of the coarse histogram, which overlays the carve-up (16-bit counters in the one-wavefront
-// kernel: kCoarseBins / 2; 32-bit counters in the workgroup-per-row kernel: kCoarseBins)
-__host__ __device__ inline int small_lds_words(int dt, int cap, int region0, int B2, int maxs, int floor = kCoarseBins / 2)
+__host__ __device__ inline int small_lds_words(int dt, int cap, int region0, int B2, int maxs)
 {
-    int wds = region0 + cap + (maxs ? 0 : cap) + ((dt == 0 && !maxs) ? cap / 2 : 0);
-    wds += 2 * B2 + small_tg_words(B2) + 16;
-    wds += (B2 + 1) + B2 * 3;
-    if (wds < floor) wds = floor;
+    int wds = region0 + (cap + 4) + (dt == 0 ? (cap + 4) / 2 : 0);
+    wds += B2 + (dt == 0 ? B2 : 0);
+    wds += maxs ? 0 : cap + (dt == 0 ? cap / 2 : 0);
+    wds += 16 + (B2 + 1) + B2 * 3;
+    if (wds < kCoarseBins / 2) wds = kCoarseBins / 2;      // 16-bit counters of the coarse histogram
     return wds;
 }
 
@@ -119,14 +111,13 @@ __device__ inline SmallLds small_carve(u32* base, int dt, int cap, int region0, 
 {
     SmallLds L;
     u32* p = base;
-    L.hist = p;            p += region0;           // region0 is even
-    L.Lent = p;            p += cap;
-    L.S = maxs ? L.Lent : p;
-    p += maxs ? 0 : cap;
-    L.Lidx = maxs ? (uint16_t*)base : (uint16_t*)p;
-    p += (dt == 0 && !maxs) ? cap / 2 : 0;
-    L.thr = p;             p += 2 * B2;            // cap is a multiple of 64: still 8-byte aligned
-    L.tg = p;              p += small_tg_words(B2);
+    L.hist = p;            p += region0;           // a multiple of four words
+    L.S = p;               p += cap + 4;
+    L.Sp = (uint16_t*)p;   p += dt == 0 ? (cap + 4) / 2 : 0;
+    L.thr = p;             p += B2;
+    L.thr_lo = p;          p += dt == 0 ? B2 : 0;
+    L.Lent = p;            p += maxs ? 0 : cap;
+    L.Lidx = (uint16_t*)p; p += (dt == 0 && !maxs) ? cap / 2 : 0;
     L.qtab = p;            p += 16;
     L.blk_start = p;       p += B2 + 1;
     L.vminb = p;           p += B2;
@@ -139,6 +130,10 @@ __device__ inline SmallLds small_carve(u32* base, int dt, int cap, int region0, 
 // LDS (checked at run time), so an address computed as an integer needs no base register.
 typedef __attribute__((address_space(3))) u32 lds_u32;
 __device__ inline lds_u32* lds_at(u32 byte_off) { return (lds_u32*)(uintptr_t)byte_off; }
+__device__ inline u32 lds_add(u32 byte_off, u32 v)
+{
+    return __hip_atomic_fetch_add(lds_at(byte_off), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 __device__ inline void lds_inc(u32 byte_off, u32 v)
 {
     __hip_atomic_fetch_add(lds_at(byte_off), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -167,9 +162,6 @@ template <int DT, int EPL, int NQ, int MAXS, bool ASYM = false>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min_waves(DT, EPL, NQ, MAXS, ASYM)))) void enc_small_kernel(SmallArgs a)
 {
     typedef Elem<DT> E;
-    typedef typename std::conditional<DT == 0, u64, u32>::type comp_t;   // bf16: key + index fit 31 bits
-    constexpr comp_t kClsBit = (comp_t)1 << (8 * sizeof(comp_t) - 1);       // set for the positive class
-    constexpr int kHiShift = DT == 0 ? 32 : 0;                               // position of the key word in a comp
     constexpr int kRegThr = 14;                                              // boundaries held in registers
     constexpr int QN = NQ ? NQ : kMaxQ;
     constexpr int EPC = DT == 0 ? 4 : 8;            // elements per 16-byte chunk
@@ -181,34 +173,24 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     if (r >= a.R) return;
     const int M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq, cap = a.cap;
     const int k = (int)a.k;
-    const u32 idxmask = (1u << w) - 1u;
     SmallLds L = small_carve(smem, DT, cap, a.region0_words, B2, MAXS);
     if (__builtin_amdgcn_groupstaticsize() != 0u) {             // integer LDS addresses assume offset 0
         if (lane == 0) a.fallback[r] = 1u;
         return;
     }
-    const u32 lent_off = (u32)(L.Lent - smem) * 4u;
-
     // ---- list entry accessors ---------------------------------------------------------------
-    // bf16: one word holds sign, key and inverted index, i.e. the comp with the class bit flipped
+    // Entry p of the list (ascending index): the class as the top bit (set for the positive one), the magnitude key below it
+    // and, for bf16, the inverted index in the low half: the whole class-extended comp.  fp32 entries have ~p as their low
+    // word where equal keys must be told apart (list positions rise with the index).
+    constexpr u32 kPos = 0x80000000u, kMag = 0x7FFFFFFFu;
     constexpr int SLN = MAXS ? MAXS : 32;          // slots of 64 entries (cap < 2048)
     u32 ent[MAXS ? MAXS : 1], eix[(MAXS && DT == 0) ? MAXS : 1];
     auto ent_word = [&](int s) -> u32 { return MAXS ? ent[MAXS ? s : 0] : L.Lent[s * kWave + (int)lane]; };
-    auto ent_index = [&](int s) -> u32 {          // fp32 only
+    auto ent_index = [&](int s) -> u32 {
+        if (DT == 1) return ~ent_word(s) & 0xFFFFu;
         return MAXS ? eix[(MAXS && DT == 0) ? s : 0] : (u32)L.Lidx[s * kWave + (int)lane];
     };
-    auto ent_cx = [&](int s) -> comp_t {          // class-extended comp of this lane's entry of slot s
-        if (DT == 0) return ((comp_t)(ent_word(s) ^ 0x80000000u) << kHiShift) | (comp_t)(u32)(~ent_index(s));
-        return (comp_t)(ent_word(s) ^ 0x80000000u);
-    };
-    auto cx_key = [&](comp_t cx) -> u32 {         // magnitude key
-        if (DT == 0) return (u32)((u64)cx >> kHiShift) & 0x7FFFFFFFu;
-        return ((u32)cx >> 16) & 0x7FFFu;
-    };
-    auto cx_idx = [&](comp_t cx) -> u32 {
-        if (DT == 0) return ~(u32)cx;
-        return 0xFFFFu - ((u32)cx & 0xFFFFu);
-    };
+    auto word_key = [&](u32 e) -> u32 { return DT == 0 ? e & kMag : (e >> 16) & 0x7FFFu; };
 
     // ---- 1. load the row, coarse histogram ------------------------------------------
     const RowChunks<DT> row(a.x, r, a.N);           // element i of the row is element head + i of its chunks
@@ -634,14 +616,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
 #pragma unroll
         for (int s = 0; s < SLN; ++s) {
             asm volatile("" : "+v"(ent[MAXS ? s : 0]));     // (the shift stays behind all of the loads)
-            if (DT == 1) ent[MAXS ? s : 0] = (ent[MAXS ? s : 0] << 16) | (ix[MAXS ? s : 0] ^ 0xFFFFu);
-            else eix[(MAXS && DT == 0) ? s : 0] = ix[MAXS ? s : 0];
+            if (DT == 1) ent[MAXS ? s : 0] = ((ent[MAXS ? s : 0] << 16) | ix[MAXS ? s : 0]) ^ (kPos | 0xFFFFu);
+            else { ent[MAXS ? s : 0] ^= kPos; eix[(MAXS && DT == 0) ? s : 0] = ix[MAXS ? s : 0]; }
         }
         wave_sync();
     } else {
         for (u32 p = lane; p < nL; p += kWave) {    // fp32: the row positions stay where they are
             const u32 i = plist[p], raw = (u32)xr[i];
-            L.Lent[p] = DT == 1 ? (raw << 16) | (i ^ 0xFFFFu) : raw;
+            L.Lent[p] = DT == 1 ? ((raw << 16) | i) ^ (kPos | 0xFFFFu) : raw ^ kPos;
         }
         wave_sync();
     }
@@ -649,7 +631,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         if (kHint && hinted) {                        // the row's largest key is the list's largest
             u32 mx = 0;
 #pragma unroll
-            for (int s = 0; s < SLN; ++s) mx = max(mx, ent[MAXS ? s : 0] & 0x7FFFFFFFu);
+            for (int s = 0; s < SLN; ++s) mx = max(mx, ent[MAXS ? s : 0] & kMag);
             kmax = wave_max_dpp(mx);
             if (DT == 1) kmax >>= 16;
         }
@@ -667,193 +649,184 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     wave_sync();
 
     // ---- 3. fine bins ---------------------------------------------------------------------
-    // 1024 bins, linear in (key - t_lo) >> sh; sh from the top of the highest occupied coarse
-    // bin.  fp32 keeps the in-bin key bits, the inverted index and the class in one word of S.
+    // 1024 bins, linear in (key - t_lo) >> sh; sh from the row's largest key.  A bin's word counts the positive class
+    // in its high half and the negative one in its low half; after the scan the halves are the places in S where the bin's
+    // members of the class go, and adding an entry moves them on: in the end they are the ends of the bin's places, which
+    // begin where those of the bin above end.
     const int nslots = (int)((nL + kWave - 1) / kWave);
     const u32 range = kmax > t_lo ? kmax - t_lo : 0u;
     const int sh = range < (u32)kFineBins ? 0 : (32 - __clz((int)range)) - 10;
-    if (DT == 0 && sh + w + 1 > 32) {
-        if (lane == 0) a.fallback[r] = 1u;
-        return;
-    }
-    const u32 inmask = (1u << sh) - 1u;
+    auto in_list = [&](int s) -> bool { return (int)lane < (int)nL - s * kWave; };      // this lane has an entry in slot s
+    auto key_bin = [&](u32 key) -> u32 { return (key - t_lo) >> sh; };
+    auto half_of = [](u32 e) -> u32 { return (e >> 27) & 16u; };                     // shift of the class's half
+    u32 b4[MAXS ? MAXS : 1];                        // byte offset of the entry's bin
 #pragma unroll(MAXS ? MAXS : 1)
     for (int s = 0; s < SLN; ++s) {
         if (s >= nslots) break;
-        const u32 p = s * kWave + lane;
-        if (p < nL) {
-            const u32 e = ent_word(s);
-            const u32 key = DT == 0 ? (e & 0x7FFFFFFFu) : ((e >> 16) & 0x7FFFu);
-            lds_inc(((key - t_lo) >> sh) << 2, (e >> 31) ? 0x800u : 1u);    // 11-bit fields: the list has fewer than 2048 entries
+        if (in_list(s)) {
+            const u32 e = ent_word(s), at = key_bin(word_key(e)) << 2;
+            if (MAXS) b4[MAXS ? s : 0] = at;
+            lds_inc(at, 1u << half_of(e));
         }
     }
     wave_sync();
-    u32 n_pos, n_neg;
+    u32 nLp, n_pos, n_neg;                          // positive entries of the list; class sizes of the kept set
     int cut_lane = 0;
-    {   // exclusive prefix from the top, per class, in the counting format pos | neg << 11 (fill << 22 is added later)
-        const int hi = kFineBins - (int)lane * 16;
-        u32 cs[16];
-        uint4* h4 = (uint4*)(L.hist + hi - 16);
+    constexpr int BPL = kFineBins / kWave;          // bins per lane, from the top
+    {
+        const int hi = kFineBins - (int)lane * BPL;
+        u32 cs[BPL];
+        uint4* h4 = (uint4*)(L.hist + hi - BPL);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint4 t = h4[3 - j];
+        for (int j = 0; j < BPL / 4; ++j) {
+            const uint4 t = h4[BPL / 4 - 1 - j];
             cs[4 * j + 0] = t.w; cs[4 * j + 1] = t.z; cs[4 * j + 2] = t.y; cs[4 * j + 3] = t.x;
         }
-        u32 local = 0;
+        u32 local = 0;                              // (the list has fewer than 2048 entries: the halves never carry)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) local += cs[j];
-        if (nL >= 1024u) {                              // a fine bin with 1024+ members overflows its 10-bit fill field
-            u32 big = 0;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) big |= ((cs[j] & 0x7FFu) + (cs[j] >> 11)) >> 10;
-            if (__ballot(big != 0u)) {
-                if (lane == 0) a.fallback[r] = 1u;
-                return;
-            }
-        }
+        for (int j = 0; j < BPL; ++j) local += cs[j];
         const u32 incl = wave_scan_dpp(local);
         const u32 tot = bcast(incl, kWave - 1);
-        n_pos = tot & 0x7FFu; n_neg = tot >> 11;        // class sizes of L (of the kept set once cut)
-        const u32 excl = incl - local;
+        nLp = tot >> 16;
+        n_pos = nLp; n_neg = tot & 0xFFFFu;
         // the lane whose bins hold overall rank k-1 (meaningful when nL > k)
-        const u32 ov_ex = (excl & 0x7FFu) + (excl >> 11), ov_in = (incl & 0x7FFu) + (incl >> 11);
+        const u32 ov_in = (incl >> 16) + (incl & 0xFFFFu), ov_ex = ov_in - (local >> 16) - (local & 0xFFFFu);
         const u64 mc = __ballot(k > 0 && ov_ex <= (u32)(k - 1) && (u32)(k - 1) < ov_in);
         cut_lane = mc ? (int)__builtin_ctzll(mc) : 0;
-        u32 acc = excl;
-        u32 o[16];
+        u32 acc = incl - local + nLp;               // the negative class follows the positive one
+        u32 o[BPL];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+        for (int j = 0; j < BPL; ++j) {
             o[j] = acc;
             acc += cs[j];
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) h4[3 - j] = make_uint4(o[4 * j + 3], o[4 * j + 2], o[4 * j + 1], o[4 * j + 0]);
+        for (int j = 0; j < BPL / 4; ++j) h4[BPL / 4 - 1 - j] = make_uint4(o[4 * j + 3], o[4 * j + 2], o[4 * j + 1], o[4 * j + 0]);
+        if (lane == 0) L.hist[kFineBins] = nLp;     // the bin above all others ends where the classes begin
+        if (lane < 4u) L.S[nL + lane] = 0;          // (read behind the last entry by the loops that take four at a time)
     }
     wave_sync();
 #pragma unroll(MAXS ? MAXS : 1)
     for (int s = 0; s < SLN; ++s) {
         if (s >= nslots) break;
-        const u32 p = s * kWave + lane;
-        if (p < nL) {
-            const u32 e = ent_word(s);
-            const u32 key = DT == 0 ? (e & 0x7FFFFFFFu) : ((e >> 16) & 0x7FFFu);
-            const u32 rel = key - t_lo;
-            const u32 old = atomicAdd(&L.hist[rel >> sh], 1u << 22);
-            const u32 at = (old & 0x7FFu) + ((old >> 11) & 0x7FFu) + (old >> 22);
-            if (DT == 0) L.S[at] = ((((rel & inmask) << w) | (idxmask - ent_index(s))) << 1) | (e >> 31);
-            else L.S[at] = e;
+        if (in_list(s)) {
+            const u32 e = ent_word(s), hf = half_of(e);
+            const u32 old = lds_add(MAXS ? b4[MAXS ? s : 0] : key_bin(word_key(e)) << 2, 1u << hf);
+            const u32 at = __builtin_amdgcn_ubfe(old, hf, 16u);
+            L.S[at] = e;
+            if (DT == 0) L.Sp[at] = (uint16_t)(s * kWave + (int)lane);
         }
     }
     wave_sync();
-    // members of a fine bin compare on the plain comp; their class
-    auto s_plain = [&](u32 s) -> u32 { return DT == 0 ? s >> 1 : s & 0x7FFFFFFFu; };
-    auto s_neg = [&](u32 s) -> u32 { return DT == 0 ? s & 1u : s >> 31; };
-    // class-extended comp of a member of fine bin `bin`
-    auto s_cx = [&](u32 s, u32 bin) -> comp_t {
-        if (DT == 0) {
-            const u32 key = ((bin << sh) | ((s >> 1) >> w)) + t_lo;
-            const u32 idx = idxmask - ((s >> 1) & idxmask);
-            return ((comp_t)(key | ((s & 1u) ? 0u : 0x80000000u)) << kHiShift) | (comp_t)(u32)(~idx);
+    auto low_of = [&](u32 at) -> u32 { return DT == 0 ? ~(u32)L.Sp[at] : 0u; };      // fp32: low word of the comp at place `at`
+    auto beats = [&](u32 x, u32 xl, u32 y, u32 yl) -> bool { return DT == 0 ? x > y || (x == y && xl > yl) : x > y; };
+    // The member of rank `rem` of c0 places from a0 and c1 places from a1, by the whole wavefront, bit by bit: for bins of many
+    // members (equal or nearly equal values), where comparing all pairs would take c^2 steps.
+    auto wave_select = [&](u32 a0, u32 c0, u32 a1, u32 c1, u32 rem, u32 mask, u32& hi, u32& lo) {
+        auto count = [&](auto take) -> u32 {
+            u32 n = 0;
+            for (u32 i = lane; i < c0 + c1; i += kWave) n += take(i < c0 ? a0 + i : a1 + (i - c0)) ? 1u : 0u;
+            return wave_sum(n);
+        };
+        hi = 0; lo = 0;
+        for (u32 bit = kPos; bit; bit >>= 1) {
+            const u32 t = hi | bit;
+            if (count([&](u32 at) -> bool { return (L.S[at] & mask) >= t; }) > rem) hi = t;
         }
-        return (comp_t)(s ^ 0x80000000u);
+        if (DT == 0) {
+            const u32 v = hi, up = count([&](u32 at) -> bool { return (L.S[at] & mask) > v; });
+            for (u32 bit = kPos; bit; bit >>= 1) {
+                const u32 t = lo | bit;
+                if (up + count([&](u32 at) -> bool { return (L.S[at] & mask) == v && low_of(at) >= t; }) > rem) lo = t;
+            }
+        }
     };
 
     // ---- top-K cut: the comp of overall rank k-1 (ATKF) -----------------------------------------
-    comp_t thrK = 0;                                // plain comp; every entry of L is kept when nL <= k
+    u32 thrK = 0, thrK_lo = 0;                      // without the class bit; every entry of L is kept when nL <= k
+    bool eq_keys = false;                           // fp32: equal keys on both sides of the cut or of a boundary: the low words decide
     if (nL > (u32)k) {
-        // open the 16 bins of the lane found by the scan: the last one whose first rank is <= k-1
-        const int hi = kFineBins - cut_lane * 16;
-        const u32 wj = lane < 16u ? L.hist[hi - 1 - (int)lane] : 0xFFFFFFFFu;
-        const u64 mj = __ballot(lane < 16u && (wj & 0x7FFu) + ((wj >> 11) & 0x7FFu) <= (u32)(k - 1));
-        const int lo = hi - (int)__popcll(mj);
-        const u32 wd = L.hist[lo];
-        const u32 pe = wd & 0x7FFu, ne = (wd >> 11) & 0x7FFu, cnt = wd >> 22, base = pe + ne;
-        const u32 rem = (u32)(k - 1) - base;
-        u32 kp = 0, kn = 0;
-        for (u32 g = 0; g < cnt; g += kWave) {       // members in groups of 64, one per lane
-            const u32 i = g + lane;
-            u32 me = 0, gt = 0;
-            if (i < cnt) {
-                me = L.S[base + i];
-                for (u32 j = 0; j < cnt; ++j) gt += s_plain(L.S[base + j]) > s_plain(me) ? 1u : 0u;
-            }
-            const bool in = i < cnt && gt <= rem;
-            kp += (u32)__popcll(__ballot(in && !s_neg(me)));
-            kn += (u32)__popcll(__ballot(in && s_neg(me)));
-            const u64 hit = __ballot(i < cnt && gt == rem);
-            if (hit) {
-                const int hl = (int)__builtin_ctzll(hit);
-                const comp_t cx = s_cx(me, (u32)lo) & ~kClsBit;
-                if (DT == 0) thrK = ((comp_t)bcast((u32)((u64)cx >> kHiShift), hl) << kHiShift) | (comp_t)bcast((u32)cx, hl);
-                else thrK = (comp_t)bcast((u32)cx, hl);
-            }
+        // open the bins of the lane found by the scan: the first one that ends behind rank k-1
+        const int hi = kFineBins - cut_lane * BPL;
+        const u32 wj = lane < (u32)BPL ? L.hist[hi - 1 - (int)lane] : 0u;
+        const u64 mj = __ballot(lane < (u32)BPL && (wj >> 16) + (wj & 0xFFFFu) - nLp > (u32)(k - 1));
+        const int fj = (int)__builtin_ctzll(mj), lo = hi - 1 - fj;
+        const u32 wd = bcast(wj, fj), wu = (u32)__builtin_amdgcn_readfirstlane((int)L.hist[lo + 1]);
+        const u32 sp = wu >> 16, sn = wu & 0xFFFFu, cp = (wd >> 16) - sp, cnt = cp + (wd & 0xFFFFu) - sn;
+        const u32 rem = (u32)(k - 1) - (sp + sn - nLp);
+        u32 kp, kn;                                 // members that stay
+        if (cnt <= (u32)kWave) {
+            const bool in = lane < cnt;
+            const u32 at = in ? (lane < cp ? sp + lane : sn + lane - cp) : 0u;
+            const u32 me = in ? L.S[at] & kMag : 0u, ml = in ? low_of(at) : 0u;
+            u32 gt = 0;
+            for (u32 j = 0; j < cnt; ++j) gt += beats(bcast(me, (int)j), bcast(ml, (int)j), me, ml) ? 1u : 0u;
+            const u64 stay = __ballot(in && gt <= rem);
+            kn = (u32)__popcll(stay);
+            kp = (u32)__popcll(stay & ((cp < 64u ? 1ull << cp : 0ull) - 1ull));
+            kn -= kp;
+            const int hl = (int)__builtin_ctzll(__ballot(in && gt == rem));
+            thrK = bcast(me, hl);
+            if (DT == 0) { thrK_lo = bcast(ml, hl); eq_keys = __popcll(__ballot(in && me == thrK)) > 1; }
+        } else {
+            wave_select(sp, cp, sn, cnt - cp, rem, kMag, thrK, thrK_lo);
+            eq_keys = true;
+            u32 n = 0;
+            for (u32 i = lane; i < cp; i += kWave) n += beats(thrK, thrK_lo, L.S[sp + i] & kMag, low_of(sp + i)) ? 0u : 1u;
+            kp = wave_sum(n);
+            kn = rem + 1u - kp;
         }
-        n_pos = pe + kp; n_neg = ne + kn;
+        n_pos = sp + kp; n_neg = sn - nLp + kn;
     }
     const u32 n = n_pos + n_neg;
     const u32 Kc[2] = { n_pos / (u32)M, n_neg / (u32)Mn };
 
-    // ---- block boundaries: comps of class ranks j*K-1, one lane per boundary ------------------------
-    // M-1 boundaries for the positive class, then Mn-1 for the negative one.  A class with fewer than M members has
-    // K = 0 and every member in its last block: its boundaries sit above every comp of the class.
+    // ---- block boundaries: comps of class ranks j*K-1 ----------------------------------------------
+    // M-1 boundaries for the positive class, then Mn-1 for the negative one, a few lanes each.  A class with fewer than M
+    // members has K = 0 and every member in its last block: its boundaries sit above every comp of the class.
+    // S holds the bin of a class rank at this very place; a search over the bins' first ranks, one lane a boundary, and
+    // lanes dealt to (boundary, member) pairs took 356 vector instructions a row of 16 blocks (bf16 [16384 x 4096]), this takes 118.
     const int ntg = B2 - 2;
-    comp_t* thr = (comp_t*)L.thr;
-    {
-        const int ntp = ntg > 0 ? ntg : 1;
-        u32* tg_bin = L.tg; u32* tg_base = L.tg + ntp; u32* tg_cnt = L.tg + 2 * ntp; u32* tg_rem = L.tg + 3 * ntp; u32* tg_pre = L.tg + 4 * ntp;
-        const bool mine = (int)lane < ntg;
-        const int cls = (int)lane >= M - 1 ? 1 : 0;
-        const int j = (cls ? (int)lane - (M - 1) : (int)lane) + 1;
-        const bool act = mine && Kc[cls] > 0;
-        const u32 R = act ? (u32)j * Kc[cls] - 1u : 0u;
-        int lo = 0, hi = kFineBins - 1;             // smallest bin whose first class rank is <= R
-        for (int it = 0; it < 10; ++it) {
-            const int mid = (lo + hi) >> 1;
-            const u32 wd = L.hist[mid];
-            const u32 pc = cls ? (wd >> 11) & 0x7FFu : wd & 0x7FFu;
-            if (pc <= R) hi = mid; else lo = mid + 1;
-        }
-        const u32 wd = L.hist[lo];
-        const u32 pe = wd & 0x7FFu, ne = (wd >> 11) & 0x7FFu;
-        const u32 cnt = act ? wd >> 22 : 0u;
-        const u32 incl = wave_scan_dpp(cnt);
-        if (mine) {
-            tg_bin[lane] = (u32)lo; tg_base[lane] = pe + ne; tg_cnt[lane] = cnt;
-            tg_rem[lane] = R - (cls ? ne : pe);
-            tg_pre[lane] = incl - cnt;
-            if (!act) thr[lane] = cls ? (comp_t)(kClsBit - 1) : ~(comp_t)0;
-        }
-        const u32 npairs = bcast(incl, kWave - 1);
-        wave_sync();
-        // one lane per (boundary, member of its bin): the member of the boundary's class
-        // with exactly `rem` class-mates above it is the boundary element
-        for (u32 g = 0; g < npairs; g += kWave) {
-            const u32 pr = g + lane;
-            if (pr < npairs) {
-                int tl = 0, th = ntg - 1;           // boundary t with tg_pre[t] <= pr < tg_pre[t] + tg_cnt[t]
-                while (tl < th) {
-                    const int mid = (tl + th + 1) >> 1;
-                    if (tg_pre[mid] <= pr) tl = mid; else th = mid - 1;
+    u32* thr = L.thr;
+    if (ntg > 0) {
+        constexpr u32 kWide = 32;                   // members from which on wave_select takes fewer steps
+        const int lg = ntg > 32 ? 0 : ntg > 16 ? 1 : ntg > 8 ? 2 : ntg > 4 ? 3 : ntg > 2 ? 4 : 5;    // log2 of the lanes per boundary
+        const u32 t = lane >> lg, sub = lane & ((1u << lg) - 1u);
+        const bool mine = (int)t < ntg;
+        const int cls = (int)t >= M - 1 ? 1 : 0;
+        const u32 j = t - (cls ? (u32)(M - 1) : 0u) + 1u, K = cls ? Kc[1] : Kc[0];
+        const bool act = mine && K > 0;
+        const u32 R = act ? j * K - 1u + (cls ? nLp : 0u) : 0u;         // its place
+        const u32 bin = act ? key_bin(word_key(L.S[R])) : 0u;
+        const u32 hf = cls ? 0u : 16u;
+        const u32 st = __builtin_amdgcn_ubfe(L.hist[bin + 1u], hf, 16u);
+        const u32 cn = act ? __builtin_amdgcn_ubfe(L.hist[bin], hf, 16u) - st : 0u, rem = R - st;
+        if (mine && !act && sub == 0) { thr[t] = cls ? kMag : ~0u; if (DT == 0) L.thr_lo[t] = ~0u; }
+        bool eq = DT == 0 && mine && !act && (cls ? n_neg : n_pos) > 0u;
+        if (cn <= kWide) {
+            // entries behind the bin's end belong to lower bins or to the negative class or are zeros: none lies above a member
+            for (u32 i = sub; i < cn; i += 1u << lg) {
+                const u32 me = L.S[st + i], ml = low_of(st + i);
+                u32 gt = 0, same = 0;
+                for (u32 jj = 0; jj < cn; jj += 4) {
+#pragma unroll
+                    for (u32 u = 0; u < 4; ++u) {
+                        const u32 x = L.S[st + jj + u];
+                        gt += beats(x, low_of(st + jj + u), me, ml) ? 1u : 0u;
+                        if (DT == 0) same += x == me ? 1u : 0u;
+                    }
                 }
-                const int t = tl;
-                const u32 tc = (u32)(t >= M - 1 ? 1 : 0);
-                const u32 bs = tg_base[t], cn = tg_cnt[t];
-                const u32 me = L.S[bs + (pr - tg_pre[t])];
-                if (s_neg(me) == tc) {
-                    // one compare per member: with the class bit moved to the top and set for the
-                    // boundary's class, "same class and larger comp" is a plain unsigned "larger"
-                    const u32 fm = DT == 0 ? (tc ^ 1u) : (tc ? 0u : 0x80000000u);
-                    auto key_of = [&](u32 sv) -> u32 {
-                        const u32 xv = sv ^ fm;
-                        return DT == 0 ? __builtin_amdgcn_alignbit(xv, xv, 1) : xv;     // fp32: rotate the class bit up
-                    };
-                    const u32 mk = key_of(me);
-                    u32 gt = 0;
-                    for (u32 jj = 0; jj < cn; ++jj) gt += key_of(L.S[bs + jj]) > mk ? 1u : 0u;
-                    if (gt == tg_rem[t]) thr[t] = s_cx(me, tg_bin[t]);
-                }
+                if (gt == rem) { thr[t] = me; if (DT == 0) { L.thr_lo[t] = ml; eq = same > 1u; } }
             }
         }
+        for (u64 wide = __ballot(sub == 0 && cn > kWide); wide; wide &= wide - 1ull) {
+            const int l = (int)__builtin_ctzll(wide);
+            u32 vh, vl;
+            wave_select(bcast(st, l), bcast(cn, l), 0u, 0u, bcast(rem, l), ~0u, vh, vl);
+            if (lane == 0) { thr[l >> lg] = vh; if (DT == 0) L.thr_lo[l >> lg] = vl; }
+            eq = eq || DT == 0;
+        }
+        if (DT == 0) eq_keys = eq_keys || __ballot(eq) != 0ull;
     }
 
     // block starts in closed form (K, ..., K, K + remainder per class)
@@ -878,43 +851,45 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     // An entry's block = number of boundaries above it, plus one for the negative class: a
     // positive entry is above every negative boundary, a negative entry below every positive
     // one.  Up to kRegThr boundaries are held in registers.
-    comp_t tx[kRegThr];
+    u32 tx[kRegThr];
 #pragma unroll
-    for (int j = 0; j < kRegThr; ++j) tx[j] = j < ntg ? thr[j] : (comp_t)0;
-    const bool tree8 = DT == 1 && M == 8 && Mn == 8;      // (one-word comps: a select is one instruction)
+    for (int j = 0; j < kRegThr; ++j) tx[j] = j < ntg ? thr[j] : 0u;
+    const bool tree8 = M == 8 && Mn == 8;
 #pragma unroll(MAXS ? MAXS : 1)
     for (int s = 0; s < SLN; ++s) {
         if (s >= nslots) break;
-        const u32 p = s * kWave + lane;
         bool kept = false;
         u32 b = 0, key = 0, idx = 0;
-        if (p < nL) {
-            const comp_t cx = ent_cx(s);
-            if ((cx & ~kClsBit) >= thrK) {
-                kept = true;
-                u32 above;
+        if (in_list(s)) {
+            const u32 cx = ent_word(s);
+            kept = (cx & kMag) >= thrK;
+            if (DT == 0 && eq_keys) kept = kept && !beats(thrK, thrK_lo, cx & kMag, ~(u32)(s * kWave + (int)lane));
+            if (kept) {
+                u32 over;
                 if (tree8) {
                     // 8 + 8 blocks: the 14 boundaries and the class bit are 15 separators in descending
                     // order; four compares walk them as a binary tree (the first is the class bit itself)
-                    const bool c1 = !(cx & kClsBit);
-                    comp_t m = c1 ? tx[10] : tx[3];
+                    const bool c1 = !(cx & kPos);
+                    u32 m = c1 ? tx[10] : tx[3];
                     const bool c2 = m > cx;
                     m = c1 ? (c2 ? tx[12] : tx[8]) : (c2 ? tx[5] : tx[1]);
                     const bool c3 = m > cx;
-                    const comp_t lo4 = c3 ? (c2 ? tx[6] : tx[2]) : (c2 ? tx[4] : tx[0]);
-                    const comp_t hi4 = c3 ? (c2 ? tx[13] : tx[9]) : (c2 ? tx[11] : tx[7]);
+                    const u32 lo4 = c3 ? (c2 ? tx[6] : tx[2]) : (c2 ? tx[4] : tx[0]);
+                    const u32 hi4 = c3 ? (c2 ? tx[13] : tx[9]) : (c2 ? tx[11] : tx[7]);
                     m = c1 ? hi4 : lo4;
                     const bool c4 = m > cx;
-                    above = (c1 ? 8u : 0u) + (c2 ? 4u : 0u) + (c3 ? 2u : 0u) + (c4 ? 1u : 0u);
+                    over = (c1 ? 8u : 0u) + (c2 ? 4u : 0u) + (c3 ? 2u : 0u) + (c4 ? 1u : 0u);
                 } else {
-                    above = (cx & kClsBit) ? 0u : 1u;
+                    over = (cx & kPos) ? 0u : 1u;
 #pragma unroll
-                    for (int j = 0; j < kRegThr; ++j) above += tx[j] > cx ? 1u : 0u;
-                    for (int j = kRegThr; j < ntg; ++j) above += thr[j] > cx ? 1u : 0u;
+                    for (int j = 0; j < kRegThr; ++j) over += tx[j] > cx ? 1u : 0u;
+                    for (int j = kRegThr; j < ntg; ++j) over += thr[j] > cx ? 1u : 0u;
                 }
-                b = above;
-                key = cx_key(cx);
-                idx = cx_idx(cx);
+                if (DT == 0 && eq_keys)              // boundaries of the same key
+                    for (int j = 0; j < ntg; ++j) over += thr[j] == cx && L.thr_lo[j] > ~(u32)(s * kWave + (int)lane) ? 1u : 0u;
+                b = over;
+                key = word_key(cx);
+                idx = ent_index(s);
                 atomicMin(&L.vminb[b], key);
                 atomicMax(&L.vmaxb[b], key);
             }
@@ -1155,7 +1130,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         a.mv.n_pos[r] = n_pos;
         a.mv.n_neg[r] = n_neg;
         a.fallback[r] = 0u;
-        if (kHint && k > 0) a.hint[hslot] = nL > (u32)k ? cx_key(thrK) : t_lo;    // this row's cut key, for a later row
+        if (kHint && k > 0) a.hint[hslot] = nL > (u32)k ? word_key(thrK) : t_lo;    // this row's cut key, for a later row
     }
 }
 

@@ -35,15 +35,55 @@ namespace slicer {
 constexpr int kWgMaxSlots = 32;        // list slots (64 entries): lists of up to 2048 entries
 constexpr int kWgMisc = 64;            // broadcast words (0..15), per-wavefront maxima (16..31), scan scratch (32..47), bounds tried (48..)
 
-// words of LDS: the one-wavefront layout (list in LDS) followed by the workgroup's own tables
+// LDS carve-up (word offsets).  The coarse histogram (2048 counters) overlays everything; region 0 is the fine histogram
+// first and later holds the block-ordered indices, the stream image, the ABQ sums and the quantiser scales.
+struct WgLds {
+    u32* hist;      // [region0]   fine histogram; later bo_idx, stream image, sums, invt
+    u32* Lent;      // [cap]       list entries, ascending index: bf16 raw << 16 | ~idx; fp32 raw
+    u32* S;         // [cap]       entries arranged by fine bin; later bo_val
+    uint16_t* Lidx; // [cap]       fp32 only: index of the entry
+    u32* thr;       // [2 * B2]    block boundaries (class-extended comps), positive class first
+    u32* tg;        // [5][ntg]    boundary work table: bin, base, count, rank in bin, pair prefix
+    u32* qtab;      // [16]        allowed bitwidths
+    u32* blk_start; // [B2 + 1]
+    u32* vminb;     // [B2] key of the block's smallest / largest element
+    u32* vmaxb;     // [B2]
+    u32* run;       // [B2]        the chosen bitwidth index
+};
+
+__host__ __device__ inline int wg_tg_words(int B2)
+{
+    const int ntg = B2 > 2 ? B2 - 2 : 1;
+    return (5 * ntg + 1) & ~1;
+}
+
 __host__ __device__ inline int wg_main_words(int dt, int cap, int region0, int B2)
 {
-    return small_lds_words(dt, cap, region0, B2, 0, kCoarseBins);
+    const int wds = region0 + 2 * cap + (dt == 0 ? cap / 2 : 0) + 2 * B2 + wg_tg_words(B2) + 16 + (B2 + 1) + B2 * 3;
+    return wds < kCoarseBins ? kCoarseBins : wds;
 }
 __host__ __device__ inline int wg_lds_words(int dt, int cap, int region0, int B2)
 {
     // misc, chunk totals (64), per-slot per-block counts as 16-bit (cap / 64 slots)
     return wg_main_words(dt, cap, region0, B2) + kWgMisc + 64 + ((cap / kWave) * B2 + 1) / 2 + 2;
+}
+
+__device__ inline WgLds wg_carve(u32* base, int dt, int cap, int region0, int B2)
+{
+    WgLds L;
+    u32* p = base;
+    L.hist = p;            p += region0;           // region0 is even
+    L.Lent = p;            p += cap;
+    L.S = p;               p += cap;
+    L.Lidx = (uint16_t*)p; p += dt == 0 ? cap / 2 : 0;
+    L.thr = p;             p += 2 * B2;            // cap is a multiple of 64: still 8-byte aligned
+    L.tg = p;              p += wg_tg_words(B2);
+    L.qtab = p;            p += 16;
+    L.blk_start = p;       p += B2 + 1;
+    L.vminb = p;           p += B2;
+    L.vmaxb = p;           p += B2;
+    L.run = p;             p += B2;
+    return L;
 }
 
 // wavefronts per SIMD the register allocator must leave room for (same rule as the one-wavefront kernel)
@@ -76,7 +116,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     if (r >= a.R) return;
     const int M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq, cap = a.cap;
     const int k = (int)a.k;
-    SmallLds L = small_carve(smem, DT, cap, a.region0_words, B2, 0);
+    WgLds L = wg_carve(smem, DT, cap, a.region0_words, B2);
     u32* misc = smem + wg_main_words(DT, cap, a.region0_words, B2);      // broadcast words and scan scratch
     u32* ctab = misc + kWgMisc;                                           // [NCH][NW] chunk totals per wavefront
     uint16_t* stab = (uint16_t*)(ctab + 64);                         // [slot][B2] entries of block b in slot s
