@@ -432,6 +432,7 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         sa.hint = (u32*)(ws + p.off_hint);
         const bool timed = g_ev_start && g_ev_stop;
         if (timed) SLICER_HIP(hipEventRecord(g_ev_start, st));
+        small_split_lanes(sa);
         const SmallLaunch sl = { p.small_epl, p.small_lds_bytes, p.small_maxs };
         SLICER_HIP(dt == SLICER_F32 ? launch_small_any<0>(sa, sl, asym, st) : launch_small_any<1>(sa, sl, asym, st));
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));

@@ -50,8 +50,23 @@ struct SmallArgs {
     Ladder lad;         // fixed multi-level mode: no sums, no search
     int guard;          // 0: relative squared-error budget; 1: DS mismatch of Eq. "DS", greedy descent (beta = delta)
     float one_plus, one_minus;   // asymmetric thresholds of Sec. 3.1 (ASYM kernels): 1 + lambda, 1 - lambda in fp32
+    int nbits, lg;      // bits of a block number; log2 of the lanes per boundary
+    int lpb, cl, es, nc;    // ABQ: lanes per block, those of them with candidate bitwidths of their own, slices of a block, candidates of a lane
     u32* hint;          // [kHintSlots] cut keys of rows encoded earlier with this workspace (any contents are safe)
 };
+
+// how the lanes of the one-wavefront kernel are dealt to B2 blocks and nq bitwidths
+inline void small_split_lanes(SmallArgs& a)
+{
+    const int B2 = a.M + a.Mn, ntg = B2 - 2;
+    a.nbits = 0;
+    while ((1 << a.nbits) < B2) ++a.nbits;
+    a.lg = ntg > 32 ? 0 : ntg > 16 ? 1 : ntg > 8 ? 2 : ntg > 4 ? 3 : ntg > 2 ? 4 : 5;
+    a.lpb = kWave / (B2 < kWave ? B2 : kWave);
+    a.cl = a.lpb < 8 ? a.lpb : 8;
+    a.es = a.lpb >= 16 ? a.lpb / 8 : 1;
+    a.nc = (a.nq + a.cl - 1) / a.cl;
+}
 
 // Threshold hints.  Rows of one tensor (tokens of one sequence, successive decode steps) have their
 // top-K cut at nearly the same magnitude, so a wave first tries the cut key some earlier row left in
@@ -722,7 +737,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     auto beats = [&](u32 x, u32 xl, u32 y, u32 yl) -> bool { return DT == 0 ? x > y || (x == y && xl > yl) : x > y; };
     // The member of rank `rem` of c0 places from a0 and c1 places from a1, by the whole wavefront, bit by bit: for bins of many
     // members (equal or nearly equal values), where comparing all pairs would take c^2 steps.
-    auto wave_select = [&](u32 a0, u32 c0, u32 a1, u32 c1, u32 rem, u32 mask, u32& hi, u32& lo) {
+    auto wave_select = [&](u32 a0, u32 c0, u32 a1, u32 c1, u32 rem, u32 mask, u32& hi, u32& lo) __attribute__((always_inline)) {
         auto count = [&](auto take) -> u32 {
             u32 n = 0;
             for (u32 i = lane; i < c0 + c1; i += kWave) n += take(i < c0 ? a0 + i : a1 + (i - c0)) ? 1u : 0u;
@@ -779,7 +794,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         n_pos = sp + kp; n_neg = sn - nLp + kn;
     }
     const u32 n = n_pos + n_neg;
-    const u32 Kc[2] = { n_pos / (u32)M, n_neg / (u32)Mn };
+    const u32 Kc[2] = { (u32)__builtin_amdgcn_readfirstlane((int)udiv16(n_pos, (u32)M)), (u32)__builtin_amdgcn_readfirstlane((int)udiv16(n_neg, (u32)Mn)) };
 
     // ---- block boundaries: comps of class ranks j*K-1 ----------------------------------------------
     // M-1 boundaries for the positive class, then Mn-1 for the negative one, a few lanes each.  A class with fewer than M
@@ -790,7 +805,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     u32* thr = L.thr;
     if (ntg > 0) {
         constexpr u32 kWide = 32;                   // members from which on wave_select takes fewer steps
-        const int lg = ntg > 32 ? 0 : ntg > 16 ? 1 : ntg > 8 ? 2 : ntg > 4 ? 3 : ntg > 2 ? 4 : 5;    // log2 of the lanes per boundary
+        const int lg = a.lg;                        // log2 of the lanes per boundary
         const u32 t = lane >> lg, sub = lane & ((1u << lg) - 1u);
         const bool mine = (int)t < ntg;
         const int cls = (int)t >= M - 1 ? 1 : 0;
@@ -830,12 +845,19 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     }
 
     // block starts in closed form (K, ..., K, K + remainder per class)
+    const bool one_key = sh == 0;                    // a bin holds one key: S has a block's largest and smallest key at its ends
     if ((int)lane < B2) {
         const int s = (int)lane >= M ? 1 : 0, m = (int)lane - s * M;
-        const u32 st = (s ? n_pos : 0u) + (u32)m * Kc[s];
+        const u32 K = s ? Kc[1] : Kc[0], st = (s ? n_pos : 0u) + (u32)m * K;
         L.blk_start[lane] = st;
         L.run[lane] = st;
-        L.vminb[lane] = 0xFFFFFFFFu; L.vmaxb[lane] = 0;
+        u32 lo = 0xFFFFFFFFu, hi = 0;
+        if (one_key) {
+            const u32 at = st + (s ? nLp - n_pos : 0u), cnt = m < (s ? Mn : M) - 1 ? K : (s ? n : n_pos) - st;
+            hi = word_key(L.S[at]);
+            lo = word_key(L.S[cnt ? at + cnt - 1u : at]);
+        }
+        L.vminb[lane] = lo; L.vmaxb[lane] = hi;
     }
     if (lane == 0) L.blk_start[B2] = n;
     wave_sync();
@@ -846,83 +868,94 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     u32* bo_val = L.S;
     uint16_t* bo_idx = (uint16_t*)(L.hist);
     u32* stage = L.hist + (k + 1) / 2;
-    int nbits = 0;
-    while ((1 << nbits) < B2) ++nbits;
     // An entry's block = number of boundaries above it, plus one for the negative class: a
     // positive entry is above every negative boundary, a negative entry below every positive
     // one.  Up to kRegThr boundaries are held in registers.
     u32 tx[kRegThr];
 #pragma unroll
     for (int j = 0; j < kRegThr; ++j) tx[j] = j < ntg ? thr[j] : 0u;
-    const bool tree8 = M == 8 && Mn == 8;
-#pragma unroll(MAXS ? MAXS : 1)
-    for (int s = 0; s < SLN; ++s) {
-        if (s >= nslots) break;
-        bool kept = false;
-        u32 b = 0, key = 0, idx = 0;
-        if (in_list(s)) {
-            const u32 cx = ent_word(s);
-            kept = (cx & kMag) >= thrK;
-            if (DT == 0 && eq_keys) kept = kept && !beats(thrK, thrK_lo, cx & kMag, ~(u32)(s * kWave + (int)lane));
-            if (kept) {
-                u32 over;
-                if (tree8) {
-                    // 8 + 8 blocks: the 14 boundaries and the class bit are 15 separators in descending
-                    // order; four compares walk them as a binary tree (the first is the class bit itself)
-                    const bool c1 = !(cx & kPos);
-                    u32 m = c1 ? tx[10] : tx[3];
-                    const bool c2 = m > cx;
-                    m = c1 ? (c2 ? tx[12] : tx[8]) : (c2 ? tx[5] : tx[1]);
-                    const bool c3 = m > cx;
-                    const u32 lo4 = c3 ? (c2 ? tx[6] : tx[2]) : (c2 ? tx[4] : tx[0]);
-                    const u32 hi4 = c3 ? (c2 ? tx[13] : tx[9]) : (c2 ? tx[11] : tx[7]);
-                    m = c1 ? hi4 : lo4;
-                    const bool c4 = m > cx;
-                    over = (c1 ? 8u : 0u) + (c2 ? 4u : 0u) + (c3 ? 2u : 0u) + (c4 ? 1u : 0u);
-                } else {
-                    over = (cx & kPos) ? 0u : 1u;
-#pragma unroll
-                    for (int j = 0; j < kRegThr; ++j) over += tx[j] > cx ? 1u : 0u;
-                    for (int j = kRegThr; j < ntg; ++j) over += thr[j] > cx ? 1u : 0u;
-                }
-                if (DT == 0 && eq_keys)              // boundaries of the same key
-                    for (int j = 0; j < ntg; ++j) over += thr[j] == cx && L.thr_lo[j] > ~(u32)(s * kWave + (int)lane) ? 1u : 0u;
-                b = over;
-                key = word_key(cx);
-                idx = ent_index(s);
-                atomicMin(&L.vminb[b], key);
-                atomicMax(&L.vmaxb[b], key);
-            }
-        }
-        // lanes of this slot in the same block: one ballot per bit of the block id
-        // (lanes that are not kept drop out through the first mask)
-        const u64 km = __ballot(kept);
-        u32 plo = (u32)km, phi = (u32)(km >> 32);
-        for (int bit = 0; bit < nbits; ++bit) {
-            const u32 onm = (u32)__builtin_amdgcn_sbfe((int)b, (u32)bit, 1u);   // all ones if the bit is set
-            const u64 bal = __ballot(onm != 0u);
-            plo &= ~((u32)bal ^ onm);
-            phi &= ~((u32)(bal >> 32) ^ onm);
-        }
+    // plo, phi: the kept lanes of this slot in the same block
+    auto place = [&](int s, u32 cx, bool kept, u32 b, u32 plo, u32 phi) __attribute__((always_inline)) {
         const u32 before = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
-        u32 basep = 0;
-        if (kept) basep = L.run[b];
-        wave_sync();
         if (kept) {
-            if (before == 0) L.run[b] = basep + (u32)__popc(plo) + (u32)__popc(phi);
-            const u32 pos = basep + before;
-            bo_val[pos] = E::value_bits(key);
-            bo_idx[pos] = (uint16_t)idx;
+            const u32 key = word_key(cx), base = L.run[b];
+            if (!one_key) { atomicMin(&L.vminb[b], key); atomicMax(&L.vmaxb[b], key); }
+            if (before == 0) L.run[b] = base + (u32)__popc(plo) + (u32)__popc(phi);
+            bo_val[base + before] = E::value_bits(key);
+            bo_idx[base + before] = (uint16_t)ent_index(s);
         }
-        wave_sync();
+    };
+    auto is_kept = [&](int s, u32 cx) -> bool {
+        bool kept = in_list(s) && (cx & kMag) >= thrK;
+        if (DT == 0 && eq_keys) kept = kept && !beats(thrK, thrK_lo, cx & kMag, ~(u32)(s * kWave + (int)lane));
+        return kept;
+    };
+    if (M == 8 && Mn == 8 && !(DT == 0 && eq_keys)) {
+        // 8 + 8 blocks: the 14 boundaries and the class bit are 15 separators in descending order; four compares walk them
+        // as a binary tree (the first is the class bit itself).  Their outcomes are the bits of the block number, and
+        // the compares' lane masks the ballots that the ranks inside a block need (split 604 -> 503 vector instructions a row,
+        // kernel 74.1 -> 68.3 us, with the block ranges read from S and no nested conditions).
+#pragma unroll(MAXS ? MAXS : 1)
+        for (int s = 0; s < SLN; ++s) {
+            if (s >= nslots) break;
+            const u32 cx = ent_word(s);
+            const bool kept = is_kept(s, cx);
+            const bool c1 = !(cx & kPos);
+            u32 m = c1 ? tx[10] : tx[3];
+            const bool c2 = m > cx;
+            m = c1 ? (c2 ? tx[12] : tx[8]) : (c2 ? tx[5] : tx[1]);
+            const bool c3 = m > cx;
+            const u32 lo4 = c3 ? (c2 ? tx[6] : tx[2]) : (c2 ? tx[4] : tx[0]);
+            const u32 hi4 = c3 ? (c2 ? tx[13] : tx[9]) : (c2 ? tx[11] : tx[7]);
+            m = c1 ? hi4 : lo4;
+            const bool c4 = m > cx;
+            const u64 km = __ballot(kept);
+            u32 b = 0, plo = (u32)km, phi = (u32)(km >> 32);
+            auto bit = [&](bool c, u32 value) __attribute__((always_inline)) {
+                const u64 bal = __ballot(c);
+                const u32 onm = c ? ~0u : 0u;
+                b |= onm & value;
+                plo &= ~((u32)bal ^ onm);
+                phi &= ~((u32)(bal >> 32) ^ onm);
+            };
+            bit(c1, 8u); bit(c2, 4u); bit(c3, 2u); bit(c4, 1u);
+            place(s, cx, kept, b, plo, phi);
+        }
+    } else {
+#pragma unroll(MAXS ? MAXS : 1)
+        for (int s = 0; s < SLN; ++s) {
+            if (s >= nslots) break;
+            const u32 cx = ent_word(s);
+            const bool kept = is_kept(s, cx);
+            u32 b = (cx & kPos) ? 0u : 1u;
+#pragma unroll
+            for (int j = 0; j < kRegThr; ++j) b += tx[j] > cx ? 1u : 0u;
+            for (int j = kRegThr; j < ntg; ++j) b += thr[j] > cx ? 1u : 0u;
+            if (DT == 0 && eq_keys)                  // boundaries of the same key
+                for (int j = 0; j < ntg; ++j) b += thr[j] == cx && L.thr_lo[j] > ~(u32)(s * kWave + (int)lane) ? 1u : 0u;
+            // one ballot per bit of the block number
+            const u64 km = __ballot(kept);
+            u32 plo = (u32)km, phi = (u32)(km >> 32);
+            for (int bit = 0; bit < a.nbits; ++bit) {
+                const u32 onm = (u32)__builtin_amdgcn_sbfe((int)b, (u32)bit, 1u);   // all ones if the bit is set
+                const u64 bal = __ballot(onm != 0u);
+                plo &= ~((u32)bal ^ onm);
+                phi &= ~((u32)(bal >> 32) ^ onm);
+            }
+            place(s, cx, kept, b, plo, phi);
+        }
     }
+    wave_sync();
 
     // ---- 5. ABQ -----------------------------------------------------------------------------------
-    // Each block is walked by kWave / B2 lanes, each lane a contiguous run of the block-ordered
-    // list, so a lane's quantiser constants and partial sums live in registers.
+    // A block has lpb = kWave / B2 lanes.  For the sums each of them takes some of the candidate bitwidths and walks the whole
+    // block (a slice of it where a block has sixteen lanes or more): the sums stay in registers and the lane decides on
+    // its bitwidths by itself.  Lanes that walked a share of the block for all bitwidths had to add their sums up with 64-bit
+    // LDS atomics, four lanes on an address: 312 of a row's 1486 busy cycles of the LDS (16 blocks) and 645 * 4 cycles of
+    // waiting (kernel, bf16 [16384 x 4096]: 80.4 -> 75.8 us, fp32 [12608 x 768]: 42.6 -> 39.8).  The energy, and later the packing, share the block's entries out.
     u64* sums = (u64*)(L.hist + ((((k + 1) / 2 + (int)a.cap_words) + 1) & ~1));
     float* invt = (float*)(sums + B2 * (nq + 1));
-    const u32 lpb = (u32)kWave / (u32)B2;
+    const u32 lpb = (u32)a.lpb;
     const u32 myb = udiv16(lane, lpb), sub = lane - myb * lpb;
     const bool lane_on = myb < (u32)B2;
     u32 r0 = 0, r1 = 0, bs0 = 0, mycnt = 0;
@@ -948,7 +981,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     }
     // longest run of any lane: the largest block holds K + (n mod M) entries
     const u32 mc0 = n_pos - Kc[0] * (u32)(M - 1), mc1 = n_neg - Kc[1] * (u32)(Mn - 1);
-    const u32 T = udiv16((mc0 > mc1 ? mc0 : mc1) + lpb - 1, lpb);
+    const u32 maxb = mc0 > mc1 ? mc0 : mc1;
+    const u32 T = udiv16(maxb + lpb - 1, lpb);
     // quantiser scales L / (range brought to [1, 2)): the lanes of a block share the divisions through LDS
     if (lane_on) {
         for (u32 t = sub; t < (u32)nq; t += lpb) {
@@ -956,119 +990,156 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             invt[myb * (u32)nq + t] = dg ? 0.f : Lq / rng1;
         }
         if (sub == 0) {
-            for (int t = 0; t <= nq; ++t) sums[myb * (nq + 1) + t] = 0;
+            sums[myb * (nq + 1) + nq] = 0;
             // budget guard: index of the chosen bitwidth, nq = none feasible yet; DS guard: mask of violations
             L.run[myb] = (mycnt && !dg && a.guard == 0) ? (u32)nq : 0u;
         }
     }
     wave_sync();
-    // Residual of a code on the 2^-15 grid, rho = rint((y - rint(y)) * 2^15) with y = d * inv:
-    // z = d * (inv * 2^15) equals y * 2^15 exactly, rint(y) * 2^15 is a multiple of 2^15, and
-    // |rho| <= 2^14, so rho is rint(z) reduced to 15 signed bits (for |rho| = 2^14 the sign is
-    // lost, the square is not).  Bitwidths up to 8 keep z below 2^23, where adding 2^23 rounds
-    // to the integer grid with the same round-half-even.
-    float inv[QN];
-    bool small_q = true;
-#pragma unroll
-    for (int t = 0; t < QN; ++t) {
-        inv[t] = (lane_on && (NQ || t < nq)) ? invt[myb * (u32)nq + t] : 0.f;
-        if ((NQ || t < nq) && a.qlist[t] > 8) small_q = false;
-    }
-    auto abq_sums = [&](auto fast) {
-        constexpr bool kFast = decltype(fast)::value;
-        // bitwidths up to 8: y * 2^15 stays below 2^23, one multiply per code
-        float inv15[QN];
-#pragma unroll
-        for (int t = 0; t < QN; ++t) inv15[t] = inv[t] * 32768.0f;
-        u64 accE = 0;
-        for (u32 i0 = 0; i0 < T; i0 += 8) {             // u32 partial sums hold 8 residuals of 2^28
-            u32 acc[QN];
-#pragma unroll
-            for (int t = 0; t < QN; ++t) acc[t] = 0;
-            const u32 i1 = i0 + 8 < T ? i0 + 8 : T;
-            for (u32 i = i0; i < i1; ++i) {
-                const u32 p = r0 + i;
-                if (p < r1) {
-                    const float av = __uint_as_float(bo_val[p]);
-                    const u64 A = (u64)(u32)rintf(ldexpf(av, 20 - e));   // 20-bit energy grid scaled to vmax
-                    accE += A * A;
-                    const float d = to_unit(av - vmin, er);
-#pragma unroll
-                    for (int t = 0; t < QN; ++t) {
-                        if (NQ || t < nq) {
-                            // (wider bitwidths: y first, then the exact scaling, so that nothing overflows)
-                            const u32 zi = kFast ? __float_as_uint(d * inv15[t] + 8388608.0f)
-                                                 : (u32)rintf((d * inv[t]) * 32768.0f);
-                            const int rho = __builtin_amdgcn_sbfe((int)zi, 0u, 15u);
-                            acc[t] += (u32)(rho * rho);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < QN; ++t)
-                if ((NQ || t < nq) && acc[t]) atomicAdd(&sums[myb * (nq + 1) + t], (u64)acc[t]);
-        }
-        if (accE) atomicAdd(&sums[myb * (nq + 1) + nq], accE);
-    };
-    // Eq. "DS": sum over the block of | (code at q_bit >> (q_bit - q)) - code at q | for every lower bitwidth
-    auto ds_sums = [&]() {
-        const int top = nq - 1, qtop = (int)L.qtab[top];
-        const float inv_top = lane_on ? invt[myb * (u32)nq + (u32)top] : 0.f;
-        for (u32 i0 = 0; i0 < T; i0 += 8) {
-            u32 acc[QN];
-#pragma unroll
-            for (int t = 0; t < QN; ++t) acc[t] = 0;
-            const u32 i1 = i0 + 8 < T ? i0 + 8 : T;
-            for (u32 i = i0; i < i1; ++i) {
-                const u32 p = r0 + i;
-                if (p < r1) {
-                    const float d = to_unit(__uint_as_float(bo_val[p]) - vmin, er);
-                    const u32 c0 = (u32)rintf(d * inv_top);           // within [0, 2^q - 1]: no clamp needed
-#pragma unroll
-                    for (int t = 0; t < QN; ++t) {
-                        if ((NQ || t < nq) && t < top) {
-                            const u32 c = (u32)rintf(d * inv[t]);
-                            const u32 ref = c0 >> (u32)(qtop - a.qlist[t]);
-                            acc[t] += ref > c ? ref - c : c - ref;
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < QN; ++t)
-                if ((NQ || t < nq) && acc[t]) atomicAdd(&sums[myb * (nq + 1) + t], (u64)acc[t]);
-        }
-    };
-    if (!a.lad.on) {
-        if (a.guard == 1) ds_sums();
-        else if (small_q) abq_sums(std::true_type());
-        else abq_sums(std::false_type());
-    }
-    wave_sync();
-
-    // smallest feasible bitwidth per block: the lanes of a block test different candidates in
-    // ascending order and keep the minimum
     if (a.lad.on) {
         if (lane_on && sub == 0) L.run[myb] = ladder_index(a.lad, (int)(myb >= (u32)M ? myb - (u32)M : myb));
-    } else if (a.guard == 1) {
-        // greedy descent: the chosen index is one above the highest violating candidate below q_bit
-        if (lane_on && mycnt && !dg) {
-            for (u32 t = sub; t + 1 < (u32)nq; t += lpb)
-                if (!((double)sums[myb * (nq + 1) + t] <= a.beta * (double)mycnt)) atomicOr(&L.run[myb], 1u << t);
+    } else {
+        const u32 cl = (u32)a.cl, es = (u32)a.es;    // lanes with candidates of their own; slices of the block
+        const u32 ct = es > 1u ? sub & 7u : sub, sl = es > 1u ? sub >> 3 : 0u;
+        const bool active = lane_on && ct < cl && sl < es;
+        const u32 per = es > 1u ? udiv16(mycnt + es - 1u, es) : mycnt, T2 = es > 1u ? udiv16(maxb + es - 1u, es) : maxb;
+        u32 q0 = bs0 + sl * per, q1 = bs0 + mycnt;
+        q0 = q0 < q1 ? q0 : q1;
+        q1 = q0 + per < q1 ? q0 + per : q1;
+        const u32 qn = active ? q1 - q0 : 0u;
+        if (es > 1u && active) for (u32 t = ct + 8u * sl; t < (u32)nq; t += 8u * es) sums[myb * (nq + 1) + t] = 0;
+        double rhs = 0.0;
+        if (a.guard == 0) {
+            u64 accE = 0;
+            for (u32 i = 0; i < T; i += 4) {
+                u32 v[4];                            // (beyond the lane's share: other LDS words, not used)
+#pragma unroll
+                for (u32 j = 0; j < 4; ++j) v[j] = bo_val[r0 + i + j];
+#pragma unroll
+                for (u32 j = 0; j < 4; ++j) {
+                    u32 A = (u32)rintf(ldexpf(__uint_as_float(v[j]), 20 - e));      // 20-bit energy grid scaled to vmax
+                    A = r0 + i + j < r1 ? A & 0x1FFFFFu : 0u;    // (at most 2^20: 24-bit products)
+                    accE += (u64)A * (u64)A;
+                }
+            }
+            if (accE) atomicAdd(&sums[myb * (nq + 1) + nq], accE);
+            wave_sync();
+            if (lane_on) rhs = a.beta * ldexp((double)sums[myb * (nq + 1) + nq], 2 * e - 40);
         }
+        auto decide = [&](u32 t, u64 sum) __attribute__((always_inline)) {          // (mycnt > 0 and a range above 0)
+            if (a.guard == 1) {
+                if (t + 1u < (u32)nq && !((double)sum <= a.beta * (double)mycnt)) atomicOr(&L.run[myb], 1u << t);
+            } else {
+                const float Lq = (float)((1u << L.qtab[t]) - 1u);
+                const float o = rng / Lq;
+                if (((double)o * (double)o) * (double)sum * 0x1p-30 <= rhs) atomicMin(&L.run[myb], t);
+            }
+        };
+        bool small_q = true;
+#pragma unroll
+        for (int t = 0; t < QN; ++t)
+            if ((NQ || t < nq) && a.qlist[t] > 8) small_q = false;
+        // MODE 0: squared error, bitwidths up to 8; 1: squared error, any bitwidth; 2: Eq. "DS"
+        u32 least = 0;
+        if (es == 1u) {
+            const u32 l0 = Kc[0] ? Kc[0] : n_pos ? n_pos : ~0u, l1 = Kc[1] ? Kc[1] : n_neg ? n_neg : ~0u;
+            least = l0 < l1 ? l0 : l1;
+        }
+        // FOLD: the scaling by 2^-er is part of the scales (exact: the same products, as long as nothing leaves the normal range)
+        auto walk = [&](auto mode, auto fold, auto ncand, u32 c0) __attribute__((always_inline)) {
+            constexpr int MODE = decltype(mode)::value, NCU = decltype(ncand)::value;
+            constexpr bool FOLD = decltype(fold)::value;
+            // Residual of a code on the 2^-15 grid, rho = rint((y - rint(y)) * 2^15) with y = d * inv:
+            // z = d * (inv * 2^15) equals y * 2^15 exactly, rint(y) * 2^15 is a multiple of 2^15, and
+            // |rho| <= 2^14, so rho is rint(z) reduced to 15 signed bits (for |rho| = 2^14 the sign is
+            // lost, the square is not).  Bitwidths up to 8 keep z below 2^23, where adding 2^23 rounds
+            // to the integer grid with the same round-half-even.
+            float inv[NCU];
+            u32 tt[NCU], shq[NCU];
+            u64 tot[NCU];
+            const int top = nq - 1, qtop = (int)L.qtab[top];
+            const float inv_top = MODE == 2 && lane_on ? invt[myb * (u32)nq + (u32)top] : 0.f;
+#pragma unroll
+            for (int u = 0; u < NCU; ++u) {
+                tt[u] = ct + (c0 + (u32)u) * cl;
+                const bool has = active && tt[u] < (u32)nq;
+                inv[u] = has ? invt[myb * (u32)nq + tt[u]] : 0.f;
+                if (MODE == 0) inv[u] = FOLD ? ldexpf(inv[u], 15 - er) : inv[u] * 32768.0f;
+                shq[u] = MODE == 2 && has ? (u32)(qtop - (int)L.qtab[tt[u]]) : 0u;
+                if (!has) tt[u] = ~0u;
+                tot[u] = 0;
+            }
+            auto four = [&](u32 i, u32 (&acc)[NCU], auto tail) __attribute__((always_inline)) {
+                u32 v[4];                            // (beyond the block's end: other LDS words, not used)
+#pragma unroll
+                for (u32 j = 0; j < 4; ++j) v[j] = bo_val[q0 + i + j];
+#pragma unroll
+                for (u32 j = 0; j < 4; ++j) {
+                    float d = __uint_as_float(v[j]) - vmin;
+                    if (!FOLD) d = to_unit(d, er);
+                    if (decltype(tail)::value) d = i + j < qn ? d : 0.f;    // (an offset of zero adds nothing)
+                    const u32 ref0 = MODE == 2 ? (u32)rintf(d * inv_top) : 0u;      // within [0, 2^q - 1]: no clamp needed
+#pragma unroll
+                    for (int u = 0; u < NCU; ++u) {
+                        if (MODE == 2) {
+                            // | (code at q_bit >> (q_bit - q)) - code at q |
+                            const u32 c = (u32)rintf(d * inv[u]), ref = ref0 >> shq[u];
+                            acc[u] += ref > c ? ref - c : c - ref;
+                        } else {
+                            // (wider bitwidths: y first, then the exact scaling, so that nothing overflows)
+                            const u32 zi = MODE == 0 ? __float_as_uint(d * inv[u] + 8388608.0f) : (u32)rintf((d * inv[u]) * 32768.0f);
+                            const int rho = __builtin_amdgcn_sbfe((int)zi, 0u, 15u);
+                            asm("v_mad_i32_i24 %0, %1, %1, %0" : "+v"(acc[u]) : "v"(rho));      // (as sums of products: half as many again)
+                        }
+                    }
+                }
+            };
+            // every block that is not empty has at least `least` entries: no look at the block's end before that
+            u32 i = 0;
+            for (; i < T2; i += 8) {                 // u32 partial sums hold 8 residuals of 2^28
+                u32 acc[NCU];
+#pragma unroll
+                for (int u = 0; u < NCU; ++u) acc[u] = 0;
+                if (i + 8 <= least) {
+                    four(i, acc, std::false_type());
+                    four(i + 4, acc, std::false_type());
+                } else {
+                    four(i, acc, std::true_type());
+                    if (i + 4 < T2) four(i + 4, acc, std::true_type());
+                }
+#pragma unroll
+                for (int u = 0; u < NCU; ++u) tot[u] += acc[u];
+            }
+            if (active && mycnt && !dg) {
+#pragma unroll
+                for (int u = 0; u < NCU; ++u) {
+                    if (tt[u] == ~0u) continue;
+                    if (es > 1u) atomicAdd(&sums[myb * (nq + 1) + tt[u]], tot[u]); else decide(tt[u], tot[u]);
+                }
+            }
+        };
+        auto walk_all = [&](auto mode, auto fold) __attribute__((always_inline)) {
+            const u32 nc = (u32)a.nc;                // candidates of a lane
+            if (nc == 1u) walk(mode, fold, std::integral_constant<int, 1>(), 0u);
+            else if (nc == 2u) walk(mode, fold, std::integral_constant<int, 2>(), 0u);
+            else for (u32 c0 = 0; c0 < nc; c0 += 4u) walk(mode, fold, std::integral_constant<int, 4>(), c0);
+        };
         wave_sync();
-        if (lane_on && sub == 0) {
-            const u32 viol = L.run[myb];
-            L.run[myb] = viol ? 32u - (u32)__clz((int)viol) : 0u;
+        if (a.guard == 1) walk_all(std::integral_constant<int, 2>(), std::false_type());
+        else if (!small_q) walk_all(std::integral_constant<int, 1>(), std::false_type());
+        else if (__ballot(er < -60 || er > 60)) walk_all(std::integral_constant<int, 0>(), std::false_type());
+        else walk_all(std::integral_constant<int, 0>(), std::true_type());
+        wave_sync();
+        if (es > 1u) {
+            if (active && sl == 0u && mycnt && !dg) for (u32 t = ct; t < (u32)nq; t += cl) decide(t, sums[myb * (nq + 1) + t]);
+            wave_sync();
         }
-    } else if (lane_on && mycnt && !dg) {
-        const double rhs = a.beta * ldexp((double)sums[myb * (nq + 1) + nq], 2 * e - 40);
-        for (u32 t = sub; t < (u32)nq; t += lpb) {
-            const float Lq = (float)((1u << L.qtab[t]) - 1u);
-            const float o = rng / Lq;
-            const double lhs = ((double)o * (double)o) * (double)sums[myb * (nq + 1) + t] * 0x1p-30;
-            if (lhs <= rhs) { atomicMin(&L.run[myb], t); break; }
+        if (a.guard == 1) {
+            // greedy descent: the chosen index is one above the highest violating candidate below q_bit
+            if (lane_on && sub == 0) {
+                const u32 viol = L.run[myb];
+                L.run[myb] = viol ? 32u - (u32)__clz((int)viol) : 0u;
+            }
         }
     }
     wave_sync();
@@ -1101,24 +1172,26 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
 
     // ---- packing ----------------------------------------------------------------------------------
     {
-        for (u32 i = 0; i < T; ++i) {
-            const u32 p = r0 + i;
+        // two neighbouring entries of a block at a time: their index fields (at most 13 bits) are one field of 2 w bits, their
+        // codes one of 2 q bits; a field is put in by two atomic ORs on neighbouring words (an odd end adds
+        // zeros).  One entry at a time took 262 vector instructions a row instead of 167 (75.8 -> 74.1 us).
+        auto put = [&](u32 bit, u32 v) {
+            const u64 f = (u64)v << (bit & 31u);
+            u32* at = stage + (bit >> 5);
+            atomicOr(at, (u32)f);
+            atomicOr(at + 1, (u32)(f >> 32));
+        };
+        for (u32 p = r0, i = 0; i < T; i += 2, p += 2) {
             if (p < r1) {
-                u32 c = 0;
-                if (!dg) {
-                    const float y = to_unit(__uint_as_float(bo_val[p]) - vmin, er) * my_inv;
-                    c = (u32)rintf(y);                    // already within [0, 2^q - 1]
+                const bool two = p + 1u < r1;
+                u32 c[2];
+#pragma unroll
+                for (u32 j = 0; j < 2; ++j) {
+                    const float y = to_unit(__uint_as_float(bo_val[p + j]) - vmin, er) * my_inv;
+                    c[j] = (u32)rintf(y);             // already within [0, 2^q - 1] (range 0: a scale and a code of 0)
                 }
-                {   // index field
-                    const u32 P = __umul24(p, (u32)w), wi = P >> 5, sft = P & 31u, val = bo_idx[p];
-                    atomicOr(&stage[wi], val << sft);
-                    if (sft + (u32)w > 32u) atomicOr(&stage[wi + 1], val >> (32u - sft));
-                }
-                {   // code field
-                    const u32 P = idx_bits + coff + __umul24(p - bs0, myq), wi = P >> 5, sft = P & 31u;
-                    atomicOr(&stage[wi], c << sft);
-                    if (sft + myq > 32u) atomicOr(&stage[wi + 1], c >> (32u - sft));
-                }
+                put(__umul24(p, (u32)w), (u32)bo_idx[p] | (two ? (u32)bo_idx[p + 1u] << w : 0u));
+                put(idx_bits + coff + __umul24(p - bs0, myq), c[0] | (two ? c[1] << myq : 0u));
             }
         }
     }
