@@ -145,8 +145,9 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     const int64_t margin = std::max<int64_t>(64, row_len / (dt == SLICER_F32 ? 16 : 32));  // room for the undecided coarse bin
     const int64_t cap = std::min<int64_t>(1984, (p.k + margin + 63) / 64 * 64);   // ranks are 11-bit fields
     const bool lists_fit = B2_all <= kWave && p.k + 64 <= cap;
-    const int64_t region0 = lists_fit ? small_region0_words(p.k, p.cap_words, B2_all, nq, (int)cap) : 0;
-    const int maxs = cap <= 640 ? 10 : cap <= 1280 ? 20 : 0;             // list held in registers
+    const int maxs = cap <= 256 ? 4 : cap <= 640 ? 10 : cap <= 1280 ? 20 : 0;             // list held in registers
+    const int64_t region0 = lists_fit ? small_region0_words(p.k, p.cap_words, B2_all, nq, (int)cap, small_fine_bins(maxs)) : 0;
+    const int64_t wg_region0 = lists_fit ? small_region0_words(p.k, p.cap_words, B2_all, nq, (int)cap, kFineBins) : 0;
     const int64_t small_lds = lists_fit ? 4 * (int64_t)small_lds_words(dt, (int)cap, (int)region0, B2_all, maxs) : 0;
     auto small_holds = [&](int64_t elements) { return lists_fit && elements <= (dt == SLICER_F32 ? 4096 : 8192) && small_lds <= 64 * 1024; };
     if (small_holds(span)) {
@@ -163,7 +164,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     // it is the faster kernel at every batch size (16384 rows of 8192: 238 against 293 us; 4096 rows of 6144:
     // 68 against 74 us); at 4096 elements and below one wavefront per row wins (115 against 189 us).
     p.wg_ept = 0; p.wg_nw = 0; p.wg_cap = 0; p.wg_region0 = 0; p.wg_lds_bytes = 0;
-    const int64_t wg_lds = lists_fit ? 4 * (int64_t)wg_lds_words(dt, (int)cap, (int)region0, B2_all) : 0;
+    const int64_t wg_lds = lists_fit ? 4 * (int64_t)wg_lds_words(dt, (int)cap, (int)wg_region0, B2_all) : 0;
     auto wg_holds = [&](int64_t elements) {
         return lists_fit && elements > 4096 && elements <= (dt == SLICER_F32 ? 16384 : 32768) && wg_lds <= 64 * 1024;
     };
@@ -174,7 +175,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
         p.wg_nw = rows <= 128 ? 16 : 4;
         const int64_t chunks = ((span + epc - 1) / epc + 64 * p.wg_nw - 1) / (64 * p.wg_nw);     // 16-byte chunks per thread
         p.wg_ept = (int)(chunks <= 1 ? 1 : chunks <= 2 ? 2 : chunks <= 4 ? 4 : chunks <= 8 ? 8 : 16);    // (kept as a chunk count)
-        p.wg_cap = (int)cap; p.wg_region0 = (int)region0; p.wg_lds_bytes = (int)wg_lds;
+        p.wg_cap = (int)cap; p.wg_region0 = (int)wg_region0; p.wg_lds_bytes = (int)wg_lds;
     }
 
     // Long rows: every pass is spread over many workgroups (slicer_encode_large.hpp).  A row that starts or ends

@@ -81,6 +81,9 @@ constexpr u32 kHintSlack = 120;
 constexpr int kCoarseBits = 11;
 constexpr int kCoarseBins = 1 << kCoarseBits;
 constexpr int kFineBins = 1024;
+// Fine bins of the one-wavefront kernel: lists of up to 256 entries need fewer of them (fp32 [12608 x 768], 115 kept: kernel
+// 37.7 us with 1024 bins, 36.9 with 512, 38.6 with 256, where the bins fill up).
+__host__ __device__ constexpr int small_fine_bins(int maxs) { return maxs == 4 ? 512 : kFineBins; }
 
 // LDS carve-up of one wave (word offsets); small_lds_words() on the host must match.
 // The coarse histogram (2048 16-bit counters) overlays everything: nothing else is live before the
@@ -103,11 +106,11 @@ struct SmallLds {
 
 // words of region 0: the row's bit mask (at most 2 * 128 words) and list positions, then the fine histogram, then indices +
 // stream image + sums + scales
-__host__ __device__ inline int small_region0_words(int64_t k, u64 cap_words, int B2, int nq, int cap)
+__host__ __device__ inline int small_region0_words(int64_t k, u64 cap_words, int B2, int nq, int cap, int bins)
 {
     const int64_t late = (((k + 1) / 2 + (int64_t)cap_words + 1) & ~(int64_t)1) + 2 * B2 * (nq + 1) + B2 * nq;
     const int64_t early = 2 * 128 + 4 + cap / 2;
-    int64_t r0 = late > kFineBins + 1 ? late : kFineBins + 1;
+    int64_t r0 = late > bins + 1 ? late : bins + 1;
     r0 = r0 > early ? r0 : early;
     return (int)((r0 + 3) & ~(int64_t)3);
 }
@@ -181,6 +184,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     constexpr int QN = NQ ? NQ : kMaxQ;
     constexpr int EPC = DT == 0 ? 4 : 8;            // elements per 16-byte chunk
     constexpr int NCH = EPL / EPC;                  // chunks per lane
+    constexpr int FB = small_fine_bins(MAXS);
     extern __shared__ u32 smem[];
 
     const u32 lane = lane_id();
@@ -654,7 +658,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     {
         uint4* h4 = (uint4*)L.hist;
 #pragma unroll
-        for (int i = 0; i < kFineBins / 4 / kWave; ++i) h4[i * kWave + lane] = make_uint4(0, 0, 0, 0);
+        for (int i = 0; i < FB / 4 / kWave; ++i) h4[i * kWave + lane] = make_uint4(0, 0, 0, 0);
     }
     if (lane == 0) {
 #pragma unroll
@@ -664,22 +668,25 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     wave_sync();
 
     // ---- 3. fine bins ---------------------------------------------------------------------
-    // 1024 bins, linear in (key - t_lo) >> sh; sh from the row's largest key.  A bin's word counts the positive class
+    // FB bins, linear in (key - t_lo) >> sh; sh from the row's largest key.  A bin's word counts the positive class
     // in its high half and the negative one in its low half; after the scan the halves are the places in S where the bin's
     // members of the class go, and adding an entry moves them on: in the end they are the ends of the bin's places, which
     // begin where those of the bin above end.
     const int nslots = (int)((nL + kWave - 1) / kWave);
     const u32 range = kmax > t_lo ? kmax - t_lo : 0u;
-    const int sh = range < (u32)kFineBins ? 0 : (32 - __clz((int)range)) - 10;
+    const int sh = range < (u32)FB ? 0 : (32 - __clz((int)range)) - (FB == 512 ? 9 : 10);
     auto in_list = [&](int s) -> bool { return (int)lane < (int)nL - s * kWave; };      // this lane has an entry in slot s
     auto key_bin = [&](u32 key) -> u32 { return (key - t_lo) >> sh; };
+    // Place of a bin's word.  A lane scans 16 consecutive bins of 1024 in four 16-byte pieces; lanes four apart would meet on
+    // the same banks, so the pieces of every fourth lane are swapped (bf16 [16384 x 4096] kernel 68.3 -> 67.6 us).
+    auto bin_word = [](u32 b) -> u32 { return b ^ ((b >> 4) & (FB == 512 ? 4u : 12u)); };
     auto half_of = [](u32 e) -> u32 { return (e >> 27) & 16u; };                     // shift of the class's half
     u32 b4[MAXS ? MAXS : 1];                        // byte offset of the entry's bin
 #pragma unroll(MAXS ? MAXS : 1)
     for (int s = 0; s < SLN; ++s) {
         if (s >= nslots) break;
         if (in_list(s)) {
-            const u32 e = ent_word(s), at = key_bin(word_key(e)) << 2;
+            const u32 e = ent_word(s), at = bin_word(key_bin(word_key(e))) << 2;
             if (MAXS) b4[MAXS ? s : 0] = at;
             lds_inc(at, 1u << half_of(e));
         }
@@ -687,14 +694,15 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     wave_sync();
     u32 nLp, n_pos, n_neg;                          // positive entries of the list; class sizes of the kept set
     int cut_lane = 0;
-    constexpr int BPL = kFineBins / kWave;          // bins per lane, from the top
+    constexpr int BPL = FB / kWave;          // bins per lane, from the top
     {
-        const int hi = kFineBins - (int)lane * BPL;
+        const int hi = FB - (int)lane * BPL;
         u32 cs[BPL];
         uint4* h4 = (uint4*)(L.hist + hi - BPL);
+        auto piece = [&](int j) -> int { return j ^ (((hi - BPL) >> 6) & (FB == 512 ? 1 : 3)); };
 #pragma unroll
         for (int j = 0; j < BPL / 4; ++j) {
-            const uint4 t = h4[BPL / 4 - 1 - j];
+            const uint4 t = h4[piece(BPL / 4 - 1 - j)];
             cs[4 * j + 0] = t.w; cs[4 * j + 1] = t.z; cs[4 * j + 2] = t.y; cs[4 * j + 3] = t.x;
         }
         u32 local = 0;                              // (the list has fewer than 2048 entries: the halves never carry)
@@ -716,8 +724,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             acc += cs[j];
         }
 #pragma unroll
-        for (int j = 0; j < BPL / 4; ++j) h4[BPL / 4 - 1 - j] = make_uint4(o[4 * j + 3], o[4 * j + 2], o[4 * j + 1], o[4 * j + 0]);
-        if (lane == 0) L.hist[kFineBins] = nLp;     // the bin above all others ends where the classes begin
+        for (int j = 0; j < BPL / 4; ++j) h4[piece(BPL / 4 - 1 - j)] = make_uint4(o[4 * j + 3], o[4 * j + 2], o[4 * j + 1], o[4 * j + 0]);
+        if (lane == 0) L.hist[FB] = nLp;     // the bin above all others ends where the classes begin
         if (lane < 4u) L.S[nL + lane] = 0;          // (read behind the last entry by the loops that take four at a time)
     }
     wave_sync();
@@ -726,7 +734,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         if (s >= nslots) break;
         if (in_list(s)) {
             const u32 e = ent_word(s), hf = half_of(e);
-            const u32 old = lds_add(MAXS ? b4[MAXS ? s : 0] : key_bin(word_key(e)) << 2, 1u << hf);
+            const u32 old = lds_add(MAXS ? b4[MAXS ? s : 0] : bin_word(key_bin(word_key(e))) << 2, 1u << hf);
             const u32 at = __builtin_amdgcn_ubfe(old, hf, 16u);
             L.S[at] = e;
             if (DT == 0) L.Sp[at] = (uint16_t)(s * kWave + (int)lane);
@@ -762,11 +770,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     bool eq_keys = false;                           // fp32: equal keys on both sides of the cut or of a boundary: the low words decide
     if (nL > (u32)k) {
         // open the bins of the lane found by the scan: the first one that ends behind rank k-1
-        const int hi = kFineBins - cut_lane * BPL;
-        const u32 wj = lane < (u32)BPL ? L.hist[hi - 1 - (int)lane] : 0u;
+        const int hi = FB - cut_lane * BPL;
+        const u32 wj = lane < (u32)BPL ? L.hist[bin_word((u32)hi - 1u - lane)] : 0u;
         const u64 mj = __ballot(lane < (u32)BPL && (wj >> 16) + (wj & 0xFFFFu) - nLp > (u32)(k - 1));
         const int fj = (int)__builtin_ctzll(mj), lo = hi - 1 - fj;
-        const u32 wd = bcast(wj, fj), wu = (u32)__builtin_amdgcn_readfirstlane((int)L.hist[lo + 1]);
+        const u32 wd = bcast(wj, fj), wu = (u32)__builtin_amdgcn_readfirstlane((int)L.hist[bin_word((u32)lo + 1u)]);
         const u32 sp = wu >> 16, sn = wu & 0xFFFFu, cp = (wd >> 16) - sp, cnt = cp + (wd & 0xFFFFu) - sn;
         const u32 rem = (u32)(k - 1) - (sp + sn - nLp);
         u32 kp, kn;                                 // members that stay
@@ -814,8 +822,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         const u32 R = act ? j * K - 1u + (cls ? nLp : 0u) : 0u;         // its place
         const u32 bin = act ? key_bin(word_key(L.S[R])) : 0u;
         const u32 hf = cls ? 0u : 16u;
-        const u32 st = __builtin_amdgcn_ubfe(L.hist[bin + 1u], hf, 16u);
-        const u32 cn = act ? __builtin_amdgcn_ubfe(L.hist[bin], hf, 16u) - st : 0u, rem = R - st;
+        const u32 st = __builtin_amdgcn_ubfe(L.hist[bin_word(bin + 1u)], hf, 16u);
+        const u32 cn = act ? __builtin_amdgcn_ubfe(L.hist[bin_word(bin)], hf, 16u) - st : 0u, rem = R - st;
         if (mine && !act && sub == 0) { thr[t] = cls ? kMag : ~0u; if (DT == 0) L.thr_lo[t] = ~0u; }
         bool eq = DT == 0 && mine && !act && (cls ? n_neg : n_pos) > 0u;
         if (cn <= kWide) {

@@ -11,7 +11,8 @@ void launch_small_epl(const SmallArgs& sa, const SmallLaunch& p, hipStream_t st)
 {
     const dim3 g((unsigned)xcd_grid(sa.R)), b(kWave);
     const size_t lds = (size_t)p.lds_bytes;
-    if (p.maxs == 10) hipLaunchKernelGGL((enc_small_kernel<DT, EPL, NQ, 10, ASYM>), g, b, lds, st, sa);
+    if (p.maxs == 4) hipLaunchKernelGGL((enc_small_kernel<DT, EPL, NQ, 4, ASYM>), g, b, lds, st, sa);
+    else if (p.maxs == 10) hipLaunchKernelGGL((enc_small_kernel<DT, EPL, NQ, 10, ASYM>), g, b, lds, st, sa);
     else if (p.maxs == 20) hipLaunchKernelGGL((enc_small_kernel<DT, EPL, NQ, 20, ASYM>), g, b, lds, st, sa);
     else hipLaunchKernelGGL((enc_small_kernel<DT, EPL, NQ, 0, ASYM>), g, b, lds, st, sa);
 }
