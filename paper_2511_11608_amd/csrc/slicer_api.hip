@@ -400,8 +400,9 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         for (int t = 0; t < kMaxQ; ++t) sa.qlist[t] = ea.qlist[t];
         sa.beta = distortion_budget;
         sa.cap_words = p.cap_words;
-        sa.row_words = ea.row_words; sa.slots = ea.slots;
+        sa.row_words = ea.row_words; sa.row_words32 = nullptr; sa.slots = ea.slots;
         sa.fallback = (u32*)(ws + p.off_fallback);
+        sa.stream = nullptr; sa.meta = meta; sa.bit_set = bit_set;
         sa.mv = ea.mv;
         sa.cap = p.wg_cap; sa.region0_words = p.wg_region0;
         sa.lad = lad;
@@ -415,16 +416,17 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
         ea.only_flagged = sa.fallback;
     }
-    if (!use_wg && p.small_epl && on_elements) {
-        // fast path; rows it cannot hold are flagged and redone by the generic kernel
+    const bool use_small = !use_wg && p.small_epl && on_elements;
+    if (use_small) {                                // one wavefront per row, whatever the row holds
         SmallArgs sa;
         sa.x = x; sa.R = rows; sa.N = row_len; sa.k = p.k;
         sa.M = n_blocks; sa.Mn = n_blocks_neg; sa.w = p.w; sa.nq = ea.nq;
         for (int t = 0; t < kMaxQ; ++t) sa.qlist[t] = ea.qlist[t];
         sa.beta = distortion_budget;
         sa.cap_words = p.cap_words;
-        sa.row_words = ea.row_words; sa.slots = ea.slots;
-        sa.fallback = (u32*)(ws + p.off_fallback);
+        sa.row_words = nullptr; sa.row_words32 = (u32*)(ws + p.off_row_words); sa.slots = ea.slots;
+        sa.fallback = nullptr;
+        sa.stream = rows == 1 ? (u32*)stream : nullptr; sa.meta = meta; sa.bit_set = bit_set;
         sa.mv = ea.mv;
         sa.cap = p.small_cap; sa.region0_words = p.small_region0;
         sa.lad = lad;
@@ -437,7 +439,7 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         const SmallLaunch sl = { p.small_epl, p.small_lds_bytes, p.small_maxs };
         SLICER_HIP(dt == SLICER_F32 ? launch_small_any<0>(sa, sl, asym, st) : launch_small_any<1>(sa, sl, asym, st));
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
-        ea.only_flagged = sa.fallback;
+        if (rows == 1) return SLICER_OK;
     }
     FinishArgs fa;
     fa.R = rows; fa.N = row_len; fa.k = p.k;
@@ -452,8 +454,9 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     fa.stream = (u32*)stream;
     fa.meta = meta;
     fa.mv = ea.mv;
-    bool done = false;                              // every row is in its slot
-    if (!asym && !ea.only_flagged && p.large_S && on_elements) {
+    fa.row_words32 = (const u32*)(ws + p.off_row_words);
+    bool done = use_small;                          // every row is in its slot
+    if (!done && !asym && !ea.only_flagged && p.large_S && on_elements) {
         // long rows: stages of many workgroups per row; rows they cannot hold are redone by the generic encoder inside the third one
         LargeArgs la;
         la.x = x; la.R = rows; la.N = row_len; la.k = p.k;
@@ -522,21 +525,35 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     const u64 grid = (u64)xcd_grid((int64_t)(((u64)rows * (u64)fa.chunks_per_row + 3) / 4));     // four wavefronts per workgroup
     if (grid >= (1ull << 31)) return SLICER_EINVAL;
     if (rows <= kScanRows) {        // small batches: repair, offsets, header and gather in one launch
-        if (dt == SLICER_F32) hipLaunchKernelGGL((enc_finish_small_kernel<0>), dim3((unsigned)grid), dim3(kScanRows), 0, st, ea, fa);
-        else hipLaunchKernelGGL((enc_finish_small_kernel<1>), dim3((unsigned)grid), dim3(kScanRows), 0, st, ea, fa);
+        if (use_small) hipLaunchKernelGGL((enc_finish_small_kernel<0, false>), dim3((unsigned)grid), dim3(kScanRows), 0, st, ea, fa);
+        else if (dt == SLICER_F32) hipLaunchKernelGGL((enc_finish_small_kernel<0, true>), dim3((unsigned)grid), dim3(kScanRows), 0, st, ea, fa);
+        else hipLaunchKernelGGL((enc_finish_small_kernel<1, true>), dim3((unsigned)grid), dim3(kScanRows), 0, st, ea, fa);
+        hipError_t e1 = hipGetLastError();
+        return e1 == hipSuccess ? SLICER_OK : hip_fail(e1);
+    }
+    if (use_small && rows <= kJoinRows) {
+        // rows per wavefront: enough workgroups for every CU first, then fewer of them, each of which adds up all counts before its rows
+        const int rpw = rows <= 4096 ? 1 : rows <= 8192 ? 2 : 4;
+        const dim3 gj((unsigned)xcd_grid((rows + 8 * rpw - 1) / (8 * rpw))), bj(kJoinThreads);
+        if (rpw == 1) hipLaunchKernelGGL((enc_join_kernel<1>), gj, bj, 0, st, fa);
+        else if (rpw == 2) hipLaunchKernelGGL((enc_join_kernel<2>), gj, bj, 0, st, fa);
+        else hipLaunchKernelGGL((enc_join_kernel<4>), gj, bj, 0, st, fa);
         hipError_t e1 = hipGetLastError();
         return e1 == hipSuccess ? SLICER_OK : hip_fail(e1);
     }
     const dim3 gscan((unsigned)((rows + kScanRows - 1) / kScanRows));
-    if (!ea.only_flagged)
-        hipLaunchKernelGGL(enc_rowscan_kernel, gscan, dim3(kScanRows), 0, st, fa);
+    if (use_small)
+        hipLaunchKernelGGL((enc_rowscan_kernel<true>), gscan, dim3(kScanRows), 0, st, fa);
+    else if (!ea.only_flagged)
+        hipLaunchKernelGGL((enc_rowscan_kernel<false>), gscan, dim3(kScanRows), 0, st, fa);
     else if (dt == SLICER_F32)      // rows a fast path flagged are redone here, just before the scan of their chunk
         hipLaunchKernelGGL((enc_fix_rowscan_kernel<0>), gscan, dim3(kScanRows), 0, st, ea, fa);
     else
         hipLaunchKernelGGL((enc_fix_rowscan_kernel<1>), gscan, dim3(kScanRows), 0, st, ea, fa);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e);
-    hipLaunchKernelGGL(enc_gather_kernel, dim3((unsigned)grid), dim3(256), 0, st, fa);
+    if (use_small) hipLaunchKernelGGL((enc_gather_kernel<true>), dim3((unsigned)grid), dim3(256), 0, st, fa);
+    else hipLaunchKernelGGL((enc_gather_kernel<false>), dim3((unsigned)grid), dim3(256), 0, st, fa);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e);
     return SLICER_OK;
@@ -698,9 +715,9 @@ int slicer_encode_csr(const void* x, slicer_dtype dt, int64_t instances, int64_t
     fa.row_words = ca.row_words;
     fa.row_off_local = (u64*)(ws + c.flat.off_row_local);
     fa.chunk_tot = (u64*)(ws + c.flat.off_chunk_tot);
-    fa.slots = nullptr; fa.cap_words = c.cap_words; fa.chunks_per_row = 1;
+    fa.row_words32 = nullptr; fa.slots = nullptr; fa.cap_words = c.cap_words; fa.chunks_per_row = 1;
     fa.stream = (u32*)stream; fa.meta = meta; fa.mv = ca.mv;
-    hipLaunchKernelGGL(enc_rowscan_kernel, dim3((unsigned)((instances + kScanRows - 1) / kScanRows)), dim3(kScanRows), 0, st, fa);
+    hipLaunchKernelGGL((enc_rowscan_kernel<false>), dim3((unsigned)((instances + kScanRows - 1) / kScanRows)), dim3(kScanRows), 0, st, fa);
     hipLaunchKernelGGL(csr_repack_kernel, dim3((unsigned)((u64)instances * nwin)), dim3(256), 0, st, ca);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SLICER_OK : hip_fail(e);

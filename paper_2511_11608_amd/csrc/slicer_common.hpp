@@ -48,6 +48,21 @@ __host__ __device__ inline MetaView meta_view(void* meta, int64_t R, int B2)
     return v;
 }
 
+// one lane writes the header of the meta block (format v1) and zeroes the padding after the last array
+__device__ inline void write_header(void* meta, int dt, int M, int Mn, int64_t R, int64_t N, int64_t k, u32 bit_set, int w, u64 total)
+{
+    u32* h32 = (u32*)meta;
+    u64* h64 = (u64*)meta;
+    h32[0] = kMagic; h32[1] = kVersion; h32[2] = (u32)dt; h32[3] = (u32)M;
+    h64[2] = (u64)R; h64[3] = (u64)N; h64[4] = (u64)k;
+    h32[10] = bit_set; h32[11] = (u32)w;
+    h64[6] = total;
+    h32[14] = Mn != M ? (u32)Mn : 0u;              // 0: the negative class has M blocks too
+    h32[15] = 0;
+    uint8_t* m8 = (uint8_t*)meta;
+    for (size_t o = kHeaderBytes + 16 * (size_t)R + 9 * (size_t)R * (M + Mn); o < meta_bytes(R, M + Mn); ++o) m8[o] = 0;
+}
+
 // ---- fixed multi-level mode (Sec. 4.1: Q = [q_1 > ... > q_M]) --------------------------------
 // Block m of either sign class takes the bitwidth qlist[index(m)]; four bits per block.
 struct Ladder {

@@ -647,6 +647,7 @@ struct FinishArgs {
     int M, Mn, w, dt;
     u32 bit_set;
     const u64* row_words;   // [R]
+    const u32* row_words32; // [R] the same from the one-wavefront kernel (which leaves no row to be redone)
     u64* row_off_local;     // [R]  offset of the row inside its chunk of kScanRows rows
     u64* chunk_tot;         // [ceil(R / kScanRows)]
     const u32* slots;
@@ -657,6 +658,11 @@ struct FinishArgs {
     MetaView mv;
 };
 
+// W32: the rows come from the one-wavefront kernel
+template <bool W32>
+__device__ inline u64 finish_words(const FinishArgs& a, int64_t r) { return W32 ? (u64)a.row_words32[r] : a.row_words[r]; }
+
+template <bool W32>
 __device__ inline void rowscan_chunk(const FinishArgs& a)
 {
     __shared__ u64 s_part[kScanRows / kWave];
@@ -664,7 +670,7 @@ __device__ inline void rowscan_chunk(const FinishArgs& a)
     const u32 lane = lane_id();
     const int wid = tid / kWave;
     const int64_t i = (int64_t)blockIdx.x * kScanRows + tid;
-    const u64 v = i < a.R ? a.row_words[i] : 0ull;
+    const u64 v = i < a.R ? finish_words<W32>(a, i) : 0ull;
     u64 inc = v;
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
@@ -683,9 +689,10 @@ __device__ inline void rowscan_chunk(const FinishArgs& a)
     if (tid == 0) a.chunk_tot[blockIdx.x] = tot;
 }
 
+template <bool W32>
 __global__ __launch_bounds__(kScanRows) void enc_rowscan_kernel(FinishArgs a)
 {
-    rowscan_chunk(a);
+    rowscan_chunk<W32>(a);
 }
 
 // The same scan, preceded by the generic encoder for the rows of this chunk that a fast
@@ -697,33 +704,20 @@ __global__ __launch_bounds__(kScanRows) void enc_fix_rowscan_kernel(EncArgs ea, 
     const int64_t r0 = (int64_t)blockIdx.x * kScanRows;
     enc_generic_rows<DT, kScanRows>(ea, r0, r0 + kScanRows < ea.R ? r0 + kScanRows : ea.R, sh);
     __syncthreads();
-    rowscan_chunk(a);
+    rowscan_chunk<false>(a);
 }
 
-// one lane writes the header of the meta block (format v1) and zeroes the padding after the last array
-__device__ inline void write_header(const FinishArgs& a, u64 total)
-{
-    u32* h32 = (u32*)a.meta;
-    u64* h64 = (u64*)a.meta;
-    h32[0] = kMagic; h32[1] = kVersion; h32[2] = (u32)a.dt; h32[3] = (u32)a.M;
-    h64[2] = (u64)a.R; h64[3] = (u64)a.N; h64[4] = (u64)a.k;
-    h32[10] = a.bit_set; h32[11] = (u32)a.w;
-    h64[6] = total;
-    h32[14] = a.Mn != a.M ? (u32)a.Mn : 0u;        // 0: the negative class has M blocks too
-    h32[15] = 0;
-    uint8_t* m8 = (uint8_t*)a.meta;
-    for (size_t o = kHeaderBytes + 16 * (size_t)a.R + 9 * (size_t)a.R * (a.M + a.Mn); o < meta_bytes(a.R, a.M + a.Mn); ++o) m8[o] = 0;
-}
+__device__ inline void write_header(const FinishArgs& a, u64 total) { write_header(a.meta, a.dt, a.M, a.Mn, a.R, a.N, a.k, a.bit_set, a.w, total); }
 
 // One wavefront copies words [c * kGatherWords, (c + 1) * kGatherWords) of row r's slot to the stream.  Bound by the
 // latency of dependent loads: eight words per lane are in flight (bf16 [16384 x 4096]: 9.5 -> 8.1 us),
 // and the first ones are on their way while offset() finds where they go.  Segments of up to 128 words, which short
 // rows have, skip the rest of the eight (fp32 [12608 x 768], 84 words a row: 6.6 us with all eight tests).
 template <class F>
-__device__ inline void gather_item(const FinishArgs& a, int64_t r, u64 c, F offset)
+__device__ inline void gather_item(const FinishArgs& a, int64_t r, u64 nw, u64 c, F offset)
 {
     const u32 lane = lane_id();
-    const u64 nw = a.row_words[r], j0 = c * (u64)kGatherWords;
+    const u64 j0 = c * (u64)kGatherWords;
     const u32 n = j0 >= nw ? 0u : nw - j0 < (u64)kGatherWords ? (u32)(nw - j0) : (u32)kGatherWords;
     const u32* __restrict__ src = a.slots + (size_t)r * a.cap_words + j0;
     u32 t[8];
@@ -748,6 +742,7 @@ __device__ inline void gather_item(const FinishArgs& a, int64_t r, u64 c, F offs
     }
 }
 
+template <bool W32>
 __global__ __launch_bounds__(256) void enc_gather_kernel(FinishArgs a)
 {
     // one wavefront per (row, kGatherWords-word chunk of its slot); no workgroup barrier
@@ -762,7 +757,7 @@ __global__ __launch_bounds__(256) void enc_gather_kernel(FinishArgs a)
         c = (u64)(item % a.chunks_per_row);
     }
     if (r >= a.R) return;
-    gather_item(a, r, c, [&]() -> u64 {
+    gather_item(a, r, finish_words<W32>(a, r), c, [&]() -> u64 {
         const int64_t my_chunk = r / kScanRows;
         const int64_t n_chunks = (a.R + kScanRows - 1) / kScanRows;
         const bool want_total = item == 0;           // this wave also writes the header
@@ -786,28 +781,95 @@ __global__ __launch_bounds__(256) void enc_gather_kernel(FinishArgs a)
     });
 }
 
+// Rows of the one-wavefront kernel in batches of more than kScanRows and up to kJoinRows: offsets, header and copy in ONE
+// launch.  A workgroup owns 8 * RPW consecutive rows (RPW to a wavefront) and adds up the word counts of all rows before them
+// itself, 4 bytes a row from the L2, while the first 256 words of its rows are on their way.  A scan kernel before the copy
+// costs a launch (encode of bf16 [16384 x 4096] 80.1 -> 76.6 us, of fp32 [12608 x 768] 43.5 -> 39.2).  With many more rows the
+// sums cost more than the launch: all counts before a workgroup's rows, 64 KB on average at the limit.
+constexpr int kJoinThreads = 512, kJoinRows = 32768;
+
+template <int RPW>
+__global__ __launch_bounds__(kJoinThreads) void enc_join_kernel(FinishArgs a)
+{
+    constexpr int NWV = kJoinThreads / kWave, ROWS = NWV * RPW, NB = 4;     // NB * 64 words of a row in flight
+    __shared__ u32 s_before[NWV], s_own[NWV];
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const u32 lane = lane_id();
+    const int64_t R = a.R, wgs = (R + ROWS - 1) / ROWS;
+    const int64_t wg = xcd_row((int64_t)blockIdx.x, wgs);       // neighbouring rows stay on one XCD
+    if (wg >= wgs) return;
+    const int64_t r0 = wg * ROWS, rw = r0 + wv * RPW;
+    const u32 cap = (u32)a.cap_words;
+    u32 nw[RPW], t[RPW][NB], own = 0;
+#pragma unroll
+    for (int u = 0; u < RPW; ++u) {
+        nw[u] = rw + u < R ? a.row_words32[rw + u] : 0u;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const u32 i = (u32)(j * kWave) + lane;
+            t[u][j] = rw + u < R && i < cap ? a.slots[(size_t)(rw + u) * cap + i] : 0u;      // (the whole slot is there, not only the row's words)
+        }
+    }
+    u32 before = 0;
+    for (int64_t i = (int64_t)tid * 4; i < r0; i += kJoinThreads * 4) {     // r0 is a multiple of four
+        const uint4 v = *(const uint4*)(a.row_words32 + i);
+        before += (v.x + v.y) + (v.z + v.w);
+    }
+#pragma unroll
+    for (int u = 0; u < RPW; ++u) own += nw[u];
+    before = wave_sum(before);
+    if (lane == 0) { s_before[wv] = before; s_own[wv] = own; }
+    __syncthreads();
+    u32 off = 0, total = 0;                          // (fewer than 2^32 words: kJoinRows rows of at most 1740)
+#pragma unroll
+    for (int i = 0; i < NWV; ++i) {
+        const u32 b = s_before[i], o = s_own[i];
+        total += b + o;
+        off += b + (i < wv ? o : 0u);
+    }
+#pragma unroll
+    for (int u = 0; u < RPW; ++u) {
+        if (rw + u >= R) break;
+        u32* __restrict__ dst = a.stream + off;
+        const u32* __restrict__ src = a.slots + (size_t)(rw + u) * cap;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const u32 i = (u32)(j * kWave) + lane;
+            if (i < nw[u]) dst[i] = t[u][j];
+        }
+        for (u32 i = (u32)(NB * kWave) + lane; i < nw[u]; i += kWave) dst[i] = src[i];
+        if (lane == 0) a.mv.row_off[rw + u] = off;
+        off += nw[u];
+    }
+    if (r0 + ROWS >= R && tid == 0) write_header(a, total);
+}
+
 // Batches of up to kScanRows rows (one decode step, one feature map, a batch of long rows): repair, row
 // offsets, header and gather in ONE launch.  Every workgroup scans the (at most 256) word counts itself and
 // copies its share of the slots.  If a fast path flagged any row, which is rare, workgroup 0 alone redoes
 // those rows with the generic encoder and then copies every row; the others leave at once.
-template <int DT>
+// FIX = false: the rows come from the one-wavefront kernel, which flags none.
+template <int DT, bool FIX>
 __global__ __launch_bounds__(kScanRows) void enc_finish_small_kernel(EncArgs ea, FinishArgs a)
 {
-    __shared__ GenericLds<kScanRows> sh;
     __shared__ u64 s_off[kScanRows + 1];
     __shared__ u64 s_wave[kScanRows / kWave];
     const int tid = threadIdx.x, wid = tid / kWave;
     const u32 lane = lane_id();
     bool alone = false;
-    u64 v = tid < a.R ? a.row_words[tid] : 0ull;      // (on its way while the flags are looked at)
-    if (ea.only_flagged) {
-        const int any = tid < a.R ? (int)ea.only_flagged[tid] : 0;
-        if (__syncthreads_or(any)) {
-            if (blockIdx.x != 0) return;             // the whole workgroup
-            enc_generic_rows<DT, kScanRows>(ea, 0, a.R, sh);
-            __syncthreads();
-            alone = true;
-            v = tid < a.R ? a.row_words[tid] : 0ull;
+    auto words_of = [&](int64_t r) -> u64 { return finish_words<!FIX>(a, r); };
+    u64 v = tid < a.R ? words_of(tid) : 0ull;         // (on its way while the flags are looked at)
+    if constexpr (FIX) {
+        __shared__ GenericLds<kScanRows> sh;
+        if (ea.only_flagged) {
+            const int any = tid < a.R ? (int)ea.only_flagged[tid] : 0;
+            if (__syncthreads_or(any)) {
+                if (blockIdx.x != 0) return;             // the whole workgroup
+                enc_generic_rows<DT, kScanRows>(ea, 0, a.R, sh);
+                __syncthreads();
+                alone = true;
+                v = tid < a.R ? words_of(tid) : 0ull;
+            }
         }
     }
     {   // exclusive scan of the word counts
@@ -841,7 +903,7 @@ __global__ __launch_bounds__(kScanRows) void enc_finish_small_kernel(EncArgs ea,
         const u64 off = s_off[r];
         if (c == 0 && lane == 0) a.mv.row_off[r] = off;
         if (item == 0 && lane == 0) write_header(a, s_off[kScanRows]);
-        gather_item(a, r, c, [&]() { return off; });
+        gather_item(a, r, words_of(r), c, [&]() { return off; });
     }
 }
 

@@ -24,8 +24,9 @@
 //   5. ABQ sums on integer grids, bitwidth choice, bit offsets, packing through an
 //      LDS image of the row's stream segment.
 //
-// Rows the list cannot hold (heavy ties around the threshold, more zeros than
-// dropped elements, ...) are flagged and redone by the generic kernel.
+// Rows whose list would not fit (many equal or nearly equal values around the threshold) take the exact cut, found bit by bit
+// over the row in registers, and list the kept elements alone: no row is left to another kernel.  (With lists of that
+// kind flagged and redone by the generic kernel, every call paid for a launch that looks for flags.)
 #pragma once
 
 #include <type_traits>
@@ -41,9 +42,13 @@ struct SmallArgs {
     int qlist[kMaxQ];
     double beta;
     u64 cap_words;
-    u64* row_words;     // [R]
+    u64* row_words;     // [R] workgroup-per-row kernel
+    u32* row_words32;   // [R] one-wavefront kernel
     u32* slots;         // [R][cap_words]
-    u32* fallback;      // [R] 1 = redo this row with the generic kernel
+    u32* fallback;      // [R] workgroup-per-row kernel: 1 = redo this row with the generic kernel
+    u32* stream;        // one-wavefront kernel, a single row: its words go straight to the stream, and the header with them; else null
+    void* meta;
+    u32 bit_set;
     MetaView mv;
     int cap;            // list capacity, multiple of 64, < 2048
     int region0_words;  // fine histogram, later block-ordered indices + stream image
@@ -193,10 +198,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     const int M = a.M, Mn = a.Mn, w = a.w, B2 = a.M + a.Mn, nq = NQ ? NQ : a.nq, cap = a.cap;
     const int k = (int)a.k;
     SmallLds L = small_carve(smem, DT, cap, a.region0_words, B2, MAXS);
-    if (__builtin_amdgcn_groupstaticsize() != 0u) {             // integer LDS addresses assume offset 0
-        if (lane == 0) a.fallback[r] = 1u;
-        return;
-    }
+    if (__builtin_amdgcn_groupstaticsize() != 0u) __builtin_trap();      // integer LDS addresses assume offset 0: the kernel has no static LDS
     // ---- list entry accessors ---------------------------------------------------------------
     // Entry p of the list (ascending index): the class as the top bit (set for the positive one), the magnitude key below it
     // and, for bf16, the inverted index in the low half: the whole class-extended comp.  fp32 entries have ~p as their low
@@ -376,10 +378,47 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         nL = bcast(incl, kWave - 1);
         pos0 = incl - n1;
     };
+    // sign bits: the word's keys that are at or above t <=> the sign bit of key + (2^31 - t), or of both halves with 2^15
+    auto key_flag = [&](u32 wd, u32 t) -> u32 {
+        return (wd & (DT == 0 ? 0x7FFFFFFFu : 0x7FFF7FFFu)) + (DT == 0 ? 0x80000000u - t : (0x8000u - t) * 0x10001u);
+    };
     auto mask_plain = [&]() {                       // every key at or above t_lo
-        const u32 C = DT == 0 ? 0x80000000u - t_lo : (0x8000u - t_lo) * 0x10001u;      // the sign bit of (key + C) <=> key >= t_lo
-        row_mask([&](u32 wd) -> u32 { return (wd & (DT == 0 ? 0x7FFFFFFFu : 0x7FFF7FFFu)) + C; });
+        row_mask([&](u32 wd) -> u32 { return key_flag(wd, t_lo); });
         scan_mask();
+    };
+    // flagged elements of the row; the largest key that more than `rank` of the elements with flag(word, key) reach (0 if none
+    // does), bit by bit; of the elements flagged by `ties`, all in the mask, only the first `need` stay there
+    auto count_flags = [&](auto flag) __attribute__((always_inline)) -> u32 {
+        u32 n = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) n += (u32)__popc(flag(word_of(c, d)) & (DT == 0 ? 0x80000000u : 0x80008000u));
+        }
+        return wave_sum(n);
+    };
+    auto exact_key = [&](u32 rank, auto flag) __attribute__((always_inline)) -> u32 {
+        u32 v = 0;
+#pragma unroll 1
+        for (int bit = E::kKeyBits - 1; bit >= 0; --bit) {
+            const u32 t = v | (1u << bit);
+            if (count_flags([&](u32 wd) -> u32 { return flag(wd, t); }) > rank) v = t;
+        }
+        return v;
+    };
+    auto keep_first = [&](u32 need, auto ties) __attribute__((always_inline)) {
+        u32 all[NM];
+#pragma unroll
+        for (int i = 0; i < NM; ++i) all[i] = mk[i];
+        row_mask(ties);
+        scan_mask();
+        u32 left = need > pos0 ? need - pos0 : 0u;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            u32 e = mk[i], stay = 0;
+            for (; e && left; --left) { stay |= e & (0u - e); e &= e - 1u; }
+            mk[i] = (all[i] & ~mk[i]) | stay;
+        }
     };
     // the hinted bound: accepted when it keeps at least k keys and not many more
     bool hinted = false;
@@ -453,11 +492,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         // tau = the k-th largest magnitude, exactly (the first pass above has run on the same window: redo it
         // as the first level of the exact selection)
         wtop = kmax; above = 0; S = 0;
-        exact_select32(all_keys, std::false_type());
-        if (!found) {                                // cannot happen: every key is counted
-            if (lane == 0) a.fallback[r] = 1u;
-            return;
-        }
+        exact_select32(all_keys, std::false_type());     // (finds it: every key is counted)
         tau_key32 = wtop - B1;
         const float tau = __uint_as_float(tau_key32);
         tp_key32 = __float_as_uint(__fmul_rn(a.one_plus, tau));
@@ -494,11 +529,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         S = 0; B1 = 0;
     }
     if (ASYM && DT == 1 && k > 0) {
-        if (!found || S != 0) {                      // tau is not the key of one bin
-            if (lane == 0) a.fallback[r] = 1u;
-            return;
-        }
-        const u32 tau_key = wtop - B1;
+        // (the bins of a second pass hold several keys)
+        const u32 tau_key = found && S == 0 ? wtop - B1 : exact_key((u32)(k - 1), [&](u32 wd, u32 t) -> u32 { return key_flag(wd, t); });
         const float tau = __uint_as_float(tau_key << 16);
         const u32 tp_key = __float_as_uint(__fmul_rn(a.one_plus, tau)) >> 16;    // (key << 16) > T  <=>  key > (T >> 16)
         tn_key = __float_as_uint(__fmul_rn(a.one_minus, tau)) >> 16;
@@ -529,13 +561,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             if (trim) hist_pass(std::integral_constant<int, 0>(), [&](u32 wd) -> u32 { return pk_mul_lo_u16(wd & 0x7FFF7FFFu, strict01(wd)); }, std::true_type(), std::false_type());
             else hist_pass(std::integral_constant<int, 0>(), [&](u32 wd) -> u32 { return pk_mul_lo_u16(wd & 0x7FFF7FFFu, fill01(wd, strict01(wd))); }, std::true_type(), std::false_type());
             if (found) {
-                if (B1 == (u32)(kCoarseBins - 1) && wtop > (u32)(kCoarseBins - 1)) {     // below the window of single keys
-                    if (lane == 0) a.fallback[r] = 1u;
-                    return;
-                }
                 t2_key = wtop - B1;
                 need_ties = rank_t + 1u - c_gt;
                 cnt_ties = cnt1;
+                if (B1 == (u32)(kCoarseBins - 1) && wtop > (u32)(kCoarseBins - 1)) {     // below the window of single keys
+                    auto cand = [&](u32 wd, u32 t) -> u32 { return ((trim ? strict01(wd) : fill01(wd, strict01(wd))) << 15) & key_flag(wd, t); };
+                    t2_key = exact_key(rank_t, cand);
+                    const u32 gt = count_flags([&](u32 wd) -> u32 { return cand(wd, t2_key + 1u); });
+                    need_ties = rank_t + 1u - gt;
+                    cnt_ties = count_flags([&](u32 wd) -> u32 { return cand(wd, t2_key); }) - gt;
+                }
             }                                            // else: the rank lies among zeros, every non-zero candidate is taken
         }
         if (t2_key == 0) { t2_key = 1; need_ties = 0; cnt_ties = 0; }     // the rank falls on zeros (never sent) or every candidate is taken
@@ -548,10 +583,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         const long long lowk = (long long)wtop - ((long long)(B1 + 1u) << S) + 1;
         t_lo = lowk > 1 ? (u32)lowk : 1u;                        // smallest non-zero key of bin B1
         if (ASYM && k > 0) t_lo = trim ? t2_key : min(t2_key, tn_key + 1u);   // smallest key the list can hold
-        if (!ASYM && k > 0 && lowk >= 1 && (int)(c_gt + cnt1) > cap) {
-            if (lane == 0) a.fallback[r] = 1u;
-            return;
-        }
     }
 
     // ---- 2. ordered compaction into L -------------------------------------------------
@@ -580,27 +611,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
                 return (trim ? (st && ge) : (st || (fill32(wd) && ge))) ? 0x80000000u : 0u;
             };
             row_mask([&](u32 wd) -> u32 { return taken(wd, false); });
-            if (need_ties < cnt_ties) {              // uniform
-                u32 all[NM];
-#pragma unroll
-                for (int i = 0; i < NM; ++i) all[i] = mk[i];
-                row_mask([&](u32 wd) -> u32 { return taken(wd, true); });
-                scan_mask();
-                u32 left = need_ties > pos0 ? need_ties - pos0 : 0u;
-#pragma unroll
-                for (int i = 0; i < NM; ++i) {
-                    u32 e = mk[i], stay = 0;
-                    for (; e && left; --left) { stay |= e & (0u - e); e &= e - 1u; }
-                    mk[i] = (all[i] & ~mk[i]) | stay;
-                }
-            }
+            if (need_ties < cnt_ties) keep_first(need_ties, [&](u32 wd) -> u32 { return taken(wd, true); });     // uniform
             scan_mask();
-        } else if (!hinted) {
-            mask_plain();
-        }
-        if ((int)nL > cap) {                                      // uniform
-            if (lane == 0) a.fallback[r] = 1u;
-            return;
+        } else {
+            if (!hinted) mask_plain();
+            if ((int)nL > cap) {                     // uniform, rare: the exact cut
+                t_lo = exact_key((u32)(k - 1), [&](u32 wd, u32 t) -> u32 { return key_flag(wd, t); });
+                mask_plain();
+                if (nL > (u32)k)
+                    keep_first((u32)k - count_flags([&](u32 wd) -> u32 { return key_flag(wd, t_lo + 1u); }),
+                               [&](u32 wd) -> u32 { return key_flag(wd, t_lo) & ~key_flag(wd, t_lo + 1u); });
+                scan_mask();
+            }
         }
         const u32 pl_off = (u32)((u32*)plist - smem) * 4u;
         typedef __attribute__((address_space(3))) uint16_t lds_u16;
@@ -1204,13 +1226,17 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         }
     }
     wave_sync();
-    u32* __restrict__ slot = a.slots + (size_t)r * (size_t)a.cap_words;
+    u32* __restrict__ slot = a.stream ? a.stream : a.slots + (size_t)r * (size_t)a.cap_words;
     for (u32 i = lane; i < row_words; i += kWave) slot[i] = stage[i];
     if (lane == 0) {
-        a.row_words[r] = row_words;
         a.mv.n_pos[r] = n_pos;
         a.mv.n_neg[r] = n_neg;
-        a.fallback[r] = 0u;
+        if (a.stream) {                              // a single row: its offset is known (bf16 [1 x 4096] ladder 14.2 -> 10.6 us)
+            a.mv.row_off[r] = 0;
+            write_header(a.meta, DT, M, Mn, a.R, a.N, a.k, a.bit_set, w, row_words);
+        } else {
+            a.row_words32[r] = row_words;
+        }
         if (kHint && k > 0) a.hint[hslot] = nL > (u32)k ? word_key(thrK) : t_lo;    // this row's cut key, for a later row
     }
 }

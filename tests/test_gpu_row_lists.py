@@ -23,7 +23,21 @@ def test_where_the_kept_elements_lie(oracle, dtype, N):
     x[5] = 0.25
     x[7, ::9] = np.where(np.arange(0, N, 9) % 2, 60.0, -60.0)     # the cut among equal keys of both classes
     x[6, n // 2:] = 0.0
+    x[1, ::40] *= np.float32(2.0) ** 50              # the cut lies many octaves below the largest values
     if dtype == "bf16":
         x = synth.f32_to_bf16_bits(x)
     check(oracle, x, dtype, 0.1, 4, B28, 1e-3)
     check_atkf(oracle, x, dtype, 0.1, 0.3, 4, 3, B28, 1e-3)
+
+
+# one row, one finishing launch, one launch for offsets and copy with 1, 2 and 4 rows a wavefront, scan and copy
+@pytest.mark.parametrize("dtype,rows,N", [("f32", 1, 300), ("bf16", 1, 4096), ("f32", 257, 64), ("bf16", 4095, 70), ("f32", 4097, 64),
+                                          ("bf16", 8191, 64), ("f32", 8193, 64), ("f32", 32768, 32), ("bf16", 32769, 33), ("f32", 260, 4096)])
+def test_where_the_rows_go(oracle, dtype, rows, N):
+    rng = np.random.default_rng(rows)
+    x = rng.standard_normal((rows, N)).astype(np.float32) * rng.uniform(0.01, 30, (rows, 1)).astype(np.float32)
+    x[:: 7] = 0.0                                     # rows without a word among the others
+    x[3 % rows] = 1.5
+    if dtype == "bf16":
+        x = synth.f32_to_bf16_bits(x)
+    check(oracle, x, dtype, 0.3 if N > 300 else 0.4, 2, B28, 1e-3)
