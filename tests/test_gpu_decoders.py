@@ -1,0 +1,30 @@
+"""The two decoders of long instances at their edges: one block to 64 of them per class, tensor rows of one column, of a few columns (sixteen
+rows a workgroup) and longer than the LDS image, output chunks that start off 16 bytes, launches below and above one workgroup per
+CU; byte-exact against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2511_11608_amd import synth
+from tests.test_gpu_parity import B28, check, check_csr
+
+pytestmark = pytest.mark.gpu
+
+
+def features(dtype, rows, N):
+    rng = np.random.default_rng(N + rows)
+    x = rng.standard_normal((rows, N)).astype(np.float32) * np.repeat(rng.uniform(0.1, 4, (rows, N // 50 + 1)).astype(np.float32), 50, 1)[:, :N]
+    x[0, : N // 2] = np.abs(x[0, : N // 2])
+    x[-1, N // 3:] = 0.0                               # one end of the row holds every entry
+    return synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+
+
+@pytest.mark.parametrize("dtype,rows,n_rows,n_cols,M", [("f32", 3, 512, 49, 64), ("bf16", 2, 3, 20000, 5), ("f32", 9, 40, 1, 4), ("bf16", 40, 701, 13, 16),
+                                                        ("f32", 2, 1, 5000, 1), ("f32", 32, 64, 784, 16), ("bf16", 1, 9000, 3, 33)])
+def test_two_dimensional(oracle, dtype, rows, n_rows, n_cols, M):
+    check_csr(oracle, features(dtype, rows, n_rows * n_cols), dtype, n_rows, n_cols, 0.2, M, B28, 1e-3)
+
+
+@pytest.mark.parametrize("dtype,rows,N,M", [("f32", 2, 33001, 64), ("bf16", 3, 100003, 1), ("f32", 40, 40004, 16), ("bf16", 33, 70002, 33), ("f32", 1, 4099, 64)])
+def test_long_rows(oracle, dtype, rows, N, M):
+    for header in (False, True):
+        check(oracle, features(dtype, rows, N), dtype, 0.1, M, B28, 1e-3, use_header=header)
