@@ -476,13 +476,15 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         // from the first code bit on are a quarter of the others; all are smaller while the launch is small
         la.pack_words = kPackWords;
         while (la.pack_words > 128 && (u64)rows * ((la.cap_words + (u64)la.pack_words - 1) / (u64)la.pack_words) < 1024) la.pack_words /= 2;
-        if (csr) while (la.pack_words * 32 / csr->wp + 2 > kPackPtrs) la.pack_words /= 2;
+        la.pack_words_ptr = std::min(la.pack_words, 256);      // (at most 1026 pointers of eight bits or more)
+        static_assert(256 * 32 / 8 + 2 <= kPackPtrs, "a window's row pointers fit the LDS table");
         la.pack_words_code = std::max(64, la.pack_words / 4);
         {
             // largest first word with code bits; words from there to the end
             const u64 ptr_bits = csr ? (u64)(n_blocks + n_blocks_neg) * (u64)(csr->n_rows + 1) * (u64)csr->wp : 0;
-            const u64 idx_words_max = (ptr_bits + (u64)p.k * (u64)(csr ? csr->wc : p.w)) / 32;
-            la.nwin_idx = (int)((idx_words_max + (u64)la.pack_words - 1) / (u64)la.pack_words);
+            const u64 ptr_words = ptr_bits / 32, idx_words_max = (ptr_bits + (u64)p.k * (u64)(csr ? csr->wc : p.w)) / 32 - ptr_words;
+            la.nwin_ptr = (int)((ptr_words + (u64)la.pack_words_ptr - 1) / (u64)la.pack_words_ptr);
+            la.nwin_idx = la.nwin_ptr + (int)((idx_words_max + (u64)la.pack_words - 1) / (u64)la.pack_words);
             const u64 code_words_max = ((u64)p.k * (u64)p.qmax + 31) / 32 + 2;
             la.nwin = la.nwin_idx + (int)((code_words_max + (u64)la.pack_words_code - 1) / (u64)la.pack_words_code);
         }

@@ -85,7 +85,8 @@ struct LargeArgs {
     // pack
     int pack_words;         // stream words per pack workgroup in the index section (<= kPackWords)
     int pack_words_code;    // ... from the first word with code bits on (fields there are short: fewer words per workgroup)
-    int nwin_idx, nwin;     // windows that may lie in the index section; windows per row
+    int pack_words_ptr;     // ... up to the first word with column bits (two-dimensional instances)
+    int nwin_ptr, nwin_idx, nwin;     // windows of row pointers; those and the ones that may lie in the index section; windows per row
     int direct;             // 1: words go to their place in the stream, 0: to the row's slot
     u32* stream;
     void* meta;
@@ -1340,7 +1341,7 @@ struct RunPacker {
     __device__ inline void finish() { if (fill > 0) put((u32)acc, true); }
 };
 
-constexpr int kPackPtrs = 4096;                   // row pointers of one window
+constexpr int kPackPtrs = 1088;                   // row pointers of one window
 
 // CSR: row pointers and columns instead of flat indices (Sec. 3.2 step 3)
 template <int DT, bool CSR>
@@ -1358,9 +1359,11 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa
     const int tid = threadIdx.x;
     const int64_t r = blockIdx.y;
     const int B2 = a.M + a.Mn, wi = CSR ? a.wc : a.w;
-    // the windows with code fields hold the most entries: they are started first
-    const int nwc = a.nwin - a.nwin_idx;
-    const int win = (int)blockIdx.x < nwc ? a.nwin_idx + (int)blockIdx.x : (int)blockIdx.x - nwc;
+    // The windows of row pointers take longest: they are started first, then those with code fields, which hold the most
+    // entries.  (As windows of 1024 words behind the others the pointers made the tail of the launch: fp32 32 x [512 x 784]
+    // pack 52 us, now 29.)
+    const int nwp = CSR ? a.nwin_ptr : 0, nwc = a.nwin - a.nwin_idx, wx = (int)blockIdx.x - nwp;
+    const int win = CSR && wx < 0 ? (int)blockIdx.x : wx < nwc ? a.nwin_idx + wx : nwp + wx - nwc;
     const u64 row_words = a.row_words[r];
     const u32 n = a.blk_start[(size_t)r * (B2 + 1) + B2];
     const u64 ptr_bits = CSR ? (u64)B2 * (u64)(a.n_rows + 1) * (u64)a.wp : 0ull;
@@ -1368,9 +1371,12 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa
     // windows of pack_words words up to the first word that holds code bits, then of pack_words_code words
     u64 c0, c1;
     {
-        const u64 wb = idx_bits >> 5;
-        if (win < a.nwin_idx) {
-            c0 = (u64)win * (u64)a.pack_words;
+        const u64 wb = idx_bits >> 5, wq = CSR ? ptr_bits >> 5 : 0ull;
+        if (CSR && win < nwp) {
+            c0 = (u64)win * (u64)a.pack_words_ptr;
+            c1 = c0 + (u64)a.pack_words_ptr < wq ? c0 + (u64)a.pack_words_ptr : wq;
+        } else if (win < a.nwin_idx) {
+            c0 = wq + (u64)(win - nwp) * (u64)a.pack_words;
             c1 = c0 + (u64)a.pack_words < wb ? c0 + (u64)a.pack_words : wb;
         } else {
             c0 = wb + (u64)(win - a.nwin_idx) * (u64)a.pack_words_code;
@@ -1515,11 +1521,23 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa
             i0 = i0 < cnt ? i0 : cnt - 1u;
             u32 i1 = part && j1 < np1 ? before(j1 - 1u) + 1u : cnt;
             i1 = i1 < cnt ? i1 : cnt;
-            for (u32 i = i0 + (u32)tid; i < i1; i += 256) {
-                const u32 row = tensor_row(bo_idx[p0 + i]), prev = i ? tensor_row(bo_idx[p0 + i - 1u]) + 1u : 0u;
-                const u32 x1 = row + 1u < j1 ? row + 1u : j1;
-                for (u32 j = prev > j0 ? prev : j0; j < x1; ++j) out[j - j0] = i;
-                if (i == cnt - 1u) for (u32 j = row + 1u > j0 ? row + 1u : j0; j < j1; ++j) out[j - j0] = cnt;
+            for (u32 ib = i0 + (u32)tid; ib < i1; ib += 4 * 256) {      // the entries of four steps in flight
+                u32 at[4], bef[4];
+#pragma unroll
+                for (u32 u = 0; u < 4; ++u) {
+                    const u32 i = ib + 256u * u < i1 ? ib + 256u * u : ib;
+                    at[u] = bo_idx[p0 + i];
+                    bef[u] = i ? bo_idx[p0 + i - 1u] : 0u;
+                }
+#pragma unroll
+                for (u32 u = 0; u < 4; ++u) {
+                    const u32 i = ib + 256u * u;
+                    if (i >= i1) break;
+                    const u32 row = tensor_row(at[u]), prev = i ? tensor_row(bef[u]) + 1u : 0u;
+                    const u32 x1 = row + 1u < j1 ? row + 1u : j1;
+                    for (u32 j = prev > j0 ? prev : j0; j < x1; ++j) out[j - j0] = i;
+                    if (i == cnt - 1u) for (u32 j = row + 1u > j0 ? row + 1u : j0; j < j1; ++j) out[j - j0] = cnt;
+                }
             }
         }
         __syncthreads();
