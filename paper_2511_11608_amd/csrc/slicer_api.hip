@@ -160,15 +160,17 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
         p.small_maxs = maxs;
     }
     // One workgroup per row (the wavefronts of a workgroup share the row): every row of more than 4096 and up to
-    // 32768 bf16 / 16384 fp32 elements.  For bf16 rows of 4097..8192 elements, which one wavefront could hold,
-    // it is the faster kernel at every batch size (16384 rows of 8192: 238 against 293 us; 4096 rows of 6144:
-    // 68 against 74 us); at 4096 elements and below one wavefront per row wins (115 against 189 us).
+    // 32768 bf16 / 16384 fp32 elements, but for bf16 rows of up to 8192 in batches of more than 256 whose list has at most 768
+    // entries.  One wavefront per row does less work in all, and takes longer for a single row; the longer the list, the
+    // longer.  Encode us, workgroup / wavefront: such lists [300 x 5120] 22.1 / 19.2, [512 x 8192] 22.1 / 20.7, [2048 x 8192]
+    // 39.6 / 25.0; but [256 x 8192] 18 / 21, and longer lists [512 x 8192] 24.1 / 26.9, [4096 x 6144], 1228 kept, 80 / 81.
     p.wg_ept = 0; p.wg_nw = 0; p.wg_cap = 0; p.wg_region0 = 0; p.wg_lds_bytes = 0;
     const int64_t wg_lds = lists_fit ? 4 * (int64_t)wg_lds_words(dt, (int)cap, (int)wg_region0, B2_all) : 0;
     auto wg_holds = [&](int64_t elements) {
         return lists_fit && elements > 4096 && elements <= (dt == SLICER_F32 ? 16384 : 32768) && wg_lds <= 64 * 1024;
     };
-    if (wg_holds(span)) {
+    const bool one_wave = p.small_epl && cap <= 768 && rows > kScanRows;
+    if (wg_holds(span) && !one_wave) {
         // wavefronts per row: sixteen for the smallest batches (more wavefronts per SIMD hide each other's
         // latencies: 4 % less latency per call), four otherwise (a 256-row batch on sixteen leaves no room
         // for a neighbouring stream's kernels: 20 % less throughput when steps overlap)

@@ -41,3 +41,12 @@ def test_where_the_rows_go(oracle, dtype, rows, N):
     if dtype == "bf16":
         x = synth.f32_to_bf16_bits(x)
     check(oracle, x, dtype, 0.3 if N > 300 else 0.4, 2, B28, 1e-3)
+
+
+@pytest.mark.parametrize("rows,N,keep", [(256, 5120, 0.1), (257, 5120, 0.1), (300, 8192, 0.05), (300, 4104, 0.14), (260, 8192, 0.07)])
+def test_rows_of_two_lengths_of_list(oracle, rows, N, keep):
+    """bf16 rows of 4097 to 8192 elements: one wavefront or one workgroup per row, by batch and list."""
+    x = np.random.default_rng(N + rows).standard_normal((rows, N)).astype(np.float32)
+    x[:, ::900] *= np.float32(40)
+    x[1] = 0.5
+    check(oracle, synth.f32_to_bf16_bits(x), "bf16", keep, 8, B28, 1e-3)
