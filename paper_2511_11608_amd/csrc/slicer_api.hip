@@ -4,7 +4,10 @@
 
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 
 #include "slicer_common.hpp"
@@ -847,10 +850,75 @@ int slicer_decode_as(const void* stream, const void* meta, void* y, slicer_dtype
     return slicer_decode_as_pn(stream, meta, y, dt, rows, row_len, n_blocks, n_blocks, hip_stream);
 }
 
+// Copies of a header on their way to the host: a slot of page-locked memory that a one-wavefront kernel fills, word by word
+// and then the ticket, while the caller polls the ticket.  A copy into the caller's memory and a wait for the stream took 18 us
+// (decode of fp32 [1 x 200704] 24.6 us in all, 13.0 now).  32 calls can be under way at once, on any threads, streams and GPUs; one more, a
+// stream under capture, and a system that gives no page-locked memory take the copy and the wait.
+struct HeaderSlot { u32 words[kHeaderBytes / 4]; u32 ticket; u32 pad[15]; };
+constexpr int kHeaderSlots = 32;
+
+static __global__ __launch_bounds__(kWave) void header_copy_kernel(const u32* meta, HeaderSlot* slot, u32 ticket)
+{
+    if (threadIdx.x < kHeaderBytes / 4)
+        __hip_atomic_store(&slot->words[threadIdx.x], meta[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();                          // (one wavefront: waits for the words of all its lanes)
+    if (threadIdx.x == 0) __hip_atomic_store(&slot->ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+static HeaderSlot* header_slots()                    // allocated once, 4 KB, kept until the process ends
+{
+    static std::once_flag once;
+    static HeaderSlot* slots = nullptr;
+    std::call_once(once, [] {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;      // (another thread may be capturing)
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        void* p = nullptr;
+        if (hipHostMalloc(&p, sizeof(HeaderSlot) * kHeaderSlots, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
+            memset(p, 0, sizeof(HeaderSlot) * kHeaderSlots);
+            slots = (HeaderSlot*)p;
+        } else {
+            (void)hipGetLastError();
+        }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    });
+    return slots;
+}
+
 static int read_header(const void* meta, hipStream_t st, uint32_t* h32)
 {
-    SLICER_HIP(hipMemcpyAsync(h32, meta, kHeaderBytes, hipMemcpyDeviceToHost, st));
-    SLICER_HIP(hipStreamSynchronize(st));
+    static std::atomic<u32> busy[kHeaderSlots];
+    static u32 tickets[kHeaderSlots];                // of the slot's last call; touched only while the slot is held
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HeaderSlot* slots = nullptr;
+    if (hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone) slots = header_slots();
+    int s = slots ? 0 : kHeaderSlots;
+    for (; s < kHeaderSlots; ++s) {
+        u32 idle = 0;
+        if (busy[s].compare_exchange_strong(idle, 1u, std::memory_order_acquire)) break;
+    }
+    if (s < kHeaderSlots) {
+        HeaderSlot* slot = slots + s;
+        const u32 ticket = ++tickets[s];
+        hipLaunchKernelGGL(header_copy_kernel, dim3(1), dim3(kWave), 0, st, (const u32*)meta, slot, ticket);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) {
+            busy[s].store(0u, std::memory_order_release);
+            return hip_fail(e);
+        }
+        const auto t0 = std::chrono::steady_clock::now();
+        bool there = false;
+        for (u32 i = 0; !there; ++i) {
+            there = __atomic_load_n(&slot->ticket, __ATOMIC_ACQUIRE) == ticket;
+            if (!there && (i & 255u) == 255u && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(1)) break;
+        }
+        if (!there) e = hipStreamSynchronize(st);    // much work before it, or an error: wait in the ordinary way
+        if (e != hipSuccess) return hip_fail(e);     // (the slot is not used again: its copy may still be under way)
+        memcpy(h32, slot->words, kHeaderBytes);
+        busy[s].store(0u, std::memory_order_release);
+    } else {
+        SLICER_HIP(hipMemcpyAsync(h32, meta, kHeaderBytes, hipMemcpyDeviceToHost, st));
+        SLICER_HIP(hipStreamSynchronize(st));
+    }
     if (h32[0] != kMagic || h32[1] != kVersion) return SLICER_EFORMAT;
     return SLICER_OK;
 }

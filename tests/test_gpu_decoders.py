@@ -28,3 +28,39 @@ def test_two_dimensional(oracle, dtype, rows, n_rows, n_cols, M):
 def test_long_rows(oracle, dtype, rows, N, M):
     for header in (False, True):
         check(oracle, features(dtype, rows, N), dtype, 0.1, M, B28, 1e-3, use_header=header)
+
+
+def test_headers_read_by_many_threads(oracle):
+    """slicer_decode and slicer_stream_words learn the shape from the header: 40 threads at once, each with a stream and a shape of its own."""
+    import threading
+    import torch
+    from paper_2511_11608_amd import binding
+    from paper_2511_11608_amd.devmem import to_device, to_host
+    jobs = []
+    for i in range(40):
+        x = features("f32", 1 + i % 3, 300 + 7 * i)
+        s_ref, m_ref = oracle.encode(x, "f32", 0.2, 2, B28, 1e-3)
+        xd = to_device(x, "f32")
+        sb, meta, ws = binding.alloc_buffers(xd, 0.2, 2, B28)
+        binding.slicer_encode(xd, 0.2, 2, B28, 1e-3, sb, meta, ws)
+        jobs.append((sb, meta, torch.full_like(xd, 7.0), oracle.decode(s_ref, m_ref), len(s_ref), []))
+    torch.cuda.synchronize()
+
+    def work(sb, meta, y, y_ref, words, bad):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for _ in range(20):
+                if binding.slicer_stream_words(meta) != words:
+                    bad.append("words")
+                y.fill_(3.0)
+                binding.slicer_decode(sb, meta, y)
+                st.synchronize()
+                if not np.array_equal(to_host(y).view(np.uint32), y_ref.view(np.uint32)):
+                    bad.append("values")
+
+    threads = [threading.Thread(target=work, args=j) for j in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not any(j[5] for j in jobs)
