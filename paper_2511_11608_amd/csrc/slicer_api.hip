@@ -884,7 +884,18 @@ static HeaderSlot* header_slots()                    // allocated once, 4 KB, ke
     return slots;
 }
 
+static int check_header(const uint32_t* h32) { return h32[0] == kMagic && h32[1] == kVersion ? SLICER_OK : SLICER_EFORMAT; }
+
 static int read_header(const void* meta, hipStream_t st, uint32_t* h32)
+{
+    SLICER_HIP(hipMemcpyAsync(h32, meta, kHeaderBytes, hipMemcpyDeviceToHost, st));
+    SLICER_HIP(hipStreamSynchronize(st));
+    return check_header(h32);
+}
+
+// For slicer_decode alone: its own kernels read meta on the same stream right after.  slicer_stream_words keeps the copy: it
+// serves any meta that a copy can reach, also that of another GPU.
+static int poll_header(const void* meta, hipStream_t st, uint32_t* h32)
 {
     static std::atomic<u32> busy[kHeaderSlots];
     static u32 tickets[kHeaderSlots];                // of the slot's last call; touched only while the slot is held
@@ -896,31 +907,22 @@ static int read_header(const void* meta, hipStream_t st, uint32_t* h32)
         u32 idle = 0;
         if (busy[s].compare_exchange_strong(idle, 1u, std::memory_order_acquire)) break;
     }
-    if (s < kHeaderSlots) {
-        HeaderSlot* slot = slots + s;
-        const u32 ticket = ++tickets[s];
-        hipLaunchKernelGGL(header_copy_kernel, dim3(1), dim3(kWave), 0, st, (const u32*)meta, slot, ticket);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) {
-            busy[s].store(0u, std::memory_order_release);
-            return hip_fail(e);
-        }
-        const auto t0 = std::chrono::steady_clock::now();
-        bool there = false;
-        for (u32 i = 0; !there; ++i) {
-            there = __atomic_load_n(&slot->ticket, __ATOMIC_ACQUIRE) == ticket;
-            if (!there && (i & 255u) == 255u && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(1)) break;
-        }
-        if (!there) e = hipStreamSynchronize(st);    // much work before it, or an error: wait in the ordinary way
-        if (e != hipSuccess) return hip_fail(e);     // (the slot is not used again: its copy may still be under way)
-        memcpy(h32, slot->words, kHeaderBytes);
-        busy[s].store(0u, std::memory_order_release);
-    } else {
-        SLICER_HIP(hipMemcpyAsync(h32, meta, kHeaderBytes, hipMemcpyDeviceToHost, st));
-        SLICER_HIP(hipStreamSynchronize(st));
+    if (s == kHeaderSlots) return read_header(meta, st, h32);
+    HeaderSlot* slot = slots + s;
+    const u32 ticket = ++tickets[s];
+    hipLaunchKernelGGL(header_copy_kernel, dim3(1), dim3(kWave), 0, st, (const u32*)meta, slot, ticket);
+    // After an error the slot is not used again: the error may be an older one and the copy under way.
+    SLICER_HIP(hipGetLastError());
+    const auto t0 = std::chrono::steady_clock::now();
+    bool there = false;
+    for (u32 i = 0; !there; ++i) {
+        there = __atomic_load_n(&slot->ticket, __ATOMIC_ACQUIRE) == ticket;
+        if (!there && (i & 255u) == 255u && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(1)) break;
     }
-    if (h32[0] != kMagic || h32[1] != kVersion) return SLICER_EFORMAT;
-    return SLICER_OK;
+    if (!there) SLICER_HIP(hipStreamSynchronize(st));    // much work before it, or an error: wait in the ordinary way
+    memcpy(h32, slot->words, kHeaderBytes);
+    busy[s].store(0u, std::memory_order_release);
+    return check_header(h32);
 }
 
 int slicer_decode(const void* stream, const void* meta, void* y, void* hip_stream)
@@ -928,7 +930,7 @@ int slicer_decode(const void* stream, const void* meta, void* y, void* hip_strea
     if (!stream || !meta || !y) return SLICER_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
     alignas(8) uint32_t h32[kHeaderBytes / 4];
-    int rc = read_header(meta, st, h32);
+    int rc = poll_header(meta, st, h32);
     if (rc) return rc;
     const uint64_t* h64 = (const uint64_t*)h32;
     const int dt = (int)h32[2], M = (int)h32[3];
