@@ -170,7 +170,7 @@ __device__ inline void lds_inc(u32 byte_off, u32 v)
 // selection over a subset of the row (the fill candidates, or the strict set when it is too large)
 // gives the last key taken, and the list is built from that rule; the equal keys at the end are cut
 // in index order.  Both selections need the exact key of their rank, i.e. one key per histogram bin:
-// rows whose ranks lie below the 2048-key window are flagged for the generic kernel.
+// ranks that lie below the 2048-key window are found bit by bit over the row in registers.
 // Wavefronts per SIMD the register allocator must leave room for.  The variants that hold the row in at most
 // 32 registers come out at 84 to 101 VGPRs, a few of them just above the limit of five wavefronts (96 VGPRs):
 // asking for five costs those a handful of spill moves outside every loop.  fp32 rows of 4096 elements (64
