@@ -130,6 +130,21 @@ __host__ __device__ inline int small_lds_words(int dt, int cap, int region0, int
     return wds;
 }
 
+// The block-ordered values are read four at a time, by lanes that all walk as many as the longest block has: a lane whose block
+// is shorter reads on behind it.  Where that can pass the end of the list, the group of four starts at `cap` at the latest:
+// S has cap + 4 words, and a group that starts higher holds no entry.
+__host__ __device__ inline u32 small_group_at(u32 at, int cap) { return at < (u32)cap ? at : (u32)cap; }
+
+// A lane's part of its block for the sums: slice sl of `per` entries of the block of cnt entries at bs0; nothing: at place 0, where
+// as many steps as any block has entries stay inside the list
+struct AbqSlice { u32 q0, qn; };
+__host__ __device__ inline AbqSlice small_abq_slice(u32 bs0, u32 cnt, u32 per, u32 sl, bool active)
+{
+    const u32 end = bs0 + cnt, q0 = bs0 + sl * per < end ? bs0 + sl * per : end, q1 = q0 + per < end ? q0 + per : end;
+    const u32 qn = active ? q1 - q0 : 0u;
+    return { qn ? q0 : 0u, qn };
+}
+
 __device__ inline SmallLds small_carve(u32* base, int dt, int cap, int region0, int B2, int maxs)
 {
     SmallLds L;
@@ -1033,18 +1048,17 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         const u32 ct = es > 1u ? sub & 7u : sub, sl = es > 1u ? sub >> 3 : 0u;
         const bool active = lane_on && ct < cl && sl < es;
         const u32 per = es > 1u ? udiv16(mycnt + es - 1u, es) : mycnt, T2 = es > 1u ? udiv16(maxb + es - 1u, es) : maxb;
-        u32 q0 = bs0 + sl * per, q1 = bs0 + mycnt;
-        q0 = q0 < q1 ? q0 : q1;
-        q1 = q0 + per < q1 ? q0 + per : q1;
-        const u32 qn = active ? q1 - q0 : 0u;
+        const AbqSlice slice = small_abq_slice(bs0, mycnt, per, sl, active);
+        const u32 q0 = slice.q0, qn = slice.qn;
         if (es > 1u && active) for (u32 t = ct + 8u * sl; t < (u32)nq; t += 8u * es) sums[myb * (nq + 1) + t] = 0;
         double rhs = 0.0;
         if (a.guard == 0) {
             u64 accE = 0;
             for (u32 i = 0; i < T; i += 4) {
-                u32 v[4];                            // (beyond the lane's share: other LDS words, not used)
+                u32 v[4];                            // (beyond the lane's share: not used)
+                const u32 at = small_group_at(r0 + i, cap);
 #pragma unroll
-                for (u32 j = 0; j < 4; ++j) v[j] = bo_val[r0 + i + j];
+                for (u32 j = 0; j < 4; ++j) v[j] = bo_val[at + j];
 #pragma unroll
                 for (u32 j = 0; j < 4; ++j) {
                     u32 A = (u32)rintf(ldexpf(__uint_as_float(v[j]), 20 - e));      // 20-bit energy grid scaled to vmax
@@ -1100,9 +1114,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
                 tot[u] = 0;
             }
             auto four = [&](u32 i, u32 (&acc)[NCU], auto tail) __attribute__((always_inline)) {
-                u32 v[4];                            // (beyond the block's end: other LDS words, not used)
+                u32 v[4];                            // (beyond the block's end: not used)
+                const u32 at = decltype(tail)::value ? small_group_at(q0 + i, cap) : q0 + i;
 #pragma unroll
-                for (u32 j = 0; j < 4; ++j) v[j] = bo_val[q0 + i + j];
+                for (u32 j = 0; j < 4; ++j) v[j] = bo_val[at + j];
 #pragma unroll
                 for (u32 j = 0; j < 4; ++j) {
                     float d = __uint_as_float(v[j]) - vmin;
