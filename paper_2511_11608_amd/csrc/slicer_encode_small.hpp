@@ -925,10 +925,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         if (kept) {
             const u32 key = word_key(cx), base = L.run[b];
             if (!one_key) { atomicMin(&L.vminb[b], key); atomicMax(&L.vmaxb[b], key); }
+            wave_sync();                            // every lane of the block has read run[b] before one moves it on
             if (before == 0) L.run[b] = base + (u32)__popc(plo) + (u32)__popc(phi);
             bo_val[base + before] = E::value_bits(key);
             bo_idx[base + before] = (uint16_t)ent_index(s);
         }
+        wave_sync();                                // the next slot reads the moved places
     };
     auto is_kept = [&](int s, u32 cx) -> bool {
         bool kept = in_list(s) && (cx & kMag) >= thrK;
