@@ -899,6 +899,9 @@ static int poll_header(const void* meta, hipStream_t st, uint32_t* h32)
 {
     static std::atomic<u32> busy[kHeaderSlots];
     static u32 tickets[kHeaderSlots];                // of the slot's last call; touched only while the slot is held
+    // An error that some earlier call of this thread left would be taken for one of the launch below: the copy leaves it to be
+    // reported where the decode kernel is launched.
+    if (hipPeekAtLastError() != hipSuccess) return read_header(meta, st, h32);
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     HeaderSlot* slots = nullptr;
     if (hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone) slots = header_slots();
@@ -911,15 +914,26 @@ static int poll_header(const void* meta, hipStream_t st, uint32_t* h32)
     HeaderSlot* slot = slots + s;
     const u32 ticket = ++tickets[s];
     hipLaunchKernelGGL(header_copy_kernel, dim3(1), dim3(kWave), 0, st, (const u32*)meta, slot, ticket);
-    // After an error the slot is not used again: the error may be an older one and the copy under way.
-    SLICER_HIP(hipGetLastError());
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {                           // nothing was launched that could write to the slot
+        busy[s].store(0u, std::memory_order_release);
+        return hip_fail(e);
+    }
     const auto t0 = std::chrono::steady_clock::now();
     bool there = false;
     for (u32 i = 0; !there; ++i) {
         there = __atomic_load_n(&slot->ticket, __ATOMIC_ACQUIRE) == ticket;
         if (!there && (i & 255u) == 255u && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(1)) break;
     }
-    if (!there) SLICER_HIP(hipStreamSynchronize(st));    // much work before it, or an error: wait in the ordinary way
+    if (!there) {                                    // much work before it, or an error: wait in the ordinary way
+        e = hipStreamSynchronize(st);
+        there = __atomic_load_n(&slot->ticket, __ATOMIC_ACQUIRE) == ticket;
+        // a copy that has not come may still be under way: its slot is not used again
+        if (e != hipSuccess || !there) {
+            if (there) busy[s].store(0u, std::memory_order_release);
+            return hip_fail(e != hipSuccess ? e : hipErrorUnknown);
+        }
+    }
     memcpy(h32, slot->words, kHeaderBytes);
     busy[s].store(0u, std::memory_order_release);
     return check_header(h32);
