@@ -24,8 +24,8 @@
 //   5. ABQ sums on integer grids, bitwidth choice, bit offsets, packing through an
 //      LDS image of the row's stream segment.
 //
-// Rows whose list would not fit (many equal or nearly equal values around the threshold) take the exact cut, found bit by bit
-// over the row in registers, and list the kept elements alone: no row is left to another kernel.  (With lists of that
+// Rows whose list would not fit (many equal or nearly equal values around the threshold) take the exact cut, found by narrower
+// histograms, and list the kept elements alone: no row is left to another kernel.  (With lists of that
 // kind flagged and redone by the generic kernel, every call paid for a launch that looks for flags.)
 #pragma once
 
@@ -187,9 +187,10 @@ __device__ inline void lds_inc(u32 byte_off, u32 v)
 // in index order.  Both selections need the exact key of their rank, i.e. one key per histogram bin:
 // ranks that lie below the 2048-key window are found bit by bit over the row in registers.
 // Wavefronts per SIMD the register allocator must leave room for.  The variants that hold the row in at most
-// 32 registers come out at 84 to 101 VGPRs, a few of them just above the limit of five wavefronts (96 VGPRs):
-// asking for five costs those a handful of spill moves outside every loop.  fp32 rows of 4096 elements (64
-// registers for the row, 166 to 181 in all) are asked for three wavefronts (168) instead of two.
+// 32 registers come out at 65 to 89 VGPRs and are asked for five wavefronts (96).  fp32 rows of more than 2048 elements (64
+// registers for the row, 138 to 154 in all) are asked for three (168); bf16 rows of more than 4096 come out at 143 to 153.  No
+// variant spills.  (With the exact cut found bit by bit over the row, whose masked words were then held from bit to bit, fp32 rows
+// of more than 2048 elements spilled 28 to 30 registers: [2048 x 4096] keep 0.10 encode 26.7 us, now 24.0.)
 constexpr int small_min_waves(int dt, int epl, int nq, int maxs, bool asym)
 {
     const int row_regs = dt == 0 ? epl : epl / 2;
@@ -401,26 +402,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         row_mask([&](u32 wd) -> u32 { return key_flag(wd, t_lo); });
         scan_mask();
     };
-    // flagged elements of the row; the largest key that more than `rank` of the elements with flag(word, key) reach (0 if none
-    // does), bit by bit; of the elements flagged by `ties`, all in the mask, only the first `need` stay there
-    auto count_flags = [&](auto flag) __attribute__((always_inline)) -> u32 {
-        u32 n = 0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) n += (u32)__popc(flag(word_of(c, d)) & (DT == 0 ? 0x80000000u : 0x80008000u));
-        }
-        return wave_sum(n);
-    };
-    auto exact_key = [&](u32 rank, auto flag) __attribute__((always_inline)) -> u32 {
-        u32 v = 0;
-#pragma unroll 1
-        for (int bit = E::kKeyBits - 1; bit >= 0; --bit) {
-            const u32 t = v | (1u << bit);
-            if (count_flags([&](u32 wd) -> u32 { return flag(wd, t); }) > rank) v = t;
-        }
-        return v;
-    };
+    // of the elements flagged by `ties`, all in the mask, only the first `need` stay there
     auto keep_first = [&](u32 need, auto ties) __attribute__((always_inline)) {
         u32 all[NM];
 #pragma unroll
@@ -434,6 +416,41 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             for (; e && left; --left) { stay |= e & (0u - e); e &= e - 1u; }
             mk[i] = (all[i] & ~mk[i]) | stay;
         }
+    };
+    // The exact key of rank rank_t among the keys a functor lets through, by histogram passes over narrowing windows, each of
+    // them inside the bin that the one before it found: on success wtop - B1 is the key, above + c_gt the number of counted
+    // keys above it, cnt1 its multiplicity.  single_keys() goes on from a pass whose bins have 2^S1 keys, or 2^(S1 + 4) (wide: after the
+    // values spread over more than 16 octaves): fp32 bins of 2^5 keys (2^9), then single keys; bf16 single keys from
+    // wide bins, where a pass without them has found the key already.
+    auto narrow = [&](int sh_done) { above += c_gt; wtop -= B1 << sh_done; };
+    auto single_keys = [&](bool wide, auto key_fn, auto skip0) {
+        if (DT == 0) {
+            if (wide) {
+                narrow(20);
+                hist_pass(std::integral_constant<int, 9>(), key_fn, skip0, std::true_type());
+                if (!found) return;
+                narrow(9);
+            } else {
+                narrow(16);
+                hist_pass(std::integral_constant<int, 5>(), key_fn, skip0, std::true_type());
+                if (!found) return;
+                narrow(5);
+            }
+            hist_pass(std::integral_constant<int, 0>(), key_fn, skip0, std::true_type());
+        } else if (wide) {
+            narrow(4);
+            hist_pass(std::integral_constant<int, 0>(), key_fn, skip0, std::false_type());
+        }
+    };
+    // from wtop with above = 0
+    auto exact_select = [&](auto key_fn, auto skip0) {
+        hist_pass(std::integral_constant<int, S1>(), key_fn, skip0, std::false_type());
+        const bool wide = found && B1 == (u32)(kCoarseBins - 1) && (wtop >> S1) > (u32)(kCoarseBins - 1);
+        if (wide) {
+            narrow(S1);
+            hist_pass(std::integral_constant<int, S1 + 4>(), key_fn, skip0, std::integral_constant<bool, DT == 0>());
+        }
+        if (found) single_keys(wide, key_fn, skip0);
     };
     // the hinted bound: accepted when it keeps at least k keys and not many more
     bool hinted = false;
@@ -449,12 +466,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         wtop = kmax;
         hist_pass(std::integral_constant<int, S1>(), all_keys, std::false_type(), std::false_type());
         if (found && B1 == (u32)(kCoarseBins - 1) && (wtop >> S1) > (u32)(kCoarseBins - 1)) {
-            above = c_gt;
-            wtop -= (u32)(kCoarseBins - 1) << S1;
+            narrow(S1);
             S = S1 + 4;
             hist_pass(std::integral_constant<int, S1 + 4>(), all_keys, std::false_type(), std::false_type());
         }
-        c_gt += above;
     }
 
     // ---- asymmetric thresholds: strict set, second selection ------------------------------------
@@ -476,30 +491,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         asm volatile("" : "+v"(wd));
         return (st ^ kOne2) & (gt01(wd & 0x7FFF7FFFu, tau2) ^ kOne2);
     };
-    // fp32: the exact key of rank rank_t among the keys a functor lets through, by histogram passes over
-    // narrowing windows: bins of 2^16 keys, then 2^5 inside the bin found, then single keys (2^20, 2^9, 1
-    // when the values spread over more than 16 octaves).  Starts from wtop with above = 0; on success
-    // wtop - B1 is the key, above + c_gt the number of counted keys above it, cnt1 its multiplicity.
-    auto narrow = [&](int sh_done) { above += c_gt; wtop -= B1 << sh_done; };
-    auto exact_select32 = [&](auto key_fn, auto skip0) {
-        hist_pass(std::integral_constant<int, 16>(), key_fn, skip0, std::false_type());
-        if (!found) return;
-        if (B1 == (u32)(kCoarseBins - 1) && (wtop >> 16) > (u32)(kCoarseBins - 1)) {
-            narrow(16);
-            hist_pass(std::integral_constant<int, 20>(), key_fn, skip0, std::true_type());
-            if (!found) return;
-            narrow(20);
-            hist_pass(std::integral_constant<int, 9>(), key_fn, skip0, std::true_type());
-            if (!found) return;
-            narrow(9);
-        } else {
-            narrow(16);
-            hist_pass(std::integral_constant<int, 5>(), key_fn, skip0, std::true_type());
-            if (!found) return;
-            narrow(5);
-        }
-        hist_pass(std::integral_constant<int, 0>(), key_fn, skip0, std::true_type());
-    };
     u32 tp_key32 = 0, tau_key32 = 0;
     auto strict32 = [&](u32 wd) -> bool { return (wd & 0x7FFFFFFFu) > ((wd >> 31) ? tn_key : tp_key32); };
     auto fill32 = [&](u32 wd) -> bool { return !strict32(wd) && (wd & 0x7FFFFFFFu) <= tau_key32; };
@@ -507,7 +498,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         // tau = the k-th largest magnitude, exactly (the first pass above has run on the same window: redo it
         // as the first level of the exact selection)
         wtop = kmax; above = 0; S = 0;
-        exact_select32(all_keys, std::false_type());     // (finds it: every key is counted)
+        exact_select(all_keys, std::false_type());     // (finds it: every key is counted)
         tau_key32 = wtop - B1;
         const float tau = __uint_as_float(tau_key32);
         tp_key32 = __float_as_uint(__fmul_rn(a.one_plus, tau));
@@ -532,8 +523,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             rank_t = trim ? (u32)(k - 1) : D - 1u;
             wtop = trim ? kmax : tau_key32;
             above = 0;
-            if (trim) exact_select32([&](u32 wd) -> u32 { return strict32(wd) ? wd & 0x7FFFFFFFu : 0u; }, std::true_type());
-            else exact_select32([&](u32 wd) -> u32 { return fill32(wd) ? wd & 0x7FFFFFFFu : 0u; }, std::true_type());
+            if (trim) exact_select([&](u32 wd) -> u32 { return strict32(wd) ? wd & 0x7FFFFFFFu : 0u; }, std::true_type());
+            else exact_select([&](u32 wd) -> u32 { return fill32(wd) ? wd & 0x7FFFFFFFu : 0u; }, std::true_type());
             if (found) {
                 t2_key = wtop - B1;
                 need_ties = rank_t + 1u - (above + c_gt);
@@ -545,7 +536,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     }
     if (ASYM && DT == 1 && k > 0) {
         // (the bins of a second pass hold several keys)
-        const u32 tau_key = found && S == 0 ? wtop - B1 : exact_key((u32)(k - 1), [&](u32 wd, u32 t) -> u32 { return key_flag(wd, t); });
+        if (S != S1) single_keys(true, all_keys, std::false_type());
+        const u32 tau_key = wtop - B1;
         const float tau = __uint_as_float(tau_key << 16);
         const u32 tp_key = __float_as_uint(__fmul_rn(a.one_plus, tau)) >> 16;    // (key << 16) > T  <=>  key > (T >> 16)
         tn_key = __float_as_uint(__fmul_rn(a.one_minus, tau)) >> 16;
@@ -573,19 +565,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             rank_t = trim ? (u32)(k - 1) : D - 1u;
             wtop = trim ? kmax : tau_key;
             above = 0;
-            if (trim) hist_pass(std::integral_constant<int, 0>(), [&](u32 wd) -> u32 { return pk_mul_lo_u16(wd & 0x7FFF7FFFu, strict01(wd)); }, std::true_type(), std::false_type());
-            else hist_pass(std::integral_constant<int, 0>(), [&](u32 wd) -> u32 { return pk_mul_lo_u16(wd & 0x7FFF7FFFu, fill01(wd, strict01(wd))); }, std::true_type(), std::false_type());
+            if (trim) exact_select([&](u32 wd) -> u32 { return pk_mul_lo_u16(wd & 0x7FFF7FFFu, strict01(wd)); }, std::true_type());
+            else exact_select([&](u32 wd) -> u32 { return pk_mul_lo_u16(wd & 0x7FFF7FFFu, fill01(wd, strict01(wd))); }, std::true_type());
             if (found) {
                 t2_key = wtop - B1;
-                need_ties = rank_t + 1u - c_gt;
+                need_ties = rank_t + 1u - (above + c_gt);
                 cnt_ties = cnt1;
-                if (B1 == (u32)(kCoarseBins - 1) && wtop > (u32)(kCoarseBins - 1)) {     // below the window of single keys
-                    auto cand = [&](u32 wd, u32 t) -> u32 { return ((trim ? strict01(wd) : fill01(wd, strict01(wd))) << 15) & key_flag(wd, t); };
-                    t2_key = exact_key(rank_t, cand);
-                    const u32 gt = count_flags([&](u32 wd) -> u32 { return cand(wd, t2_key + 1u); });
-                    need_ties = rank_t + 1u - gt;
-                    cnt_ties = count_flags([&](u32 wd) -> u32 { return cand(wd, t2_key); }) - gt;
-                }
             }                                            // else: the rank lies among zeros, every non-zero candidate is taken
         }
         if (t2_key == 0) { t2_key = 1; need_ties = 0; cnt_ties = 0; }     // the rank falls on zeros (never sent) or every candidate is taken
@@ -631,11 +616,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         } else {
             if (!hinted) mask_plain();
             if ((int)nL > cap) {                     // uniform, rare: the exact cut
-                t_lo = exact_key((u32)(k - 1), [&](u32 wd, u32 t) -> u32 { return key_flag(wd, t); });
+                single_keys(S != S1, all_keys, std::false_type());
+                t_lo = wtop - B1;
                 mask_plain();
                 if (nL > (u32)k)
-                    keep_first((u32)k - count_flags([&](u32 wd) -> u32 { return key_flag(wd, t_lo + 1u); }),
-                               [&](u32 wd) -> u32 { return key_flag(wd, t_lo) & ~key_flag(wd, t_lo + 1u); });
+                    keep_first((u32)k - (above + c_gt), [&](u32 wd) -> u32 { return key_flag(wd, t_lo) & ~key_flag(wd, t_lo + 1u); });
                 scan_mask();
             }
         }
