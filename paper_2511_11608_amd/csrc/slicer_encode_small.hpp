@@ -765,25 +765,48 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     wave_sync();
     auto low_of = [&](u32 at) -> u32 { return DT == 0 ? ~(u32)L.Sp[at] : 0u; };      // fp32: low word of the comp at place `at`
     auto beats = [&](u32 x, u32 xl, u32 y, u32 yl) -> bool { return DT == 0 ? x > y || (x == y && xl > yl) : x > y; };
-    // The member of rank `rem` of c0 places from a0 and c1 places from a1, by the whole wavefront, bit by bit: for bins of many
-    // members (equal or nearly equal values), where comparing all pairs would take c^2 steps.
-    auto wave_select = [&](u32 a0, u32 c0, u32 a1, u32 c1, u32 rem, u32 mask, u32& hi, u32& lo) __attribute__((always_inline)) {
+    // The member of rank `rem` of the c0 places from a0 and the c1 places from a1, all of one bin, by the whole wavefront: for bins
+    // of many members (equal or nearly equal values), where comparing all pairs would take c^2 steps.  Its key bit by bit, over
+    // the bits in which the members' keys differ; then, of the list's entries with this key and class (classes: the class bits
+    // that count), which come in the order of their ranks, the one that is left.  Equal values, as constant or coarsely
+    // quantised rows have them, need no bit and one pass over the list (a bit of key and list position at a time: fp32 [1 x 4096] of one value,
+    // 8 + 8 blocks, 314 us, now 44).
+    auto wave_select = [&](u32 a0, u32 c0, u32 a1, u32 c1, u32 rem, u32 classes, u32 cls, u32& hi, u32& lo) __attribute__((always_inline)) {
+        auto key_at = [&](u32 i) -> u32 { return word_key(L.S[i < c0 ? a0 + i : a1 + (i - c0)]); };
         auto count = [&](auto take) -> u32 {
             u32 n = 0;
-            for (u32 i = lane; i < c0 + c1; i += kWave) n += take(i < c0 ? a0 + i : a1 + (i - c0)) ? 1u : 0u;
+            for (u32 i = lane; i < c0 + c1; i += kWave) n += take(key_at(i)) ? 1u : 0u;
             return wave_sum(n);
         };
-        hi = 0; lo = 0;
-        for (u32 bit = kPos; bit; bit >>= 1) {
-            const u32 t = hi | bit;
-            if (count([&](u32 at) -> bool { return (L.S[at] & mask) >= t; }) > rem) hi = t;
-        }
-        if (DT == 0) {
-            const u32 v = hi, up = count([&](u32 at) -> bool { return (L.S[at] & mask) > v; });
-            for (u32 bit = kPos; bit; bit >>= 1) {
-                const u32 t = lo | bit;
-                if (up + count([&](u32 at) -> bool { return (L.S[at] & mask) == v && low_of(at) >= t; }) > rem) lo = t;
+        u32 mx = 0, inv = 0;                        // largest key, complement of the smallest
+        for (u32 i = lane; i < c0 + c1; i += kWave) { const u32 x = key_at(i); mx = max(mx, x); inv = max(inv, ~x); }
+        u32 key = wave_max_dpp(mx), left = rem;
+        const u32 differ = key ^ ~wave_max_dpp(inv);
+        if (differ) {
+            u32 bit = 0x80000000u >> __clz((int)differ);
+            key &= ~(2u * bit - 1u);
+            for (; bit; bit >>= 1) {
+                const u32 t = key | bit;
+                if (count([&](u32 x) -> bool { return x >= t; }) > rem) key = t;
             }
+            left -= count([&](u32 x) -> bool { return x > key; });
+        }
+        hi = 0; lo = 0;
+        u32 entries = nL;
+        asm volatile("" : "+s"(entries));           // (or the slots' lane masks would be held for the whole row)
+#pragma unroll(MAXS ? MAXS : 1)
+        for (int s = 0; s < SLN; ++s) {
+            if (s >= nslots) break;
+            const u32 x = ent_word(s);
+            const bool is = (int)lane < (int)entries - s * kWave && word_key(x) == key && (x & classes) == cls;
+            const u64 m = __ballot(is);
+            const u32 c = (u32)__popcll(m);
+            if (left < c) {
+                const int l = (int)__builtin_ctzll(__ballot(is && mask_rank(m) == left));
+                hi = bcast(x, l); lo = ~(u32)(s * kWave + l);
+                break;
+            }
+            left -= c;
         }
     };
 
@@ -814,7 +837,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             thrK = bcast(me, hl);
             if (DT == 0) { thrK_lo = bcast(ml, hl); eq_keys = __popcll(__ballot(in && me == thrK)) > 1; }
         } else {
-            wave_select(sp, cp, sn, cnt - cp, rem, kMag, thrK, thrK_lo);
+            wave_select(sp, cp, sn, cnt - cp, rem, 0u, 0u, thrK, thrK_lo);
+            thrK &= kMag;
             eq_keys = true;
             u32 n = 0;
             for (u32 i = lane; i < cp; i += kWave) n += beats(thrK, thrK_lo, L.S[sp + i] & kMag, low_of(sp + i)) ? 0u : 1u;
@@ -867,7 +891,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         for (u64 wide = __ballot(sub == 0 && cn > kWide); wide; wide &= wide - 1ull) {
             const int l = (int)__builtin_ctzll(wide);
             u32 vh, vl;
-            wave_select(bcast(st, l), bcast(cn, l), 0u, 0u, bcast(rem, l), ~0u, vh, vl);
+            wave_select(bcast(st, l), bcast(cn, l), 0u, 0u, bcast(rem, l), kPos, bcast(cls ? 0u : kPos, l), vh, vl);
             if (lane == 0) { thr[l >> lg] = vh; if (DT == 0) L.thr_lo[l >> lg] = vl; }
             eq = eq || DT == 0;
         }
