@@ -812,7 +812,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
 
     // ---- top-K cut: the comp of overall rank k-1 (ATKF) -----------------------------------------
     u32 thrK = 0, thrK_lo = 0;                      // without the class bit; every entry of L is kept when nL <= k
-    bool eq_keys = false;                           // fp32: equal keys on both sides of the cut or of a boundary: the low words decide
+    bool eq_cut = false;                            // fp32: equal keys on both sides of the cut: the low words decide
     if (nL > (u32)k) {
         // open the bins of the lane found by the scan: the first one that ends behind rank k-1
         const int hi = FB - cut_lane * BPL;
@@ -835,11 +835,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             kn -= kp;
             const int hl = (int)__builtin_ctzll(__ballot(in && gt == rem));
             thrK = bcast(me, hl);
-            if (DT == 0) { thrK_lo = bcast(ml, hl); eq_keys = __popcll(__ballot(in && me == thrK)) > 1; }
+            if (DT == 0) { thrK_lo = bcast(ml, hl); eq_cut = __popcll(__ballot(in && me == thrK)) > 1; }
         } else {
             wave_select(sp, cp, sn, cnt - cp, rem, 0u, 0u, thrK, thrK_lo);
             thrK &= kMag;
-            eq_keys = true;
+            eq_cut = true;
             u32 n = 0;
             for (u32 i = lane; i < cp; i += kWave) n += beats(thrK, thrK_lo, L.S[sp + i] & kMag, low_of(sp + i)) ? 0u : 1u;
             kp = wave_sum(n);
@@ -857,6 +857,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     // lanes dealt to (boundary, member) pairs took 356 vector instructions a row of 16 blocks (bf16 [16384 x 4096]), this takes 118.
     const int ntg = B2 - 2;
     u32* thr = L.thr;
+    u64 eq_thr = 0;                                 // fp32: boundaries with equal keys on both sides (bit t << lg): the low words decide
     if (ntg > 0) {
         constexpr u32 kWide = 32;                   // members from which on wave_select takes fewer steps
         const int lg = a.lg;                        // log2 of the lanes per boundary
@@ -871,7 +872,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         const u32 st = __builtin_amdgcn_ubfe(L.hist[bin_word(bin + 1u)], hf, 16u);
         const u32 cn = act ? __builtin_amdgcn_ubfe(L.hist[bin_word(bin)], hf, 16u) - st : 0u, rem = R - st;
         if (mine && !act && sub == 0) { thr[t] = cls ? kMag : ~0u; if (DT == 0) L.thr_lo[t] = ~0u; }
-        bool eq = DT == 0 && mine && !act && (cls ? n_neg : n_pos) > 0u;
+        bool eq = DT == 0 && mine && !act && kmax == kMag;      // (no finite value is equal to the boundary above a class)
         if (cn <= kWide) {
             // entries behind the bin's end belong to lower bins or to the negative class or are zeros: none lies above a member
             for (u32 i = sub; i < cn; i += 1u << lg) {
@@ -893,9 +894,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             u32 vh, vl;
             wave_select(bcast(st, l), bcast(cn, l), 0u, 0u, bcast(rem, l), kPos, bcast(cls ? 0u : kPos, l), vh, vl);
             if (lane == 0) { thr[l >> lg] = vh; if (DT == 0) L.thr_lo[l >> lg] = vl; }
-            eq = eq || DT == 0;
+            eq = eq || (DT == 0 && (int)lane == l);
         }
-        if (DT == 0) eq_keys = eq_keys || __ballot(eq) != 0ull;
+        // (a boundary's lanes: the one that found its member, moved to the lowest)
+        if (DT == 0)
+            for (u64 found_by = __ballot(eq); found_by; found_by &= found_by - 1ull) eq_thr |= 1ull << (__builtin_ctzll(found_by) >> lg << lg);
     }
 
     // block starts in closed form (K, ..., K, K + remainder per class)
@@ -943,10 +946,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     };
     auto is_kept = [&](int s, u32 cx) -> bool {
         bool kept = in_list(s) && (cx & kMag) >= thrK;
-        if (DT == 0 && eq_keys) kept = kept && !beats(thrK, thrK_lo, cx & kMag, ~(u32)(s * kWave + (int)lane));
+        if (DT == 0 && eq_cut) kept = kept && !beats(thrK, thrK_lo, cx & kMag, ~(u32)(s * kWave + (int)lane));
         return kept;
     };
-    if (M == 8 && Mn == 8 && !(DT == 0 && eq_keys)) {
+    if (M == 8 && Mn == 8 && !(DT == 0 && eq_thr)) {
         // 8 + 8 blocks: the 14 boundaries and the class bit are 15 separators in descending order; four compares walk them
         // as a binary tree (the first is the class bit itself).  Their outcomes are the bits of the block number, and
         // the compares' lane masks the ballots that the ranks inside a block need (split 604 -> 503 vector instructions a row,
@@ -987,8 +990,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
 #pragma unroll
             for (int j = 0; j < kRegThr; ++j) b += tx[j] > cx ? 1u : 0u;
             for (int j = kRegThr; j < ntg; ++j) b += thr[j] > cx ? 1u : 0u;
-            if (DT == 0 && eq_keys)                  // boundaries of the same key
-                for (int j = 0; j < ntg; ++j) b += thr[j] == cx && L.thr_lo[j] > ~(u32)(s * kWave + (int)lane) ? 1u : 0u;
+            if (DT == 0)                             // boundaries of the same key, one or two in most rows that have any
+                for (u64 m = eq_thr; m; m &= m - 1ull) {
+                    const int j = (int)__builtin_ctzll(m) >> a.lg;
+                    b += thr[j] == cx && L.thr_lo[j] > ~(u32)(s * kWave + (int)lane) ? 1u : 0u;
+                }
             // one ballot per bit of the block number
             const u64 km = __ballot(kept);
             u32 plo = (u32)km, phi = (u32)(km >> 32);
