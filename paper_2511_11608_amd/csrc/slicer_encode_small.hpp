@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     // LDS address); the pass then reports found = false when the rank lies beyond the counted keys
     // windowed (fp32 narrowing passes): keys above the window or below its 2048 bins are not counted at all
     // (they would all meet on the first or the last bin's LDS address); `above` then only enters the rank
-    auto hist_pass = [&](auto shift, auto key_pair, auto skip0, auto windowed) {
+    auto hist_pass = [&](auto shift, auto key_pair, auto skip0, auto windowed) __attribute__((always_inline)) {
         constexpr int SH = decltype(shift)::value;
         constexpr bool kSkip0 = decltype(skip0)::value;
         constexpr bool kWindowed = decltype(windowed)::value;
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     uint16_t* plist = (MAXS || DT == 1) ? (uint16_t*)(smem + 2 * EPL + 4) : L.Lidx;      // row positions of the list's entries
     u32 t_lo = 1u, nL = 0, mk[NM], pos0 = 0;        // pos0: entries of the lanes below
     // flag(word): bf16: bits 15 and 31 set where the word's elements are taken; fp32: bit 31
-    auto row_mask = [&](auto flag) {
+    auto row_mask = [&](auto flag) __attribute__((always_inline)) {
         unsigned char* mb = (unsigned char*)smem;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         }
         wave_sync();
     };
-    auto scan_mask = [&]() {
+    auto scan_mask = [&]() __attribute__((always_inline)) {
         u32 n1 = 0;
 #pragma unroll
         for (int i = 0; i < NM; ++i) n1 += (u32)__popc(mk[i]);
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     auto key_flag = [&](u32 wd, u32 t) -> u32 {
         return (wd & (DT == 0 ? 0x7FFFFFFFu : 0x7FFF7FFFu)) + (DT == 0 ? 0x80000000u - t : (0x8000u - t) * 0x10001u);
     };
-    auto mask_plain = [&]() {                       // every key at or above t_lo
+    auto mask_plain = [&]() __attribute__((always_inline)) {                       // every key at or above t_lo
         row_mask([&](u32 wd) -> u32 { return key_flag(wd, t_lo); });
         scan_mask();
     };
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     // values spread over more than 16 octaves): fp32 bins of 2^5 keys (2^9), then single keys; bf16 single keys from
     // wide bins, where a pass without them has found the key already.
     auto narrow = [&](int sh_done) { above += c_gt; wtop -= B1 << sh_done; };
-    auto single_keys = [&](bool wide, auto key_fn, auto skip0) {
+    auto single_keys = [&](bool wide, auto key_fn, auto skip0) __attribute__((always_inline)) {
         if (DT == 0) {
             if (wide) {
                 narrow(20);
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         }
     };
     // from wtop with above = 0
-    auto exact_select = [&](auto key_fn, auto skip0) {
+    auto exact_select = [&](auto key_fn, auto skip0) __attribute__((always_inline)) {
         hist_pass(std::integral_constant<int, S1>(), key_fn, skip0, std::false_type());
         const bool wide = found && B1 == (u32)(kCoarseBins - 1) && (wtop >> S1) > (u32)(kCoarseBins - 1);
         if (wide) {
@@ -615,7 +615,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             scan_mask();
         } else {
             if (!hinted) mask_plain();
-            if ((int)nL > cap) {                     // uniform, rare: the exact cut
+            if (__builtin_expect((int)nL > cap, 0)) {       // uniform, rare: the exact cut
                 single_keys(S != S1, all_keys, std::false_type());
                 t_lo = wtop - B1;
                 mask_plain();
@@ -823,7 +823,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         const u32 sp = wu >> 16, sn = wu & 0xFFFFu, cp = (wd >> 16) - sp, cnt = cp + (wd & 0xFFFFu) - sn;
         const u32 rem = (u32)(k - 1) - (sp + sn - nLp);
         u32 kp, kn;                                 // members that stay
-        if (cnt <= (u32)kWave) {
+        if (__builtin_expect(cnt <= (u32)kWave, 1)) {
             const bool in = lane < cnt;
             const u32 at = in ? (lane < cp ? sp + lane : sn + lane - cp) : 0u;
             const u32 me = in ? L.S[at] & kMag : 0u, ml = in ? low_of(at) : 0u;
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
                 if (gt == rem) { thr[t] = me; if (DT == 0) { L.thr_lo[t] = ml; eq = same > 1u; } }
             }
         }
-        for (u64 wide = __ballot(sub == 0 && cn > kWide); wide; wide &= wide - 1ull) {
+        for (u64 wide = __ballot(sub == 0 && cn > kWide); __builtin_expect(wide != 0ull, 0); wide &= wide - 1ull) {
             const int l = (int)__builtin_ctzll(wide);
             u32 vh, vl;
             wave_select(bcast(st, l), bcast(cn, l), 0u, 0u, bcast(rem, l), kPos, bcast(cls ? 0u : kPos, l), vh, vl);
@@ -898,7 +898,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         }
         // (a boundary's lanes: the one that found its member, moved to the lowest)
         if (DT == 0)
-            for (u64 found_by = __ballot(eq); found_by; found_by &= found_by - 1ull) eq_thr |= 1ull << (__builtin_ctzll(found_by) >> lg << lg);
+            for (u64 found_by = __ballot(eq); __builtin_expect(found_by != 0ull, 0); found_by &= found_by - 1ull) eq_thr |= 1ull << (__builtin_ctzll(found_by) >> lg << lg);
     }
 
     // block starts in closed form (K, ..., K, K + remainder per class)
@@ -946,7 +946,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     };
     auto is_kept = [&](int s, u32 cx) -> bool {
         bool kept = in_list(s) && (cx & kMag) >= thrK;
-        if (DT == 0 && eq_cut) kept = kept && !beats(thrK, thrK_lo, cx & kMag, ~(u32)(s * kWave + (int)lane));
+        if (DT == 0 && __builtin_expect(eq_cut, 0)) kept = kept && !beats(thrK, thrK_lo, cx & kMag, ~(u32)(s * kWave + (int)lane));
         return kept;
     };
     if (M == 8 && Mn == 8 && !(DT == 0 && eq_thr)) {
@@ -991,7 +991,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             for (int j = 0; j < kRegThr; ++j) b += tx[j] > cx ? 1u : 0u;
             for (int j = kRegThr; j < ntg; ++j) b += thr[j] > cx ? 1u : 0u;
             if (DT == 0)                             // boundaries of the same key, one or two in most rows that have any
-                for (u64 m = eq_thr; m; m &= m - 1ull) {
+                for (u64 m = eq_thr; __builtin_expect(m != 0ull, 0); m &= m - 1ull) {
                     const int j = (int)__builtin_ctzll(m) >> a.lg;
                     b += thr[j] == cx && L.thr_lo[j] > ~(u32)(s * kWave + (int)lane) ? 1u : 0u;
                 }
