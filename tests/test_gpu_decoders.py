@@ -128,3 +128,11 @@ def test_older_errors_cost_no_header_slot(oracle):
     decode()
     check_values()
     assert fastest() < 1.5 * before                  # the copy and the wait take twice as long
+
+
+@pytest.mark.parametrize("dtype,rows,n_rows,n_cols,keep,M", [("f32", 2, 40000, 2, 0.1, 8), ("bf16", 3, 2048, 49, 0.1, 64), ("f32", 40, 512, 49, 0.1, 8), ("f32", 1, 100000, 3, 0.05, 16),
+                                                             ("f32", 9, 9000, 1, 0.2, 2), ("f32", 12, 512, 784, 0.1, 16), ("f32", 1, 100, 7, 0.2, 4)])
+def test_windows_of_row_pointers(oracle, dtype, rows, n_rows, n_cols, keep, M):
+    """Encoders' windows of 128 to 1024 words of pointers, walked and searched, before and behind the windows of codes; instances of a few
+    elements a tensor row for the decoder."""
+    check_csr(oracle, features(dtype, rows, n_rows * n_cols), dtype, n_rows, n_cols, keep, M, B28, 1e-3)
