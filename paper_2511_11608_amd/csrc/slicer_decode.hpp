@@ -280,10 +280,12 @@ __global__ __launch_bounds__(256) void meta_check_kernel(CheckArgs a)
 //
 // What bounds it: a chain of dependent reads (counts, pointers, fields) per workgroup, so what counts is how many
 // wavefronts share a CU and how few steps the chain has.  A thread takes a run of consecutive entries: it finds block
-// and tensor row of the first one and then moves on with them, four entries' fields in flight; prefixes
+// and tensor row of the first one and then moves on with them; prefixes
 // over the blocks are scans of one wavefront; the image is cleared and stored 16 bytes at a time; neighbouring workgroups,
 // which read neighbouring fields of every block, run on one XCD.  (One thread adding up the blocks, every entry searching its
-// block and row by itself and 45 KB of LDS: fp32 [32 x 512 x 784] 58 us, now 23.)
+// block and row by itself and 45 KB of LDS: fp32 [32 x 512 x 784] 59 us, now 21.6.)  Small instances take as long as the code between their few
+// loads: with the fields of four entries in flight, six row pointers at a time and 16-byte stores for rows of a few elements, fp32 [100 x 7]
+// took 4.40 us instead of 3.91 and [512 x 49] 4.72 instead of 4.60; now 3.89 and 4.30.
 struct DecCsrArgs {
     const u32* stream;
     void* y;
@@ -363,15 +365,8 @@ __global__ __launch_bounds__(kCsrThreads) void dec_csr_kernel(DecCsrArgs a)
     }
     __syncthreads();
     if (tid < B2) {
-        u32 run = 0;
-        for (int j0 = 0; j0 <= nr; j0 += 6) {        // six reads in flight
-            u32 v[6];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) v[j] = j0 + j <= nr ? ptrs[tid * PR + j0 + j] : 0u;
-#pragma unroll
-            for (int j = 0; j < 6; ++j)
-                if (j0 + j <= nr) { run = v[j] > run ? v[j] : run; ptrs[tid * PR + j0 + j] = run; }
-        }
+        u32 run = ptrs[tid * PR];
+        for (int j = 1; j <= nr; ++j) { const u32 x = ptrs[tid * PR + j]; run = x > run ? x : run; ptrs[tid * PR + j] = run; }
     }
     __syncthreads();
     if (tid < kWave)
@@ -396,37 +391,25 @@ __global__ __launch_bounds__(kCsrThreads) void dec_csr_kernel(DecCsrArgs a)
             }
             u32 end = pre[b + 1], shift = ptrs[b * PR] - pre[b], bend = ptrs[b * PR + 1];
             int row = 0;
-            for (; t < t1; t += 4) {
-                u32 col[4], cd[4];
-                int bb[4], at[4];
-#pragma unroll
-                for (u32 u = 0; u < 4; ++u) {
-                    bb[u] = -1; col[u] = 0; cd[u] = 0; at[u] = 0;
-                    if (t + u >= t1) continue;
-                    if (t + u >= end) {
-                        do { ++b; end = pre[b + 1]; } while (t + u >= end);
-                        shift = ptrs[b * PR] - pre[b]; bend = ptrs[b * PR + 1];
-                        row = 0;
-                    }
-                    const u32 p = t + u + shift;
-                    while (p >= bend && row + 1 < nr) { ++row; bend = ptrs[b * PR + row + 1]; }
-                    bb[u] = b; at[u] = row * len;
-                    col[u] = read_bits(rw, ptr_bits + (u64)(istart[b] + p) * (u64)wc, wc);
-                    cd[u] = read_bits(rw, cstart[b] + (u64)p * qv[b], (int)qv[b]);
+            for (; t < t1; ++t) {
+                if (t >= end) {
+                    do { ++b; end = pre[b + 1]; } while (t >= end);
+                    shift = ptrs[b * PR] - pre[b]; bend = ptrs[b * PR + 1];
+                    row = 0;
                 }
-#pragma unroll
-                for (u32 u = 0; u < 4; ++u) {
-                    const int64_t c = (int64_t)col[u] - c0;
-                    if (bb[u] < 0 || c < 0 || c >= len) continue;
-                    float v = __fadd_rn(vminf[bb[u]], __fmul_rn((float)cd[u], stepf[bb[u]]));
-                    if (bb[u] >= M) v = -v;
-                    tile[at[u] + (int)c] = DT == 0 ? (raw_t)__float_as_uint(v) : (raw_t)f32_to_bf16_rne(v);
-                }
+                const u32 p = t + shift;
+                while (p >= bend && row + 1 < nr) { ++row; bend = ptrs[b * PR + row + 1]; }
+                const int64_t c = (int64_t)read_bits(rw, ptr_bits + (u64)(istart[b] + p) * (u64)wc, wc) - c0;
+                const u32 cd = read_bits(rw, cstart[b] + (u64)p * qv[b], (int)qv[b]);
+                if (c < 0 || c >= len) continue;
+                float v = __fadd_rn(vminf[b], __fmul_rn((float)cd, stepf[b]));
+                if (b >= M) v = -v;
+                tile[row * len + (int)c] = DT == 0 ? (raw_t)__float_as_uint(v) : (raw_t)f32_to_bf16_rne(v);
             }
         }
         __syncthreads();
         raw_t* __restrict__ out = yrow + c0;         // (nr > 1: c0 = 0, whole rows, contiguous in y)
-        if (((uintptr_t)out & 15u) == 0) {
+        if (img > 2 * TH && ((uintptr_t)out & 15u) == 0) {
             const int n16 = img * ESZ / 16;
             for (int i = tid; i < n16; i += TH) {
                 const uint4 v = dec_smem[i];
