@@ -163,16 +163,20 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
         p.small_maxs = maxs;
     }
     // One workgroup per row (the wavefronts of a workgroup share the row): every row of more than 4096 and up to
-    // 32768 bf16 / 16384 fp32 elements, but for bf16 rows of up to 8192 in batches of more than 256 whose list has at most 768
-    // entries.  One wavefront per row does less work in all, and takes longer for a single row; the longer the list, the
-    // longer.  Encode us, workgroup / wavefront: such lists [300 x 5120] 22.1 / 19.2, [512 x 8192] 22.1 / 20.7, [2048 x 8192]
-    // 39.6 / 25.0; but [256 x 8192] 18 / 21, and longer lists [512 x 8192] 24.1 / 26.9, [4096 x 6144], 1228 kept, 80 / 81.
+    // 32768 bf16 / 16384 fp32 elements, but for bf16 rows of up to 8192 whose list has at most 768 entries, in large batches.  One
+    // wavefront per row does less work in all, and takes longer for a single row: the longer, the longer the list and the more
+    // blocks.  Encode us, workgroup / wavefront, 8 + 8 blocks: [300 x 5120], 256 kept, 20.4 / 15.2, [512 x 8192], 409 kept, 21.5 / 18.3,
+    // [2048 x 8192] 39 / 24; but [256 x 8192] 18 / 21, and lists of more entries [512 x 8192] 24.1 / 26.9, [4096 x 6144], 1228 kept, 80 / 81.
+    // 16 + 16 blocks: [512 x 8192], 163 kept, 0.88 of the workgroup's time, 327 kept 1.14, and with 1024 rows 0.96; 24 + 24 and 32 + 32 blocks:
+    // [257 x 5120], 51 kept, 0.95 and 0.99, 256 kept 1.20; [1500 x 6144], 245 kept, 0.97, 430 kept 1.03 and 1.08; with 2048 rows 0.60 to 0.84.
     p.wg_ept = 0; p.wg_nw = 0; p.wg_cap = 0; p.wg_region0 = 0; p.wg_lds_bytes = 0;
     const int64_t wg_lds = lists_fit ? 4 * (int64_t)wg_lds_words(dt, (int)cap, (int)wg_region0, B2_all) : 0;
     auto wg_holds = [&](int64_t elements) {
         return lists_fit && elements > 4096 && elements <= (dt == SLICER_F32 ? 16384 : 32768) && wg_lds <= 64 * 1024;
     };
-    const bool one_wave = p.small_epl && cap <= 768 && rows > kScanRows;
+    const int64_t few = B2_all <= 16 || (B2_all <= 32 && p.k <= 256) || p.k <= 64 ? kScanRows
+                      : B2_all <= 32 ? 768 : p.k <= 256 ? 1024 : 2047;            // rows up to which the workgroup is faster
+    const bool one_wave = p.small_epl && cap <= 768 && rows > few;
     if (wg_holds(span) && !one_wave) {
         // wavefronts per row: sixteen for the smallest batches (more wavefronts per SIMD hide each other's
         // latencies: 4 % less latency per call), four otherwise (a 256-row batch on sixteen leaves no room

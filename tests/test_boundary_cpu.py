@@ -83,6 +83,16 @@ def test_encode_path_by_shape(lib):
     assert binding.slicer_encode_path(binding.SLICER_F32, 3, 4097, 0.5, 3, B) == 0           # odd length
 
 
+@pytest.mark.parametrize("rows,N,keep,M,path", [
+    (257, 8192, 0.05, 8, 1), (256, 8192, 0.05, 8, 3), (257, 8192, 0.0625, 8, 1), (257, 8192, 0.0627, 8, 3),      # batch; 512 kept + 256 = 768 list entries, 513 kept
+    (257, 4097, 0.1, 8, 1), (257, 8184, 0.05, 8, 1), (257, 8193, 0.05, 8, 3), (257, 8191, 0.05, 8, 3),            # (8191 may start inside a chunk)
+    (257, 8192, 0.0313, 16, 1), (768, 8192, 0.0315, 16, 3), (769, 8192, 0.0315, 16, 1),                           # 32 blocks: 256 entries, or 769 rows
+    (257, 8192, 0.0079, 32, 1), (1024, 8192, 0.008, 32, 3), (1025, 8192, 0.008, 32, 1), (2047, 8192, 0.05, 32, 3), (2048, 8192, 0.05, 32, 1)])
+def test_one_wavefront_or_one_workgroup_per_row(lib, rows, N, keep, M, path):
+    from paper_2511_11608_amd import binding, synth
+    assert binding.slicer_encode_path(binding.SLICER_BF16, rows, N, keep, M, synth.BITS_2_TO_8) == path
+
+
 @pytest.mark.parametrize("dt", [0, 1])
 def test_long_rows_up_to_two_to_the_23(lib, dt):
     """The stages of many workgroups per row take rows of up to 2^23 elements, in every batch size."""
