@@ -149,8 +149,8 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     const int64_t cap = std::min<int64_t>(1984, (p.k + margin + 63) / 64 * 64);   // ranks are 11-bit fields
     const bool lists_fit = B2_all <= kWave && p.k + 64 <= cap;
     const int maxs = cap <= 256 ? 4 : cap <= 640 ? 10 : cap <= 1280 ? 20 : 0;             // list held in registers
-    const int64_t region0 = lists_fit ? small_region0_words(p.k, p.cap_words, B2_all, nq, (int)cap, small_fine_bins(maxs)) : 0;
-    const int64_t wg_region0 = lists_fit ? small_region0_words(p.k, p.cap_words, B2_all, nq, (int)cap, kFineBins) : 0;
+    const int64_t region0 = lists_fit ? small_region0_words(dt, p.k, p.cap_words, B2_all, nq, (int)cap, small_fine_bins(maxs)) : 0;
+    const int64_t wg_region0 = lists_fit ? wg_region0_words(p.k, p.cap_words, B2_all, nq) : 0;
     const int64_t small_lds = lists_fit ? 4 * (int64_t)small_lds_words(dt, (int)cap, (int)region0, B2_all, maxs) : 0;
     auto small_holds = [&](int64_t elements) { return lists_fit && elements <= (dt == SLICER_F32 ? 4096 : 8192) && small_lds <= 64 * 1024; };
     if (small_holds(span)) {
@@ -401,8 +401,8 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     ea.one_plus = 1.0f + (float)lambda;
     ea.one_minus = 1.0f - (float)lambda;
 
-    // asymmetric thresholds need a second selection over a subset of the row: the generic kernel has it for
-    // every shape, the row-resident kernel for bf16 rows (rows it flags are redone generically, same rule)
+    // asymmetric thresholds need a second selection over a subset of the row: the one-wavefront kernel has it for every row that
+    // it holds, the generic kernel for every shape
     const bool use_wg = p.wg_ept && !asym && on_elements;
     if (use_wg) {
         // one workgroup per row; rows it cannot hold are flagged and redone by the generic kernel

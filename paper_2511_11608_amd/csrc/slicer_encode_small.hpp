@@ -92,12 +92,14 @@ __host__ __device__ constexpr int small_fine_bins(int maxs) { return maxs == 4 ?
 
 // LDS carve-up of one wave (word offsets); small_lds_words() on the host must match.
 // The coarse histogram (2048 16-bit counters) overlays everything: nothing else is live before the
-// compaction.  Region 0 is the fine histogram first; once the boundaries are known it holds
-// the block-ordered indices, the stream image, the ABQ sums and the quantiser scales.
+// compaction.  Region 0 is the fine histogram and fp32's list positions first; once the boundaries are known it holds
+// the block-ordered indices, the stream image, the ABQ sums and the quantiser scales.  With the positions in a place of their
+// own and room for sums that lanes keep in registers, long fp32 lists cost a CU one or two of its wavefronts: fp32 [2048 x 4096]
+// keep 0.25, 16 + 16 blocks, all 16 bitwidths 88.4 us of encode at seven a CU, 56.7 at eleven.
 struct SmallLds {
-    u32* hist;      // [region0]   fine histogram and a word for the bin above it; later bo_idx, stream image, sums, invt
+    u32* hist;      // [region0]   fine histogram and a word for the bin above it, Sp; later bo_idx, stream image, sums, invt
     u32* S;         // [cap + 4]   entries arranged by class and fine bin (bf16: comp; fp32: its key word), then zeros; later bo_val
-    uint16_t* Sp;   // [cap + 4]   fp32 only: the entry's list position
+    uint16_t* Sp;   // [cap + 4]   fp32 only, in region 0: the list position of the entry in S
     u32* thr;       // [B2]        block boundaries (class-extended comps; fp32: their key words), positive class first
     u32* thr_lo;    // [B2]        fp32 only: the low words
     u32* Lent;      // [cap]       MAXS = 0 only: list entries, ascending index (as `ent` in the kernel)
@@ -109,20 +111,23 @@ struct SmallLds {
     u32* run;       // [B2]        next free position of the block; later the chosen bitwidth index
 };
 
-// words of region 0: the row's bit mask (at most 2 * 128 words) and list positions, then the fine histogram, then indices +
-// stream image + sums + scales
-__host__ __device__ inline int small_region0_words(int64_t k, u64 cap_words, int B2, int nq, int cap, int bins)
+// 64-bit sums of a block in LDS: the energy, and one for each bitwidth where several lanes add to it (blocks of sixteen lanes or more)
+__host__ __device__ inline int small_block_sums(int B2, int nq) { return kWave / B2 >= 16 ? nq + 1 : 1; }
+
+// words of region 0: the row's bit mask (at most 2 * 128 words) and list positions, then the fine histogram and fp32's Sp, then
+// indices + stream image + sums + scales
+__host__ __device__ inline int small_region0_words(int dt, int64_t k, u64 cap_words, int B2, int nq, int cap, int bins)
 {
-    const int64_t late = (((k + 1) / 2 + (int64_t)cap_words + 1) & ~(int64_t)1) + 2 * B2 * (nq + 1) + B2 * nq;
-    const int64_t early = 2 * 128 + 4 + cap / 2;
-    int64_t r0 = late > bins + 1 ? late : bins + 1;
+    const int64_t late = (((k + 1) / 2 + (int64_t)cap_words + 1) & ~(int64_t)1) + 2 * B2 * small_block_sums(B2, nq) + B2 * nq;
+    const int64_t early = 2 * 128 + 4 + cap / 2, fine = bins + 4 + (dt == 0 ? (cap + 4) / 2 : 0);
+    int64_t r0 = late > fine ? late : fine;
     r0 = r0 > early ? r0 : early;
     return (int)((r0 + 3) & ~(int64_t)3);
 }
 
 __host__ __device__ inline int small_lds_words(int dt, int cap, int region0, int B2, int maxs)
 {
-    int wds = region0 + (cap + 4) + (dt == 0 ? (cap + 4) / 2 : 0);
+    int wds = region0 + (cap + 4);
     wds += B2 + (dt == 0 ? B2 : 0);
     wds += maxs ? 0 : cap + (dt == 0 ? cap / 2 : 0);
     wds += 16 + (B2 + 1) + B2 * 3;
@@ -151,7 +156,7 @@ __device__ inline SmallLds small_carve(u32* base, int dt, int cap, int region0, 
     u32* p = base;
     L.hist = p;            p += region0;           // a multiple of four words
     L.S = p;               p += cap + 4;
-    L.Sp = (uint16_t*)p;   p += dt == 0 ? (cap + 4) / 2 : 0;
+    L.Sp = (uint16_t*)(base + small_fine_bins(maxs) + 4);
     L.thr = p;             p += B2;
     L.thr_lo = p;          p += dt == 0 ? B2 : 0;
     L.Lent = p;            p += maxs ? 0 : cap;
@@ -1016,7 +1021,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
     // LDS atomics, four lanes on an address: 312 of a row's 1486 busy cycles of the LDS (16 blocks) and 645 * 4 cycles of
     // waiting (kernel, bf16 [16384 x 4096]: 80.4 -> 75.8 us, fp32 [12608 x 768]: 42.6 -> 39.8).  The energy, and later the packing, share the block's entries out.
     u64* sums = (u64*)(L.hist + ((((k + 1) / 2 + (int)a.cap_words) + 1) & ~1));
-    float* invt = (float*)(sums + B2 * (nq + 1));
+    const int ns = small_block_sums(B2, nq);         // a block's sums; the last one is its energy
+    float* invt = (float*)(sums + B2 * ns);
     const u32 lpb = (u32)a.lpb;
     const u32 myb = udiv16(lane, lpb), sub = lane - myb * lpb;
     const bool lane_on = myb < (u32)B2;
@@ -1052,7 +1058,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
             invt[myb * (u32)nq + t] = dg ? 0.f : Lq / rng1;
         }
         if (sub == 0) {
-            sums[myb * (nq + 1) + nq] = 0;
+            sums[myb * ns + ns - 1] = 0;
             // budget guard: index of the chosen bitwidth, nq = none feasible yet; DS guard: mask of violations
             L.run[myb] = (mycnt && !dg && a.guard == 0) ? (u32)nq : 0u;
         }
@@ -1067,7 +1073,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         const u32 per = es > 1u ? udiv16(mycnt + es - 1u, es) : mycnt, T2 = es > 1u ? udiv16(maxb + es - 1u, es) : maxb;
         const AbqSlice slice = small_abq_slice(bs0, mycnt, per, sl, active);
         const u32 q0 = slice.q0, qn = slice.qn;
-        if (es > 1u && active) for (u32 t = ct + 8u * sl; t < (u32)nq; t += 8u * es) sums[myb * (nq + 1) + t] = 0;
+        if (es > 1u && active) for (u32 t = ct + 8u * sl; t < (u32)nq; t += 8u * es) sums[myb * ns + t] = 0;
         double rhs = 0.0;
         if (a.guard == 0) {
             u64 accE = 0;
@@ -1083,9 +1089,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
                     accE += (u64)A * (u64)A;
                 }
             }
-            if (accE) atomicAdd(&sums[myb * (nq + 1) + nq], accE);
+            if (accE) atomicAdd(&sums[myb * ns + ns - 1], accE);
             wave_sync();
-            if (lane_on) rhs = a.beta * ldexp((double)sums[myb * (nq + 1) + nq], 2 * e - 40);
+            if (lane_on) rhs = a.beta * ldexp((double)sums[myb * ns + ns - 1], 2 * e - 40);
         }
         auto decide = [&](u32 t, u64 sum) __attribute__((always_inline)) {          // (mycnt > 0 and a range above 0)
             if (a.guard == 1) {
@@ -1176,7 +1182,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
 #pragma unroll
                 for (int u = 0; u < NCU; ++u) {
                     if (tt[u] == ~0u) continue;
-                    if (es > 1u) atomicAdd(&sums[myb * (nq + 1) + tt[u]], tot[u]); else decide(tt[u], tot[u]);
+                    if (es > 1u) atomicAdd(&sums[myb * ns + tt[u]], tot[u]); else decide(tt[u], tot[u]);
                 }
             }
         };
@@ -1193,7 +1199,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         else walk_all(std::integral_constant<int, 0>(), std::true_type());
         wave_sync();
         if (es > 1u) {
-            if (active && sl == 0u && mycnt && !dg) for (u32 t = ct; t < (u32)nq; t += cl) decide(t, sums[myb * (nq + 1) + t]);
+            if (active && sl == 0u && mycnt && !dg) for (u32 t = ct; t < (u32)nq; t += cl) decide(t, sums[myb * ns + t]);
             wave_sync();
         }
         if (a.guard == 1) {

@@ -57,6 +57,14 @@ __host__ __device__ inline int wg_tg_words(int B2)
     return (5 * ntg + 1) & ~1;
 }
 
+// words of region 0: fine histogram, or indices + stream image + sums + scales
+__host__ __device__ inline int wg_region0_words(int64_t k, u64 cap_words, int B2, int nq)
+{
+    const int64_t late = (((k + 1) / 2 + (int64_t)cap_words + 1) & ~(int64_t)1) + 2 * B2 * (nq + 1) + B2 * nq;
+    const int64_t r0 = late > kFineBins ? late : kFineBins;
+    return (int)((r0 + 1) & ~(int64_t)1);
+}
+
 __host__ __device__ inline int wg_main_words(int dt, int cap, int region0, int B2)
 {
     const int wds = region0 + 2 * cap + (dt == 0 ? cap / 2 : 0) + 2 * B2 + wg_tg_words(B2) + 16 + (B2 + 1) + B2 * 3;

@@ -1,5 +1,5 @@
 // Host check of the row kernel's reads of block-ordered values (S, cap + 4 words of LDS): walks the sums' and the energy's loops as
-// the kernel's lanes do and looks at every address.  Prints the number of layouts looked at; ends with 1 at the first bad read.
+// the kernel's lanes do and looks at every address; and how many rows a CU's LDS holds.  Prints the number of layouts looked at; ends with 1 at the first bad read.
 #include <cmath>
 #include <cstdio>
 
@@ -53,8 +53,24 @@ static int check(int cap, int n_pos, int n_neg, int M, int Mn, int nq)
     return 0;
 }
 
+// fp32 rows of 4096 elements whose LDS decides how many of them a CU holds (160 KB, dealt in units of 1280 bytes); the list positions,
+// the sums and the scales lie inside region 0
+static int check_lds(int k, int cap, int maxs, int M, int nq, int qmax, int per_cu)
+{
+    const int B2 = 2 * M;
+    const u64 cap_words = ((u64)k * (u64)(12 + qmax) + 31) / 32;
+    const int region0 = small_region0_words(0, k, cap_words, B2, nq, cap, small_fine_bins(maxs)), words = small_lds_words(0, cap, region0, B2, maxs);
+    const int held = 160 * 1024 / ((4 * words + 1279) / 1280 * 1280);
+    const int sums = (((k + 1) / 2 + (int)cap_words) + 1) & ~1;
+    if (held >= per_cu && small_fine_bins(maxs) + 4 + (cap + 4) / 2 <= region0 && sums + 2 * B2 * small_block_sums(B2, nq) + B2 * nq <= region0) return 0;
+    printf("%d of 4096, %d + %d blocks, %d bitwidths: %d words, region 0 %d, %d rows a CU, not %d\n", k, M, M, nq, words, region0, held, per_cu);
+    return 1;
+}
+
 int main()
 {
+    if (check_lds(1024, 1280, 20, 16, 16, 16, 8) || check_lds(1228, 1536, 0, 16, 7, 8, 6) || check_lds(1228, 1536, 0, 1, 7, 8, 7) ||
+        check_lds(1024, 1280, 20, 16, 7, 8, 10)) return 1;
     long seen = 0;
     const int ks[] = { 1, 2, 63, 115, 204, 409, 512, 819, 1024, 1500, 1856, 1920 };
     const int blocks[] = { 1, 2, 3, 4, 5, 8, 11, 16, 31, 32 };

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2511_11608_amd import synth
-from tests.test_gpu_parity import B28, check, check_atkf
+from tests.test_gpu_parity import B28, check, check_atkf, check_ds
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +50,19 @@ def test_rows_of_two_lengths_of_list(oracle, rows, N, keep):
     x[:, ::900] *= np.float32(40)
     x[1] = 0.5
     check(oracle, synth.f32_to_bf16_bits(x), "bf16", keep, 8, B28, 1e-3)
+
+
+@pytest.mark.parametrize("dtype,N,keep", [("f32", 300, 0.3), ("f32", 4096, 0.25), ("f32", 4096, 0.3), ("bf16", 1024, 0.2), ("bf16", 4096, 0.1)])
+def test_few_and_many_bitwidths(oracle, dtype, N, keep):
+    """A block's lanes are dealt to candidate bitwidths and slices: sets of one, two, three and all sixteen, classes with few and many blocks."""
+    x = np.random.default_rng(N).standard_normal((6, N)).astype(np.float32)
+    x[0] = np.abs(x[0])                               # one class alone
+    x[1, ::5] *= np.float32(30)
+    x[2] = -np.abs(x[2])
+    if dtype == "bf16":
+        x = synth.f32_to_bf16_bits(x)
+    for bits in (1 << 4, 1 << 4 | 1 << 8, 1 << 2 | 1 << 5 | 1 << 9, 0x1FFFE):
+        for Mp, Mn in ((1, 1), (1, 8), (4, 4), (3, 1), (16, 16), (2, 29)):
+            check_atkf(oracle, x, dtype, keep, 0.0, Mp, Mn, bits, 1e-3)
+        for M in (2, 4, 16):
+            check_ds(oracle, x, dtype, keep, M, bits, 0.3)
