@@ -485,24 +485,22 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         // from the first code bit on are a quarter of the others; all are smaller while the launch is small
         la.pack_words = kPackWords;
         while (la.pack_words > 128 && (u64)rows * ((la.cap_words + (u64)la.pack_words - 1) / (u64)la.pack_words) < 1024) la.pack_words /= 2;
+        const u64 ptr_bits = csr ? (u64)(n_blocks + n_blocks_neg) * (u64)(csr->n_rows + 1) * (u64)csr->wp : 0, ptr_words = ptr_bits / 32;
+        // Row pointers have windows of their own, 256 words each and started first, where these are few (a workgroup per CU), or
+        // not many (five) and a block has as many entries as pointers: then a window's walk or searches are long, and windows as long as the others'
+        // made the tail of the launch.  Elsewhere the window's tables cost more than that tail.  Encode us, windows of their own / not:
+        // fp32 32 x [64 x 3136] keep 0.2, 32 blocks 95 / 101, 32 x [512 x 784] 8 blocks 120 / 143, 32 blocks 128 / 151; but 32 x [256 x 196] 128 blocks
+        // 96 / 91, 32 x [2048 x 49] 128 blocks 169 / 128, 8 x [401408 x 1] 584 / 365.  (At the line's foot, with as many entries as
+        // pointers, [256 x 196] 32 blocks 64 / 70, [2048 x 49] 8 blocks 75 / 73.)
+        const u64 ptr_wins = csr ? (u64)rows * ((ptr_words + 255) / 256) : 0;
+        const bool ptr_own = csr && (ptr_wins <= 256 || (ptr_wins <= 1280 && p.k >= (int64_t)(n_blocks + n_blocks_neg) * (csr->n_rows + 1)));
+        la.pack_words_ptr = std::min(la.pack_words, 256);      // at most 1026 pointers: slicer_encode_csr refuses this route to widths below eight bits
+        if (csr && !ptr_own) while (la.pack_words * 32 / csr->wp + 2 > kPackPtrs) la.pack_words /= 2;
         la.pack_words_code = std::max(64, la.pack_words / 4);
         {
             // largest first word with code bits; words from there to the end
-            const u64 ptr_bits = csr ? (u64)(n_blocks + n_blocks_neg) * (u64)(csr->n_rows + 1) * (u64)csr->wp : 0;
-            const u64 ptr_words = ptr_bits / 32, idx_words_max = (ptr_bits + (u64)p.k * (u64)(csr ? csr->wc : p.w)) / 32 - ptr_words;
-            // Windows of row pointers.  Blocks of the usual size that are walked take long: their windows are started first and are short
-            // as long as there are few (fp32 32 x [512 x 784] encode call 135 -> 127 us).  Searched pointers cost a window less than its
-            // tables: 256 words each took 583 us for fp32 8 x [401408 x 1], 173 for bf16 32 x [2048 x 49] of 128 blocks; now, long and
-            // after the windows with code fields, 363 and 133.
-            la.ptr_first = csr && csr_walked((u32)(p.k / (n_blocks + n_blocks_neg)), (u32)csr->n_rows + 1u) ? 1 : 0;
-            la.pack_words_ptr = la.pack_words;
-            if (la.ptr_first && la.pack_words >= 256) {
-                la.pack_words_ptr = kPackWords;
-                while (la.pack_words_ptr > 256 && (u64)rows * ((ptr_words + (u64)la.pack_words_ptr - 1) / (u64)la.pack_words_ptr) < 1024) la.pack_words_ptr /= 2;
-            }
-            // (256 words hold at most 1026 pointers: slicer_encode_csr refuses this route to widths below eight bits)
-            if (csr) while (la.pack_words_ptr * 32 / csr->wp + 2 > kPackPtrs) la.pack_words_ptr /= 2;
-            la.nwin_ptr = (int)((ptr_words + (u64)la.pack_words_ptr - 1) / (u64)la.pack_words_ptr);
+            const u64 own_words = ptr_own ? ptr_words : 0, idx_words_max = (ptr_bits + (u64)p.k * (u64)(csr ? csr->wc : p.w)) / 32 - own_words;
+            la.nwin_ptr = (int)((own_words + (u64)la.pack_words_ptr - 1) / (u64)la.pack_words_ptr);
             la.nwin_idx = la.nwin_ptr + (int)((idx_words_max + (u64)la.pack_words - 1) / (u64)la.pack_words);
             const u64 code_words_max = ((u64)p.k * (u64)p.qmax + 31) / 32 + 2;
             la.nwin = la.nwin_idx + (int)((code_words_max + (u64)la.pack_words_code - 1) / (u64)la.pack_words_code);

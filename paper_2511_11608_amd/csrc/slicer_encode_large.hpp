@@ -85,9 +85,8 @@ struct LargeArgs {
     // pack
     int pack_words;         // stream words per pack workgroup in the index section (<= kPackWords)
     int pack_words_code;    // ... from the first word with code bits on (fields there are short: fewer words per workgroup)
-    int pack_words_ptr;     // ... up to the first word with column bits (two-dimensional instances)
-    int ptr_first;          // 1: the windows of row pointers are started before the others
-    int nwin_ptr, nwin_idx, nwin;     // windows of row pointers; those and the ones that may lie in the index section; windows per row
+    int pack_words_ptr;     // ... up to the first word with column bits, where row pointers have windows of their own
+    int nwin_ptr, nwin_idx, nwin;     // windows of row pointers alone; those and the ones that may lie in the index section; windows per row
     int direct;             // 1: words go to their place in the stream, 0: to the row's slot
     u32* stream;
     void* meta;
@@ -1342,10 +1341,7 @@ struct RunPacker {
     __device__ inline void finish() { if (fill > 0) put((u32)acc, true); }
 };
 
-constexpr int kPackPtrs = 3072;                   // row pointers of one window at most (20 KB of LDS in all: eight workgroups a CU, as their wavefronts allow)
-
-// Row pointers of a block of cnt entries: by a walk over its entries, or by a search for each pointer
-__host__ __device__ inline bool csr_walked(u32 cnt, u32 np1) { return cnt * 8u >= np1 && cnt <= 16u * np1; }
+constexpr int kPackPtrs = 4096;                   // row pointers of one window at most
 
 // CSR: row pointers and columns instead of flat indices (Sec. 3.2 step 3)
 template <int DT, bool CSR>
@@ -1363,11 +1359,11 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa
     const int tid = threadIdx.x;
     const int64_t r = blockIdx.y;
     const int B2 = a.M + a.Mn, wi = CSR ? a.wc : a.w;
-    // The windows of row pointers take longest where blocks are walked: they are started first, then those with code fields,
-    // which hold the most entries.  (As windows of 1024 words behind the others the pointers made the tail of the launch: fp32
-    // 32 x [512 x 784] pack 52 us, now 29.)
-    const int nwp = CSR ? a.nwin_ptr : 0, early = CSR && a.ptr_first ? nwp : 0, nwc = a.nwin - a.nwin_idx, wx = (int)blockIdx.x - early;
-    const int win = wx < 0 ? (int)blockIdx.x : wx < nwc ? a.nwin_idx + wx : early + wx - nwc;
+    // Windows of row pointers alone, which take longest, are started first, then those with code fields, which hold the most
+    // entries.  (As windows of 1024 words behind the others the pointers made the tail of the launch: fp32 32 x [512 x 784] pack
+    // 52 us, now 29.)
+    const int nwp = CSR ? a.nwin_ptr : 0, nwc = a.nwin - a.nwin_idx, wx = (int)blockIdx.x - nwp;
+    const int win = wx < 0 ? (int)blockIdx.x : wx < nwc ? a.nwin_idx + wx : nwp + wx - nwc;
     const u64 row_words = a.row_words[r];
     const u32 n = a.blk_start[(size_t)r * (B2 + 1) + B2];
     const u64 ptr_bits = CSR ? (u64)B2 * (u64)(a.n_rows + 1) * (u64)a.wp : 0ull;
@@ -1375,7 +1371,7 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa
     // windows of pack_words words up to the first word that holds code bits, then of pack_words_code words
     u64 c0, c1;
     {
-        const u64 wb = idx_bits >> 5, wq = CSR ? ptr_bits >> 5 : 0ull;
+        const u64 wb = idx_bits >> 5, wq = nwp ? ptr_bits >> 5 : 0ull;
         if (CSR && win < nwp) {
             c0 = (u64)win * (u64)a.pack_words_ptr;
             c1 = c0 + (u64)a.pack_words_ptr < wq ? c0 + (u64)a.pack_words_ptr : wq;
@@ -1475,7 +1471,7 @@ __global__ __launch_bounds__(256) void lr_pack_kernel(LargeArgs a, FinishArgs fa
         const u64 f0 = lo / (u64)a.wp, fe = (hi + (u64)a.wp - 1) / (u64)a.wp, f1 = fe < n_ptr ? fe : n_ptr;
         const u32 bl0 = (u32)(f0 / np1), bl1 = (u32)((f1 - 1) / np1), first = (u32)(f0 - (u64)bl0 * np1);
         const float rnp = 1.0f / (float)np1;
-        auto walked = [&](u32 cnt) -> bool { return csr_walked(cnt, np1); };
+        auto walked = [&](u32 cnt) -> bool { return cnt * 8u >= np1 && cnt <= 16u * np1; };
         auto search = [&](u32 p0, u32 cnt, u32 j) -> u32 {
             const u64 target = (u64)j * ncols;
             u32 l = 0, h = cnt;
