@@ -68,8 +68,13 @@ inline void small_split_lanes(SmallArgs& a)
     while ((1 << a.nbits) < B2) ++a.nbits;
     a.lg = ntg > 32 ? 0 : ntg > 16 ? 1 : ntg > 8 ? 2 : ntg > 4 ? 3 : ntg > 2 ? 4 : 5;
     a.lpb = kWave / (B2 < kWave ? B2 : kWave);
-    a.cl = a.lpb < 8 ? a.lpb : 8;
-    a.es = a.lpb >= 16 ? a.lpb / 8 : 1;
+    // Up to eight lanes with candidates of their own; blocks of sixteen lanes or more are sliced among such groups.  Where such blocks are long,
+    // a lane takes up to four candidates instead, and there are as many more slices: a walk of fewer steps, but more lanes that add
+    // to a sum.  Encode us, eight lanes / four candidates: fp32 [8192 x 4096] keep 0.4, one block a class, 328 / 304, one class alone,
+    // DS guard, 448 / 386 (417 when every lane had a share of the block for all candidates); at 409 kept elements equal, at 204
+    // up to 6 % longer, below 100 up to 20 %.
+    a.cl = a.lpb < 8 ? a.lpb : a.lpb < 16 || a.k < 512 ? 8 : a.nq <= 4 ? 1 : a.nq <= 8 ? 2 : 4;
+    a.es = a.lpb >= 16 ? a.lpb / a.cl : 1;
     a.nc = (a.nq + a.cl - 1) / a.cl;
 }
 
@@ -184,7 +189,8 @@ __device__ inline void lds_inc(u32 byte_off, u32 v)
 
 // NQ > 0: the number of allowed bitwidths is known at compile time (loops over the
 // candidate bitwidths unroll without predicates); NQ == 0: any number up to 16.
-// MAXS > 0: the list has at most 64 * MAXS entries and lives in registers.
+// MAXS > 0: the list has at most 64 * MAXS entries and lives in registers (fp32 with MAXS = 20: one of its two arrays in scratch, 96
+// bytes a lane).
 // ASYM: the asymmetric thresholds of Sec. 3.1 with lambda > 0.  The kept set is not a
 // plain top-K then: after the first selection has given tau, the strict set is counted, a second
 // selection over a subset of the row (the fill candidates, or the strict set when it is too large)
@@ -1068,12 +1074,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         if (lane_on && sub == 0) L.run[myb] = ladder_index(a.lad, (int)(myb >= (u32)M ? myb - (u32)M : myb));
     } else {
         const u32 cl = (u32)a.cl, es = (u32)a.es;    // lanes with candidates of their own; slices of the block
-        const u32 ct = es > 1u ? sub & 7u : sub, sl = es > 1u ? sub >> 3 : 0u;
+        const u32 ct = es > 1u ? sub & (cl - 1u) : sub, sl = es > 1u ? sub >> __builtin_ctz(cl) : 0u;     // (cl: a power of two then)
         const bool active = lane_on && ct < cl && sl < es;
         const u32 per = es > 1u ? udiv16(mycnt + es - 1u, es) : mycnt, T2 = es > 1u ? udiv16(maxb + es - 1u, es) : maxb;
         const AbqSlice slice = small_abq_slice(bs0, mycnt, per, sl, active);
         const u32 q0 = slice.q0, qn = slice.qn;
-        if (es > 1u && active) for (u32 t = ct + 8u * sl; t < (u32)nq; t += 8u * es) sums[myb * ns + t] = 0;
+        if (es > 1u && active) for (u32 t = ct + cl * sl; t < (u32)nq; t += cl * es) sums[myb * ns + t] = 0;
         double rhs = 0.0;
         if (a.guard == 0) {
             u64 accE = 0;

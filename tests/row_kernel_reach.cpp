@@ -14,10 +14,10 @@ static int bad(const char* what, int cap, int n_pos, int n_neg, int M, int Mn, i
     return 1;
 }
 
-static int check(int cap, int n_pos, int n_neg, int M, int Mn, int nq)
+static int check(int k, int cap, int n_pos, int n_neg, int M, int Mn, int nq)
 {
     SmallArgs a = {};
-    a.M = M; a.Mn = Mn; a.nq = nq;
+    a.k = k; a.M = M; a.Mn = Mn; a.nq = nq;
     small_split_lanes(a);
     const int B2 = M + Mn, n = n_pos + n_neg;
     const u32 K0 = n_pos / M, K1 = n_neg / Mn, lpb = a.lpb, es = a.es, cl = a.cl;
@@ -85,7 +85,7 @@ int main()
                         for (int n : { 1, k / 3 + 1, k - 1, k })
                             for (int n_neg : { 0, 1, n / 2, n - 1, n }) {
                                 if (n <= 0 || n > k || n_neg < 0 || n_neg > n) continue;
-                                if (check(cap, n - n_neg, n_neg, M, Mn, nq)) return 1;
+                                if (check(k, cap, n - n_neg, n_neg, M, Mn, nq)) return 1;
                                 ++seen;
                             }
         }
