@@ -19,8 +19,11 @@
  *         a zero tensor.
  *
  * Every pointer named x, y, stream, meta or workspace is a DEVICE pointer owned by
- * the caller; the library neither allocates nor frees device memory, and keeps no
- * state between calls.  Kernels are enqueued on `hip_stream` (a hipStream_t cast
+ * the caller; the library neither allocates nor frees device memory.  No result
+ * depends on an earlier call.  What outlives a call: the threshold hints that an
+ * encoder leaves in the caller's workspace (any contents are safe), the array of
+ * slicer_encode_static, and 4 KB of page-locked host memory through which
+ * slicer_decode learns the header.  Kernels are enqueued on `hip_stream` (a hipStream_t cast
  * to void*, NULL = the default stream); unless stated otherwise a call returns
  * without waiting for them.  Calls return SLICER_OK (0) or a negative code.
  *
@@ -106,7 +109,8 @@ int slicer_encode(const void* x, slicer_dtype dt, int64_t rows, int64_t row_len,
  * SLICER_ETOOBIG otherwise.  All calls on one
  * GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two host
  * threads) race and give undefined output; calls on one stream are ordered and safe.  The
- * array keeps the last call's contents; the kernels write every word before they read it.
+ * array keeps the last call's contents; no output depends on a word that the call has not written
+ * (the threshold hints decide how a row is searched, and copies may read a slot past its row's words).
  */
 #define SLICER_STATIC_SCRATCH_BYTES (64u << 20)
 int slicer_encode_static(const void* x, slicer_dtype dt, int64_t rows, int64_t row_len,
@@ -116,9 +120,16 @@ int slicer_encode_static(const void* x, slicer_dtype dt, int64_t rows, int64_t r
 /*
  * Decode (Eq. "dequnt": de-quantise every block and scatter it into a zero
  * tensor).  y receives [rows][row_len] in the dtype recorded in meta; every
- * element is written.  This call first copies the 64-byte header to the host and
- * waits for `hip_stream`, validates it (SLICER_EFORMAT), then enqueues the decode
- * kernel.
+ * element is written.  This call first brings the 64-byte header to the host and
+ * waits until it is there, i.e. for the work queued before it on `hip_stream`; it
+ * validates the header (SLICER_EFORMAT), then enqueues the decode kernel.
+ * The header travels through one of 32 slots of page-locked host memory (4 KB in all, allocated
+ * by the process's first call and kept to its end), which a small kernel on `hip_stream` fills;
+ * a call holds its slot until it has the header.  The stream itself is waited for, and an error of
+ * earlier work on it reported by this call, only where the header takes longer than a millisecond.
+ * A copy and a wait for the stream take the kernel's place where all slots are held, the
+ * calling thread has an error pending, the stream is being captured (which fails, as a wait does
+ * under capture), or no page-locked memory is to be had.  Safe on any threads, streams and GPUs.
  */
 int slicer_decode(const void* stream, const void* meta, void* y, void* hip_stream);
 
@@ -182,8 +193,9 @@ int slicer_check_pn(const void* meta, uint64_t stream_words, slicer_dtype dt, in
  * then the codes (v), LSB-first, padded to a word.  Header: offset 44 holds wc, offset 60 n_cols (0
  * there marks the flat index format of slicer_encode); meta arrays as slicer_encode.
  *   stream_capacity_bytes  instances * ceil((2 n_blocks (n_rows + 1) wp + k (wc + q_bit)) / 32) * 4
- * n_rows * n_cols < 2^31.  The flat encoder of the shape does the work (its stream goes to the
- * workspace) and two short kernels re-pack the index section into this form.  slicer_decode reads the
+ * n_rows * n_cols < 2^31.  Long instances are packed in this form by the long-row stages themselves; elsewhere
+ * the flat encoder of the shape does the work (its stream goes to the workspace) and short kernels re-pack
+ * the index section.  slicer_decode reads the
  * index format from the header; slicer_decode_as_csr takes the shape from the caller (it reads k from
  * the header in meta for the pointer width, nothing else).  slicer_check_csr is slicer_check for these
  * metas (slicer_check itself rejects them); the decoder clamps every row pointer to its block and every
@@ -249,9 +261,9 @@ int slicer_bound(slicer_dtype dt, int64_t rows, int64_t row_len, double keep_rat
 /*
  * Which kernel family slicer_encode uses for a shape (for benchmarks and profiles, which
  * name the dominant kernel): 0 = generic (one workgroup per row, any shape), 1 = row-resident
- * (one wavefront per row, rows up to 4096 elements), 2 = long-row stages
- * (rows of more than 4096 elements that the other two do not take), 3 = one workgroup per row
- * (rows of 4097..32768 bf16 / 4097..16384 fp32 elements).
+ * (one wavefront per row: rows up to 4096 elements, and in large batches bf16 rows up to 8192 of which few elements are
+ * kept), 2 = long-row stages (rows of more than 4096 elements that the other two do not take), 3 = one workgroup per row
+ * (other rows of 4097..32768 bf16 / 4097..16384 fp32 elements).
  * Assumes a 16-byte aligned x and the budget guard.  Negative: error code.
  */
 int slicer_encode_path(slicer_dtype dt, int64_t rows, int64_t row_len, double keep_ratio,

@@ -296,7 +296,7 @@ def slicer_check(meta: torch.Tensor, stream_words: int, y_like: torch.Tensor, n_
 
 
 def slicer_decode(stream_buf: torch.Tensor, meta: torch.Tensor, y: torch.Tensor, stream=None) -> None:
-    """Decode into y using the header stored in meta (reads it to the host, waits for the stream)."""
+    """Decode into y using the header stored in meta (waits until the header is on the host)."""
     _check("slicer_decode", load().slicer_decode(stream_buf.data_ptr(), meta.data_ptr(), y.data_ptr(),
                                                  _stream_handle(stream)))
 

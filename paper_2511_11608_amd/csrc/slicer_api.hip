@@ -303,7 +303,7 @@ int launch_decode(const void* stream, const void* meta, void* y, int dt, int64_t
             hipLaunchKernelGGL((dec_small_kernel<0>), dim3((unsigned)xcd_grid(rows)), dim3(kWave), lds, st, da);
         else
             hipLaunchKernelGGL((dec_small_kernel<1>), dim3((unsigned)xcd_grid(rows)), dim3(kWave), lds, st, da);
-    } else if (grid <= 256) {       // a workgroup per CU at most: more threads shorten its chain (fp32 [1 x 200704] 6.5 -> 6.2 us; full chips: 24 -> 29)
+    } else if (grid <= 256) {       // a workgroup per CU at most: more threads shorten its chain (fp32 [1 x 200704] 5.9 -> 5.5 us; a full chip, [32 x 401408]: 20.5 -> 24.2)
         if (dt == SLICER_F32) hipLaunchKernelGGL((dec_kernel<0, 512>), dim3((unsigned)grid), dim3(512), 0, st, da);
         else hipLaunchKernelGGL((dec_kernel<1, 512>), dim3((unsigned)grid), dim3(512), 0, st, da);
     } else {
@@ -864,7 +864,7 @@ int slicer_decode_as(const void* stream, const void* meta, void* y, slicer_dtype
 
 // Copies of a header on their way to the host: a slot of page-locked memory that a one-wavefront kernel fills, word by word
 // and then the ticket, while the caller polls the ticket.  A copy into the caller's memory and a wait for the stream took 18 us
-// (decode of fp32 [1 x 200704] 24.6 us in all, 13.0 now).  32 calls can be under way at once, on any threads, streams and GPUs; one more, a
+// (decode of fp32 [1 x 200704] 26.6 us in all, 12.5 now).  32 calls can be under way at once, on any threads, streams and GPUs; one more, a
 // stream under capture, and a system that gives no page-locked memory take the copy and the wait.
 struct HeaderSlot { u32 words[kHeaderBytes / 4]; u32 ticket; u32 pad[15]; };
 constexpr int kHeaderSlots = 32;

@@ -146,8 +146,8 @@ __global__ __launch_bounds__(BLOCK) void dec_kernel(DecArgs a)
     __syncthreads();
 
     // A thread takes a run of consecutive entries: it finds the block of the first one and moves on with them, the fields
-    // of four entries in flight (with a search per entry and one thread adding up the blocks: fp32 [32 x 401408] 26.1 us, now
-    // 21.6; one map of 200704 elements 7.0 -> 5.6).
+    // of four entries in flight (with a search per entry and one thread adding up the blocks: fp32 [32 x 401408] 24.6 us, now
+    // 20.5; one map of 200704 elements 6.9 -> 5.5).
     const u32 total = pre[B2], per = (total + (u32)BLOCK - 1u) / (u32)BLOCK;
     u32 t = (u32)tid * per;
     const u32 t1 = t + per < total ? t + per : total;
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(256) void meta_check_kernel(CheckArgs a)
 // and tensor row of the first one and then moves on with them; prefixes
 // over the blocks are scans of one wavefront; the image is cleared and stored 16 bytes at a time; neighbouring workgroups,
 // which read neighbouring fields of every block, run on one XCD.  (One thread adding up the blocks, every entry searching its
-// block and row by itself and 45 KB of LDS: fp32 [32 x 512 x 784] 59 us, now 21.6.)  Small instances take as long as the code between their few
+// block and row by itself and 45 KB of LDS: fp32 [32 x 512 x 784] 57 us, now 21.)  Small instances take as long as the code between their few
 // loads: with the fields of four entries in flight, six row pointers at a time and 16-byte stores for rows of a few elements, fp32 [100 x 7]
 // took 4.40 us instead of 3.91 and [512 x 49] 4.72 instead of 4.60; now 3.89 and 4.30.
 struct DecCsrArgs {
