@@ -90,25 +90,36 @@ int count_bits(int64_t k)      // bits that hold any value in 0..k
     return w;
 }
 
-// Elements per tile of the long-row stages: short tiles while they do not fill the chip (one tile per CU), and in large
-// batches where they leave out a quarter or more of what long tiles would cover (bf16 [4096 x 8192] 461 -> 428 us, fp32
-// [4096 x 20480] 529 -> 510; with a sixth left out the added tiles cost more: bf16 [4096 x 33001] 758 -> 826)
+// Elements per tile of the long-row stages, a multiple of 512, at most 16384: short tiles while they do not fill the chip (one tile per CU), and in
+// large batches where they leave out a quarter or more of what long tiles would cover (bf16 [4096 x 8192] 461 -> 428 us, fp32
+// [4096 x 20480] 529 -> 510; with a sixth left out the added tiles cost more: bf16 [4096 x 33001] 758 -> 826).  Between the two as
+// many tiles as can run at once, four a CU, and all of one size: fp32 [32 x 401408], 32 tiles a row, 120.5 us, with 49 tiles 126.0, with 25, which
+// leave four tiles to one CU and three to the next, 134.7.
 int large_tile(int64_t rows, int64_t row_len)
 {
     const int64_t n8 = (row_len + 8191) / 8192;
-    return rows * n8 <= 256 || (rows > kScanRows && (n8 == 1 || n8 == 3)) ? 8192 : 16384;
+    if (rows * n8 <= 256 || (rows > kScanRows && (n8 == 1 || n8 == 3))) return 8192;
+    const int64_t S = std::max<int64_t>((row_len + 16383) / 16384, std::min<int64_t>(1024 / rows, n8));
+    return (int)((row_len + 512 * S - 1) / (512 * S) * 512);
+}
+
+// Members of the fine bins that hold a block's first or last element (two per block, most of them shared), about: a bin is filled
+// with 8 to 16 entries, or with the list's share and up to twice as many, and all of them together cannot hold more than the list, about 1.4 k.
+int64_t large_members(int fine_bins, int64_t k, int B2)
+{
+    return std::min<int64_t>((B2 + 2) * std::max<int64_t>(12, k * 3 / (fine_bins * 7 / 5)), k * 14 / 10 + 100);
 }
 
 // Fine bins per row of the long-row stages.  Few of them in large batches (encode with 4096 and with 1024: fp32 [4096 x 20480]
-// 821 and 529 us, bf16 [9494 x 8738] keep 0.01 M 64 2367 and 1146, bf16 [512 x 8193] M 40 113 and 108), where the bins
-// that hold a block's first or last element (two per block, most of them shared) should fit a row's room of 1536 members: a bin
-// is filled with 8 to 16 entries, or with k / 700 and up to twice as many, and all of them together cannot
-// hold more than the list, about 1.4 k.
+// 821 and 529 us, bf16 [9494 x 8738] keep 0.01 M 64 2367 and 1146, bf16 [512 x 8193] M 40 113 and 108), where the members
+// should fit a row's room of 1536.
 int large_fine_bins(int64_t rows, int64_t k, int B2)
 {
-    const int64_t members = std::min<int64_t>((B2 + 2) * std::max<int64_t>(12, k * 3 / 1400), k * 14 / 10 + 100);
-    return rows > kScanRows && members <= 1200 ? kFBNarrow : kFBWide;
+    return rows > kScanRows && large_members(kFBNarrow, k, B2) <= 1200 ? kFBNarrow : kFBWide;
 }
+
+// the bounds stage with the larger room
+bool large_many_members(int64_t k, int B2) { return large_members(kFBWide, k, B2) > 4800; }
 
 // aligned: x starts on a 16-byte boundary (the workspace layout does not depend on it, only the choice of kernel)
 // long_rows: the long-row stages may serve the call; without them (the generic kernel) it needs less workspace
@@ -189,7 +200,7 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
 
     // Long rows: every pass is spread over many workgroups (slicer_encode_large.hpp).  A row that starts or ends
     // inside a 16-byte chunk takes them from 8192 elements on: below, one workgroup of the generic kernel is as fast.
-    // The workspace holds the stages' tables (16 KB a tile and more) only where some row of this length can reach the
+    // The workspace holds the stages' tables (8 KB a tile and more) only where some row of this length can reach the
     // stages: not where a row-resident kernel holds the row wherever it starts.
     p.large_S = 0; p.large_capL = 0; p.large_fb = 0;
     {
@@ -237,11 +248,14 @@ hipError_t launch_small_any(const SmallArgs& sa, const SmallLaunch& p, bool asym
 template <int DT, int FB>
 void launch_large_stages(const LargeArgs& la, const EncArgs& ea, const FinishArgs& fa, hipStream_t st)
 {
-    const dim3 gT((unsigned)la.S, (unsigned)la.R), gR((unsigned)la.R), gW((unsigned)la.nwin, (unsigned)la.R), bT(kTileThreads);
-    hipLaunchKernelGGL((lr_sample_kernel<DT, FB>), gR, dim3(FB / 4), 0, st, la);
-    if (la.tile == 8192) hipLaunchKernelGGL((lr_compact_kernel<DT, 2, FB>), gT, bT, 0, st, la);
+    const dim3 gT((unsigned)la.S, (unsigned)la.R), gR((unsigned)la.R), gB((unsigned)(la.R * la.parts)), gW((unsigned)la.nwin, (unsigned)la.R), bT(kTileThreads);
+    const dim3 bR((unsigned)lr_row_threads(FB));
+    hipLaunchKernelGGL((lr_sample_kernel<DT, FB>), gR, bR, 0, st, la);
+    if (la.tile <= 8192) hipLaunchKernelGGL((lr_compact_kernel<DT, 2, FB>), gT, bT, 0, st, la);
     else hipLaunchKernelGGL((lr_compact_kernel<DT, 4, FB>), gT, bT, 0, st, la);
-    hipLaunchKernelGGL((lr_bounds_kernel<DT, FB>), gR, dim3(FB / 4), 0, st, la, ea);
+    if (FB == kFBWide && large_many_members(la.k, la.M + la.Mn))
+        hipLaunchKernelGGL((lr_bounds_kernel<DT, FB, FB == kFBWide>), gB, bR, 0, st, la, ea);
+    else hipLaunchKernelGGL((lr_bounds_kernel<DT, FB, false>), gB, bR, 0, st, la, ea);
     const size_t lds = (size_t)lr_split_carve(FB, la.M + la.Mn, la.nq).total;
     if (la.nq == 7) hipLaunchKernelGGL((lr_split_kernel<DT, 7, FB>), gT, bT, lds, st, la);   // {2..8}: the benchmarked set
     else hipLaunchKernelGGL((lr_split_kernel<DT, 0, FB>), gT, bT, lds, st, la);
@@ -477,8 +491,11 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         la.beta = distortion_budget; la.cap_words = csr ? csr->cap_words : p.cap_words;
         const int epc = dt == SLICER_F32 ? 4 : 8;
         la.tile = large_tile(rows, row_len);
-        la.S = (int)((row_len + (row_len % epc == 0 && aligned ? 0 : epc - 1) + la.tile - 1) / la.tile);
+        la.S = (int)((row_len + la.tile - 1) / la.tile);
         la.capL = p.large_capL;
+        // workgroups that share a row in the bounds stage: as many as there are CUs for
+        la.parts = rows <= 32 ? 8 : rows <= 64 ? 4 : rows <= 128 ? 2 : 1;
+        lr_sample_plan(la, p.large_fb, epc);
         la.n_rows = csr ? csr->n_rows : 0; la.n_cols = csr ? csr->n_cols : 0;
         la.wp = csr ? csr->wp : 0; la.wc = csr ? csr->wc : 0;
         // pack windows: index fields are w bits, code fields as short as one bit, so the windows

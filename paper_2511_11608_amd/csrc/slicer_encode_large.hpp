@@ -4,11 +4,11 @@
 //
 //   sample    per row: up to 4096 evenly spread 16-byte chunks.  Their histogram gives a lower bound that a
 //             little more than k elements reach, and a table that maps the elements above it to at
-//             most 4096 "fine bins" of about equal population
-//   compact   per tile of 8192 or 16384 elements: ordered compaction of everything at or above the bound into a list
+//             most 2048 "fine bins" of about equal population
+//   compact   per tile of up to 16384 elements: ordered compaction of everything at or above the bound into a list
 //             segment, the tile's histogram over the fine bins (as "entries at or above the bin"), and the
 //             list positions arranged by fine bin
-//   bounds    per row: sums the tiles' histograms; the top-K cut (ATKF, Sec. 3.1) and the first and last
+//   bounds    per row, by up to eight workgroups: the tiles' histograms are summed; the top-K cut (ATKF, Sec. 3.1) and the first and last
 //             element of every block (MS, Sec. 3.2) are order statistics whose fine bin is found in the sums and
 //             which are resolved among the few members of that bin; rows that do not fit are redone here by the generic encoder
 //   split     per tile: block of every entry, stable split by block (ascending index inside a block), integer
@@ -22,11 +22,13 @@
 // before it does anything and a workgroup lives three to six memory round trips, so the stages were
 // chosen for their number: counting exactly before compacting, separate block counts, sums and choice, and a
 // final gather made ten launches.  One atomic per entry on a table in memory is no way to
-// join the tiles' histograms (29 G atomics/s: 100 us for 3 M of them); the per-tile tables cost 16 KB
-// per tile, written and read once.  Inside a stage the lanes' LDS lookups are written as straight-line code for several
+// join the tiles' histograms (29 G atomics/s: 100 us for 3 M of them); the per-tile tables cost 8 KB
+// per tile, written once.  Inside a stage the lanes' LDS lookups are written as straight-line code for several
 // entries at once: behind branches they wait for each other (split kernel 68 -> 41 us on 32 maps of 401408, together with four instead of
 // eight entries per thread, which spill nothing, and the choice of the guard taken outside the entry loop).
-// Encode call: fp32 [1 x 200704] 73 -> 53 us, fp32 [32 x 401408] 161 -> 136 us, with CSR blocks 203 -> 173 us.
+// Measured (us, fp32 [1 x 200704] and [32 x 401408] keep 0.2, 16 + 16 blocks): sample 5 and 9, compact 6 and 18, bounds 12 and 18,
+// split 15 and 41, pack 6 and 22; the calls 44.7 and 114, with CSR blocks 144.  Before the changes that the stages' comments name: sample 9.5 and 13,
+// compact 6 and 29, bounds 15.7 and 24; the calls 53 and 134, CSR 164.
 //
 // Order: comp = key << w | (2^w - 1 - index): larger comp = larger magnitude, then lower index.  c32 is
 // its leading 31 (fp32: the key) or 32 bits (bf16: the key and the first 17 bits of the inverted
@@ -41,12 +43,15 @@ namespace slicer {
 constexpr int kTileThreads = 512;   // a compact / split workgroup handles a tile of 8192 or 16384 elements
 constexpr int kMaxTab = 510, kTabSize = kMaxTab + 2;        // sample bins with fine bins of their own: 16 octaves above the bound
 // Fine bins per row, a template parameter (FB) of the stages.  A batch of up to 256 rows has a CU for every row and takes the
-// many bins, few members each, and FB / 4 = 1024 threads per row where a stage works on whole rows; there a row's latency counts.
-// In a larger batch the rows wait for each other and what counts is a row's cost: tables of 16 KB a tile to write and
-// sum, and one row per CU at a time (the bounds stage's LDS), made fp32 [4096 x 20480] 821 us.
-constexpr int kFBWide = 4096, kFBNarrow = 1024;
+// many bins, few members each, and 1024 threads per row where a stage works on whole rows; there a row's latency counts.
+// In a larger batch the rows wait for each other and what counts is a row's cost.  4096 bins had half the members a bin and tables of
+// twice the size: the bounds stage's sums of fp32 [32 x 401408] took 5.5 us instead of 3.5, and compact's LDS let three workgroups on a CU instead
+// of four, 768 of 800 at once.
+constexpr int kFBWide = 2048, kFBNarrow = 1024;
+constexpr int lr_row_threads(int FB) { return FB == kFBWide ? 1024 : 256; }    // of the per-row stages
 constexpr int kSampleBins = 8192;   // 32 bins per octave
-constexpr int lr_mem_cap(int FB) { return FB == kFBWide ? 6144 : 1536; }       // members of the bins that hold order statistics, per row
+// members of the bins that hold order statistics, per row (BIG: for lists of many entries, at one row a CU)
+constexpr int lr_mem_cap(int FB, bool BIG) { return FB == kFBWide ? (BIG ? 16384 : 6144) : 1536; }
 constexpr int kPackWords = 1024;    // stream words per pack workgroup
 constexpr u64 kTop = 1ull << 63;
 
@@ -57,7 +62,10 @@ struct LargeArgs {
     int qlist[kMaxQ];
     double beta;
     u64 cap_words;
+    u32 sample_target;      // see lr_sample_plan
+    float sample_scale;
     int tile, S;            // elements of a tile, tiles per row
+    int parts;              // workgroups that share a row in the bounds stage
     u32 capL;               // list capacity per row
     uint16_t* tab;          // [R][kTabSize]  first fine bin of a sample bin | log2 of its number of fine bins << 12; one guard at either end
     u32* cum;               // [R][S][FB]     entries of the tile at or above the bin: positive | negative << 16
@@ -94,6 +102,17 @@ struct LargeArgs {
     int64_t n_rows, n_cols;
     int wp, wc;
 };
+
+// What the sample stage aims at: how many of the sample's elements must reach the bound, i.e. the expected number of the k kept ones plus
+// four standard deviations, taken as if the elements of a chunk were all alike; and the row's elements per sampled one.  (Of the
+// row's chunks counted from its start: one that starts inside a chunk may have one more, which the margin covers.)
+inline void lr_sample_plan(LargeArgs& a, int fine_bins, int epc)
+{
+    const int64_t Q = (a.N + epc - 1) / epc, room = fine_bins == kFBWide ? 4096 : 2048;
+    const double G = (double)(Q < room ? Q : room), f = (double)a.k / (double)a.N;
+    a.sample_target = (u32)(f * G * epc + 4.0 * epc * sqrt(G * f * (1.0 - f))) + 1u;
+    a.sample_scale = (float)((double)a.N / (G * epc));
+}
 
 // coding of `map` (up to 62 blocks; with more of them the split searches the thresholds)
 constexpr u32 kMapMixed = 0x80u, kMapMany = 0x40u, kMapNone = 0x3Fu;
@@ -150,11 +169,11 @@ __device__ inline u64 lr_comp(u32 key, u32 idx, int w) { return ((u64)key << w) 
 
 // ---- 1. sample ------------------------------------------------------------------------------------
 template <int DT, int FB>
-__global__ __launch_bounds__(FB / 4) __attribute__((amdgpu_waves_per_eu(FB == kFBWide ? 4 : DT == 0 ? 6 : 5))) void lr_sample_kernel(LargeArgs a)
+__global__ __launch_bounds__(lr_row_threads(FB)) __attribute__((amdgpu_waves_per_eu(FB == kFBWide ? 4 : DT == 0 ? 6 : 5))) void lr_sample_kernel(LargeArgs a)
 {
     typedef Elem<DT> E;
-    constexpr int TH = FB / 4, NU = FB == kFBWide ? 4 : 8, LG = FB == kFBWide ? 12 : 11;     // 4096 or 2048 chunks
-    constexpr int EPC = RowChunks<DT>::EPC, SH = LrOrder<DT>::kSh, SUB = FB == kFBWide ? 12 : 10;
+    constexpr int TH = lr_row_threads(FB), NU = FB == kFBWide ? 4 : 8, LG = FB == kFBWide ? 12 : 11;     // 4096 or 2048 chunks
+    constexpr int EPC = RowChunks<DT>::EPC, SH = LrOrder<DT>::kSh, SUB = FB == kFBWide ? 11 : 10;
     static_assert(TH * NU == 1 << LG && FB == 1 << SUB && TH * NU * EPC < 65536, "16-bit counters");
     constexpr bool kHalf = FB != kFBWide;            // two counters per word (more rows per CU; a single row is 0.4 us faster with words)
     __shared__ u32 h[kHalf ? kSampleBins / 2 : kSampleBins];
@@ -185,7 +204,7 @@ __global__ __launch_bounds__(FB / 4) __attribute__((amdgpu_waves_per_eu(FB == kF
     {
         uint4* h4 = (uint4*)h;
         for (int i = tid; i < (kHalf ? kSampleBins / 8 : kSampleBins / 4); i += TH) h4[i] = make_uint4(0, 0, 0, 0);
-        ((uint4*)h2)[tid] = make_uint4(0, 0, 0, 0);
+        if (tid < FB / 4) ((uint4*)h2)[tid] = make_uint4(0, 0, 0, 0);
         if (tid < 8) s_v[tid] = tid == 5 ? (u32)kSampleBins - 1u : 0u;
     }
     auto count_of = [&](u32 bin) -> u32 { return kHalf ? (h[bin >> 1] >> (16u * (bin & 1u))) & 0xFFFFu : h[bin]; };
@@ -204,12 +223,9 @@ __global__ __launch_bounds__(FB / 4) __attribute__((amdgpu_waves_per_eu(FB == kF
             if (c) atomicAdd(&h[kHalf ? bin >> 1 : bin], kHalf ? 1u << (16u * (bin & 1u)) : 1u);
         }
     __syncthreads();
-    // how many of the sample's elements must reach the bound: the expected number of the k kept ones plus four
-    // standard deviations, taken as if the elements of a chunk were all alike; a complete sample needs no margin
+    // how many of the sample's elements must reach the bound; a complete sample needs no margin
     const bool whole = G == Q && !rg;
-    const double f = (double)a.k / (double)a.N;
-    const double want = whole ? (double)a.k : f * G * EPC + 4.0 * EPC * sqrt((double)G * f * (1.0 - f));
-    const u32 target = (u32)want + (whole && a.k > 0 ? 0u : 1u);
+    const u32 target = whole ? (a.k > 0 ? (u32)a.k : 1u) : a.sample_target;
     constexpr int BPT = kSampleBins / TH;
     const int hi = kSampleBins - tid * BPT;         // thread t owns the BPT bins below kSampleBins - BPT t
     u32 cs[BPT];
@@ -235,13 +251,20 @@ __global__ __launch_bounds__(FB / 4) __attribute__((amdgpu_waves_per_eu(FB == kF
             if (acc < target && target <= acc + cs[j]) { s_v[0] = (u32)(hi - 1 - j); s_v[1] = acc; s_v[2] = 1u; }
             acc += cs[j];
         }
-        if (local) {
-            int topj = 0, botj = 0;
+        // the sample's largest and smallest bin: one lane of a wavefront knows its own (an LDS atomic of every lane, all at one address, took 3 us:
+        // stage on fp32 [1 x 200704] 9.5 -> 6.5)
+        const u64 some = __ballot(local != 0u);
+        const int ln = (int)lane_id();
+        if (local && ln == __ffsll((unsigned long long)some) - 1) {
+            int topj = 0;
 #pragma unroll
             for (int j = BPT - 1; j >= 0; --j) if (cs[j]) topj = j;
+            atomicMax(&s_v[3], (u32)(hi - 1 - topj));
+        }
+        if (local && ln == 63 - __clzll((long long)some)) {
+            int botj = 0;
 #pragma unroll
             for (int j = 0; j < BPT; ++j) if (cs[j]) botj = j;
-            atomicMax(&s_v[3], (u32)(hi - 1 - topj));
             atomicMin(&s_v[5], (u32)(hi - 1 - botj));
         }
     }
@@ -260,13 +283,15 @@ __global__ __launch_bounds__(FB / 4) __attribute__((amdgpu_waves_per_eu(FB == kF
                     if (c && (c >> SH) == B) atomicAdd(&h2[(c >> (SH - SUB)) & (u32)(FB - 1)], 1u);
                 }
             __syncthreads();
-            const int hi2 = FB - tid * 4;
-            const uint4 t = ((const uint4*)h2)[hi2 / 4 - 1];
-            const u32 c2[4] = { t.w, t.z, t.y, t.x };
-            u32 tot2;
-            u32 acc = block_excl_scan<TH>(t.x + t.y + t.z + t.w, scr, &tot2);
+            constexpr int BPT2 = FB / TH;
+            const int hi2 = FB - tid * BPT2;
+            u32 c2[BPT2], sum2 = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < BPT2; ++j) { c2[j] = h2[hi2 - 1 - j]; sum2 += c2[j]; }
+            u32 tot2;
+            u32 acc = block_excl_scan<TH>(sum2, scr, &tot2);
+#pragma unroll
+            for (int j = 0; j < BPT2; ++j) {
                 if (acc < rem && rem <= acc + c2[j]) s_v[4] = (u32)(hi2 - 1 - j);
                 acc += c2[j];
             }
@@ -283,7 +308,7 @@ __global__ __launch_bounds__(FB / 4) __attribute__((amdgpu_waves_per_eu(FB == kF
     u32 Btop = s_v[3] > Blo ? s_v[3] : Blo;
     if (Btop - Blo > (u32)kMaxTab - 1u) Btop = Blo + (u32)kMaxTab - 1u;
     const u32 nb = Btop - Blo + 1u;
-    const float scale = (float)((double)a.N / ((double)G * EPC));
+    const float scale = a.sample_scale;
     const u32 room = (u32)FB - 2u - nb;
     float per = scale * (float)((tot < target ? tot : target) + count_of(Blo)) / (float)room + 1.0f;
     per = per < 8.0f ? 8.0f : per;
@@ -316,52 +341,55 @@ __global__ __launch_bounds__(FB / 4) __attribute__((amdgpu_waves_per_eu(FB == kF
 }
 
 // ---- 2. compact -----------------------------------------------------------------------------------
-// A wavefront owns NR * 512 consecutive elements, all of them in registers from the start, and works through them
-// 512 at a time: the entries above the bound are first squeezed into its own piece of LDS (index order), then every
-// lane takes whole entries.  With a fifth of the elements above the bound the work per entry (fine bin, atomic,
-// stores) would otherwise run with a fifth of the lanes; nothing in between is a workgroup barrier.
+// A wavefront owns up to NR * 512 consecutive elements, all of them on their way to its registers from the start, and squeezes the entries
+// above the bound into its own piece of LDS (index order) as they arrive; then every lane takes whole entries.  With a fifth of the
+// elements above the bound the work per entry (fine bin, atomics, stores) would otherwise run with a fifth of the lanes.
+// The lanes hold consecutive 32-bit words, so that the order of the elements is that of (word of the lane, lane) and an entry's place
+// follows from the ballot of its word's flags.  With 16 bytes a lane the places took prefix sums of per-lane counts, behind a count
+// of everything; with the fine bins of all entries kept in registers from the histogram to the positions, up to 49 of them spilled.
+// A tile with a wavefront of more than kLrEntries entries is read again, 512 elements at a time.
+constexpr int kLrEntries = 640;
 template <int DT, int NR, int FB>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(FB == kFBWide ? 8 : 6))) void lr_compact_kernel(LargeArgs a)
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void lr_compact_kernel(LargeArgs a)
 {
-    constexpr int EPC = RowChunks<DT>::EPC, CPR = 8 / EPC;           // chunks per lane and round: 2 (fp32), 1 (bf16)
-    constexpr int NCH = NR * CPR, NWV = kTileThreads / kWave, RE = 8 * kWave, WCH = NCH * kWave;     // chunks of a wavefront
-    constexpr int kBuf = NWV * RE * 6, kPass = kBuf / 2;     // bytes; list positions arranged at a time
-    __shared__ u32 hist[FB];                         // positive | negative << 16; later the entries above the bin
+    constexpr int EPW = DT == 0 ? 1 : 2, WPR = 8 / EPW;              // elements of a word, words per lane and round
+    constexpr int NW = NR * WPR, NWV = kTileThreads / kWave, RE = 8 * kWave, NS = kLrEntries / kWave;       // words of a lane; elements of a round; entries of a lane
+    typedef typename Elem<DT>::raw_t raw_t;
+    __shared__ u32 hist[FB];                         // positive | negative << 16; later the place of the bin's next entry
     __shared__ __align__(4) uint16_t tab[kTabSize];
-    __shared__ __align__(16) unsigned char buf[kBuf];
+    __shared__ __align__(16) unsigned char buf[NWV * kLrEntries * 6];
     __shared__ u32 wtot[NWV];
     __shared__ u32 scr[NWV + 1];
     __shared__ u32 s_base;
-    const int tid = threadIdx.x, s = blockIdx.x, w = a.w, wv = tid / kWave;
-    u32* braw = (u32*)buf + wv * RE;                 // a round's entries of this wavefront
-    uint16_t* bidx = (uint16_t*)(buf + NWV * RE * 4) + wv * RE;
+    const int tid = threadIdx.x, s = blockIdx.x, w = a.w, wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    u32* braw = (u32*)buf + wv * kLrEntries;         // entries of this wavefront
+    uint16_t* bidx = (uint16_t*)(buf + NWV * kLrEntries * 4) + wv * kLrEntries;
     uint16_t* bpos = (uint16_t*)buf;                 // in the end: list positions by fine bin
     const u32 lane = lane_id();
     const int64_t r = blockIdx.y;
     u32* st = a.rowst + (size_t)r * 16;
-    const RowChunks<DT> row(a.x, r, a.N);
-    const int qt = s * (NWV * WCH), q0 = qt + wv * WCH;          // first chunk of the tile, of the wavefront
-    uint4 v[NCH];
-    {
-        const bool rg = row.ragged();
+    const u32 WE = (u32)a.tile / NWV, tile0 = (u32)s * (u32)a.tile, we0 = (u32)wv * WE;       // elements of a wavefront; first one of the tile, of the wavefront in the tile
+    // Buffer loads: what lies behind the wavefront's share or the row's end reads as zeros, which are below every bound.  Words where
+    // the row consists of whole ones; bf16 rows of odd length or at odd places by halves.
+    const raw_t* row = (const raw_t*)a.x + (size_t)r * (size_t)a.N;
+    const u32 first = tile0 + we0, behind = first < (u32)a.N ? (u32)a.N - first : 0u, mine = behind < WE ? behind : WE;
+    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<raw_t*>(row) + (behind ? first : 0u), 0, (int)(mine * (u32)sizeof(raw_t)), 0x00020000);
+    const bool words = DT == 0 || ((a.N & 1) == 0 && ((uintptr_t)row & 3) == 0);
+    auto load = [&](auto& v, int at) {
+        constexpr int n = sizeof(v) / 4;
+        if (words) {
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int q = q0 + c * kWave + (int)lane;
-            v[c] = q * EPC < row.Nh && (!rg || row.whole(q)) ? row.base[q] : make_uint4(0, 0, 0, 0);
-        }
-        if (rg) {
-            const int ql = (row.Nh - 1) / EPC;
-            if (ql >= q0 && ql < q0 + WCH) {         // (uniform in the wavefront, as the next one)
-                const uint4 e = row.partial(ql);
+            for (int c = 0; c < n; ++c) v[c] = __builtin_amdgcn_raw_buffer_load_b32(rs, at + c * (4 * kWave), 0, 0);
+        } else {
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) if (q0 + c * kWave + (int)lane == ql) v[c] = e;
-            }
-            if (q0 == 0) {
-                const uint4 e = row.partial(0);
-                if (lane == 0) v[0] = e;
+            for (int c = 0; c < n; ++c) {
+                const u32 lo = __builtin_amdgcn_raw_buffer_load_b16(rs, at + c * (4 * kWave), 0, 0);
+                v[c] = lo | ((u32)__builtin_amdgcn_raw_buffer_load_b16(rs, at + c * (4 * kWave) + 2, 0, 0) << 16);
             }
         }
-    }
+    };
+    u32 v[NW];
+    load(v, (int)(lane * 4u));
     const u32 T = st[kStT], Blo = st[kStBlo], nb = st[kStNb];
     {
         uint4* h4 = (uint4*)hist;
@@ -369,48 +397,87 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(FB
         const u32* tg = (const u32*)(a.tab + (size_t)r * kTabSize);
         if (tid < kTabSize / 2) ((u32*)tab)[tid] = tg[tid];
     }
-    const int e_base = qt * EPC - row.head, le0 = (wv * WCH + (int)lane) * EPC;      // index of the tile's first element; this lane's first one in the tile
-    auto above = [&](int c, int e) -> bool {         // at or above the bound
-        const u32 raw = chunk_elem<DT>(v[c], e);
-        if (DT == 0) return (raw & 0x7FFFFFFFu) >= T;
-        const u32 key = raw & 0x7FFFu;
-        return key && lr_c32<DT>(key, (u32)(e_base + le0 + c * (kWave * EPC) + e), w) >= T;
+    // bf16: 17 bits of the inverted index (an element behind the row's end has key 0 and stays below the least bound, 2^17)
+    const u32 inv0 = (1u << w) - 1u - (tile0 + we0 + lane * (u32)EPW);
+    const int up = w < 17 ? 17 - w : 0, down = w < 17 ? 0 : w - 17;
+    // the entries of word c (elements c * 64 * EPW ... of the wavefront) to its piece, behind `run` others
+    auto squeeze = [&](u32 x, u32 c, u32& run) {
+        const u32 e = (c * (u32)kWave + lane) * (u32)EPW;
+        if (DT == 0) {
+            const bool in = (x & 0x7FFFFFFFu) >= T;
+            const u64 m = __ballot(in);
+            const u32 pos = run + mask_rank(m);
+            run += (u32)__popcll(m);
+            if (run <= (u32)kLrEntries && in) { braw[pos] = x; bidx[pos] = (uint16_t)e; }
+        } else {
+            const u32 k0 = (x << 16) & 0x7FFF0000u, k1 = x & 0x7FFF0000u, inv = inv0 - c * (u32)(kWave * EPW);
+            const bool in0 = ((k0 << 1) | __builtin_amdgcn_ubfe(inv << up, (u32)down, 17u)) >= T;
+            const bool in1 = ((k1 << 1) | __builtin_amdgcn_ubfe((inv - 1u) << up, (u32)down, 17u)) >= T;
+            const u64 m0 = __ballot(in0), m1 = __ballot(in1);
+            const u32 pos = run + mask_rank(m0) + mask_rank(m1), pos1 = pos + (in0 ? 1u : 0u);
+            run += (u32)__popcll(m0) + (u32)__popcll(m1);
+            if (run <= (u32)kLrEntries) {
+                if (in0) { braw[pos] = x << 16; bidx[pos] = (uint16_t)e; }
+                if (in1) { braw[pos1] = x & 0xFFFF0000u; bidx[pos1] = (uint16_t)(e + 1u); }
+            }
+        }
     };
-    u32 base[NCH], wn = 0;                           // positions inside the wavefront's entries
+    auto bin_of = [&](u32 raw, u32 ix) -> u32 {      // fine bin | negative << 31
+        const u32 key = DT == 0 ? raw & 0x7FFFFFFFu : (raw >> 16) & 0x7FFFu;
+        return lr_fine_bin<DT>(lr_c32<DT>(key, first + ix, w), tab, Blo, nb) | (raw & 0x80000000u);
+    };
+    auto one = [&](u32 b) -> u32 { return b >> 31 ? 0x10000u : 1u; };
+    u32 wn = 0;
 #pragma unroll
-    for (int g = 0; g < (NCH + 2) / 3; ++g) {        // counts of three chunks per scan, 10-bit fields
-        u32 pk = 0;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            if (3 * g + j < NCH) {
-                u32 n1 = 0;
-#pragma unroll
-                for (int e = 0; e < EPC; ++e) n1 += above(3 * g + j, e) ? 1u : 0u;
-                pk |= n1 << (10 * j);
-            }
-        }
-        const u32 incl = wave_scan_dpp(pk);
-        const u32 tt = bcast(incl, kWave - 1);
-        const u32 ex = incl - pk;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            if (3 * g + j < NCH) {
-                base[3 * g + j] = wn + ((ex >> (10 * j)) & 0x3FFu);
-                wn += (tt >> (10 * j)) & 0x3FFu;
-            }
-        }
-    }
+    for (int c = 0; c < NW; ++c) squeeze(v[c], (u32)c, wn);
     if (lane == 0) wtot[wv] = wn;
     __syncthreads();
-    u32 wbase = 0, ntile = 0;                        // entries of the wavefronts before this one, of the tile
+    u32 wbase = 0, ntile = 0, most = 0;              // entries of the wavefronts before this one, of the tile
 #pragma unroll
-    for (int i = 0; i < NWV; ++i) { const u32 t = wtot[i]; if (i < wv) wbase += t; ntile += t; }
+    for (int i = 0; i < NWV; ++i) { const u32 t = wtot[i]; if (i < wv) wbase += t; ntile += t; most = t > most ? t : most; }
+    const bool dense = most > (u32)kLrEntries;       // uniform
     if (tid == 0) {
         u32 b = atomicAdd(&st[kStCursor], ntile);
         if (b > a.capL || ntile > a.capL - b) { b = 0xFFFFFFFFu; st[kStFlag] = 1u; }     // the list is full: the row is redone generically
         s_base = b;
     }
-    const u32 we0 = (u32)(wv * WCH * EPC);           // the wavefront's first element in the tile
+    // a dense tile's entries, 512 elements of every wavefront at a time: f(entries before, entry, raw, index in the wavefront)
+    auto rounds = [&](auto&& f) {
+        u32 before = 0;
+#pragma unroll 1
+        for (int g = 0; g < NR; ++g) {
+            u32 t[WPR], run = 0;
+            load(t, (int)(lane * 4u) + g * (RE * (int)sizeof(raw_t)));
+#pragma unroll
+            for (int j = 0; j < WPR; ++j) squeeze(t[j], (u32)(g * WPR + j), run);
+            wave_sync();
+#pragma unroll 1
+            for (u32 i = lane; i < run; i += kWave) f(before + i, braw[i], (u32)bidx[i]);
+            wave_sync();
+            before += run;
+        }
+    };
+    u32 bf[NS];
+    if (dense) rounds([&](u32, u32 raw, u32 ix) { const u32 b = bin_of(raw, ix); atomicAdd(&hist[b & 0xFFFu], one(b)); });
+    else {
+#pragma unroll
+        for (int h = 0; h < NS; h += 2) {            // two entries per lane at a time, their lookups side by side
+            if ((u32)(h * kWave) >= wn) break;       // uniform in the wavefront
+            u32 raw[2], ix[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const u32 i = (u32)((h + e) * kWave) + lane;
+                raw[e] = braw[i]; ix[e] = (u32)bidx[i];
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) bf[h + e] = bin_of(raw[e], ix[e]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {            // (lanes without an entry add nothing, each to a bin of its own)
+                const bool in = (u32)((h + e) * kWave) + lane < wn;
+                atomicAdd(&hist[in ? bf[h + e] & 0xFFFu : lane], in ? one(bf[h + e]) : 0u);
+            }
+        }
+    }
     __syncthreads();
     const u32 seg0 = s_base;
     const bool full = seg0 == 0xFFFFFFFFu;
@@ -418,117 +485,54 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(FB
     u32* __restrict__ Lraw = list.raw + seg0 + wbase;
     uint16_t* __restrict__ Lidx = list.idx + seg0 + wbase;
     uint16_t* __restrict__ Lpos = list.pos + seg0;
-    u32 bf[NR][8];                                   // fine bin | entries of the bin before this one << 12 | negative << 31
-    u32 g0 = 0;
-#pragma unroll
-    for (int g = 0; g < NR; ++g) {
-        const u32 g1 = g + 1 < NR ? bcast(base[(g + 1) * CPR < NCH ? (g + 1) * CPR : 0], 0) : wn;
-        const u32 ng = g1 - g0;
-#pragma unroll
-        for (int cc = 0; cc < CPR; ++cc) {
-            const int c = g * CPR + cc;
-            u32 pos = base[c] - g0;
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                if (above(c, e)) {
-                    const u32 raw = chunk_elem<DT>(v[c], e);
-                    braw[pos] = DT == 0 ? raw : raw << 16;
-                    bidx[pos] = (uint16_t)(c * (kWave * EPC) + (int)lane * EPC + e);
-                    ++pos;
-                }
-            }
-        }
-        wave_sync();
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {                // two entries per lane at a time, their lookups side by side
-#pragma unroll
-            for (int e = 0; e < 2; ++e) bf[g][2 * h + e] = 0;
-            if ((u32)(2 * h * kWave) >= ng) continue;        // uniform in the wavefront
-            u32 rw[2], ix[2], bin[2];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const u32 i = (u32)((2 * h + e) * kWave) + lane;
-                rw[e] = braw[i]; ix[e] = we0 + (u32)bidx[i];
-            }
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const u32 key = DT == 0 ? rw[e] & 0x7FFFFFFFu : (rw[e] >> 16) & 0x7FFFu;
-                bin[e] = lr_fine_bin<DT>(lr_c32<DT>(key, (u32)e_base + ix[e], w), tab, Blo, nb);
-            }
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const u32 i = (u32)((2 * h + e) * kWave) + lane;
-                const bool in = i < ng, neg = rw[e] >> 31;
-                // (lanes without an entry add nothing, each to a bin of its own)
-                const u32 old = atomicAdd(&hist[in ? bin[e] : lane], in ? (neg ? 0x10000u : 1u) : 0u);
-                bf[g][2 * h + e] = bin[e] | ((neg ? old >> 16 : old & 0xFFFFu) << 12) | (rw[e] & 0x80000000u);
-            }
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const u32 i = (u32)((2 * h + e) * kWave) + lane;
-                if (i < ng && !full) { Lraw[g0 + i] = rw[e]; Lidx[g0 + i] = (uint16_t)ix[e]; }
-            }
-        }
-        wave_sync();
-        g0 = g1;
-    }
-    __syncthreads();
     u32* seg = a.seg + ((size_t)r * a.S + s) * 2;
     {
-        // bins per thread from the top, 8 or 2; the halves add up separately: no sum reaches 2^16
+        // bins per thread from the top, 4 or 2; the halves add up separately: no sum reaches 2^16
         constexpr int BPT = FB / kTileThreads;
-        typedef u32 bins_t __attribute__((ext_vector_type(BPT < 4 ? BPT : 4)));
-        constexpr int VW = BPT < 4 ? BPT : 4, NV = BPT / VW;
-        bins_t* h4 = (bins_t*)hist + (FB - tid * BPT) / VW;
-        bins_t t[NV];
+        typedef u32 bins_t __attribute__((ext_vector_type(BPT)));
+        bins_t* h4 = (bins_t*)hist + (FB / BPT - 1 - tid);
+        const bins_t t = *h4;
         u32 local = 0;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            t[i] = h4[-1 - i];
-#pragma unroll
-            for (int j = 0; j < VW; ++j) local += t[i][j];
-        }
+        for (int j = 0; j < BPT; ++j) local += t[j];
         u32 tot;
         u32 at = block_excl_scan<kTileThreads>(local, scr, &tot);
         const u32 off = (tot & 0xFFFFu) << 16;       // the negative entries follow the positive ones
-        bins_t* out = (bins_t*)(a.cum + ((size_t)r * a.S + s) * FB) + (FB - tid * BPT) / VW;
+        bins_t up, st0;                              // entries at or above the bin; place of the bin's first one
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            bins_t up, st0;                          // entries at or above the bin; place of the bin's first one
-#pragma unroll
-            for (int j = VW - 1; j >= 0; --j) { st0[j] = at + off; at += t[i][j]; up[j] = at; }
-            out[-1 - i] = up;
-            h4[-1 - i] = st0;
-        }
+        for (int j = BPT - 1; j >= 0; --j) { st0[j] = at + off; at += t[j]; up[j] = at; }
+        ((bins_t*)(a.cum + ((size_t)r * a.S + s) * FB))[FB / BPT - 1 - tid] = up;
+        *h4 = st0;
         if (tid == 0) { seg[0] = seg0; seg[1] = tot; }
     }
     if (full || ntile == 0u) return;                 // uniform
-    __syncthreads();
-    for (u32 p0 = 0; p0 < ntile; p0 += kPass) {      // one pass unless more than three quarters of the tile are above the bound
-    g0 = 0;
+    if (dense) {
+        __syncthreads();
+        rounds([&](u32 i, u32 raw, u32 ix) {
+            Lraw[i] = raw; Lidx[i] = (uint16_t)(we0 + ix);
+            const u32 b = bin_of(raw, ix), at = atomicAdd(&hist[b & 0xFFFu], one(b));
+            Lpos[b >> 31 ? at >> 16 : at & 0xFFFFu] = (uint16_t)(wbase + i);
+        });
+        return;
+    }
 #pragma unroll
-    for (int g = 0; g < NR; ++g) {
-        const u32 g1 = g + 1 < NR ? bcast(base[(g + 1) * CPR < NCH ? (g + 1) * CPR : 0], 0) : wn;
-        const u32 ng = g1 - g0;
+    for (int h = 0; h < NS; ++h) {
+        const u32 i = (u32)(h * kWave) + lane;
+        if ((u32)(h * kWave) >= wn) break;
+        if (i < wn) { Lraw[i] = braw[i]; Lidx[i] = (uint16_t)(we0 + (u32)bidx[i]); }
+    }
+    __syncthreads();                                 // the entries have been read: their storage takes the positions
 #pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            if ((u32)(2 * h * kWave) >= ng) continue;
-            u32 hv[2];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) hv[e] = hist[bf[g][2 * h + e] & 0xFFFu];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const u32 i = (u32)((2 * h + e) * kWave) + lane, t = bf[g][2 * h + e];
-                const u32 at = ((t >> 31) ? hv[e] >> 16 : hv[e] & 0xFFFFu) + ((t >> 12) & 0x7FFFu) - p0;
-                if (i < ng && at < (u32)kPass) bpos[at] = (uint16_t)(wbase + g0 + i);
-            }
+    for (int h = 0; h < NS; ++h) {
+        if ((u32)(h * kWave) >= wn) break;
+        const u32 i = (u32)(h * kWave) + lane;
+        if (i < wn) {
+            const u32 at = atomicAdd(&hist[bf[h] & 0xFFFu], one(bf[h]));
+            bpos[bf[h] >> 31 ? at >> 16 : at & 0xFFFFu] = (uint16_t)(wbase + i);
         }
-        g0 = g1;
     }
     __syncthreads();
-    for (u32 i = (u32)tid; i < (u32)kPass && p0 + i < ntile; i += kTileThreads) Lpos[p0 + i] = bpos[i];
-    __syncthreads();
-    }
+    for (u32 i = (u32)tid; i < ntile; i += kTileThreads) Lpos[i] = bpos[i];
 }
 
 // ---- bitwidths, bit offsets and the row's length ----------------------------------------------------
@@ -570,12 +574,15 @@ __device__ inline void lr_finish_row(const LargeArgs& a, int64_t r, u32 n_pos, u
 // ---- 3. bounds ------------------------------------------------------------------------------------
 constexpr int kMaxTargets = 2 * kMaxB2;
 
-template <int FB>
+// a member: comp in the low 55 bits (31 of the key, up to 24 of the index), its group, its class
+constexpr int kMemGroup = 55;
+constexpr u64 kMemComp = (1ull << kMemGroup) - 1ull;
+
+template <int FB, bool BIG>
 struct LrBoundsLds {
-    static constexpr int kMemCap = lr_mem_cap(FB);
-    u32 at_p[FB + 1], at_n[FB + 1];                // list entries at or above the bin
-    u64 mem[kMemCap];                                // members of the bins that hold a target
-    u32 mem_g[kMemCap];                              // their group | tile << 8
+    static constexpr int kMemCap = lr_mem_cap(FB, BIG);
+    u32 at_p[FB + 4], at_n[FB + 4];                // list entries at or above the bin
+    u64 mem[kMemCap + 4];                            // members of the bins that hold a target
     u32 tg_bin[kMaxTargets], tg_rem[kMaxTargets];    // target 2 b: first element of block b, 2 b + 1: its last one
     u64 tg_comp[kMaxTargets];
     u32 g_bin[kMaxTargets], g_cls[kMaxTargets];      // groups of consecutive targets in one bin; class 2: both
@@ -583,16 +590,21 @@ struct LrBoundsLds {
     u32 v[8];
 };
 
-template <int DT, int FB>
-__global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs ea)
+template <int DT, int FB, bool BIG>
+__global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs a, EncArgs ea)
 {
-    constexpr int TH = FB / 4, kMemCap = lr_mem_cap(FB);
+    constexpr int TH = lr_row_threads(FB), kMemCap = lr_mem_cap(FB, BIG);
     constexpr bool kRedo = FB == kFBWide;            // rows that do not fit are redone here (else: after the pack stage)
-    constexpr size_t kOwn = sizeof(LrBoundsLds<FB>), kRedoLds = kRedo ? sizeof(GenericLds<1024>) : 0;
+    constexpr size_t kOwn = sizeof(LrBoundsLds<FB, BIG>), kRedoLds = kRedo ? sizeof(GenericLds<1024>) : 0;
     __shared__ __align__(16) unsigned char lds[kOwn > kRedoLds ? kOwn : kRedoLds];
-    LrBoundsLds<FB>& L = *(LrBoundsLds<FB>*)lds;
+    LrBoundsLds<FB, BIG>& L = *(LrBoundsLds<FB, BIG>*)lds;
     const int tid = threadIdx.x, w = a.w, M = a.M, Mn = a.Mn, B2 = M + Mn, S = a.S;
-    const int64_t r = blockIdx.x;
+    // P workgroups share a row: all of them sum the tables and find the bins, each resolves its share of these.  A bin's members lie one or two
+    // to a cache line, a thousand lines and more for a row, at the end of three dependent loads: one workgroup of fp32 [32 x 401408] took
+    // 18 us to gather and compare them, eight take 5.  (A row's workgroups are R apart in the grid: on one XCD when R is a
+    // multiple of eight, so that its L2 serves the tables.)
+    const int P = a.parts, part = (int)(blockIdx.x / (u32)a.R);
+    const int64_t r = blockIdx.x % (u32)a.R;
     u32* st = a.rowst + (size_t)r * 16;
     const u32 k = (u32)a.k;
     const u32* __restrict__ cum = a.cum + (size_t)r * S * FB;
@@ -602,25 +614,39 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
     const uint16_t* __restrict__ Lidx = list.idx;
     const uint16_t* __restrict__ Lpos = list.pos;
     u32* pair = a.pair + (size_t)r * B2 * S;
-    const int head = RowChunks<DT>(a.x, r, a.N).head;
     bool bad = st[kStFlag] != 0u;                    // uniform
     const u32 T = st[kStT];
 
-    // sums of the tiles' tables: a thread takes four bins, eight tiles in flight
+    // sums of the tiles' tables: a thread takes four bins of every GT-th tile, eight of them in flight
     {
+        constexpr int GT = 4 * TH / FB;
+        static_assert(GT == 1 || GT == 2, "the groups' sums meet in one step");
+        const int gt = tid / (FB / 4), c4 = tid - gt * (FB / 4);
         u32 p[4] = { 0, 0, 0, 0 }, n[4] = { 0, 0, 0, 0 };
-        for (int s0 = 0; s0 < S; s0 += 8) {
+        for (int s0 = gt; s0 < S; s0 += 8 * GT) {
             uint4 t[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = s0 + u < S ? ((const uint4*)(cum + (size_t)(s0 + u) * FB))[tid] : make_uint4(0, 0, 0, 0);
+            for (int u = 0; u < 8; ++u) t[u] = s0 + u * GT < S ? ((const uint4*)(cum + (size_t)(s0 + u * GT) * FB))[c4] : make_uint4(0, 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 p[0] += t[u].x & 0xFFFFu; p[1] += t[u].y & 0xFFFFu; p[2] += t[u].z & 0xFFFFu; p[3] += t[u].w & 0xFFFFu;
                 n[0] += t[u].x >> 16; n[1] += t[u].y >> 16; n[2] += t[u].z >> 16; n[3] += t[u].w >> 16;
             }
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { L.at_p[tid * 4 + j] = p[j]; L.at_n[tid * 4 + j] = n[j]; }
+        uint4* ap = (uint4*)L.at_p + c4;
+        uint4* an = (uint4*)L.at_n + c4;
+        if (GT > 1) {
+            if (gt) { *ap = make_uint4(p[0], p[1], p[2], p[3]); *an = make_uint4(n[0], n[1], n[2], n[3]); }
+            __syncthreads();
+        }
+        if (!gt) {
+            if (GT > 1) {
+                const uint4 tp = *ap, tn = *an;
+                p[0] += tp.x; p[1] += tp.y; p[2] += tp.z; p[3] += tp.w;
+                n[0] += tn.x; n[1] += tn.y; n[2] += tn.z; n[3] += tn.w;
+            }
+            *ap = make_uint4(p[0], p[1], p[2], p[3]); *an = make_uint4(n[0], n[1], n[2], n[3]);
+        }
         if (tid == 0) { L.at_p[FB] = 0; L.at_n[FB] = 0; }
         if (tid < 8) L.v[tid] = 0;
     }
@@ -629,14 +655,16 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
     if (nL < k && T > LrOrder<DT>::kLeast) bad = true;       // the sample's bound was too high
 
     auto at_c = [&](u32 cls, u32 b) -> u32 { return cls == 0u ? L.at_p[b] : cls == 1u ? L.at_n[b] : L.at_p[b] + L.at_n[b]; };
-    // members of the bins of groups 0 .. ng - 1 (g_start: room per group), tile by tile; up to eight threads share a tile's
+    // members of the bins of groups ga .. gb - 1 (g_start: room per group), tile by tile; up to eight threads share a tile's
     // members while there are threads to spare (equal values fill a bin: fp32 [1 x 200704] quantised to 256 levels 119 -> 113 us, bf16
     // to 16 levels 84 -> 70; what remains there is the comparison of all members of a bin with each other)
-    auto gather = [&](int ng) {
+    auto gather = [&](int ga, int gb) {
+        const int ng = gb - ga;
+        const u32 m0 = L.g_start[ga];
         int lp = 0;                                  // log2 of the threads that share
         while (lp < 3 && (ng * S << (lp + 1)) <= TH) ++lp;
         for (int i = tid; i < ng * S << lp; i += TH) {
-            const int gs = i >> lp, part = i - (gs << lp), g = gs / S, s = gs - g * S;
+            const int gs = i >> lp, share_of = i - (gs << lp), gi = gs / S, s = gs - gi * S, g = ga + gi;
             const u32 cls = L.g_cls[g], b = L.g_bin[g];
             const u32 c0 = cum[(size_t)s * FB + b], c1 = b + 1u < (u32)FB ? cum[(size_t)s * FB + b + 1u] : 0u;
             const u32 seg0 = seg[2 * s], np = seg[2 * s + 1] & 0xFFFFu;
@@ -644,11 +672,11 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
             for (u32 h = 0; h < 2u; ++h) {
                 if (cls != 2u && cls != h) continue;
                 const u32 n0 = h ? c0 >> 16 : c0 & 0xFFFFu, n1 = h ? c1 >> 16 : c1 & 0xFFFFu, cn = n0 - n1;
-                if (cls != 2u && part == 0)          // entries of the tile above the bin: the start of the blocks' counts
+                if (cls != 2u && share_of == 0)          // entries of the tile above the bin: the start of the blocks' counts
                     for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t) if (t & 1u) pair[(size_t)(t >> 1) * S + s] = n1;
-                const u32 share = (cn + (1u << lp) - 1u) >> lp, p0 = (u32)part * share, p1 = p0 + share < cn ? p0 + share : cn;
+                const u32 share = (cn + (1u << lp) - 1u) >> lp, p0 = (u32)share_of * share, p1 = p0 + share < cn ? p0 + share : cn;
                 if (p0 >= p1) continue;
-                const u32 slot = L.g_start[g] + atomicAdd(&L.g_fill[g], p1 - p0) - p0;
+                const u32 slot = L.g_start[g] - m0 + atomicAdd(&L.g_fill[g], p1 - p0) - p0;
                 for (u32 j0 = p0; j0 < p1; j0 += 4) {
                     u32 lp[4], rw[4], ix[4];
 #pragma unroll
@@ -659,8 +687,7 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
                     for (u32 u = 0; u < 4; ++u) {
                         if (j0 + u < p1) {
                             const u32 key = DT == 0 ? rw[u] & 0x7FFFFFFFu : (rw[u] >> 16) & 0x7FFFu;
-                            L.mem[slot + j0 + u] = lr_comp(key, (u32)(s * a.tile - head) + ix[u], w) | (h ? kTop : 0ull);
-                            L.mem_g[slot + j0 + u] = (u32)g | ((u32)s << 8);
+                            L.mem[slot + j0 + u] = lr_comp(key, (u32)(s * a.tile) + ix[u], w) | ((u64)g << kMemGroup) | (h ? kTop : 0ull);
                         }
                     }
                 }
@@ -675,8 +702,8 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
         else if (n_pos == 0u) n_neg = k;
         else {                                       // ATKF cut: overall rank k - 1
 #pragma unroll
-            for (u32 j = 0; j < 4; ++j) {
-                const u32 b = (u32)tid * 4u + j;
+            for (u32 j = 0; j < (u32)(FB / TH); ++j) {
+                const u32 b = (u32)tid * (u32)(FB / TH) + j;
                 if (at_c(2, b) > k - 1u && at_c(2, b + 1u) <= k - 1u) {
                     L.g_bin[0] = b; L.g_cls[0] = 2; L.g_start[0] = 0; L.g_start[1] = at_c(2, b) - at_c(2, b + 1u);
                     L.g_fill[0] = 0;
@@ -686,12 +713,18 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
             const u32 cn = L.g_start[1], cb = L.g_bin[0];
             if (cn > (u32)kMemCap) bad = true;
             else {
-                gather(1);
+                gather(0, 1);
                 const u32 rem = k - 1u - at_c(2, cb + 1u);
                 for (u32 i = (u32)tid; i < cn; i += TH) {
                     const u64 me = L.mem[i] & ~kTop;
                     u32 gt = 0;
-                    for (u32 j = 0; j < cn; ++j) gt += (L.mem[j] & ~kTop) > me ? 1u : 0u;
+                    for (u32 j = 0; j < cn; j += 4) {
+                        u64 m4[4];
+#pragma unroll
+                        for (u32 u = 0; u < 4; ++u) m4[u] = L.mem[j + u] & ~kTop;
+#pragma unroll
+                        for (u32 u = 0; u < 4; ++u) gt += (u32)(j + u < cn) & (u32)(m4[u] > me);
+                    }
                     if (gt <= rem) atomicAdd(&L.v[(L.mem[i] & kTop) ? 1 : 0], 1u);
                 }
                 __syncthreads();
@@ -703,30 +736,33 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
     }
     const u32 Kc0 = n_pos / (u32)M, Kc1 = n_neg / (u32)Mn;
     if (!bad) {
-        if (tid < 2 * B2) {
-            const int b = tid >> 1, c = b >= M ? 1 : 0, m = b - c * M, Ms = c ? Mn : M;
-            const u32 K = c ? Kc1 : Kc0, cnt = m < Ms - 1 ? K : (c ? n_neg : n_pos) - K * (u32)(Ms - 1);
-            u32 bin = 0xFFFFFFFFu, rem = 0;          // an empty block has no elements
-            if (cnt) {
-                const u32 rank = (u32)m * K + ((tid & 1) ? cnt - 1u : 0u);
-                const u32* at = c ? L.at_n : L.at_p;
-                int lo = 0, hi = FB - 1;            // the last bin with more than `rank` entries at or above it
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (at[mid] > rank) lo = mid; else hi = mid - 1;
-                }
-                bin = (u32)lo;
-                rem = rank - at[lo + 1];
+        // the bin of every target, sixteen lanes a target: the last one with more than `rank` entries at or above it
+        for (int t0 = 0; t0 < 2 * B2; t0 += TH / 16) {
+            const int t = t0 + tid / 16, b = t >> 1, c = b >= M ? 1 : 0, m = b - c * M, Ms = c ? Mn : M;
+            const u32 K = c ? Kc1 : Kc0, cnt = t >= 2 * B2 ? 0u : m < Ms - 1 ? K : (c ? n_neg : n_pos) - K * (u32)(Ms - 1);
+            const u32 rank = (u32)m * K + ((t & 1) && cnt ? cnt - 1u : 0u);
+            const u32* at = c ? L.at_n : L.at_p;
+            u32 lo = 0;                              // (an empty block's search finds nothing of use)
+#pragma unroll
+            for (int step = FB > 256 ? (FB + 255) / 256 * 16 : 16; step; step = step > 16 ? 16 : step > 1 ? 1 : 0) {
+                const u32 b2 = lo + (u32)((tid & 15) * step);
+                const u64 above = __ballot(b2 < (u32)FB && at[b2 < (u32)FB ? b2 : 0u] > rank);
+                const u32 mine = (u32)(above >> (tid & 48)) & 0xFFFFu;
+                lo += (mine ? 31u - (u32)__clz((int)mine) : 0u) * (u32)step;
             }
-            L.tg_bin[tid] = bin; L.tg_rem[tid] = rem; L.tg_comp[tid] = ~0ull;
+            if (t < 2 * B2 && (tid & 15) == 0) {
+                L.tg_bin[t] = cnt ? lo : 0xFFFFFFFFu;        // an empty block has no elements
+                L.tg_rem[t] = cnt ? rank - at[lo + 1u] : 0u;
+                L.tg_comp[t] = ~0ull;
+            }
         }
         __syncthreads();
         if (tid < kWave) {                           // groups: a target opens one unless the target before it lies in the same bin
+            const int TL = (2 * B2 + kWave - 1) / kWave;     // targets a lane
             u32 lead = 0, room = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int t = tid * 4 + j;
-                if (t >= 2 * B2) continue;
+            for (int j = 0; j < TL; ++j) {
+                const int t = tid * TL + j;
+                if (t >= 2 * B2) break;
                 const u32 b = L.tg_bin[t], c = (t >> 1) >= M ? 1u : 0u;
                 const bool same = t > 0 && L.tg_bin[t - 1] == b && (((t - 1) >> 1) >= M ? 1u : 0u) == c;
                 if (b != 0xFFFFFFFFu && !same) { lead |= 1u << j; room += at_c(c, b) - at_c(c, b + 1u); }
@@ -734,9 +770,8 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
             const u32 nl = (u32)__popc(lead);
             const u32 incl = wave_scan_dpp(nl), incr = wave_scan_dpp(room);
             u32 g = incl - nl, at = incr - room;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int t = tid * 4 + j;
+            for (int j = 0; j < TL; ++j) {
+                const int t = tid * TL + j;
                 if (!((lead >> j) & 1u)) continue;
                 const u32 b = L.tg_bin[t], c = (t >> 1) >= M ? 1u : 0u;
                 L.g_bin[g] = b; L.g_cls[g] = c; L.g_start[g] = at; L.g_fill[g] = 0; L.g_t0[g] = (u32)t;
@@ -747,37 +782,55 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
         }
         __syncthreads();
         const int ng = (int)L.v[2];
-        const u32 nm = L.g_start[ng];
-        if (nm > (u32)kMemCap) bad = true;
-        else {
-            gather(ng);
-            for (u32 i = (u32)tid; i < nm; i += TH) {
-                const u32 g = L.mem_g[i] & 0xFFu, m1 = L.g_start[g + 1];
-                const u64 me = L.mem[i];
+        for (int i = 0; i < P; ++i) bad |= L.g_start[ng * (i + 1) / P] - L.g_start[ng * i / P] > (u32)kMemCap;
+        if (!bad) {
+            const int ga = ng * part / P, gb = ng * (part + 1) / P;
+            const u32 m0 = L.g_start[ga], nm = L.g_start[gb] - m0;
+            gather(ga, gb);
+            // rank of every member in its group, by up to sixteen lanes a member (one lane: 2.7 us of a row's 13 with 90 members a group)
+            int lr = 0;
+            while (lr < 4 && (nm << (lr + 1)) <= (u32)TH) ++lr;
+            const u32 sl = (u32)tid & ((1u << lr) - 1u), lanes = 1u << lr;
+            for (u32 i0 = 0; i0 < nm; i0 += (u32)TH >> lr) {
+                const u32 i = i0 + ((u32)tid >> lr);
+                const u64 me = i < nm ? L.mem[i] : 0ull;
+                const u32 g = i < nm ? (u32)(me >> kMemGroup) & 0xFFu : (u32)ga, m1 = L.g_start[g + 1] - m0, t1 = L.g_t0[g + 1], gb_bin = L.g_bin[g];
                 u32 gt = 0;
-                for (u32 j = L.g_start[g]; j < m1; ++j) gt += L.mem[j] > me ? 1u : 0u;
-                for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t)
-                    if (L.tg_bin[t] == L.g_bin[g] && L.tg_rem[t] == gt) L.tg_comp[t] = me & ~kTop;
+                for (u32 j = L.g_start[g] - m0 + sl; j < m1; j += 4 * lanes) {
+                    u64 m4[4];
+#pragma unroll
+                    for (u32 u = 0; u < 4; ++u) m4[u] = L.mem[j + u * lanes < m1 ? j + u * lanes : m1 - 1u];
+#pragma unroll
+                    for (u32 u = 0; u < 4; ++u) gt += (u32)(j + u * lanes < m1) & (u32)(m4[u] > me);
+                }
+                for (int d = 1; d < (int)lanes; d <<= 1) gt += (u32)__shfl_xor((int)gt, d);
+                for (u32 t = L.g_t0[g] + sl; i < nm && t < t1; t += lanes)
+                    if (L.tg_bin[t] == gb_bin && L.tg_rem[t] == gt) L.tg_comp[t] = me & kMemComp;
             }
             __syncthreads();
             // per tile: entries of the class from the block's last element up
             for (u32 i = (u32)tid; i < nm; i += TH) {
-                const u32 g = L.mem_g[i] & 0xFFu;
-                const u64 me = L.mem[i] & ~kTop;
+                const u32 g = (u32)(L.mem[i] >> kMemGroup) & 0xFFu;
+                const u64 me = L.mem[i] & kMemComp;
+                const u32 s = ((1u << w) - 1u - ((u32)me & ((1u << w) - 1u))) / (u32)a.tile;      // its tile
                 for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t)
-                    if ((t & 1u) && me >= L.tg_comp[t]) atomicAdd(&pair[(size_t)(t >> 1) * S + (L.mem_g[i] >> 8)], 1u);
+                    if ((t & 1u) && me >= L.tg_comp[t]) atomicAdd(&pair[(size_t)(t >> 1) * S + s], 1u);
             }
-            for (int b = tid; b < B2; b += TH) {
-                const u64 first = L.tg_comp[2 * b], last = L.tg_comp[2 * b + 1];
-                a.thr[(size_t)r * B2 + b] = last;
-                a.vminb[(size_t)r * B2 + b] = last == ~0ull ? 0u : (u32)(last >> w);
-                a.vmaxb[(size_t)r * B2 + b] = last == ~0ull ? 0u : (u32)(first >> w);
+            for (int t = tid; t < 2 * B2; t += TH) {
+                const u64 c = L.tg_comp[t];
+                const size_t rb = (size_t)r * B2 + (t >> 1);
+                const bool empty = L.tg_bin[t] == 0xFFFFFFFFu;
+                if (empty ? part != 0 : c == ~0ull) continue;            // (another workgroup's)
+                const u32 key = empty ? 0u : (u32)(c >> w);
+                if (t & 1) { a.thr[rb] = c; a.vminb[rb] = key; } else a.vmaxb[rb] = key;
             }
-            for (int b = tid; b <= B2; b += TH) {  // K, ..., K, K + remainder per class
-                const int c = b >= M ? 1 : 0, m = b - c * M;
-                a.blk_start[(size_t)r * (B2 + 1) + b] = b == B2 ? n_pos + n_neg : (c ? n_pos : 0u) + (u32)m * (c ? Kc1 : Kc0);
+            if (part == 0) {
+                for (int b = tid; b <= B2; b += TH) {  // K, ..., K, K + remainder per class
+                    const int c = b >= M ? 1 : 0, m = b - c * M;
+                    a.blk_start[(size_t)r * (B2 + 1) + b] = b == B2 ? n_pos + n_neg : (c ? n_pos : 0u) + (u32)m * (c ? Kc1 : Kc0);
+                }
+                if (tid == 0) { st[kStNpos] = n_pos; st[kStNneg] = n_neg; }
             }
-            if (tid == 0) { st[kStNpos] = n_pos; st[kStNneg] = n_neg; }
             // block of every fine bin, for the split: only the bins that hold a boundary need a look at the element
 #pragma unroll
             for (u32 c = 0; c < 2u; ++c) {
@@ -791,6 +844,7 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
                     if (K) { if (q * K > rank) --q; if ((q + 1u) * K <= rank) ++q; }        // (the product is off by less than one)
                     return b0 + (q < Ms ? q : Ms - 1u);
                 };
+                if (tid >= FB / 4 || tid * P / (FB / 4) != part) continue;      // (a share of the bins each)
                 u32 wd = 0;
 #pragma unroll
                 for (u32 j = 0; j < 4u; ++j) {
@@ -807,6 +861,7 @@ __global__ __launch_bounds__(FB / 4) void lr_bounds_kernel(LargeArgs a, EncArgs 
             }
         }
     }
+    if (part != 0) return;
     if constexpr (!kRedo) {
         if (tid == 0) {
             a.redo[r] = bad ? 1u : 0u;
@@ -963,8 +1018,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     const LrList list(a, r);
     const u32* __restrict__ Lraw = list.raw + seg0;
     const uint16_t* __restrict__ Lidx = list.idx + seg0;
-    const int head = RowChunks<DT>(a.x, r, a.N).head;
-    const u32 tile0 = (u32)(s * a.tile - head);       // index of the tile's element 0 (modulo 2^32)
+    const u32 tile0 = (u32)(s * a.tile);             // index of the tile's element 0
     const bool want_sums = !a.lad.on;
 
     u32 rw[NE], ix[NE];
@@ -977,6 +1031,21 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
         }
     };
     fetch(0);
+    // the tile's place in every block: the entries of the tiles before it, sixteen lanes a block and a scan
+    for (int b0 = 0; b0 < B2; b0 += kTileThreads / 16) {
+        const int b = b0 + tid / 16;
+        const u32* pr = a.pair + ((size_t)r * B2 + (b < B2 ? b : 0)) * S;
+        u32 n = 0;
+        for (int t0 = tid & 15; t0 < s; t0 += 64) {
+            u32 c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[u] = t0 + 16 * u < s ? pr[t0 + 16 * u] : 0u;
+            n += (c[0] + c[1]) + (c[2] + c[3]);
+        }
+        n = row_scan_dpp(n);
+        if (b < B2 && (tid & 15) == 15) cntb[b] = n;     // with the blocks of its class before it (an empty block's is not looked at)
+    }
+    float* rngf = (float*)val;
     if (tid < B2) {
         const size_t rb = (size_t)r * B2 + tid;
         const u64 t = a.thr[rb];
@@ -985,6 +1054,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
         const u32 lo = E::value_bits(a.vminb[rb]), hi = E::value_bits(a.vmaxb[rb]);
         const float vmin = __uint_as_float(lo), rng = __uint_as_float(hi) - vmin;
         vminf[tid] = vmin;
+        rngf[tid] = rng;
         er_tab[tid] = rng > 0.f ? range_exp(rng) : 0;                // only a range of exactly 0 is degenerate
         e_tab[tid] = t != ~0ull ? ilogb_bits(hi) + 1 : 0;
     }
@@ -998,18 +1068,12 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     __syncthreads();
     for (int i = tid; i < B2 * nq; i += kTileThreads) {              // quantiser scales 2^15 L / (range brought to [1, 2))
         const int b = i / nq, t = i - b * nq;
-        const size_t rb = (size_t)r * B2 + b;
-        const float rng = __uint_as_float(E::value_bits(a.vmaxb[rb])) - vminf[b];
+        const float rng = rngf[b];
         invt[i] = rng > 0.f ? (float)((1u << a.qlist[t]) - 1u) / unit_range(rng, er_tab[b]) * 32768.0f : 0.f;      // (times 2^15: exact)
     }
-    // the tile's place in every block: the entries of the tiles before it
-    for (int i = tid; i < B2 * s; i += kTileThreads) {
-        const int b = i / s, t = i - b * s;
-        if (thr[b] == ~0ull) continue;               // an empty block
-        const u32* pr = a.pair + ((size_t)r * B2 + b) * S + t;
-        const bool first = b == 0 || b == M || thr[b - 1] == ~0ull;
-        const u32 d = pr[0] - (first ? 0u : *(pr - S));
-        if (d) atomicAdd(&gbase[b], d);
+    if (tid < B2) {
+        const bool first = tid == 0 || tid == M || thr[tid - 1] == ~0ull;
+        gbase[tid] += cntb[tid] - (first ? 0u : cntb[tid - 1]);
     }
     int nbits = 0;
     while ((1 << nbits) < B2) ++nbits;

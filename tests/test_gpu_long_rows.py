@@ -109,3 +109,18 @@ def test_csr_of_long_rows_through_the_flat_stream(oracle, dtype, shift):
     words = binding.slicer_stream_words(meta)
     assert np.array_equal(meta.cpu().numpy(), m_ref)
     assert np.array_equal(sb[:words].cpu().numpy().view(np.uint32), s_ref)
+
+
+@pytest.mark.parametrize("dtype,rows,N,keep,M", [("f32", 3, 40_000, 0.8, 8), ("f32", 40, 65_549, 0.3, 8), ("bf16", 3, 40_001, 0.8, 8), ("bf16", 40, 65_549, 0.2, 8),
+                                                 ("bf16", 90, 30_002, 0.5, 3), ("f32", 130, 17_000, 0.2, 16), ("f32", 2, 140_000, 0.5, 64), ("f32", 1, 600_000, 0.03, 4)])
+def test_dense_tiles_and_shared_rows(oracle, dtype, rows, N, keep, M):
+    """Wavefronts with more entries than their room (640) beside emptier ones; one to eight workgroups for a row's order statistics; tiles that are no
+    power of two; rows of odd length whose words hold halves of two rows; the larger room for a row's bin members."""
+    x = features(dtype, rows, N, N)
+    x[:, N // 3: N // 2] = 0                            # some tiles hold nothing ...
+    x[:, N // 2: N // 2 + 3000] = features(dtype, rows, 3000, 1)
+    for i in range(rows):                               # ... and some hold only entries
+        lo = (i * 997) % (N - 6000)
+        big = np.abs(features("f32", 1, 5000, i)[0]) + 4
+        x[i, lo:lo + 5000] = synth.f32_to_bf16_bits(big) if dtype == "bf16" else big
+    check(oracle, x, dtype, keep, M, B28, 1e-3)
