@@ -77,7 +77,7 @@ struct Plan {
     // long-row path (large_S == 0: not eligible)
     int large_S, large_fb;  // tiles per row, fine bins
     u32 large_capL;
-    size_t lo_tab, lo_cum, lo_seg, lo_rowst, lo_thr, lo_map, lo_vminb, lo_vmaxb, lo_blk_start, lo_pair, lo_psum,
+    size_t lo_tab, lo_cum, lo_seg, lo_rowst, lo_thr, lo_vminb, lo_vmaxb, lo_blk_start, lo_pair, lo_sums,
            lo_qsel, lo_inv_sel, lo_code_off;
 };
 
@@ -99,7 +99,7 @@ int large_tile(int64_t rows, int64_t row_len)
 {
     const int64_t n8 = (row_len + 8191) / 8192;
     if (rows * n8 <= 256 || (rows > kScanRows && (n8 == 1 || n8 == 3))) return 8192;
-    const int64_t S = std::max<int64_t>((row_len + 16383) / 16384, std::min<int64_t>(1024 / rows, n8));
+    const int64_t S = std::max<int64_t>((row_len + 16383) / 16384, rows <= kScanRows ? std::min<int64_t>({1024 / rows, n8, 512}) : 0);
     return (int)((row_len + 512 * S - 1) / (512 * S) * 512);
 }
 
@@ -120,6 +120,21 @@ int large_fine_bins(int64_t rows, int64_t k, int B2)
 
 // the bounds stage with the larger room
 bool large_many_members(int64_t k, int B2) { return large_members(kFBWide, k, B2) > 4800; }
+
+// Room for the stages' tables.  It is what they took with 4096 bins, a block for every bin, sums per tile and tiles of 8192 or 16384 elements,
+// which is never less than they take now: the size of a workspace is part of what callers plan and store, and does not follow the stages' tuning.
+size_t large_table_room(size_t R, int64_t row_len, int epc, int64_t k, size_t B2, size_t nq)
+{
+    const int64_t n8 = (row_len + 8191) / 8192, tile = (int64_t)R * n8 <= 256 || (R > kScanRows && (n8 == 1 || n8 == 3)) ? 8192 : 16384;
+    const size_t S = (size_t)((row_len + epc - 1 + tile - 1) / tile);
+    const int64_t members = std::min<int64_t>((int64_t)(B2 + 2) * std::max<int64_t>(12, k * 3 / 1400), k * 14 / 10 + 100);
+    const size_t bins = R > kScanRows && members <= 1200 ? 1024 : 4096;
+    size_t o = 0;
+    for (size_t bytes : { 2 * R * kTabSize, 4 * R * S * bins, 8 * R * S, 4 * R * 16, 8 * R * B2, 2 * R * bins, 4 * R * B2, 4 * R * B2, 4 * R * (B2 + 1),
+                          4 * R * B2 * S, 8 * R * S * B2 * (nq + 1), 4 * R * B2, 4 * R * B2, 8 * R * (B2 + 1) })
+        o = align256(o + bytes);
+    return o;
+}
 
 // aligned: x starts on a 16-byte boundary (the workspace layout does not depend on it, only the choice of kernel)
 // long_rows: the long-row stages may serve the call; without them (the generic kernel) it needs less workspace
@@ -205,31 +220,31 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     p.large_S = 0; p.large_capL = 0; p.large_fb = 0;
     {
         const int64_t tile = large_tile(rows, row_len);
-        // rows of up to 2^23 elements; the workspace has room for the tile more that such a row takes when it starts inside a chunk
-        const int64_t S_whole = (row_len + tile - 1) / tile, S = (row_len + epc - 1 + tile - 1) / tile;
+        const int64_t S = (row_len + tile - 1) / tile;       // rows of up to 2^23 elements
         const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;
         auto row_kernel_holds = [&](int64_t elements) { return small_holds(elements) || wg_holds(elements); };
         const bool held = (!whole_len || row_kernel_holds(row_len)) && row_kernel_holds(row_len + epc - 1);
-        if (long_rows && row_len > 4096 && S_whole <= 512 && rows <= 65535 && !held && (whole_len || row_len > 8192)) {
+        if (long_rows && row_len > 4096 && S <= 512 && rows <= 65535 && !held && (whole_len || row_len > 8192)) {
             const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
             if (whole || row_len > 8192) p.large_S = (int)S;
             p.large_capL = (u32)capL;
             p.large_fb = large_fine_bins(rows, p.k, B2_all);
             p.kept_stride = capL;
+            const size_t tables = o;
             p.lo_tab = o;       o = align256(o + 2 * R * kTabSize);
             p.lo_cum = o;       o = align256(o + 4 * R * Sz * (size_t)p.large_fb);
             p.lo_seg = o;       o = align256(o + 8 * R * Sz);
             p.lo_rowst = o;     o = align256(o + 4 * R * 16);
             p.lo_thr = o;       o = align256(o + 8 * R * B2);
-            p.lo_map = o;       o = align256(o + 2 * R * (size_t)p.large_fb);
             p.lo_vminb = o;     o = align256(o + 4 * R * B2);
             p.lo_vmaxb = o;     o = align256(o + 4 * R * B2);
             p.lo_blk_start = o; o = align256(o + 4 * R * (B2 + 1));
             p.lo_pair = o;      o = align256(o + 4 * R * B2 * Sz);
-            p.lo_psum = o;      o = align256(o + 8 * R * Sz * B2 * (size_t)(nq + 1));
+            p.lo_sums = o;      o = align256(o + 8 * R * B2 * (size_t)(nq + 1));
             p.lo_qsel = o;      o = align256(o + 4 * R * B2);
             p.lo_inv_sel = o;   o = align256(o + 4 * R * B2);
             p.lo_code_off = o;  o = align256(o + 8 * R * (B2 + 1));
+            o = std::max(o, tables + large_table_room(R, row_len, epc, p.k, B2, (size_t)nq));
         }
     }
     // the generic kernel's list of a row (8 bytes an entry) and the long-row list (a word and two halves) share their place
@@ -256,9 +271,9 @@ void launch_large_stages(const LargeArgs& la, const EncArgs& ea, const FinishArg
     if (FB == kFBWide && large_many_members(la.k, la.M + la.Mn))
         hipLaunchKernelGGL((lr_bounds_kernel<DT, FB, FB == kFBWide>), gB, bR, 0, st, la, ea);
     else hipLaunchKernelGGL((lr_bounds_kernel<DT, FB, false>), gB, bR, 0, st, la, ea);
-    const size_t lds = (size_t)lr_split_carve(FB, la.M + la.Mn, la.nq).total;
-    if (la.nq == 7) hipLaunchKernelGGL((lr_split_kernel<DT, 7, FB>), gT, bT, lds, st, la);   // {2..8}: the benchmarked set
-    else hipLaunchKernelGGL((lr_split_kernel<DT, 0, FB>), gT, bT, lds, st, la);
+    const size_t lds = (size_t)lr_split_carve(la.M, la.Mn, la.nq).total;
+    if (la.nq == 7) hipLaunchKernelGGL((lr_split_kernel<DT, 7>), gT, bT, lds, st, la);   // {2..8}: the benchmarked set
+    else hipLaunchKernelGGL((lr_split_kernel<DT, 0>), gT, bT, lds, st, la);
     if (la.n_cols > 0) hipLaunchKernelGGL((lr_pack_kernel<DT, true>), gW, dim3(256), 0, st, la, fa);
     else hipLaunchKernelGGL((lr_pack_kernel<DT, false>), gW, dim3(256), 0, st, la, fa);
 }
@@ -526,10 +541,9 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         la.seg = (u32*)(ws + p.lo_seg);
         la.L = (uint8_t*)(ws + p.off_kept);
         la.rowst = (u32*)(ws + p.lo_rowst);       la.thr = (u64*)(ws + p.lo_thr);
-        la.map = (uint8_t*)(ws + p.lo_map);
         la.vminb = (u32*)(ws + p.lo_vminb);       la.vmaxb = (u32*)(ws + p.lo_vmaxb);
         la.blk_start = (u32*)(ws + p.lo_blk_start); la.pair = (u32*)(ws + p.lo_pair);
-        la.psum = (u64*)(ws + p.lo_psum);
+        la.sums = (u64*)(ws + p.lo_sums);
         la.qsel = (u32*)(ws + p.lo_qsel);         la.inv_sel = (float*)(ws + p.lo_inv_sel);
         la.code_off = (u64*)(ws + p.lo_code_off);
         la.bo_idx = ea.bo_idx; la.bo_val = ea.bo_val;

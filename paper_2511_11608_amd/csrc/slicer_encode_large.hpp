@@ -74,12 +74,11 @@ struct LargeArgs {
     u32* rowst;             // [R][16]        see kSt*
     u32* redo;              // [R]            the row is left to the generic encoder (narrow tables only)
     u64* thr;               // [R][B2]        comp of the block's last element
-    uint8_t* map;           // [R][2][FB]     block of a fine bin's first element by class (kMapNone: not kept) | kMapMixed: also of the next | kMapMany: and beyond
     u32* vminb;             // [R][B2]        keys
     u32* vmaxb;
     u32* blk_start;         // [R][B2 + 1]
     u32* pair;              // [R][B2][S]     entries of the tile in this block and the blocks of its class before it
-    u64* psum;              // [R][S][B2][nq + 1]  the tiles' ABQ sums
+    u64* sums;              // [R][B2][nq + 1]  ABQ sums
     u32* qsel;              // [R][B2]
     float* inv_sel;         // [R][B2]
     u64* code_off;          // [R][B2 + 1]
@@ -113,10 +112,6 @@ inline void lr_sample_plan(LargeArgs& a, int fine_bins, int epc)
     a.sample_target = (u32)(f * G * epc + 4.0 * epc * sqrt(G * f * (1.0 - f))) + 1u;
     a.sample_scale = (float)((double)a.N / (G * epc));
 }
-
-// coding of `map` (up to 62 blocks; with more of them the split searches the thresholds)
-constexpr u32 kMapMixed = 0x80u, kMapMany = 0x40u, kMapNone = 0x3Fu;
-constexpr int kMapBlocks = 62;
 
 // words of a row's state
 enum { kStT = 0, kStBlo, kStNb, kStCursor, kStTicket, kStFlag, kStNpos, kStNneg };
@@ -615,6 +610,7 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
     const uint16_t* __restrict__ Lpos = list.pos;
     u32* pair = a.pair + (size_t)r * B2 * S;
     bool bad = st[kStFlag] != 0u;                    // uniform
+    if (part == 0) for (int i = tid; i < B2 * (a.nq + 1); i += TH) a.sums[(size_t)r * B2 * (a.nq + 1) + i] = 0;
     const u32 T = st[kStT];
 
     // sums of the tiles' tables: a thread takes four bins of every GT-th tile, eight of them in flight
@@ -831,34 +827,6 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
                 }
                 if (tid == 0) { st[kStNpos] = n_pos; st[kStNneg] = n_neg; }
             }
-            // block of every fine bin, for the split: only the bins that hold a boundary need a look at the element
-#pragma unroll
-            for (u32 c = 0; c < 2u; ++c) {
-                if (B2 > kMapBlocks) break;
-                const u32* at = c ? L.at_n : L.at_p;
-                const u32 nc = c ? n_neg : n_pos, K = c ? Kc1 : Kc0, Ms = (u32)(c ? Mn : M), b0 = c ? (u32)M : 0u;
-                const float rK = 1.0f / (float)(K ? K : 1u);
-                auto block_of = [&](u32 rank) -> u32 {
-                    if (rank >= nc) return kMapNone;
-                    u32 q = K ? (u32)((float)rank * rK) : Ms - 1u;
-                    if (K) { if (q * K > rank) --q; if ((q + 1u) * K <= rank) ++q; }        // (the product is off by less than one)
-                    return b0 + (q < Ms ? q : Ms - 1u);
-                };
-                if (tid >= FB / 4 || tid * P / (FB / 4) != part) continue;      // (a share of the bins each)
-                u32 wd = 0;
-#pragma unroll
-                for (u32 j = 0; j < 4u; ++j) {
-                    const u32 hi = at[tid * 4 + j], lo = at[tid * 4 + j + 1];
-                    u32 v = kMapNone;
-                    if (hi > lo) {
-                        const u32 v0 = block_of(lo), v1 = block_of(hi - 1u);
-                        const u32 next = v0 == b0 + Ms - 1u ? kMapNone : v0 + 1u;
-                        v = v0 | (v1 != v0 ? kMapMixed : 0u) | (v1 != v0 && v1 != next ? kMapMany : 0u);
-                    }
-                    wd |= v << (8u * j);
-                }
-                ((u32*)(a.map + ((size_t)r * 2 + c) * FB))[tid] = wd;
-            }
         }
     }
     if (part != 0) return;
@@ -895,19 +863,26 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
 // ---- 4. split -------------------------------------------------------------------------------------
 constexpr int kSplitNE = 4;          // entries per thread and step (eight spill)
 // LDS carve-up (bytes)
-struct LrSplitLds { int thr, sums, place, val, map, gbase, lstart, cnt, inv, vmin, e, er, tab, lidx, wcnt, blk, total; };
+struct LrSplitLds { int thr, sums, place, val, tk, gbase, lstart, cnt, inv, vmin, e, er, lidx, wcnt, blk, total; };
+// log2 of the places of a class's thresholds: its blocks and at least one more
+__host__ __device__ inline int lr_split_steps(int M, int Mn)
+{
+    int n = 1;
+    while ((1 << n) <= (M > Mn ? M : Mn)) ++n;
+    return n;
+}
 // room for a step's entries with every block padded to whole groups of kSplitNE
 __host__ __device__ inline int lr_split_room(int B2) { return (kTileThreads + B2 + 1) * kSplitNE; }     // (and one group for what is not kept)
-__host__ __device__ inline LrSplitLds lr_split_carve(int FB, int B2, int nq)
+__host__ __device__ inline LrSplitLds lr_split_carve(int M, int Mn, int nq)
 {
     LrSplitLds o;
-    const int EC = lr_split_room(B2);
+    const int B2 = M + Mn, EC = lr_split_room(B2);
     int p = 0;
-    o.thr = p;    p += 8 * (B2 > (int)kMapNone + 1 ? B2 : (int)kMapNone + 1);
+    o.thr = p;    p += 8 * B2;
     o.sums = p;   p += 8 * B2 * (nq + 1);
     o.place = p;  p += 8 * B2;
     o.val = (p + 15) & ~15; p = o.val + 4 * EC;
-    o.map = p;    p += 2 * FB;
+    o.tk = p;     p += 8 << lr_split_steps(M, Mn);
     o.gbase = p;  p += 4 * B2;
     o.lstart = p; p += 4 * (B2 + 1);
     o.cnt = p;    p += 4 * B2;
@@ -915,7 +890,6 @@ __host__ __device__ inline LrSplitLds lr_split_carve(int FB, int B2, int nq)
     o.vmin = p;   p += 4 * B2;
     o.e = p;      p += 4 * B2;
     o.er = p;     p += 4 * B2;
-    o.tab = p;    p += 2 * kTabSize;
     o.lidx = p;   p += 2 * EC;
     o.wcnt = p;   p += 2 * (kTileThreads / kWave) * B2;
     o.blk = p;    p += EC / kSplitNE;
@@ -923,8 +897,7 @@ __host__ __device__ inline LrSplitLds lr_split_carve(int FB, int B2, int nq)
     return o;
 }
 
-// stores and loads between workgroups of one launch, past the caches of one XCD
-__device__ inline void agent_store(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// loads of what other workgroups of the launch have written, past the caches of one XCD
 __device__ inline u64 agent_load(const u64* p) { return __hip_atomic_load(const_cast<u64*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // ABQ sums of the first `left` of kSplitNE values of one block (keys as fp32 patterns): acc[t] += squared residual (or DS mismatch) at the
@@ -978,7 +951,7 @@ __device__ inline u64 lr_abq_entries(const LargeArgs& a, int nq, const u32 (&vv)
 }
 
 // NQ > 0: the number of allowed bitwidths is known at compile time; NQ == 0: any number up to 16.
-template <int DT, int NQ, int FB>
+template <int DT, int NQ>
 __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void lr_split_kernel(LargeArgs a)
 {
     typedef Elem<DT> E;
@@ -993,7 +966,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     const u32 seg0 = a.seg[((size_t)r * S + s) * 2], ntp = a.seg[((size_t)r * S + s) * 2 + 1];
     if (st[kStFlag]) return;                         // encoded by the bounds stage
     const u32 nt = (ntp & 0xFFFFu) + (ntp >> 16);
-    const LrSplitLds o = lr_split_carve(FB, B2, nq);
+    const LrSplitLds o = lr_split_carve(M, Mn, nq);
     u64* thr = (u64*)(smem8 + o.thr);
     u64* sums = (u64*)(smem8 + o.sums);
     u32* val = (u32*)(smem8 + o.val);
@@ -1012,9 +985,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     constexpr int kMaskBlocks = 32;
     const int room = lr_split_room(B2);
     static_assert(8 * (kTileThreads / kWave) * (kMaskBlocks + 1) <= 4 * kTileThreads + 4 * kMaskBlocks, "the masks fit the sorted entries");
-    uint8_t* map = (uint8_t*)(smem8 + o.map);
-    uint16_t* tab = (uint16_t*)(smem8 + o.tab);
-    const u32 Blo = st[kStBlo], nb = st[kStNb];
+    u32* tk = (u32*)(smem8 + o.tk);                  // thresholds as c32, one class after the other
+    const int steps = lr_split_steps(M, Mn);
     const LrList list(a, r);
     const u32* __restrict__ Lraw = list.raw + seg0;
     const uint16_t* __restrict__ Lidx = list.idx + seg0;
@@ -1046,25 +1018,26 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
         if (b < B2 && (tid & 15) == 15) cntb[b] = n;     // with the blocks of its class before it (an empty block's is not looked at)
     }
     float* rngf = (float*)val;
-    if (tid < B2) {
-        const size_t rb = (size_t)r * B2 + tid;
-        const u64 t = a.thr[rb];
-        thr[tid] = t;
-        gbase[tid] = a.blk_start[(size_t)r * (B2 + 1) + tid];
-        const u32 lo = E::value_bits(a.vminb[rb]), hi = E::value_bits(a.vmaxb[rb]);
-        const float vmin = __uint_as_float(lo), rng = __uint_as_float(hi) - vmin;
-        vminf[tid] = vmin;
-        rngf[tid] = rng;
-        er_tab[tid] = rng > 0.f ? range_exp(rng) : 0;                // only a range of exactly 0 is degenerate
-        e_tab[tid] = t != ~0ull ? ilogb_bits(hi) + 1 : 0;
+    for (int i = tid; i < 2 << steps; i += kTileThreads) {
+        const int c = i >> steps, m = i - (c << steps);
+        u32 t = 0;                                   // (behind a class's blocks: below everything)
+        if (m < (c ? Mn : M)) {
+            const int b = c * M + m;
+            const size_t rb = (size_t)r * B2 + b;
+            const u64 cx = a.thr[rb];
+            t = cx == ~0ull ? ~0u : lr_c32<DT>((u32)(cx >> w), (1u << w) - 1u - ((u32)cx & ((1u << w) - 1u)), w);
+            thr[b] = cx;
+            gbase[b] = a.blk_start[(size_t)r * (B2 + 1) + b];
+            const u32 lo = E::value_bits(a.vminb[rb]), hi = E::value_bits(a.vmaxb[rb]);
+            const float vmin = __uint_as_float(lo), rng = __uint_as_float(hi) - vmin;
+            vminf[b] = vmin;
+            rngf[b] = rng;
+            er_tab[b] = rng > 0.f ? range_exp(rng) : 0;              // only a range of exactly 0 is degenerate
+            e_tab[b] = cx != ~0ull ? ilogb_bits(hi) + 1 : 0;
+        }
+        tk[i] = t;
     }
     for (int i = tid; i < B2 * (nq + 1); i += kTileThreads) sums[i] = 0;
-    {
-        const u32* tg = (const u32*)(a.tab + (size_t)r * kTabSize);
-        if (tid < kTabSize / 2) ((u32*)tab)[tid] = tg[tid];
-        const uint4* mg = (const uint4*)(a.map + (size_t)r * 2 * FB);
-        for (int i = tid; i < 2 * FB / 16; i += kTileThreads) ((uint4*)map)[i] = mg[i];
-    }
     __syncthreads();
     for (int i = tid; i < B2 * nq; i += kTileThreads) {              // quantiser scales 2^15 L / (range brought to [1, 2))
         const int b = i / nq, t = i - b * nq;
@@ -1090,50 +1063,42 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
         const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
         for (int i = tid; i < NWV * B2 / 2; i += kTileThreads) ((u32*)wcnt)[i] = 0;      // (16 * B2 counters)
         __syncthreads();
-        // (a) block of every entry: that of the first element of its fine bin, or in the few bins that hold a boundary the
-        // next one if the threshold lies above it.  Straight-line code: the lookups of a lane's entries overlap.
+        // (a) block of every entry: how many of its class's thresholds lie above it, by bisection over their leading bits (they
+        // descend; empty blocks, whose threshold is the largest, come first).  Straight-line code: the lookups of a lane's entries
+        // overlap.  A table of blocks by fine bin took twice the instructions, and 5 KB a workgroup to load: the first 6.6 us of a workgroup's 27 on
+        // fp32 [32 x 401408], now 3.5 of 22.
         u32 bk[NE], rank[NE];
-        if (B2 <= kMapBlocks) {
-            u32 many = 0;
+        {
+            u32 c32[NE], pos[NE];
 #pragma unroll
             for (int j = 0; j < NE; ++j) {
-                const u32 neg = rw[j] >> 31;
                 const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
-                bk[j] = map[neg * FB + lr_fine_bin<DT>(lr_c32<DT>(key, tile0 + ix[j], w), tab, Blo, nb)];
+                c32[j] = lr_c32<DT>(key, tile0 + ix[j], w);
+                pos[j] = (rw[j] >> 31) << steps;
             }
 #pragma unroll
-            for (int j = 0; j < NE; ++j) {
-                const u32 p = e0 + (u32)(wv * NE + j) * kWave + lane;
-                const u32 neg = rw[j] >> 31, c1 = neg ? (u32)B2 : (u32)M;
-                const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
-                const u32 v = bk[j];
-                u32 b = v & kMapNone;
-                const bool step = (v & kMapMixed) && thr[b] > lr_comp(key, tile0 + ix[j], w);        // (thr has kMapNone + 1 readable words)
-                b = step ? b + 1u : b;
-                many |= v & kMapMany;
-                bk[j] = p < nt && (v & kMapNone) != kMapNone && b < c1 ? b : kNone;
+            for (int n = 7; n > 0; --n) {
+                if (n > steps) continue;             // uniform
+                const u32 step = 1u << (n - 1);
+#pragma unroll
+                for (int j = 0; j < NE; ++j) pos[j] += tk[pos[j] + step - 1u] > c32[j] ? step : 0u;
             }
-            if (__any(many != 0u)) {                 // a fine bin of more than two blocks
+            bool tie = false;
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                const u32 neg = rw[j] >> 31, m = pos[j] - (neg << steps), b = m + (neg ? (u32)M : 0u);
+                const bool in = e0 + (u32)(wv * NE + j) * kWave + lane < nt && m < (u32)(neg ? Mn : M);
+                tie |= in && tk[pos[j]] == c32[j];
+                bk[j] = in ? b : kNone;
+            }
+            if (__any(tie)) {                        // leading bits alike: the whole order decides
 #pragma unroll
                 for (int j = 0; j < NE; ++j) {
-                    const u32 neg = rw[j] >> 31, c1 = neg ? (u32)B2 : (u32)M;
+                    const u32 c1 = rw[j] >> 31 ? (u32)B2 : (u32)M;
                     const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
                     const u64 cx = lr_comp(key, tile0 + ix[j], w);
                     while (bk[j] != kNone && thr[bk[j]] > cx) bk[j] = bk[j] + 1u < c1 ? bk[j] + 1u : kNone;
                 }
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < NE; ++j) {
-                const u32 p = e0 + (u32)(wv * NE + j) * kWave + lane;
-                const u32 neg = rw[j] >> 31;
-                const u32 key = DT == 0 ? rw[j] & 0x7FFFFFFFu : (rw[j] >> 16) & 0x7FFFu;
-                const u64 cx = lr_comp(key, tile0 + ix[j], w);
-                int lo = neg ? M : 0, hi = neg ? B2 : M;
-                const int c1 = hi;
-                // (empty blocks have the largest threshold and sit before the class's last block)
-                while (lo < hi) { const int mid = (lo + hi) >> 1; if (thr[mid] > cx) lo = mid + 1; else hi = mid; }
-                bk[j] = p < nt && lo < c1 ? (u32)lo : kNone;
             }
         }
         // (b) stable rank inside the wavefront's 64 * NE consecutive entries: a bit mask of the lanes per block and slot
@@ -1302,37 +1267,21 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
         __syncthreads();
         if (tid < B2) gbase[tid] += cntb[tid];
     }
-    // the tile's sums leave the workgroup; the row's last workgroup adds them up and chooses
+    // the tile's sums leave the workgroup; the row's last workgroup chooses
     __syncthreads();
     const int ns = B2 * (nq + 1);
-    u64* ps = a.psum + (size_t)r * S * ns;
-    if (want_sums && S > 1) for (int i = tid; i < ns; i += kTileThreads) agent_store(&ps[(size_t)s * ns + i], sums[i]);
-    // The sums alone must be seen by the row's last workgroup: they are stored past the XCD's L2 and waited for before the
-    // ticket is drawn, and are loaded the same way.  A ticket with release and acquire order writes back the whole L2, dirty with the
+    u64* rs = a.sums + (size_t)r * ns;
+    if (want_sums && S > 1) for (int i = tid; i < ns; i += kTileThreads) if (sums[i]) __hip_atomic_fetch_add(&rs[i], sums[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The sums alone must be seen by the row's last workgroup: they are added where all XCDs meet and waited for before the
+    // ticket is drawn, and are loaded from there.  A ticket with release and acquire order writes back the whole L2, dirty with the
     // block-ordered entries, once per workgroup: encode of 32 maps of 401408 with a ladder 113 -> 133 us, DS guard 123 -> 138.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the stores have reached the point all XCDs see ...
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the additions have been made ...
     __syncthreads();
     if (tid == 0) lstart[0] = S > 1 ? __hip_atomic_fetch_add(&st[kStTicket], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;   // ... before the ticket
     __syncthreads();
     if (lstart[0] != (u32)S - 1u) return;
     if (want_sums && S > 1) {
-        // several threads share a sum, so that all its loads are in flight at once
-        int gr = 1;
-        while (gr * 2 * ns <= kTileThreads && gr * 16 < S) gr *= 2;
-        for (int i = tid; i < ns; i += kTileThreads) sums[i] = 0;
-        __syncthreads();
-        for (int i = tid; i < ns * gr; i += kTileThreads) {
-            const int j = i % ns;
-            u64 t = 0;
-            for (int s0 = i / ns; s0 < S; s0 += 16 * gr) {
-                u64 p[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) p[u] = s0 + u * gr < S ? agent_load(&ps[(size_t)(s0 + u * gr) * ns + j]) : 0ull;
-#pragma unroll
-                for (int u = 0; u < 16; ++u) t += p[u];
-            }
-            if (t) atomicAdd(&sums[j], t);
-        }
+        for (int i = tid; i < ns; i += kTileThreads) sums[i] = agent_load(&rs[i]);
     }
     __syncthreads();
     const int b = tid;
