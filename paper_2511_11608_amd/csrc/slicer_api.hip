@@ -74,6 +74,7 @@ struct Plan {
     int small_epl, small_cap, small_region0, small_lds_bytes, small_maxs;
     // workgroup-per-row path for rows of up to 32768 bf16 or 16384 fp32 elements (0 = not eligible)
     int wg_ept, wg_nw, wg_cap, wg_region0, wg_lds_bytes;
+    bool one_wave;          // a row that either row-resident kernel holds goes to one wavefront (lambda = 0)
     // long-row path (large_S == 0: not eligible)
     int large_S, large_fb;  // tiles per row, fine bins
     u32 large_capL;
@@ -202,8 +203,8 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     };
     const int64_t few = B2_all <= 16 || (B2_all <= 32 && p.k <= 256) || p.k <= 64 ? kScanRows
                       : B2_all <= 32 ? 768 : p.k <= 256 ? 1024 : 2047;            // rows up to which the workgroup is faster
-    const bool one_wave = p.small_epl && cap <= 768 && rows > few;
-    if (wg_holds(span) && !one_wave) {
+    p.one_wave = p.small_epl && (!wg_holds(span) || (cap <= 768 && rows > few));
+    if (wg_holds(span)) {
         // wavefronts per row: sixteen for the smallest batches (more wavefronts per SIMD hide each other's
         // latencies: 4 % less latency per call), four otherwise (a 256-row batch on sixteen leaves no room
         // for a neighbouring stream's kernels: 20 % less throughput when steps overlap)
@@ -377,7 +378,7 @@ int slicer_encode_path(slicer_dtype dt, int64_t rows, int64_t row_len, double ke
     int rc = check_args((int)dt, rows, row_len, keep_ratio, n_blocks, bit_set);
     if (rc) return rc;
     Plan p = make_plan((int)dt, rows, row_len, keep_ratio, n_blocks, n_blocks, bit_set);
-    return p.wg_ept ? 3 : p.small_epl ? 1 : (p.large_S ? 2 : 0);
+    return p.one_wave ? 1 : p.wg_ept ? 3 : p.large_S ? 2 : 0;
 }
 
 // two-dimensional instances whose stream the long-row stages write in CSR form themselves
@@ -430,9 +431,12 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
     ea.one_plus = 1.0f + (float)lambda;
     ea.one_minus = 1.0f - (float)lambda;
 
-    // asymmetric thresholds need a second selection over a subset of the row: the one-wavefront kernel has it for every row that
-    // it holds, the generic kernel for every shape
-    const bool use_wg = p.wg_ept && !asym && on_elements;
+    // asymmetric thresholds need a second selection over a subset of the row: the row-resident kernels have it for every row that
+    // they hold, the generic kernel for every shape.  One wavefront takes long for two selections over a row of more than 4096 elements, so
+    // the workgroup has all of these but the narrower ones of large batches.  Encode us, wavefront / workgroup, lambda = 0.1, 8 + 8 blocks: bf16
+    // [1 x 8192] 42 / 23, [256 x 8192] 49 / 29, [300 x 4160] 39 / 27, [4096 x 8192] 160 / 109 (1228 kept), [8192 x 8192] 162 / 158 (409 kept),
+    // [8903 x 6144] 169 / 167; but [13000 x 4160] 195 / 210.
+    const bool use_wg = p.wg_ept && on_elements && !(p.one_wave && (!asym || (rows > 4096 && row_len <= 6144)));
     if (use_wg) {
         // one workgroup per row; rows it cannot hold are flagged and redone by the generic kernel
         SmallArgs sa;
@@ -453,7 +457,8 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         const bool timed = g_ev_start && g_ev_stop;
         if (timed) SLICER_HIP(hipEventRecord(g_ev_start, st));
         const WgLaunch wl = { p.wg_nw, p.wg_ept, p.wg_lds_bytes };
-        SLICER_HIP(dt == SLICER_F32 ? launch_wg<0>(sa, wl, st) : launch_wg<1>(sa, wl, st));
+        if (asym) SLICER_HIP((dt == SLICER_F32 ? launch_wg<0, true> : launch_wg<1, true>)(sa, wl, st));
+        else SLICER_HIP((dt == SLICER_F32 ? launch_wg<0, false> : launch_wg<1, false>)(sa, wl, st));
         if (timed) SLICER_HIP(hipEventRecord(g_ev_stop, st));
         ea.only_flagged = sa.fallback;
     }

@@ -23,7 +23,7 @@
 // What bounds it: the chain of barriers and dependent LDS reads, not the arithmetic (bf16 [256 x 8192]: 26.0 us
 // when wavefront 0 did the serial steps for all and members of a bin were read one by one, 20.9 us now).
 //
-// Either guard or a fixed ladder, lambda = 0; rows it cannot hold are flagged for the generic kernel.  bf16 entries
+// Either guard or a fixed ladder, any lambda; rows it cannot hold are flagged for the generic kernel.  bf16 entries
 // are one word (sign, key, inverted index); fp32 entries keep the raw word in the list and the index
 // beside it, and the members of a fine bin compare on "in-bin key bits, inverted index, class".
 #pragma once
@@ -103,7 +103,12 @@ constexpr int wg_min_waves(int dt, int nw, int ept)
     return want > per_wg ? want : per_wg;
 }
 
-template <int DT, int NW, int EPT, int NQ>
+// ASYM: the asymmetric thresholds of Sec. 3.1 with lambda > 0, in the steps of the one-wavefront kernel: tau by exact histogram
+// passes over narrowing windows, a second selection over the fill candidates (or the strict set), then the list from
+// the rule itself, so that it holds the kept set and nothing else.  Before, the generic kernel read such rows from memory some ten times:
+// encode call of fp32 [2048 x 8192] keep 0.15 549 us, now 100; [6990 x 4800] keep 0.1 1409, now 226; [1 x 8192] 154, now 29; bf16 [2048 x 12288]
+// keep 0.1 636, now 84.
+template <int DT, int NW, int EPT, int NQ, bool ASYM = false>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_min_waves(DT, NW, EPT)))) void enc_wg_kernel(SmallArgs a)
 {
     typedef Elem<DT> E;
@@ -147,7 +152,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     // chunk), then the wavefronts' chunk totals are scanned in chunk order.
     u32 t_lo = 1u, nL = 0;
     u32 cntc[NCH], basec[NCH];
-    auto count_pass = [&]() {
+    auto flags_pass = [&]() __attribute__((always_inline)) {                        // cntc: entries of the chunk at or above t_lo
         const u32 C16 = (0x8000u - t_lo) * 0x10001u;             // bit 15 / 31 of (key + C16) <=> key >= t_lo
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
@@ -159,6 +164,8 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
             }
             cntc[c] = n1;
         }
+    };
+    auto scan_pass = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < (NCH + 2) / 3; ++g) {
             u32 pk = cntc[3 * g];
@@ -184,6 +191,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
             for (int c = 0; c < NCH; ++c) basec[c] += bcast(ex, c * kWgWaves + (int)wv);
         }
     };
+    auto count_pass = [&]() __attribute__((always_inline)) { flags_pass(); scan_pass(); };
 
     // Threshold hint (see slicer_encode_small.hpp): the cut key an earlier row left in the workspace,
     // lowered a few steps; accepted when it keeps at least k keys and not many more.  The count decides.
@@ -191,7 +199,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     // all of them tried the same one.
     const u32 hslot = (u32)blockIdx.x & (u32)(kHintSlots - 1);
     bool hinted = false;
-    if (k > 0) {
+    if (!ASYM && k > 0) {
         const u32 hint_key = (u32)__builtin_amdgcn_readfirstlane((int)a.hint[hslot]) & kKeyMask;
         const u32 dlt = kHintDelta << (DT == 0 ? 16 : 0);
         t_lo = hint_key > dlt ? hint_key - dlt : 1u;
@@ -222,7 +230,158 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
 #pragma unroll
         for (int i = 0; i < NW; ++i) kmax = max(kmax, misc[16 + i]);
     };
-    if (!hinted) {
+    u32 fm[ASYM ? NCH : 1];                          // ASYM: a bit per element of the chunk that goes to the list
+    if constexpr (ASYM) {
+        __syncthreads();
+        row_kmax();
+        if (k > 0) {
+            u32 wtop = kmax, above = 0, B1 = 0, c_gt = 0, cnt1 = 0, rank_t = (u32)(k - 1);
+            bool found = false;
+            auto elem_key = [&](int c, int e) -> u32 { return DT == 0 ? word_of(c, e) & 0x7FFFFFFFu : (word_of(c, e >> 1) >> (16 * (e & 1))) & 0x7FFFu; };
+            auto elem_neg = [&](int c, int e) -> bool { return DT == 0 ? word_of(c, e) >> 31 : ((word_of(c, e >> 1) >> (16 * (e & 1) + 15)) & 1u) != 0u; };
+            // the bin of rank rank_t - above among the keys that key_fn lets through (0: not that element; zeros count with kZeros alone), not above
+            // wtop; a last pass's bins catch all smaller keys in the last one
+            auto select_pass = [&](auto shift, auto key_fn, auto zeros, auto windowed) __attribute__((always_inline)) {
+                constexpr int SH = decltype(shift)::value;
+                constexpr bool kZeros = decltype(zeros)::value, kWindowed = decltype(windowed)::value;
+                {
+                    uint4* h4 = (uint4*)smem;
+                    for (int i = (int)tid; i < kCoarseBins / 4; i += kWgThreads) h4[i] = make_uint4(0, 0, 0, 0);
+                    if (tid < 4) misc[tid] = 0;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    if ((c * kWgThreads + (int)tid) * EPC < Nh) {
+#pragma unroll
+                        for (int e = 0; e < EPC; ++e) {
+                            const u32 key = key_fn(c, e), bin = (wtop - key) >> SH;
+                            if ((kZeros || key) && key <= wtop && (!kWindowed || bin < (u32)kCoarseBins)) lds_inc(min(bin, (u32)(kCoarseBins - 1)) << 2, 1u);
+                        }
+                    }
+                }
+                __syncthreads();
+                constexpr int BPT = kCoarseBins / kWgThreads;
+                u32 cs[BPT], local = 0;
+#pragma unroll
+                for (int j = 0; j < BPT; ++j) { cs[j] = smem[(int)tid * BPT + j]; local += cs[j]; }
+                u32 total;
+                u32 acc = block_excl_scan<kWgThreads>(local, misc + 32, &total);
+                const u32 rem = rank_t - above;
+#pragma unroll
+                for (int j = 0; j < BPT; ++j) {
+                    if (acc <= rem && rem < acc + cs[j]) { misc[0] = tid * BPT + j; misc[1] = acc; misc[2] = cs[j]; misc[3] = 1u; }
+                    acc += cs[j];
+                }
+                __syncthreads();
+                found = misc[3] != 0u;
+                if (found) { B1 = misc[0]; c_gt = misc[1]; cnt1 = misc[2]; }
+                __syncthreads();
+            };
+            // the exact key of rank rank_t: wtop - B1; above + c_gt counted keys lie above it, cnt1 of them are equal to it
+            auto exact_select = [&](auto key_fn, auto zeros) __attribute__((always_inline)) {
+                constexpr int S1 = DT == 0 ? 16 : 0;
+                typedef std::true_type yes;
+                typedef std::false_type no;
+                above = 0;
+                select_pass(std::integral_constant<int, S1>(), key_fn, zeros, no());
+                if (!found) return;
+                const bool wide = B1 == (u32)(kCoarseBins - 1) && (wtop >> S1) > (u32)(kCoarseBins - 1);
+                auto narrow = [&](int sh) { above += c_gt; wtop -= B1 << sh; };
+                if (wide) {
+                    narrow(S1);
+                    select_pass(std::integral_constant<int, S1 + 4>(), key_fn, zeros, yes());
+                    if (!found) return;
+                    narrow(S1 + 4);
+                    if (DT == 0) {
+                        select_pass(std::integral_constant<int, DT == 0 ? 9 : 0>(), key_fn, zeros, yes());
+                        if (!found) return;
+                        narrow(9);
+                    }
+                    select_pass(std::integral_constant<int, 0>(), key_fn, zeros, yes());
+                } else if (DT == 0) {
+                    narrow(16);
+                    select_pass(std::integral_constant<int, 5>(), key_fn, zeros, yes());
+                    if (!found) return;
+                    narrow(5);
+                    select_pass(std::integral_constant<int, 0>(), key_fn, zeros, yes());
+                }
+            };
+            exact_select(elem_key, std::true_type());            // (finds it: every key is counted)
+            const u32 tau_key = wtop - B1;
+            const float tau = __uint_as_float(E::value_bits(tau_key));
+            u32 tp_key = __float_as_uint(__fmul_rn(a.one_plus, tau)), tn_key = __float_as_uint(__fmul_rn(a.one_minus, tau));
+            if (DT == 1) { tp_key >>= 16; tn_key >>= 16; }       // (key << 16) > T  <=>  key > (T >> 16)
+            auto strict = [&](int c, int e) -> bool { return elem_key(c, e) > (elem_neg(c, e) ? tn_key : tp_key); };
+            auto fill = [&](int c, int e) -> bool { return !strict(c, e) && elem_key(c, e) <= tau_key; };
+            u32 acc = 0;                             // strictly retained | fill candidates << 16
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                if ((c * kWgThreads + (int)tid) * EPC < Nh) {
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) acc += strict(c, e) ? 1u : fill(c, e) ? 0x10000u : 0u;
+                }
+            }
+            acc = wave_sum(acc);                     // (at most 32768 elements and 7 more)
+            if (lane == 0) misc[32 + wv] = acc;
+            __syncthreads();
+            acc = 0;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) acc += misc[32 + i];
+            const u32 c_strict = acc & 0xFFFFu, f_fill = acc >> 16;
+            const bool trim = c_strict >= (u32)k;
+            const u32 D = trim ? 0u : (u32)k - c_strict;
+            u32 t2_key = 0, need_ties = 0, cnt_ties = 0;
+            __syncthreads();
+            if (trim || f_fill > D) {                // rank k - 1 of the strict set, or rank D - 1 of the fill candidates
+                rank_t = trim ? (u32)(k - 1) : D - 1u;
+                wtop = trim ? kmax : tau_key;
+                if (trim) exact_select([&](int c, int e) -> u32 { return strict(c, e) ? elem_key(c, e) : 0u; }, std::false_type());
+                else exact_select([&](int c, int e) -> u32 { return fill(c, e) ? elem_key(c, e) : 0u; }, std::false_type());
+                if (found) {
+                    t2_key = wtop - B1;
+                    need_ties = rank_t + 1u - (above + c_gt);
+                    cnt_ties = cnt1;
+                }                                    // else: the rank lies among zeros, every non-zero candidate is taken
+            }
+            if (t2_key == 0) { t2_key = 1; need_ties = 0; cnt_ties = 0; }
+            t_lo = trim ? t2_key : min(t2_key, tn_key + 1u);     // smallest key the list can hold
+            // taken: the strict set or its largest part, and the fill candidates down to the last key taken; of several
+            // elements with that key the first need_ties stay
+            const bool some_ties = need_ties < cnt_ties;         // uniform
+            u32 tm[NCH];
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                fm[ASYM ? c : 0] = tm[c] = 0;
+                if ((c * kWgThreads + (int)tid) * EPC < Nh) {
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) {
+                        const u32 key = elem_key(c, e);
+                        const bool st = strict(c, e), cand = trim ? st : fill(c, e);
+                        fm[ASYM ? c : 0] |= ((st && !trim) || (cand && key >= t2_key)) ? 1u << e : 0u;
+                        tm[c] |= cand && key == t2_key ? 1u << e : 0u;
+                    }
+                }
+            }
+            if (some_ties) {
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) cntc[c] = (u32)__popc(tm[c]);
+                scan_pass();
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    const u32 stay = need_ties > basec[c] ? need_ties - basec[c] : 0u;
+                    u32 m = tm[c];
+                    for (u32 i = 0; i < stay && m; ++i) m &= m - 1u;         // what is left goes
+                    fm[ASYM ? c : 0] &= ~m;
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) cntc[c] = (u32)__popc(fm[ASYM ? c : 0]);
+            scan_pass();
+        }
+    }
+    if (!ASYM && !hinted) {
     __syncthreads();
     row_kmax();
 
@@ -323,6 +482,19 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         for (int c = 0; c < NCH; ++c) {
             u32 wa = lent_off + basec[c] * 4u;
             const u32 idx0 = (u32)((c * kWgThreads + (int)tid) * EPC - head);
+            if (ASYM) {
+                for (u32 m = fm[ASYM ? c : 0]; m; m &= m - 1u, wa += 4u) {
+                    const u32 e = (u32)__builtin_ctz(m), d = DT == 0 ? e : e >> 1;
+                    const u32 wd = d == 0 ? v[c].x : d == 1 ? v[c].y : d == 2 ? v[c].z : v[c].w;
+                    if (DT == 0) {
+                        *lds_at(wa) = wd;
+                        *(__attribute__((address_space(3))) uint16_t*)(uintptr_t)(lidx_off + ((wa - lent_off) >> 1)) = (uint16_t)(idx0 + e);
+                    } else {
+                        *lds_at(wa) = ((e & 1u) ? wd & 0xFFFF0000u : wd << 16) | ((idx0 + e) ^ 0xFFFFu);
+                    }
+                }
+                continue;
+            }
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 const u32 wd = word_of(c, d);
@@ -883,7 +1055,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         a.mv.n_pos[r] = n_pos;
         a.mv.n_neg[r] = n_neg;
         a.fallback[r] = 0u;
-        if (k > 0) a.hint[hslot] = nL > (u32)k ? (DT == 0 ? (u32)((u64)thrK >> kHiShift) & 0x7FFFFFFFu : ((u32)thrK >> 16) & 0x7FFFu)
+        if (!ASYM && k > 0) a.hint[hslot] = nL > (u32)k ? (DT == 0 ? (u32)((u64)thrK >> kHiShift) & 0x7FFFFFFFu : ((u32)thrK >> 16) & 0x7FFFu)
                                                : t_lo;           // this row's cut key, for a later row
     }
 }

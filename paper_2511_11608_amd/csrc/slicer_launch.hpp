@@ -13,6 +13,6 @@ struct WgLaunch { int nw, chunks, lds_bytes; };
 
 // NQ = 7: sets of seven bitwidths ({2..8} is the benchmarked one); NQ = 0: any other set
 template <int DT, bool ASYM, int NQ> hipError_t launch_small(const SmallArgs& sa, const SmallLaunch& p, hipStream_t st);
-template <int DT> hipError_t launch_wg(const SmallArgs& sa, const WgLaunch& p, hipStream_t st);
+template <int DT, bool ASYM> hipError_t launch_wg(const SmallArgs& sa, const WgLaunch& p, hipStream_t st);
 
 }  // namespace slicer

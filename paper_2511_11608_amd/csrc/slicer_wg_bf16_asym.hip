@@ -1,0 +1,5 @@
+#include "slicer_launch_wg.hpp"
+
+namespace slicer {
+template <> hipError_t launch_wg<1, true>(const SmallArgs& sa, const WgLaunch& p, hipStream_t st) { return launch_wg_all<1, true>(sa, p, st); }
+}  // namespace slicer

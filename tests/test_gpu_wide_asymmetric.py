@@ -1,0 +1,39 @@
+"""Asymmetric thresholds on rows that a workgroup holds, byte-exact against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2511_11608_amd import synth
+from tests.test_gpu_parity import B28, check_atkf
+
+pytestmark = pytest.mark.gpu
+
+
+def structures(dtype, rows, N, seed):
+    """Rows of every kind in turn: plain, few distinct values, one sign, mostly negative, sparse over thirty octaves, few non-zeros, equal, zero."""
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((rows, N)).astype(np.float32)
+    x[1::9] = np.round(x[1::9] * 4) / 4
+    x[2::9] = np.abs(x[2::9])
+    x[3::9] = -np.abs(x[3::9]) + (rng.random(x[3::9].shape) < 0.02) * 3
+    x[4::9] *= (rng.random(x[4::9].shape) < 0.3) * np.exp2(rng.uniform(-15, 15, x[4::9].shape))
+    x[5::9] *= rng.random(x[5::9].shape) < 0.01
+    x[6::9] = np.where(rng.random(x[6::9].shape) < 0.5, 1.5, -1.5)
+    x[7::9, : N // 2] *= 1e-6
+    x[8::9] = 0
+    return synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+
+
+@pytest.mark.parametrize("rows", [10, 140])
+@pytest.mark.parametrize("dtype,N,keep,Mp,Mn", [("bf16", 4104, 0.1, 8, 8), ("bf16", 5001, 0.2, 3, 9), ("bf16", 8192, 0.05, 16, 16), ("bf16", 12288, 0.1, 8, 8),
+                                                ("bf16", 32761, 0.02, 4, 4), ("f32", 4100, 0.25, 8, 8), ("f32", 5003, 0.1, 1, 1), ("f32", 8192, 0.15, 32, 32),
+                                                ("f32", 16381, 0.05, 8, 2)])
+def test_kinds_of_rows(oracle, dtype, N, keep, Mp, Mn, rows):
+    x = structures(dtype, rows, N, N + rows)
+    for lam in (0.1, 0.7):
+        check_atkf(oracle, x, dtype, keep, lam, Mp, Mn, B28, 1e-3)
+    check_atkf(oracle, x[:, : N - 1].copy(), dtype, keep, 0.3, Mp, Mn, (1 << 3) | (1 << 11), 1e-3)
+
+
+@pytest.mark.parametrize("rows,N", [(4100, 4104), (4100, 6152), (300, 8192)])
+def test_one_wavefront_or_one_workgroup(oracle, rows, N):
+    check_atkf(oracle, structures("bf16", rows, N, 3), "bf16", 0.05, 0.2, 8, 8, B28, 1e-3)
