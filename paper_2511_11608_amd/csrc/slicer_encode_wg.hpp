@@ -106,7 +106,7 @@ constexpr int wg_min_waves(int dt, int nw, int ept)
 // ASYM: the asymmetric thresholds of Sec. 3.1 with lambda > 0, in the steps of the one-wavefront kernel: tau by exact histogram
 // passes over narrowing windows, a second selection over the fill candidates (or the strict set), then the list from
 // the rule itself, so that it holds the kept set and nothing else.  Before, the generic kernel read such rows from memory some ten times:
-// encode call of fp32 [2048 x 8192] keep 0.15 549 us, now 100; [6990 x 4800] keep 0.1 1409, now 226; [1 x 8192] 154, now 29; bf16 [2048 x 12288]
+// encode call of fp32 [2048 x 8192] keep 0.15 549 us, now 88 (100 with every bin narrowed down by two more passes); [1 x 8192] 154, now 28; bf16 [2048 x 12288]
 // keep 0.1 636, now 84.
 template <int DT, int NW, int EPT, int NQ, bool ASYM = false>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_min_waves(DT, NW, EPT)))) void enc_wg_kernel(SmallArgs a)
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
                 {
                     uint4* h4 = (uint4*)smem;
                     for (int i = (int)tid; i < kCoarseBins / 4; i += kWgThreads) h4[i] = make_uint4(0, 0, 0, 0);
-                    if (tid < 4) misc[tid] = 0;
+                    if (tid < 5) misc[tid] = 0;
                 }
                 __syncthreads();
 #pragma unroll
@@ -288,7 +288,36 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
                 if (!found) return;
                 const bool wide = B1 == (u32)(kCoarseBins - 1) && (wtop >> S1) > (u32)(kCoarseBins - 1);
                 auto narrow = [&](int sh) { above += c_gt; wtop -= B1 << sh; };
-                if (wide) {
+                // a bin of up to 64 members: these meet in LDS, and every wavefront counts for each of them those above it
+                auto few_members = [&](int sh) __attribute__((always_inline)) {
+                    narrow(sh);
+                    const u32 rem = rank_t - above, n = cnt1;
+#pragma unroll
+                    for (int c = 0; c < NCH; ++c) {
+                        if ((c * kWgThreads + (int)tid) * EPC < Nh) {
+#pragma unroll
+                            for (int e = 0; e < EPC; ++e) {
+                                const u32 key = key_fn(c, e);
+                                if ((decltype(zeros)::value || key) && key <= wtop && ((wtop - key) >> sh) == 0u) smem[atomicAdd(&misc[4], 1u) & (u32)(kWave - 1)] = key;
+                            }
+                        }
+                    }
+                    __syncthreads();
+                    const u32 me = lane < n ? smem[lane] : 0u;
+                    u32 gt = 0, ge = 0;
+                    for (u32 j = 0; j < n; ++j) {
+                        const u32 other = bcast(me, (int)j);
+                        gt += other > me ? 1u : 0u;
+                        ge += other >= me ? 1u : 0u;
+                    }
+                    const u64 hit = __ballot(lane < n && gt <= rem && rem < ge);
+                    const int src = hit ? (int)__builtin_ctzll(hit) : 0;
+                    wtop = bcast(me, src); B1 = 0;
+                    c_gt = bcast(gt, src); cnt1 = bcast(ge, src) - c_gt;
+                    __syncthreads();
+                };
+                if (DT == 0 && !wide && cnt1 <= (u32)kWave) few_members(16);         // uniform
+                else if (wide) {
                     narrow(S1);
                     select_pass(std::integral_constant<int, S1 + 4>(), key_fn, zeros, yes());
                     if (!found) return;

@@ -37,3 +37,18 @@ def test_kinds_of_rows(oracle, dtype, N, keep, Mp, Mn, rows):
 @pytest.mark.parametrize("rows,N", [(4100, 4104), (4100, 6152), (300, 8192)])
 def test_one_wavefront_or_one_workgroup(oracle, rows, N):
     check_atkf(oracle, structures("bf16", rows, N, 3), "bf16", 0.05, 0.2, 8, 8, B28, 1e-3)
+
+
+@pytest.mark.parametrize("N,keep", [(768, 0.15), (2048, 0.1), (4096, 0.05), (5000, 0.05), (9000, 0.03)])
+@pytest.mark.parametrize("members", [1, 2, 63, 64, 65, 90])
+def test_members_of_one_bin(oracle, N, keep, members):
+    """fp32 rows whose selections end in a bin of the first histogram pass (65536 keys) with this many members, some of them equal."""
+    rng = np.random.default_rng(N + members)
+    k, rows = int(keep * N), 4
+    x = np.empty((rows, N), dtype=np.float32)
+    for i in range(rows):
+        top = max(0, k - 1 - (i * members) // 4)
+        v = np.concatenate([8 + 4 * rng.random(top), 1 + np.floor(rng.random(members) * 40) * 2.0 ** -16, 0.5 * rng.random(N - top - members)])
+        x[i] = rng.permutation(v) * rng.choice([-1, 1], N)
+    for lam in (0.0, 0.05, 0.5):
+        check_atkf(oracle, x, "f32", keep, lam, 4, 4, B28, 1e-3)
