@@ -24,11 +24,11 @@
 // final gather made ten launches.  One atomic per entry on a table in memory is no way to
 // join the tiles' histograms (29 G atomics/s: 100 us for 3 M of them); the per-tile tables cost 8 KB
 // per tile, written once.  Inside a stage the lanes' LDS lookups are written as straight-line code for several
-// entries at once: behind branches they wait for each other (split kernel 68 -> 41 us on 32 maps of 401408, together with four instead of
+// entries at once: behind branches they wait for each other (split kernel 68 -> 41 us on 32 maps of 401408 at the time, together with four instead of
 // eight entries per thread, which spill nothing, and the choice of the guard taken outside the entry loop).
-// Measured (us, fp32 [1 x 200704] and [32 x 401408] keep 0.2, 16 + 16 blocks): sample 5 and 9, compact 6 and 18, bounds 12 and 18,
-// split 15 and 41, pack 6 and 22; the calls 44.7 and 114, with CSR blocks 144.  Before the changes that the stages' comments name: sample 9.5 and 13,
-// compact 6 and 29, bounds 15.7 and 24; the calls 53 and 134, CSR 164.
+// Measured (us, fp32 [1 x 200704] and [32 x 401408] keep 0.2, 16 + 16 blocks): sample 6 and 10, compact 6 and 21.5, bounds 12 and 19,
+// split 14 and 37, pack 6 and 22; the calls 43.7 and 113, with CSR blocks and decode 143.  Before the changes that the stages' comments name: sample 9.5 and
+// 13, compact 6 and 29, bounds 15.7 and 24, split 15 and 41; the calls 53 and 135, with CSR blocks and decode 165.
 //
 // Order: comp = key << w | (2^w - 1 - index): larger comp = larger magnitude, then lower index.  c32 is
 // its leading 31 (fp32: the key) or 32 bits (bf16: the key and the first 17 bits of the inverted
