@@ -113,8 +113,8 @@ inline void lr_sample_plan(LargeArgs& a, int fine_bins, int epc)
     a.sample_scale = (float)((double)a.N / (G * epc));
 }
 
-// words of a row's state
-enum { kStT = 0, kStBlo, kStNb, kStCursor, kStTicket, kStFlag, kStNpos, kStNneg };
+// words of a row's state.  kStFlag (encoded generically): written by compact, and by the bounds stage when no part of the row reads it any more
+enum { kStT = 0, kStBlo, kStNb, kStCursor, kStTicket, kStFlag, kStNpos, kStNneg, kStLeft };
 
 struct LrList {
     u32* raw;               // [capL]  fp32: the raw word; bf16: the raw half in the high 16 bits
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(lr_row_threads(FB)) __attribute__((amdgpu_waves_per
     }
     auto count_of = [&](u32 bin) -> u32 { return kHalf ? (h[bin >> 1] >> (16u * (bin & 1u))) & 0xFFFFu : h[bin]; };
     u32* st = a.rowst + (size_t)r * 16;
-    if (tid == 0) { st[kStCursor] = 0; st[kStTicket] = 0; st[kStFlag] = 0; }
+    if (tid == 0) { st[kStCursor] = 0; st[kStTicket] = 0; st[kStFlag] = 0; st[kStLeft] = 0; }
     __syncthreads();
     auto c32_of = [&](int u, int e) -> u32 {
         const u32 key = E::key((typename E::raw_t)chunk_elem<DT>(v[u], e));
@@ -829,14 +829,22 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
             }
         }
     }
-    if (part != 0) return;
-    if constexpr (!kRedo) {
+    if (!bad && part != 0) return;
+    if constexpr (!kRedo) {                          // (one workgroup a row)
         if (tid == 0) {
             a.redo[r] = bad ? 1u : 0u;
             if (bad) { st[kStFlag] = 1u; a.row_words[r] = 0; a.blk_start[(size_t)r * (B2 + 1) + B2] = 0; }     // (nothing for the pack stage)
         }
     } else if (bad) {                                // rare: the row goes to its slot by the generic encoder
+        // The generic encoder's list takes the place of the row's, which other parts may be reading for the cut, as they may the flag.  All
+        // parts come to the same decision; the last one to have made it, behind everybody's reads, has the row.
         __syncthreads();
+        if (P > 1) {
+            if (tid == 0) L.v[3] = __hip_atomic_fetch_add(&st[kStLeft], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            if (L.v[3] != (u32)P - 1u) return;       // uniform
+            __syncthreads();                         // (the encoder's LDS is the same)
+        }
         if (tid == 0) st[kStFlag] = 1u;
         enc_generic_rows<DT, 1024>(ea, r, r + 1, *(GenericLds<1024>*)lds);
         __syncthreads();
