@@ -225,6 +225,29 @@ __device__ inline u32 block_excl_scan(u32 v, u32* scratch, u32* total)
     return base + inc - v;
 }
 
+// Sorts n elements in LDS with the whole block, the largest key first.  A bitonic network whose merges begin with mirrored halves: every step
+// moves the larger key to the lower place, so that n needs no padding.  Ends with a barrier.  (What bounds it are the instructions: steps
+// inside a wavefront's own run of places without a barrier, or four pairs at a time, were no faster.)
+template <int BLOCK, typename T, typename F>
+__device__ inline void block_sort(T* p, u32 n, F key)
+{
+    u32 half = 1;
+    while (half < n) half <<= 1;
+    half >>= 1;                                      // pairs of a step
+    for (u32 size = 2; size <= 2u * half; size <<= 1) {
+        for (u32 d = size >> 1; d; d >>= 1) {
+            for (u32 t = threadIdx.x; t < half; t += BLOCK) {
+                const u32 off = t & (d - 1u), i = ((t - off) << 1) + off, j = d == size >> 1 ? i + size - 1u - 2u * off : i + d;
+                if (j < n) {
+                    const T a = p[i], b = p[j];
+                    if (key(a) < key(b)) { p[i] = b; p[j] = a; }
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // Sum over the 64 lanes, in every lane (data-parallel-primitive moves: no LDS crossbar traffic).
 __device__ inline u32 wave_sum(u32 v) { return bcast(wave_scan_dpp(v), kWave - 1); }
 

@@ -23,7 +23,7 @@
 // What bounds it: the chain of barriers and dependent LDS reads, not the arithmetic (bf16 [256 x 8192]: 26.0 us
 // when wavefront 0 did the serial steps for all and members of a bin were read one by one, 20.9 us now).
 //
-// Either guard or a fixed ladder, any lambda; rows it cannot hold are flagged for the generic kernel.  bf16 entries
+// Either guard or a fixed ladder, any lambda; lambda = 0: rows it cannot hold are flagged for the generic kernel.  bf16 entries
 // are one word (sign, key, inverted index); fp32 entries keep the raw word in the list and the index
 // beside it, and the members of a fine bin compare on "in-bin key bits, inverted index, class".
 #pragma once
@@ -94,22 +94,30 @@ __device__ inline WgLds wg_carve(u32* base, int dt, int cap, int region0, int B2
     return L;
 }
 
-// wavefronts per SIMD the register allocator must leave room for (same rule as the one-wavefront kernel)
-constexpr int wg_min_waves(int dt, int nw, int ept)
+// Largest fine bin whose members are compared with each other (lambda > 0): of one key, of several keys
+constexpr u32 kWgTieBin = 64, kWgSortBin = 256;
+
+// wavefronts per SIMD the register allocator must leave room for (same rule as the one-wavefront kernel; eight where a word or two of
+// scalar registers would cost the eighth: bf16 [8000 x 8192] keep 0.05, lambda = 0.1, 167 us with seven, 158 with eight)
+constexpr int wg_min_waves(int dt, int nw, int ept, int nq, bool asym)
 {
     const int row_regs = dt == 0 ? ept : ept / 2;
     const int per_wg = (nw + 3) / 4;                  // wavefronts of one workgroup on a SIMD
-    const int want = row_regs <= 32 ? 5 : row_regs == 64 ? 3 : 1;
+    const int want = asym && dt == 1 && nq == 7 && nw == 4 && row_regs <= 32 ? 8 : row_regs <= 32 ? 5 : row_regs == 64 ? 3 : 1;
     return want > per_wg ? want : per_wg;
 }
 
 // ASYM: the asymmetric thresholds of Sec. 3.1 with lambda > 0, in the steps of the one-wavefront kernel: tau by exact histogram
 // passes over narrowing windows, a second selection over the fill candidates (or the strict set), then the list from
-// the rule itself, so that it holds the kept set and nothing else.  Before, the generic kernel read such rows from memory some ten times:
+// the rule itself, so that it holds the kept set and nothing else.  No row is left over: a flagged row would be redone by one workgroup after
+// the other rows of its chunk, and many equal values or few non-zeros are ordinary (batches of them took 20 to 450 times as long; us, generic
+// kernel for fp32 or one wavefront for bf16 / a workgroup here, lambda = 0.1, 8 + 8 blocks: fp32 keep 0.15 [256 x 8192] a tenth non-zero 177 / 56,
+// [2048 x 8192] 721 / 255, clipped at 1.3 sigma 691 / 224; bf16 keep 0.2 [256 x 8192] clipped 98 / 42, whole numbers 98 / 45, [1024 x 8192] 118 / 79).
+// Before, the generic kernel read such rows from memory some ten times:
 // encode call of fp32 [2048 x 8192] keep 0.15 549 us, now 88 (100 with every bin narrowed down by two more passes); [1 x 8192] 154, now 28; bf16 [2048 x 12288]
 // keep 0.1 636, now 84.
 template <int DT, int NW, int EPT, int NQ, bool ASYM = false>
-__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_min_waves(DT, NW, EPT)))) void enc_wg_kernel(SmallArgs a)
+__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_min_waves(DT, NW, EPT, NQ, ASYM)))) void enc_wg_kernel(SmallArgs a)
 {
     typedef Elem<DT> E;
     constexpr int kWgThreads = NW * kWave, kWgWaves = NW;
@@ -408,6 +416,19 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
 #pragma unroll
             for (int c = 0; c < NCH; ++c) cntc[c] = (u32)__popc(fm[ASYM ? c : 0]);
             scan_pass();
+            if (__builtin_expect(t_lo == 1u, 0)) {                        // the rule bounds nothing (fewer non-zeros than k): the smallest kept key does
+                u32 low = 0;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) low = max(low, ((fm[ASYM ? c : 0] >> e) & 1u) ? 0x7FFFFFFFu - elem_key(c, e) : 0u);
+                low = wave_max_dpp(low);
+                if (lane == 0) misc[48 + wv] = low;
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < NW; ++i) low = max(low, misc[48 + i]);
+                t_lo = 0x7FFFFFFFu - low;
+            }
         }
     }
     if (!ASYM && !hinted) {
@@ -574,7 +595,10 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     // ---- 3. fine bins: 1024 bins linear in (key - t_lo) >> sh, both classes packed 11 + 11 bits --------
     const u32 range = kmax > t_lo ? kmax - t_lo : 0u;
     const int sh = range < (u32)kFineBins ? 0 : (32 - __clz((int)range)) - 10;
-    if (DT == 0 && sh + w + 1 > 32) {                             // in-bin key bits, index and class must share a word
+    // ASYM: rows with a fine bin of many members of several keys, or with kept magnitudes of more octaves than a word can order inside a bin, get
+    // their list sorted whole, so that every row stays here.  (Members of one key are in the list in their order.)
+    bool sorted = DT == 0 && sh + w + 1 > 32;                     // in-bin key bits, index and class must share a word
+    if (!ASYM && sorted) {
         give_up();
         return;
     }
@@ -594,14 +618,21 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         for (int j = 0; j < FPT; ++j) cs[j] = L.hist[hi - 1 - j];
         u32 local = 0, big = 0;
 #pragma unroll
-        for (int j = 0; j < FPT; ++j) { local += cs[j]; big |= ((cs[j] & 0x7FFu) + (cs[j] >> 11)) >> 10; }
-        if (nL >= 1024u && big != 0u) misc[10] = 1u;        // a fine bin with 1024+ members overflows its 10-bit fill field
+        for (int j = 0; j < FPT; ++j) {
+            const u32 members = (cs[j] & 0x7FFu) + (cs[j] >> 11);
+            local += cs[j];
+            big |= ASYM ? (sh && members > kWgSortBin ? 1u : 0u) : members >> 10;
+        }
+        if ((ASYM || nL >= 1024u) && big != 0u) misc[10] = 1u;       // (a fine bin with 1024+ members overflows its 10-bit fill field)
         const u32 inc_w = wave_scan_dpp(local);             // (the wavefronts' totals meet in misc: the block scan has a barrier more)
         if (lane == kWave - 1) misc[32 + wv] = inc_w;
         __syncthreads();
         if (misc[10]) {
-            give_up();
-            return;
+            if (!ASYM) {
+                give_up();
+                return;
+            }
+            sorted = true;
         }
         u32 tot = 0, excl = inc_w - local;
 #pragma unroll
@@ -617,10 +648,22 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         for (int j = 0; j < FPT; ++j) L.hist[hi - 1 - j] = o[j];
     }
     __syncthreads();
+    if (ASYM && __builtin_expect(sorted, 0)) {
+        // class and comp descending; fp32 sorts the entries' places in the list, whose order is that of the index
+#pragma unroll
+        for (int j = 0; j < kWgSlots; ++j) {
+            const u32 p = (u32)(j * kWgWaves + (int)wv) * kWave + lane;
+            if (p < nL) L.S[p] = DT == 0 ? p : ent[j] ^ 0x80000000u;
+        }
+        __syncthreads();
+        block_sort<kWgThreads>(L.S, nL, [&](u32 s) -> comp_t {
+            return DT == 0 ? ((comp_t)(L.Lent[s] ^ 0x80000000u) << kHiShift) | (comp_t)(u32)~s : (comp_t)s;
+        });
+    }
 #pragma unroll
     for (int j = 0; j < kWgSlots; ++j) {
         const u32 p = (u32)(j * kWgWaves + (int)wv) * kWave + lane;
-        if (p < nL) {
+        if (p < nL && !(ASYM && sorted)) {
             const u32 e = ent[j];
             const u32 rel = ent_key(j) - t_lo;
             const u32 old = atomicAdd(&L.hist[rel >> sh], 1u << 22);
@@ -700,6 +743,14 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         const int jb = (cls ? (int)lane - (M - 1) : (int)lane) + 1;
         const bool act = mine && Kc[cls] > 0;
         const u32 Rk = act ? (u32)jb * Kc[cls] - 1u : 0u;
+        if (ASYM && __builtin_expect(sorted, 0)) {
+            if (mine) {                              // (all wavefronts write the same words)
+                const u32 s = L.S[(cls ? n_pos : 0u) + Rk];
+                comp_t cx = (comp_t)s;
+                if (DT == 0 && act) cx = ((comp_t)(L.Lent[s] ^ 0x80000000u) << kHiShift) | (comp_t)(u32)(~(u32)L.Lidx[s]);
+                thr[lane] = act ? cx : cls ? (comp_t)(kClsBit - 1) : ~(comp_t)0;
+            }
+        } else {
         // smallest bin whose first class rank is <= Rk: three probes a step, so five dependent reads instead of ten
         int lo = 0, len = kFineBins;
         const u32 csh = cls ? 11u : 0u;
@@ -711,9 +762,15 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
             lo += q * (int)(f0 + f1 + f2);           // (first ranks fall as the bins rise)
             len = q;
         }
-        const u32 wd = L.hist[lo];
+        const u32 wd = L.hist[lo], wd_low = ASYM ? L.hist[lo ? lo - 1 : 0] : 0u;
         const u32 pe = wd & 0x7FFu, ne = (wd >> 11) & 0x7FFu;
-        const u32 cnt = act ? wd >> 22 : 0u;
+        u32 cnt = act ? wd >> 22 : 0u;
+        bool tie = false;                            // the boundary lies among many members of one key
+        if (ASYM && sh == 0) {
+            const u32 nx = lo ? wd_low : n_pos | (n_neg << 11);      // (the fill field of such a bin may have overflown)
+            tie = act && (nx & 0x7FFu) + ((nx >> 11) & 0x7FFu) - pe - ne > kWgTieBin;
+            if (tie) cnt = 0;
+        }
         const u32 incl = wave_scan_dpp(cnt);
         if (mine) {                                  // (all wavefronts write the same words)
             tg_bin[lane] = (u32)lo; tg_base[lane] = pe + ne; tg_cnt[lane] = cnt;
@@ -753,6 +810,36 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
                 }
                 if (s_neg(me) == tc && gt == rem) thr[t] = s_cx(me, bin);
             }
+        }
+        if (ASYM && sh == 0) {
+            u32 turn = 0;
+            for (u64 tm = __ballot(tie); __builtin_expect(tm != 0ull, 0); tm &= tm - 1ull, ++turn) {
+                if (turn % (u32)NW != wv) continue;
+                const int t = (int)__builtin_ctzll(tm);
+                const u32 tc = bcast((u32)cls, t), want = (tc << 31) | (((u32)bcast((u32)lo, t) + t_lo) << (DT == 0 ? 0 : 16));
+                u32 left = bcast(Rk - (cls ? ne : pe), t);       // entries of that key and class before it
+                bool done = false;
+                for (u32 p0 = 0; p0 < nL && !done; p0 += 4 * kWave) {
+                    u32 e[4];
+#pragma unroll
+                    for (u32 u = 0; u < 4; ++u) { const u32 p = p0 + u * kWave + lane; e[u] = L.Lent[p < nL ? p : 0u]; }
+#pragma unroll
+                    for (u32 u = 0; u < 4; ++u) {
+                        const u32 p = p0 + u * kWave + lane;
+                        const bool in = p < nL && (DT == 0 ? e[u] : e[u] & 0xFFFF0000u) == want;
+                        const u64 m = __ballot(in);
+                        const u32 c = (u32)__popcll(m);
+                        if (!done && left < c) {
+                            if (in && mask_rank(m) == left)
+                                thr[t] = DT == 0 ? ((comp_t)(e[u] ^ 0x80000000u) << kHiShift) | (comp_t)(u32)(~(u32)L.Lidx[DT == 0 ? p : 0u])
+                                                 : (comp_t)(e[u] ^ 0x80000000u);
+                            done = true;
+                        }
+                        left -= done ? 0u : c;
+                    }
+                }
+            }
+        }
         }
     }
     __syncthreads();

@@ -52,3 +52,55 @@ def test_members_of_one_bin(oracle, N, keep, members):
         x[i] = rng.permutation(v) * rng.choice([-1, 1], N)
     for lam in (0.0, 0.05, 0.5):
         check_atkf(oracle, x, "f32", keep, lam, 4, 4, B28, 1e-3)
+
+
+def crowded(dtype, rows, N, seed):
+    """Rows whose kept elements crowd into one fine bin or spread over more octaves than a bin's members can share a word for: fewer non-zeros than
+    kept elements, clipped, of few levels, a far outlier above a crowd, denormals beside large values, one value from 250 places on."""
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((rows, N)).astype(np.float32)
+    x[0::7] *= rng.random(x[0::7].shape) < 0.05
+    x[1::7] = np.clip(x[1::7], -1.3, 1.3)
+    x[2::7] = np.round(x[2::7])
+    x[3::7, N // 2] = 1e30
+    x[4::7] *= (rng.random(x[4::7].shape) < 0.1) * np.exp2(rng.uniform(-140, 120, x[4::7].shape))
+    for i, row in enumerate(x[5::7]):
+        row[rng.permutation(N)[: 250 + 4 * (i % 4)]] = -2.5
+    x[6::7] = np.where(rng.random(x[6::7].shape) < 0.1, 0.25 * np.sign(x[6::7]), x[6::7] * 1e-40)
+    return synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+
+
+@pytest.mark.parametrize("rows", [14, 150, 300])
+@pytest.mark.parametrize("dtype,N,keep,Mp,Mn", [("bf16", 4104, 0.45, 8, 8), ("bf16", 6001, 0.3, 32, 32), ("bf16", 8192, 0.2, 8, 8), ("bf16", 12288, 0.15, 1, 3),
+                                                ("f32", 4100, 0.4, 32, 32), ("f32", 8192, 0.15, 8, 8), ("f32", 16384, 0.1, 16, 2)])
+def test_crowded_rows(oracle, dtype, N, keep, Mp, Mn, rows):
+    x = crowded(dtype, rows, N, N + rows)
+    for lam in (0.1, 0.95):
+        check_atkf(oracle, x, dtype, keep, lam, Mp, Mn, B28, 1e-3)
+
+
+@pytest.mark.parametrize("dtype,rows,N,keep", [("f32", 256, 8192, 0.15), ("f32", 2048, 8192, 0.15), ("bf16", 256, 8192, 0.2), ("bf16", 1024, 8192, 0.2)])
+@pytest.mark.parametrize("kind", ["sparse", "clipped", "levels"])
+def test_no_row_is_left_to_the_generic_kernel(dtype, rows, N, keep, kind):
+    """Rows that are left over are encoded one after the other by a few workgroups, which takes 20 to 450 times as long as the batch; a row that
+    stays takes at most a few times as long as one of continuous values, by the sort of its list."""
+    import torch
+    from paper_2511_11608_amd import binding
+    x = torch.randn((rows, N), device="cuda")
+    y = {"sparse": x * (torch.rand_like(x) < 0.1), "clipped": x.clamp(-1.3, 1.3), "levels": torch.round(x)}[kind]
+    out = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def best(v):
+        v = v.to(out).contiguous()
+        bufs = binding.alloc_buffers_pn(v, keep, 8, 8, B28)
+        times = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            binding.slicer_encode_atkf(v, keep, 0.1, 8, 8, B28, 1e-3, *bufs)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+    plain, crowd = best(x), best(y)
+    assert crowd < 8 * plain, (crowd, plain)
