@@ -572,6 +572,9 @@ constexpr int kMaxTargets = 2 * kMaxB2;
 // a member: comp in the low 55 bits (31 of the key, up to 24 of the index), its group, its class
 constexpr int kMemGroup = 55;
 constexpr u64 kMemComp = (1ull << kMemGroup) - 1ull;
+// Largest bin whose members are compared with each other; with a larger one in the row they are sorted.  Encode us, 1024 / 512: fp32 [1 x 200704]
+// in steps of 1/40 133 / 117, [1 x 4000000] keep 0.3 209 / 150, [32 x 401408] clipped at 3 sigma 137 / 121.
+constexpr u32 kLrSortBin = 512;
 
 template <int FB, bool BIG>
 struct LrBoundsLds {
@@ -652,13 +655,12 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
 
     auto at_c = [&](u32 cls, u32 b) -> u32 { return cls == 0u ? L.at_p[b] : cls == 1u ? L.at_n[b] : L.at_p[b] + L.at_n[b]; };
     // members of the bins of groups ga .. gb - 1 (g_start: room per group), tile by tile; up to eight threads share a tile's
-    // members while there are threads to spare (equal values fill a bin: fp32 [1 x 200704] quantised to 256 levels 119 -> 113 us, bf16
-    // to 16 levels 84 -> 70; what remains there is the comparison of all members of a bin with each other)
-    auto gather = [&](int ga, int gb) {
+    // members while there are threads to spare, and more of them where a bin is crowded
+    auto gather = [&](int ga, int gb, bool crowded) {
         const int ng = gb - ga;
         const u32 m0 = L.g_start[ga];
         int lp = 0;                                  // log2 of the threads that share
-        while (lp < 3 && (ng * S << (lp + 1)) <= TH) ++lp;
+        while (lp < (crowded ? 8 : 3) && (ng * S << (lp + 1)) <= TH) ++lp;
         for (int i = tid; i < ng * S << lp; i += TH) {
             const int gs = i >> lp, share_of = i - (gs << lp), gi = gs / S, s = gs - gi * S, g = ga + gi;
             const u32 cls = L.g_cls[g], b = L.g_bin[g];
@@ -709,9 +711,17 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
             const u32 cn = L.g_start[1], cb = L.g_bin[0];
             if (cn > (u32)kMemCap) bad = true;
             else {
-                gather(0, 1);
+                const bool crowded = cn > kLrSortBin;
+                gather(0, 1, crowded);
                 const u32 rem = k - 1u - at_c(2, cb + 1u);
-                for (u32 i = (u32)tid; i < cn; i += TH) {
+                if (__builtin_expect(crowded, 0)) {
+                    block_sort<TH>(L.mem, cn, [](u64 m) { return m & ~kTop; });
+                    for (u32 i0 = 0; i0 <= rem; i0 += TH) {
+                        const u32 i = i0 + (u32)tid, in_n = (u32)__popcll(__ballot(i <= rem && (L.mem[i <= rem ? i : 0u] & kTop)));
+                        const u32 in = (u32)__popcll(__ballot(i <= rem));
+                        if (lane_id() == 0u && in) { atomicAdd(&L.v[0], in - in_n); atomicAdd(&L.v[1], in_n); }
+                    }
+                } else for (u32 i = (u32)tid; i < cn; i += TH) {
                     const u64 me = L.mem[i] & ~kTop;
                     u32 gt = 0;
                     for (u32 j = 0; j < cn; j += 4) {
@@ -755,14 +765,18 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
         __syncthreads();
         if (tid < kWave) {                           // groups: a target opens one unless the target before it lies in the same bin
             const int TL = (2 * B2 + kWave - 1) / kWave;     // targets a lane
-            u32 lead = 0, room = 0;
+            u32 lead = 0, room = 0, most = 0;
             for (int j = 0; j < TL; ++j) {
                 const int t = tid * TL + j;
                 if (t >= 2 * B2) break;
                 const u32 b = L.tg_bin[t], c = (t >> 1) >= M ? 1u : 0u;
                 const bool same = t > 0 && L.tg_bin[t - 1] == b && (((t - 1) >> 1) >= M ? 1u : 0u) == c;
-                if (b != 0xFFFFFFFFu && !same) { lead |= 1u << j; room += at_c(c, b) - at_c(c, b + 1u); }
+                if (b != 0xFFFFFFFFu && !same) {
+                    const u32 n = at_c(c, b) - at_c(c, b + 1u);
+                    lead |= 1u << j; room += n; most = n > most ? n : most;
+                }
             }
+            if (__any(most > kLrSortBin) && tid == 0) L.v[3] = 1u;
             const u32 nl = (u32)__popc(lead);
             const u32 incl = wave_scan_dpp(nl), incr = wave_scan_dpp(room);
             u32 g = incl - nl, at = incr - room;
@@ -778,11 +792,42 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
         }
         __syncthreads();
         const int ng = (int)L.v[2];
-        for (int i = 0; i < P; ++i) bad |= L.g_start[ng * (i + 1) / P] - L.g_start[ng * i / P] > (u32)kMemCap;
+        const int lgP = __builtin_ctz((u32)P);       // (P is a power of two)
+        if (__builtin_expect(L.g_start[ng] > (u32)kMemCap, 0))
+            for (int i = 0; i < P; ++i) bad |= L.g_start[ng * (i + 1) >> lgP] - L.g_start[ng * i >> lgP] > (u32)kMemCap;
         if (!bad) {
-            const int ga = ng * part / P, gb = ng * (part + 1) / P;
+            const int ga = ng * part >> lgP, gb = ng * (part + 1) >> lgP;
             const u32 m0 = L.g_start[ga], nm = L.g_start[gb] - m0;
-            gather(ga, gb);
+            const bool crowded = L.v[3] != 0u;       // uniform
+            gather(ga, gb, crowded);
+            if (__builtin_expect(crowded, 0)) {
+                // Groups in their order, the members of each from the largest comp down: a target is found by its rank.  All against all grew with
+                // the square of the bin: fp32 [1 x 140000] keep 0.5, 64 + 64 blocks, 16000 equal values of either sign 4.2 ms, now 0.28 (by the generic
+                // encoder 9.4); 16000 of one sign for the cut alone 18.9 ms; [1 x 200704] in steps of 1/20 338 us, now 110.
+                block_sort<TH>(L.mem, nm, [](u64 m) { return m ^ ~kMemComp; });
+                const int lane = (int)lane_id();
+                for (int g = ga + tid / kWave; g < gb; g += TH / kWave)
+                    for (int t = (int)L.g_t0[g] + lane; t < (int)L.g_t0[g + 1]; t += kWave)
+                        if (L.tg_bin[t] == L.g_bin[g]) L.tg_comp[t] = L.mem[L.g_start[g] - m0 + L.tg_rem[t]] & kMemComp;
+                __syncthreads();
+                // per tile: entries of the class from the block's last element up.  Equal values of a tile follow each other: one addition a run
+                for (u32 i0 = (u32)(tid / kWave * kWave); i0 < nm; i0 += TH) {
+                    const u32 i = i0 + (u32)lane;
+                    const u64 me = L.mem[i < nm ? i : nm - 1u];
+                    const u32 g = (u32)(me >> kMemGroup) & 0xFFu, t0 = L.g_t0[g], t1 = L.g_t0[g + 1];
+                    const u32 s = ((1u << w) - 1u - ((u32)me & ((1u << w) - 1u))) / (u32)a.tile, run = s | (g << 16);
+                    const u32 before = (u32)__shfl_up((int)run, 1);          // (by all lanes)
+                    const bool head = lane == 0 || before != run;
+                    const u64 heads = __ballot(head), above = heads & ~((2ull << lane) - 1ull);       // (lane 63: none)
+                    const u64 mine = (above ? (1ull << __builtin_ctzll(above)) - 1ull : ~0ull) & ~((1ull << lane) - 1ull);
+                    const u32 ta = bcast(t0, 0), tb = bcast(t1, kWave - 1);
+                    for (u32 t = ta | 1u; t < tb; t += 2u) {
+                        const u64 from = __ballot(i < nm && t >= t0 && t < t1 && (me & kMemComp) >= L.tg_comp[t]);
+                        const u32 n = (u32)__popcll(from & mine);
+                        if (head && n) atomicAdd(&pair[(size_t)(t >> 1) * S + s], n);
+                    }
+                }
+            } else {
             // rank of every member in its group, by up to sixteen lanes a member (one lane: 2.7 us of a row's 13 with 90 members a group)
             int lr = 0;
             while (lr < 4 && (nm << (lr + 1)) <= (u32)TH) ++lr;
@@ -812,6 +857,7 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
                 for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t)
                     if ((t & 1u) && me >= L.tg_comp[t]) atomicAdd(&pair[(size_t)(t >> 1) * S + s], 1u);
             }
+            }
             for (int t = tid; t < 2 * B2; t += TH) {
                 const u64 c = L.tg_comp[t];
                 const size_t rb = (size_t)r * B2 + (t >> 1);
@@ -840,9 +886,9 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
         // parts come to the same decision; the last one to have made it, behind everybody's reads, has the row.
         __syncthreads();
         if (P > 1) {
-            if (tid == 0) L.v[3] = __hip_atomic_fetch_add(&st[kStLeft], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) L.v[4] = __hip_atomic_fetch_add(&st[kStLeft], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
-            if (L.v[3] != (u32)P - 1u) return;       // uniform
+            if (L.v[4] != (u32)P - 1u) return;       // uniform
             __syncthreads();                         // (the encoder's LDS is the same)
         }
         if (tid == 0) st[kStFlag] = 1u;
