@@ -280,8 +280,11 @@ void launch_large_stages(const LargeArgs& la, const EncArgs& ea, const FinishArg
     const dim3 gT((unsigned)la.S, (unsigned)la.R), gR((unsigned)la.R), gB((unsigned)(la.R * la.parts)), gW((unsigned)la.nwin, (unsigned)la.R), bT(kTileThreads);
     const dim3 bR((unsigned)lr_row_threads(FB));
     hipLaunchKernelGGL((lr_sample_kernel<DT, FB>), gR, bR, 0, st, la);
-    if (la.tile <= 8192) hipLaunchKernelGGL((lr_compact_kernel<DT, 2, FB>), gT, bT, 0, st, la);
-    else hipLaunchKernelGGL((lr_compact_kernel<DT, 4, FB>), gT, bT, 0, st, la);
+    if (la.dense) {
+        if (la.tile <= 8192) hipLaunchKernelGGL((lr_compact_kernel<DT, 2, FB, true>), gT, bT, 0, st, la);
+        else hipLaunchKernelGGL((lr_compact_kernel<DT, 4, FB, true>), gT, bT, 0, st, la);
+    } else if (la.tile <= 8192) hipLaunchKernelGGL((lr_compact_kernel<DT, 2, FB, false>), gT, bT, 0, st, la);
+    else hipLaunchKernelGGL((lr_compact_kernel<DT, 4, FB, false>), gT, bT, 0, st, la);
     if (FB == kFBWide && large_many_members(la.k, la.M + la.Mn))
         hipLaunchKernelGGL((lr_bounds_kernel<DT, FB, FB == kFBWide>), gB, bR, 0, st, la, ea);
     else hipLaunchKernelGGL((lr_bounds_kernel<DT, FB, false>), gB, bR, 0, st, la, ea);

@@ -65,6 +65,7 @@ struct LargeArgs {
     u32 sample_target;      // see lr_sample_plan
     float sample_scale;
     int tile, S;            // elements of a tile, tiles per row
+    bool dense;             // most wavefronts of the compact stage have more entries than kLrEntries
     int parts;              // workgroups that share a row in the bounds stage
     u32 capL;               // list capacity per row
     uint16_t* tab;          // [R][kTabSize]  first fine bin of a sample bin | log2 of its number of fine bins << 12; one guard at either end
@@ -102,6 +103,8 @@ struct LargeArgs {
     int wp, wc;
 };
 
+constexpr int kLrEntries = 640;      // room for a wavefront's entries in the compact stage
+
 // What the sample stage aims at: how many of the sample's elements must reach the bound, i.e. the expected number of the k kept ones plus
 // four standard deviations, taken as if the elements of a chunk were all alike; and the row's elements per sampled one.  (Of the
 // row's chunks counted from its start: one that starts inside a chunk may have one more, which the margin covers.)
@@ -111,6 +114,8 @@ inline void lr_sample_plan(LargeArgs& a, int fine_bins, int epc)
     const double G = (double)(Q < room ? Q : room), f = (double)a.k / (double)a.N;
     a.sample_target = (u32)(f * G * epc + 4.0 * epc * sqrt(G * f * (1.0 - f))) + 1u;
     a.sample_scale = (float)((double)a.N / (G * epc));
+    // the line: fp32 [316 x 126280], expected 551 entries a wavefront, dense 783 us, else 768, [64 x 630000] 246 and 239; 591 entries 280 and 303, 252 and 284
+    a.dense = (double)a.sample_target / (G * epc) * (a.tile / (kTileThreads / kWave)) > 0.9 * kLrEntries;
 }
 
 // words of a row's state.  kStFlag (encoded generically): written by compact, and by the bounds stage when no part of the row reads it any more
@@ -343,22 +348,25 @@ __global__ __launch_bounds__(lr_row_threads(FB)) __attribute__((amdgpu_waves_per
 // follows from the ballot of its word's flags.  With 16 bytes a lane the places took prefix sums of per-lane counts, behind a count
 // of everything; with the fine bins of all entries kept in registers from the histogram to the positions, up to 49 of them spilled.
 // A tile with a wavefront of more than kLrEntries entries is read again, 512 elements at a time.
-constexpr int kLrEntries = 640;
-template <int DT, int NR, int FB>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void lr_compact_kernel(LargeArgs a)
+// DENSE: for lists with more entries than that in most wavefronts, where reading again took half the stage's time (encode, fp32 [40 x 985624] keep
+// 0.8 729 -> 573 us, [316 x 126280] keep 0.3 353 -> 293).  The elements stay in registers and give way, 512 at a time, to the bins and places of their entries.
+template <int DT, int NR, int FB, bool DENSE>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(DENSE && NR > 2 ? 6 : 8))) void lr_compact_kernel(LargeArgs a)
 {
     constexpr int EPW = DT == 0 ? 1 : 2, WPR = 8 / EPW;              // elements of a word, words per lane and round
     constexpr int NW = NR * WPR, NWV = kTileThreads / kWave, RE = 8 * kWave, NS = kLrEntries / kWave;       // words of a lane; elements of a round; entries of a lane
+    constexpr int kRoom = DENSE ? RE : kLrEntries;   // entries of a wavefront's piece of LDS
+    constexpr int kBuf = DENSE && NR * RE * NWV * 2 > NWV * kRoom * 6 ? NR * RE * NWV * 2 : NWV * kRoom * 6;
     typedef typename Elem<DT>::raw_t raw_t;
     __shared__ u32 hist[FB];                         // positive | negative << 16; later the place of the bin's next entry
     __shared__ __align__(4) uint16_t tab[kTabSize];
-    __shared__ __align__(16) unsigned char buf[NWV * kLrEntries * 6];
+    __shared__ __align__(16) unsigned char buf[kBuf];
     __shared__ u32 wtot[NWV];
     __shared__ u32 scr[NWV + 1];
     __shared__ u32 s_base;
     const int tid = threadIdx.x, s = blockIdx.x, w = a.w, wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-    u32* braw = (u32*)buf + wv * kLrEntries;         // entries of this wavefront
-    uint16_t* bidx = (uint16_t*)(buf + NWV * kLrEntries * 4) + wv * kLrEntries;
+    u32* braw = (u32*)buf + wv * kRoom;              // entries of this wavefront
+    uint16_t* bidx = (uint16_t*)(buf + NWV * kRoom * 4) + wv * kRoom;
     uint16_t* bpos = (uint16_t*)buf;                 // in the end: list positions by fine bin
     const u32 lane = lane_id();
     const int64_t r = blockIdx.y;
@@ -395,15 +403,16 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     // bf16: 17 bits of the inverted index (an element behind the row's end has key 0 and stays below the least bound, 2^17)
     const u32 inv0 = (1u << w) - 1u - (tile0 + we0 + lane * (u32)EPW);
     const int up = w < 17 ? 17 - w : 0, down = w < 17 ? 0 : w - 17;
-    // the entries of word c (elements c * 64 * EPW ... of the wavefront) to its piece, behind `run` others
-    auto squeeze = [&](u32 x, u32 c, u32& run) {
+    // the entries of word c (elements c * 64 * EPW ... of the wavefront) to its piece, behind `run` others; or only their number
+    auto squeeze = [&](u32 x, u32 c, u32& run, auto store) {
+        constexpr bool kStore = decltype(store)::value;
         const u32 e = (c * (u32)kWave + lane) * (u32)EPW;
         if (DT == 0) {
             const bool in = (x & 0x7FFFFFFFu) >= T;
             const u64 m = __ballot(in);
             const u32 pos = run + mask_rank(m);
             run += (u32)__popcll(m);
-            if (run <= (u32)kLrEntries && in) { braw[pos] = x; bidx[pos] = (uint16_t)e; }
+            if (kStore && run <= (u32)kRoom && in) { braw[pos] = x; bidx[pos] = (uint16_t)e; }
         } else {
             const u32 k0 = (x << 16) & 0x7FFF0000u, k1 = x & 0x7FFF0000u, inv = inv0 - c * (u32)(kWave * EPW);
             const bool in0 = ((k0 << 1) | __builtin_amdgcn_ubfe(inv << up, (u32)down, 17u)) >= T;
@@ -411,12 +420,13 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
             const u64 m0 = __ballot(in0), m1 = __ballot(in1);
             const u32 pos = run + mask_rank(m0) + mask_rank(m1), pos1 = pos + (in0 ? 1u : 0u);
             run += (u32)__popcll(m0) + (u32)__popcll(m1);
-            if (run <= (u32)kLrEntries) {
+            if (kStore && run <= (u32)kRoom) {
                 if (in0) { braw[pos] = x << 16; bidx[pos] = (uint16_t)e; }
                 if (in1) { braw[pos1] = x & 0xFFFF0000u; bidx[pos1] = (uint16_t)(e + 1u); }
             }
         }
     };
+    typedef std::true_type yes;
     auto bin_of = [&](u32 raw, u32 ix) -> u32 {      // fine bin | negative << 31
         const u32 key = DT == 0 ? raw & 0x7FFFFFFFu : (raw >> 16) & 0x7FFFu;
         return lr_fine_bin<DT>(lr_c32<DT>(key, first + ix, w), tab, Blo, nb) | (raw & 0x80000000u);
@@ -424,13 +434,13 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     auto one = [&](u32 b) -> u32 { return b >> 31 ? 0x10000u : 1u; };
     u32 wn = 0;
 #pragma unroll
-    for (int c = 0; c < NW; ++c) squeeze(v[c], (u32)c, wn);
+    for (int c = 0; c < NW; ++c) squeeze(v[c], (u32)c, wn, std::integral_constant<bool, !DENSE>());
     if (lane == 0) wtot[wv] = wn;
     __syncthreads();
     u32 wbase = 0, ntile = 0, most = 0;              // entries of the wavefronts before this one, of the tile
 #pragma unroll
     for (int i = 0; i < NWV; ++i) { const u32 t = wtot[i]; if (i < wv) wbase += t; ntile += t; most = t > most ? t : most; }
-    const bool dense = most > (u32)kLrEntries;       // uniform
+    const bool dense = !DENSE && most > (u32)kLrEntries;     // uniform
     if (tid == 0) {
         u32 b = atomicAdd(&st[kStCursor], ntile);
         if (b > a.capL || ntile > a.capL - b) { b = 0xFFFFFFFFu; st[kStFlag] = 1u; }     // the list is full: the row is redone generically
@@ -444,7 +454,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
             u32 t[WPR], run = 0;
             load(t, (int)(lane * 4u) + g * (RE * (int)sizeof(raw_t)));
 #pragma unroll
-            for (int j = 0; j < WPR; ++j) squeeze(t[j], (u32)(g * WPR + j), run);
+            for (int j = 0; j < WPR; ++j) squeeze(t[j], (u32)(g * WPR + j), run, yes());
             wave_sync();
 #pragma unroll 1
             for (u32 i = lane; i < run; i += kWave) f(before + i, braw[i], (u32)bidx[i]);
@@ -452,11 +462,45 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
             before += run;
         }
     };
-    u32 bf[NS];
-    if (dense) rounds([&](u32, u32 raw, u32 ix) { const u32 b = bin_of(raw, ix); atomicAdd(&hist[b & 0xFFFu], one(b)); });
+    u32 bf[DENSE ? NR * 8 : NS], nr[NR];             // bins, and DENSE: | entries of the bin before this one << 12; entries of a round
+    if (DENSE) __syncthreads();                      // s_base
+    const u32 seg0d = DENSE ? s_base : 0u;
+    if (DENSE) {
+        u32* __restrict__ Lraw = LrList(a, r).raw + seg0d + wbase;
+        uint16_t* __restrict__ Lidx = LrList(a, r).idx + seg0d + wbase;
+        u32 before = 0;
+#pragma unroll
+        for (int g = 0; g < NR; ++g) {
+            u32 run = 0;
+#pragma unroll
+            for (int j = 0; j < WPR; ++j) squeeze(v[g * WPR + j], (u32)(g * WPR + j), run, yes());
+            nr[g] = run;
+            wave_sync();
+#pragma unroll
+            for (int h = 0; h < 8; h += 2) {         // two entries per lane at a time, their lookups side by side
+                bf[DENSE ? g * 8 + h : 0] = bf[DENSE ? g * 8 + h + 1 : 0] = 0;
+                if ((u32)(h * kWave) >= run) continue;       // uniform in the wavefront
+                u32 raw[2], ix[2], b[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) { const u32 i = (u32)((h + e) * kWave) + lane; raw[e] = braw[i]; ix[e] = (u32)bidx[i]; }
+#pragma unroll
+                for (int e = 0; e < 2; ++e) b[e] = bin_of(raw[e], ix[e]);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {        // (lanes without an entry add nothing, each to a bin of its own)
+                    const u32 i = (u32)((h + e) * kWave) + lane;
+                    const bool in = i < run;
+                    const u32 old = atomicAdd(&hist[in ? b[e] & 0xFFFu : lane], in ? one(b[e]) : 0u);
+                    bf[DENSE ? g * 8 + h + e : 0] = b[e] | ((b[e] >> 31 ? old >> 16 : old & 0xFFFFu) << 12);
+                    if (in && seg0d != 0xFFFFFFFFu) { Lraw[before + i] = raw[e]; Lidx[before + i] = (uint16_t)(we0 + ix[e]); }
+                }
+            }
+            wave_sync();
+            before += run;
+        }
+    } else if (dense) rounds([&](u32, u32 raw, u32 ix) { const u32 b = bin_of(raw, ix); atomicAdd(&hist[b & 0xFFFu], one(b)); });
     else {
 #pragma unroll
-        for (int h = 0; h < NS; h += 2) {            // two entries per lane at a time, their lookups side by side
+        for (int h = 0; h < (DENSE ? 0 : NS); h += 2) {            // two entries per lane at a time, their lookups side by side
             if ((u32)(h * kWave) >= wn) break;       // uniform in the wavefront
             u32 raw[2], ix[2];
 #pragma unroll
@@ -501,6 +545,23 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
         if (tid == 0) { seg[0] = seg0; seg[1] = tot; }
     }
     if (full || ntile == 0u) return;                 // uniform
+    if (DENSE) {
+        __syncthreads();
+        u32 before = 0;
+#pragma unroll
+        for (int g = 0; g < NR; ++g) {
+#pragma unroll
+            for (int h = 0; h < 8; ++h) {
+                if ((u32)(h * kWave) >= nr[g]) continue;     // uniform in the wavefront
+                const u32 i = (u32)(h * kWave) + lane, t = bf[DENSE ? g * 8 + h : 0], at = hist[t & 0xFFFu];
+                if (i < nr[g]) bpos[(t >> 31 ? at >> 16 : at & 0xFFFFu) + ((t >> 12) & 0x7FFFu)] = (uint16_t)(wbase + before + i);
+            }
+            before += nr[g];
+        }
+        __syncthreads();
+        for (u32 i = (u32)tid; i < ntile; i += kTileThreads) Lpos[i] = bpos[i];
+        return;
+    }
     if (dense) {
         __syncthreads();
         rounds([&](u32 i, u32 raw, u32 ix) {
@@ -511,14 +572,14 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
         return;
     }
 #pragma unroll
-    for (int h = 0; h < NS; ++h) {
+    for (int h = 0; h < (DENSE ? 0 : NS); ++h) {
         const u32 i = (u32)(h * kWave) + lane;
         if ((u32)(h * kWave) >= wn) break;
         if (i < wn) { Lraw[i] = braw[i]; Lidx[i] = (uint16_t)(we0 + (u32)bidx[i]); }
     }
     __syncthreads();                                 // the entries have been read: their storage takes the positions
 #pragma unroll
-    for (int h = 0; h < NS; ++h) {
+    for (int h = 0; h < (DENSE ? 0 : NS); ++h) {
         if ((u32)(h * kWave) >= wn) break;
         const u32 i = (u32)(h * kWave) + lane;
         if (i < wn) {

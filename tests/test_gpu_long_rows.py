@@ -113,9 +113,10 @@ def test_csr_of_long_rows_through_the_flat_stream(oracle, dtype, shift):
 
 @pytest.mark.parametrize("dtype,rows,N,keep,M", [("f32", 3, 40_000, 0.8, 8), ("f32", 40, 65_549, 0.3, 8), ("bf16", 3, 40_001, 0.8, 8), ("bf16", 40, 65_549, 0.2, 8),
                                                  ("bf16", 90, 30_002, 0.5, 3), ("f32", 130, 17_000, 0.2, 16), ("f32", 2, 140_000, 0.5, 64), ("f32", 1, 600_000, 0.03, 4),
-                                                 ("f32", 4, 401_000, 0.1, 8), ("bf16", 1, 1_700_003, 0.05, 4), ("f32", 16, 400_001, 0.05, 4)])
+                                                 ("f32", 4, 401_000, 0.1, 8), ("bf16", 1, 1_700_003, 0.05, 4), ("f32", 16, 400_001, 0.05, 4), ("bf16", 130, 50_001, 0.7, 4), ("f32", 130, 50_002, 0.6, 64),
+                                                 ("f32", 130, 50_000, 1.0, 5), ("bf16", 260, 30_000, 1.0, 2), ("f32", 260, 30_001, 0.5, 3)])
 def test_dense_tiles_and_shared_rows(oracle, dtype, rows, N, keep, M):
-    """Wavefronts with more entries than their room (640) beside emptier ones; one to eight workgroups for a row's order statistics; tiles that are no
+    """Wavefronts with more entries than their room (640) beside emptier ones, in lists that are sparse, dense or the whole row; one to eight workgroups for a row's order statistics; tiles that are no
     power of two; rows of odd length whose words hold halves of two rows; the larger room for a row's bin members."""
     x = features(dtype, rows, N, N)
     x[:, N // 3: N // 2] = 0                            # some tiles hold nothing ...
