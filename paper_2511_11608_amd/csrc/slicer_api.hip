@@ -232,13 +232,13 @@ Plan make_plan(int dt, int64_t rows, int64_t row_len, double keep_ratio, int n_b
     // The workspace holds the stages' tables (8 KB a tile and more) only where some row of this length can reach the
     // stages: not where a row-resident kernel holds the row wherever it starts.
     p.large_S = 0; p.large_capL = 0; p.large_fb = 0;
-    {
+    auto row_kernel_holds = [&](int64_t elements) { return small_holds(elements) || wg_holds(elements); };
+    auto held = [&] { return (!whole_len || row_kernel_holds(row_len)) && row_kernel_holds(row_len + epc - 1); };
+    if (long_rows && row_len > 4096 && rows <= 65535 && (whole_len || row_len > 8192) && !held()) {      // (a call for short rows divides nothing here)
         const int64_t tile = large_tile(rows, row_len);
         const int64_t S = (row_len + tile - 1) / tile;       // rows of up to 2^23 elements
         const int64_t capL = (p.k + std::max<int64_t>(4096, row_len / 16) + 7) & ~(int64_t)7;
-        auto row_kernel_holds = [&](int64_t elements) { return small_holds(elements) || wg_holds(elements); };
-        const bool held = (!whole_len || row_kernel_holds(row_len)) && row_kernel_holds(row_len + epc - 1);
-        if (long_rows && row_len > 4096 && S <= 512 && rows <= 65535 && !held && (whole_len || row_len > 8192)) {
+        if (S <= 512) {
             const size_t R = (size_t)rows, B2 = (size_t)B2_all, Sz = (size_t)S;
             if (whole || row_len > 8192) p.large_S = (int)S;
             p.large_capL = (u32)capL;

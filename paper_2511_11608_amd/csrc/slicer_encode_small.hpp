@@ -469,9 +469,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(small_min
         wave_sync();
     };
     auto single_keys = [&](bool wide, auto key_fn, auto skip0) __attribute__((always_inline)) {
-        if (DT == 0 && cnt1 <= (u32)kWave) {         // uniform
-            few_members(wide ? 20 : 16, key_fn, skip0);
-            return;
+        if constexpr (DT == 0) {
+            if (cnt1 <= (u32)kWave) {                // uniform
+                few_members(wide ? 20 : 16, key_fn, skip0);
+                return;
+            }
         }
         if (DT == 0) {
             if (wide) {
