@@ -889,35 +889,35 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
                     }
                 }
             } else {
-            // rank of every member in its group, by up to sixteen lanes a member (one lane: 2.7 us of a row's 13 with 90 members a group)
-            int lr = 0;
-            while (lr < 4 && (nm << (lr + 1)) <= (u32)TH) ++lr;
-            const u32 sl = (u32)tid & ((1u << lr) - 1u), lanes = 1u << lr;
-            for (u32 i0 = 0; i0 < nm; i0 += (u32)TH >> lr) {
-                const u32 i = i0 + ((u32)tid >> lr);
-                const u64 me = i < nm ? L.mem[i] : 0ull;
-                const u32 g = i < nm ? (u32)(me >> kMemGroup) & 0xFFu : (u32)ga, m1 = L.g_start[g + 1] - m0, t1 = L.g_t0[g + 1], gb_bin = L.g_bin[g];
-                u32 gt = 0;
-                for (u32 j = L.g_start[g] - m0 + sl; j < m1; j += 4 * lanes) {
-                    u64 m4[4];
+                // rank of every member in its group, by up to sixteen lanes a member (one lane: 2.7 us of a row's 13 with 90 members a group)
+                int lr = 0;
+                while (lr < 4 && (nm << (lr + 1)) <= (u32)TH) ++lr;
+                const u32 sl = (u32)tid & ((1u << lr) - 1u), lanes = 1u << lr;
+                for (u32 i0 = 0; i0 < nm; i0 += (u32)TH >> lr) {
+                    const u32 i = i0 + ((u32)tid >> lr);
+                    const u64 me = i < nm ? L.mem[i] : 0ull;
+                    const u32 g = i < nm ? (u32)(me >> kMemGroup) & 0xFFu : (u32)ga, m1 = L.g_start[g + 1] - m0, t1 = L.g_t0[g + 1], gb_bin = L.g_bin[g];
+                    u32 gt = 0;
+                    for (u32 j = L.g_start[g] - m0 + sl; j < m1; j += 4 * lanes) {
+                        u64 m4[4];
 #pragma unroll
-                    for (u32 u = 0; u < 4; ++u) m4[u] = L.mem[j + u * lanes < m1 ? j + u * lanes : m1 - 1u];
+                        for (u32 u = 0; u < 4; ++u) m4[u] = L.mem[j + u * lanes < m1 ? j + u * lanes : m1 - 1u];
 #pragma unroll
-                    for (u32 u = 0; u < 4; ++u) gt += (u32)(j + u * lanes < m1) & (u32)(m4[u] > me);
+                        for (u32 u = 0; u < 4; ++u) gt += (u32)(j + u * lanes < m1) & (u32)(m4[u] > me);
+                    }
+                    for (int d = 1; d < (int)lanes; d <<= 1) gt += (u32)__shfl_xor((int)gt, d);
+                    for (u32 t = L.g_t0[g] + sl; i < nm && t < t1; t += lanes)
+                        if (L.tg_bin[t] == gb_bin && L.tg_rem[t] == gt) L.tg_comp[t] = me & kMemComp;
                 }
-                for (int d = 1; d < (int)lanes; d <<= 1) gt += (u32)__shfl_xor((int)gt, d);
-                for (u32 t = L.g_t0[g] + sl; i < nm && t < t1; t += lanes)
-                    if (L.tg_bin[t] == gb_bin && L.tg_rem[t] == gt) L.tg_comp[t] = me & kMemComp;
-            }
-            __syncthreads();
-            // per tile: entries of the class from the block's last element up
-            for (u32 i = (u32)tid; i < nm; i += TH) {
-                const u32 g = (u32)(L.mem[i] >> kMemGroup) & 0xFFu;
-                const u64 me = L.mem[i] & kMemComp;
-                const u32 s = ((1u << w) - 1u - ((u32)me & ((1u << w) - 1u))) / (u32)a.tile;      // its tile
-                for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t)
-                    if ((t & 1u) && me >= L.tg_comp[t]) atomicAdd(&pair[(size_t)(t >> 1) * S + s], 1u);
-            }
+                __syncthreads();
+                // per tile: entries of the class from the block's last element up
+                for (u32 i = (u32)tid; i < nm; i += TH) {
+                    const u32 g = (u32)(L.mem[i] >> kMemGroup) & 0xFFu;
+                    const u64 me = L.mem[i] & kMemComp;
+                    const u32 s = ((1u << w) - 1u - ((u32)me & ((1u << w) - 1u))) / (u32)a.tile;      // its tile
+                    for (u32 t = L.g_t0[g]; t < L.g_t0[g + 1]; ++t)
+                        if ((t & 1u) && me >= L.tg_comp[t]) atomicAdd(&pair[(size_t)(t >> 1) * S + s], 1u);
+                }
             }
             for (int t = tid; t < 2 * B2; t += TH) {
                 const u64 c = L.tg_comp[t];

@@ -416,19 +416,6 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
 #pragma unroll
             for (int c = 0; c < NCH; ++c) cntc[c] = (u32)__popc(fm[ASYM ? c : 0]);
             scan_pass();
-            if (__builtin_expect(t_lo == 1u, 0)) {                        // the rule bounds nothing (fewer non-zeros than k): the smallest kept key does
-                u32 low = 0;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                    for (int e = 0; e < EPC; ++e) low = max(low, ((fm[ASYM ? c : 0] >> e) & 1u) ? 0x7FFFFFFFu - elem_key(c, e) : 0u);
-                low = wave_max_dpp(low);
-                if (lane == 0) misc[48 + wv] = low;
-                __syncthreads();
-#pragma unroll
-                for (int i = 0; i < NW; ++i) low = max(low, misc[48 + i]);
-                t_lo = 0x7FFFFFFFu - low;
-            }
         }
     }
     if (!ASYM && !hinted) {
@@ -592,6 +579,19 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
     auto ent_key = [&](int j) -> u32 { return DT == 0 ? ent[j] & 0x7FFFFFFFu : (ent[j] >> 16) & 0x7FFFu; };
     auto ent_idx = [&](int j) -> u32 { return DT == 0 ? eix[DT == 0 ? j : 0] : 0xFFFFu - (ent[j] & 0xFFFFu); };
 
+    if (ASYM && __builtin_expect(t_lo == 1u, 0)) {   // the rule bounds nothing (fewer non-zeros than k): the smallest kept key does
+        u32 low = 0;
+#pragma unroll
+        for (int j = 0; j < kWgSlots; ++j)
+            if ((u32)(j * kWgWaves + (int)wv) * kWave + lane < nL) low = max(low, 0x7FFFFFFFu - ent_key(j));
+        low = wave_max_dpp(low);
+        if (lane == 0) misc[48 + wv] = low;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NW; ++i) low = max(low, misc[48 + i]);
+        t_lo = 0x7FFFFFFFu - low;
+    }
+
     // ---- 3. fine bins: 1024 bins linear in (key - t_lo) >> sh, both classes packed 11 + 11 bits --------
     const u32 range = kmax > t_lo ? kmax - t_lo : 0u;
     const int sh = range < (u32)kFineBins ? 0 : (32 - __clz((int)range)) - 10;
@@ -659,17 +659,18 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
         block_sort<kWgThreads>(L.S, nL, [&](u32 s) -> comp_t {
             return DT == 0 ? ((comp_t)(L.Lent[s] ^ 0x80000000u) << kHiShift) | (comp_t)(u32)~s : (comp_t)s;
         });
-    }
+    } else {
 #pragma unroll
-    for (int j = 0; j < kWgSlots; ++j) {
-        const u32 p = (u32)(j * kWgWaves + (int)wv) * kWave + lane;
-        if (p < nL && !(ASYM && sorted)) {
-            const u32 e = ent[j];
-            const u32 rel = ent_key(j) - t_lo;
-            const u32 old = atomicAdd(&L.hist[rel >> sh], 1u << 22);
-            const u32 at = (old & 0x7FFu) + ((old >> 11) & 0x7FFu) + (old >> 22);
-            if (DT == 0) L.S[at] = ((((rel & inmask) << w) | (idxmask - ent_idx(j))) << 1) | (e >> 31);
-            else L.S[at] = e;
+        for (int j = 0; j < kWgSlots; ++j) {
+            const u32 p = (u32)(j * kWgWaves + (int)wv) * kWave + lane;
+            if (p < nL) {
+                const u32 e = ent[j];
+                const u32 rel = ent_key(j) - t_lo;
+                const u32 old = atomicAdd(&L.hist[rel >> sh], 1u << 22);
+                const u32 at = (old & 0x7FFu) + ((old >> 11) & 0x7FFu) + (old >> 22);
+                if (DT == 0) L.S[at] = ((((rel & inmask) << w) | (idxmask - ent_idx(j))) << 1) | (e >> 31);
+                else L.S[at] = e;
+            }
         }
     }
     __syncthreads();
@@ -751,95 +752,95 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(wg_m
                 thr[lane] = act ? cx : cls ? (comp_t)(kClsBit - 1) : ~(comp_t)0;
             }
         } else {
-        // smallest bin whose first class rank is <= Rk: three probes a step, so five dependent reads instead of ten
-        int lo = 0, len = kFineBins;
-        const u32 csh = cls ? 11u : 0u;
+            // smallest bin whose first class rank is <= Rk: three probes a step, so five dependent reads instead of ten
+            int lo = 0, len = kFineBins;
+            const u32 csh = cls ? 11u : 0u;
 #pragma unroll
-        for (int it = 0; it < 5; ++it) {
-            const int q = len >> 2;
-            const u32 w0 = L.hist[lo + q - 1], w1 = L.hist[lo + 2 * q - 1], w2 = L.hist[lo + 3 * q - 1];
-            const u32 f0 = ((w0 >> csh) & 0x7FFu) > Rk ? 1u : 0u, f1 = ((w1 >> csh) & 0x7FFu) > Rk ? 1u : 0u, f2 = ((w2 >> csh) & 0x7FFu) > Rk ? 1u : 0u;
-            lo += q * (int)(f0 + f1 + f2);           // (first ranks fall as the bins rise)
-            len = q;
-        }
-        const u32 wd = L.hist[lo], wd_low = ASYM ? L.hist[lo ? lo - 1 : 0] : 0u;
-        const u32 pe = wd & 0x7FFu, ne = (wd >> 11) & 0x7FFu;
-        u32 cnt = act ? wd >> 22 : 0u;
-        bool tie = false;                            // the boundary lies among many members of one key
-        if (ASYM && sh == 0) {
-            const u32 nx = lo ? wd_low : n_pos | (n_neg << 11);      // (the fill field of such a bin may have overflown)
-            tie = act && (nx & 0x7FFu) + ((nx >> 11) & 0x7FFu) - pe - ne > kWgTieBin;
-            if (tie) cnt = 0;
-        }
-        const u32 incl = wave_scan_dpp(cnt);
-        if (mine) {                                  // (all wavefronts write the same words)
-            tg_bin[lane] = (u32)lo; tg_base[lane] = pe + ne; tg_cnt[lane] = cnt;
-            tg_rem[lane] = Rk - (cls ? ne : pe);
-            tg_pre[lane] = incl - cnt;
-            if (!act) thr[lane] = cls ? (comp_t)(kClsBit - 1) : ~(comp_t)0;
-        }
-        const u32 npairs = bcast(incl, kWave - 1);
-        wave_sync();
-        for (u32 g = wv * kWave; g < npairs; g += kWgThreads) {
-            const u32 pr = g + lane;
-            if (pr < npairs) {
-                int tl = 0, th = ntg - 1;
-                while (tl < th) {
-                    const int mid = (tl + th + 1) >> 1;
-                    if (tg_pre[mid] <= pr) tl = mid; else th = mid - 1;
-                }
-                const int t = tl;
-                const u32 tc = (u32)(t >= M - 1 ? 1 : 0);
-                const u32 bs = tg_base[t], cn = tg_cnt[t], rem = tg_rem[t], bin = tg_bin[t];
-                const u32 me = L.S[bs + (pr - tg_pre[t])];
-                // one compare per member: with the class bit moved to the top and set for the boundary's
-                // class, "same class and larger comp" is a plain unsigned "larger"
-                const u32 fm = DT == 0 ? (tc ^ 1u) : (tc ? 0u : 0x80000000u);
-                auto key_of = [&](u32 sv) -> u32 {
-                    const u32 xv = sv ^ fm;
-                    return DT == 0 ? __builtin_amdgcn_alignbit(xv, xv, 1) : xv;     // fp32: rotate the class bit up
-                };
-                const u32 mk = key_of(me);
-                u32 gt = 0;
-                for (u32 jj = 0; jj < cn; jj += 4) {
-                    u32 t4[4];
-#pragma unroll
-                    for (u32 u = 0; u < 4; ++u) t4[u] = L.S[bs + (jj + u < cn ? jj + u : 0u)];
-#pragma unroll
-                    for (u32 u = 0; u < 4; ++u) gt += jj + u < cn && key_of(t4[u]) > mk ? 1u : 0u;
-                }
-                if (s_neg(me) == tc && gt == rem) thr[t] = s_cx(me, bin);
+            for (int it = 0; it < 5; ++it) {
+                const int q = len >> 2;
+                const u32 w0 = L.hist[lo + q - 1], w1 = L.hist[lo + 2 * q - 1], w2 = L.hist[lo + 3 * q - 1];
+                const u32 f0 = ((w0 >> csh) & 0x7FFu) > Rk ? 1u : 0u, f1 = ((w1 >> csh) & 0x7FFu) > Rk ? 1u : 0u, f2 = ((w2 >> csh) & 0x7FFu) > Rk ? 1u : 0u;
+                lo += q * (int)(f0 + f1 + f2);           // (first ranks fall as the bins rise)
+                len = q;
             }
-        }
-        if (ASYM && sh == 0) {
-            u32 turn = 0;
-            for (u64 tm = __ballot(tie); __builtin_expect(tm != 0ull, 0); tm &= tm - 1ull, ++turn) {
-                if (turn % (u32)NW != wv) continue;
-                const int t = (int)__builtin_ctzll(tm);
-                const u32 tc = bcast((u32)cls, t), want = (tc << 31) | (((u32)bcast((u32)lo, t) + t_lo) << (DT == 0 ? 0 : 16));
-                u32 left = bcast(Rk - (cls ? ne : pe), t);       // entries of that key and class before it
-                bool done = false;
-                for (u32 p0 = 0; p0 < nL && !done; p0 += 4 * kWave) {
-                    u32 e[4];
+            const u32 wd = L.hist[lo], wd_low = ASYM ? L.hist[lo ? lo - 1 : 0] : 0u;
+            const u32 pe = wd & 0x7FFu, ne = (wd >> 11) & 0x7FFu;
+            u32 cnt = act ? wd >> 22 : 0u;
+            bool tie = false;                            // the boundary lies among many members of one key
+            if (ASYM && sh == 0) {
+                const u32 nx = lo ? wd_low : n_pos | (n_neg << 11);      // (the fill field of such a bin may have overflown)
+                tie = act && (nx & 0x7FFu) + ((nx >> 11) & 0x7FFu) - pe - ne > kWgTieBin;
+                if (tie) cnt = 0;
+            }
+            const u32 incl = wave_scan_dpp(cnt);
+            if (mine) {                                  // (all wavefronts write the same words)
+                tg_bin[lane] = (u32)lo; tg_base[lane] = pe + ne; tg_cnt[lane] = cnt;
+                tg_rem[lane] = Rk - (cls ? ne : pe);
+                tg_pre[lane] = incl - cnt;
+                if (!act) thr[lane] = cls ? (comp_t)(kClsBit - 1) : ~(comp_t)0;
+            }
+            const u32 npairs = bcast(incl, kWave - 1);
+            wave_sync();
+            for (u32 g = wv * kWave; g < npairs; g += kWgThreads) {
+                const u32 pr = g + lane;
+                if (pr < npairs) {
+                    int tl = 0, th = ntg - 1;
+                    while (tl < th) {
+                        const int mid = (tl + th + 1) >> 1;
+                        if (tg_pre[mid] <= pr) tl = mid; else th = mid - 1;
+                    }
+                    const int t = tl;
+                    const u32 tc = (u32)(t >= M - 1 ? 1 : 0);
+                    const u32 bs = tg_base[t], cn = tg_cnt[t], rem = tg_rem[t], bin = tg_bin[t];
+                    const u32 me = L.S[bs + (pr - tg_pre[t])];
+                    // one compare per member: with the class bit moved to the top and set for the boundary's
+                    // class, "same class and larger comp" is a plain unsigned "larger"
+                    const u32 fm = DT == 0 ? (tc ^ 1u) : (tc ? 0u : 0x80000000u);
+                    auto key_of = [&](u32 sv) -> u32 {
+                        const u32 xv = sv ^ fm;
+                        return DT == 0 ? __builtin_amdgcn_alignbit(xv, xv, 1) : xv;     // fp32: rotate the class bit up
+                    };
+                    const u32 mk = key_of(me);
+                    u32 gt = 0;
+                    for (u32 jj = 0; jj < cn; jj += 4) {
+                        u32 t4[4];
 #pragma unroll
-                    for (u32 u = 0; u < 4; ++u) { const u32 p = p0 + u * kWave + lane; e[u] = L.Lent[p < nL ? p : 0u]; }
+                        for (u32 u = 0; u < 4; ++u) t4[u] = L.S[bs + (jj + u < cn ? jj + u : 0u)];
 #pragma unroll
-                    for (u32 u = 0; u < 4; ++u) {
-                        const u32 p = p0 + u * kWave + lane;
-                        const bool in = p < nL && (DT == 0 ? e[u] : e[u] & 0xFFFF0000u) == want;
-                        const u64 m = __ballot(in);
-                        const u32 c = (u32)__popcll(m);
-                        if (!done && left < c) {
-                            if (in && mask_rank(m) == left)
-                                thr[t] = DT == 0 ? ((comp_t)(e[u] ^ 0x80000000u) << kHiShift) | (comp_t)(u32)(~(u32)L.Lidx[DT == 0 ? p : 0u])
-                                                 : (comp_t)(e[u] ^ 0x80000000u);
-                            done = true;
+                        for (u32 u = 0; u < 4; ++u) gt += jj + u < cn && key_of(t4[u]) > mk ? 1u : 0u;
+                    }
+                    if (s_neg(me) == tc && gt == rem) thr[t] = s_cx(me, bin);
+                }
+            }
+            if (ASYM && sh == 0) {
+                u32 turn = 0;
+                for (u64 tm = __ballot(tie); __builtin_expect(tm != 0ull, 0); tm &= tm - 1ull, ++turn) {
+                    if (turn % (u32)NW != wv) continue;
+                    const int t = (int)__builtin_ctzll(tm);
+                    const u32 tc = bcast((u32)cls, t), want = (tc << 31) | (((u32)bcast((u32)lo, t) + t_lo) << (DT == 0 ? 0 : 16));
+                    u32 left = bcast(Rk - (cls ? ne : pe), t);       // entries of that key and class before it
+                    bool done = false;
+                    for (u32 p0 = 0; p0 < nL && !done; p0 += 4 * kWave) {
+                        u32 e[4];
+#pragma unroll
+                        for (u32 u = 0; u < 4; ++u) { const u32 p = p0 + u * kWave + lane; e[u] = L.Lent[p < nL ? p : 0u]; }
+#pragma unroll
+                        for (u32 u = 0; u < 4; ++u) {
+                            const u32 p = p0 + u * kWave + lane;
+                            const bool in = p < nL && (DT == 0 ? e[u] : e[u] & 0xFFFF0000u) == want;
+                            const u64 m = __ballot(in);
+                            const u32 c = (u32)__popcll(m);
+                            if (!done && left < c) {
+                                if (in && mask_rank(m) == left)
+                                    thr[t] = DT == 0 ? ((comp_t)(e[u] ^ 0x80000000u) << kHiShift) | (comp_t)(u32)(~(u32)L.Lidx[DT == 0 ? p : 0u])
+                                                     : (comp_t)(e[u] ^ 0x80000000u);
+                                done = true;
+                            }
+                            left -= done ? 0u : c;
                         }
-                        left -= done ? 0u : c;
                     }
                 }
             }
-        }
         }
     }
     __syncthreads();
