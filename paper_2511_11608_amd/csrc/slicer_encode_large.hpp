@@ -35,12 +35,14 @@
 // index), so that bins can cut through a run of equal bf16 keys.
 #pragma once
 
+#include <algorithm>
+
 #include "slicer_common.hpp"
 #include "slicer_encode_generic.hpp"
 
 namespace slicer {
 
-constexpr int kTileThreads = 512;   // a compact / split workgroup handles a tile of 8192 or 16384 elements
+constexpr int kTileThreads = 512;   // a compact / split workgroup handles a tile of up to 16384 elements
 constexpr int kMaxTab = 510, kTabSize = kMaxTab + 2;        // sample bins with fine bins of their own: 16 octaves above the bound
 // Fine bins per row, a template parameter (FB) of the stages.  A batch of up to 256 rows has a CU for every row and takes the
 // many bins, few members each, and 1024 threads per row where a stage works on whole rows; there a row's latency counts.
@@ -102,6 +104,33 @@ struct LargeArgs {
     int64_t n_rows, n_cols;
     int wp, wc;
 };
+
+// Elements per tile of the long-row stages, a multiple of 512 from 4608 to 16384: 8192 while these do
+// not fill the chip, and in large batches where they leave out a quarter or more of what long tiles would cover (bf16 [4096 x 8192] 461 -> 428 us, fp32
+// [4096 x 20480] 529 -> 510; with a sixth left out the added tiles cost more: bf16 [4096 x 33001] 758 -> 826).  Between the two as many tiles as
+// can run at once, four a CU, but no more than tiles of 8192 would be.  Rows of many tiles are cut so that every CU has as many as
+// the next one: fp32 [32 x 401408], 32 tiles a row, 120.5 us, with 49 tiles 126.0, with 25 134.7; [16 x 401408] 32 tiles 84.5 us, 49 92,
+// 25 97; [4 x 401408] 64 tiles 61.6, 49 65.2 (rows of few tiles gain less by it than they lose: [32 x 100352] 8 tiles 58.5, 13 54.3).  A
+// row has at most 128 tiles where these are no longer than 16384: one workgroup adds up their tables ([1 x 2000000] 245 tiles
+// 89 us, 128 76).
+inline int large_tile(int64_t rows, int64_t row_len)
+{
+    const int64_t n8 = (row_len + 8191) / 8192, n16 = (row_len + 16383) / 16384;
+    auto of = [&](int64_t S) { return (int)((row_len + 512 * S - 1) / (512 * S) * 512); };
+    if (rows > kScanRows) return n8 == 1 || n8 == 3 ? 8192 : of(n16);
+    const int64_t most = std::max<int64_t>(128, n16);
+    auto even = [&](int64_t per_cu, int64_t shortest) {          // tiles of a row where every CU has per_cu of them; 0: they would be too short, too long or few
+        const int64_t S = 256 * per_cu / rows;
+        return S >= 24 && S <= most && of(S) >= shortest && of(S) <= 16384 ? S : 0;
+    };
+    if (const int64_t S = even(4, 8192)) return of(S);
+    if (const int64_t S = even(2, 8192)) return of(S);
+    if (rows * n8 <= 256) {
+        if (const int64_t S = even(1, 6144)) return of(S);       // (below the 8192 that the workspace's tables are sized for)
+        return n8 <= most ? 8192 : of(most);
+    }
+    return of(std::max(n16, std::min({1024 / rows, n8, most})));
+}
 
 constexpr int kLrEntries = 640;      // room for a wavefront's entries in the compact stage
 

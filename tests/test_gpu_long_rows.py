@@ -46,7 +46,7 @@ def test_large_batches(oracle, dtype, rows, N, keep, M):
 
 @pytest.mark.parametrize("dtype,shift", [("f32", 0), ("f32", 1), ("bf16", 0), ("bf16", 7)])
 def test_longest_rows(oracle, dtype, shift):
-    """2^23 elements: 512 tiles, 513 when the row starts inside a 16-byte chunk."""
+    """2^23 elements: 512 tiles, wherever the row starts in its first 16 bytes."""
     import torch
     from paper_2511_11608_amd import binding
     from paper_2511_11608_amd.devmem import to_device
