@@ -10,7 +10,8 @@
 //             list positions arranged by fine bin
 //   bounds    per row, by up to eight workgroups: the tiles' histograms are summed; the top-K cut (ATKF, Sec. 3.1) and the first and last
 //             element of every block (MS, Sec. 3.2) are order statistics whose fine bin is found in the sums and
-//             which are resolved among the few members of that bin; rows that do not fit are redone here by the generic encoder
+//             which are resolved among the few members of that bin, or by a sort of a bin of many; rows that do not fit are redone by the
+//             generic encoder, in the row's last workgroup to find that out
 //   split     per tile: block of every entry, stable split by block (ascending index inside a block), integer
 //             ABQ sums (Sec. 3.2.1); the last workgroup of a row chooses the bitwidths and bit offsets
 //   pack      one window of stream words per workgroup, written straight to its place in the stream when
@@ -26,8 +27,9 @@
 // per tile, written once.  Inside a stage the lanes' LDS lookups are written as straight-line code for several
 // entries at once: behind branches they wait for each other (split kernel 68 -> 41 us on 32 maps of 401408 at the time, together with four instead of
 // eight entries per thread, which spill nothing, and the choice of the guard taken outside the entry loop).
-// Measured (us, fp32 [1 x 200704] and [32 x 401408] keep 0.2, 16 + 16 blocks): sample 6 and 10, compact 6 and 21.5, bounds 12 and 19,
-// split 14 and 37, pack 6 and 22; the calls 43.7 and 113, with CSR blocks and decode 143.  Before the changes that the stages' comments name: sample 9.5 and
+// Measured (us, fp32 [1 x 200704] and [32 x 401408] keep 0.2, 16 + 16 blocks; every step on inputs that no cache holds): sample 12.4 and 14.9,
+// compact 6.5 and 21.6, bounds 11.3 and 17.8, split 14.0 and 36.2, pack 6.3 and 22.4.  Where the row is in a cache the sample takes 6 and 10; the
+// calls then take 43.1 and 111.7, with CSR blocks and decode 142.  Before the changes that the stages' comments name (in a cache): sample 9.5 and
 // 13, compact 6 and 29, bounds 15.7 and 24, split 15 and 41; the calls 53 and 135, with CSR blocks and decode 165.
 //
 // Order: comp = key << w | (2^w - 1 - index): larger comp = larger magnitude, then lower index.  c32 is
