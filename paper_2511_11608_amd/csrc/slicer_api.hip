@@ -251,7 +251,7 @@ hipError_t launch_small_any(const SmallArgs& sa, const SmallLaunch& p, bool asym
 template <int DT, int FB>
 void launch_large_stages(const LargeArgs& la, const EncArgs& ea, const FinishArgs& fa, hipStream_t st)
 {
-    const dim3 gT((unsigned)la.S, (unsigned)la.R), gR((unsigned)la.R), gB((unsigned)(la.R * la.parts)), gW((unsigned)la.nwin, (unsigned)la.R), bT(kTileThreads);
+    const dim3 gT((unsigned)la.S, (unsigned)la.R), gR((unsigned)la.R), gB((unsigned)(la.part_step * la.parts)), gW((unsigned)la.nwin, (unsigned)la.R), bT(kTileThreads);
     const dim3 bR((unsigned)lr_row_threads(FB));
     hipLaunchKernelGGL((lr_sample_kernel<DT, FB>), gR, bR, 0, st, la);
     if (la.dense) {
@@ -507,6 +507,9 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
         la.capL = p.large_capL;
         // workgroups that share a row in the bounds stage: as many as there are CUs for
         la.parts = rows <= 32 ? 8 : rows <= 64 ? 4 : rows <= 128 ? 2 : 1;
+        // a row's workgroups on one XCD, rows on one after the other: its L2 serves their tables, and where a row is redone the row (five
+        // rows of 597761 that are: 1897 us where their last workgroups ran, two of them on one XCD, 1390 now; [3 x 401408] 60.4 -> 56.7)
+        la.part_step = la.parts == 1 || rows == 1 ? (int)rows : (int)((rows + 7) / 8 * 8);
         lr_sample_plan(la, p.large_fb, epc);
         la.n_rows = csr ? csr->n_rows : 0; la.n_cols = csr ? csr->n_cols : 0;
         la.wp = csr ? csr->wp : 0; la.wc = csr ? csr->wc : 0;

@@ -70,7 +70,8 @@ struct LargeArgs {
     float sample_scale;
     int tile, S;            // elements of a tile, tiles per row
     bool dense;             // most wavefronts of the compact stage have more entries than kLrEntries
-    int parts;              // workgroups that share a row in the bounds stage
+    int parts;              // workgroups that share a row in the bounds stage,
+    int part_step;          // and how far apart they are in its grid
     u32 capL;               // list capacity per row
     uint16_t* tab;          // [R][kTabSize]  first fine bin of a sample bin | log2 of its number of fine bins << 12; one guard at either end
     u32* cum;               // [R][S][FB]     entries of the tile at or above the bin: positive | negative << 16
@@ -691,10 +692,10 @@ __global__ __launch_bounds__(lr_row_threads(FB)) void lr_bounds_kernel(LargeArgs
     const int tid = threadIdx.x, w = a.w, M = a.M, Mn = a.Mn, B2 = M + Mn, S = a.S;
     // P workgroups share a row: all of them sum the tables and find the bins, each resolves its share of these.  A bin's members lie one or two
     // to a cache line, a thousand lines and more for a row, at the end of three dependent loads: one workgroup of fp32 [32 x 401408] took
-    // 18 us to gather and compare them, eight take 5.  (A row's workgroups are R apart in the grid: on one XCD when R is a
-    // multiple of eight, so that its L2 serves the tables.)
-    const int P = a.parts, part = (int)(blockIdx.x / (u32)a.R);
-    const int64_t r = blockIdx.x % (u32)a.R;
+    // 18 us to gather and compare them, eight take 5.
+    const int P = a.parts, part = (int)(blockIdx.x / (u32)a.part_step);
+    const int64_t r = blockIdx.x % (u32)a.part_step;
+    if (r >= a.R) return;
     u32* st = a.rowst + (size_t)r * 16;
     const u32 k = (u32)a.k;
     const u32* __restrict__ cum = a.cum + (size_t)r * S * FB;

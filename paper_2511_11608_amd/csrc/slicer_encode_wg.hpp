@@ -98,7 +98,7 @@ __device__ inline WgLds wg_carve(u32* base, int dt, int cap, int region0, int B2
 constexpr u32 kWgTieBin = 64, kWgSortBin = 256;
 
 // wavefronts per SIMD the register allocator must leave room for (same rule as the one-wavefront kernel; eight where a word or two of
-// scalar registers would cost the eighth: bf16 [8000 x 8192] keep 0.05, lambda = 0.1, 167 us with seven, 158 with eight)
+// scalar registers would cost the eighth: bf16 [8000 x 8192] keep 0.05, lambda = 0.1, 167 us with seven, 156 with eight)
 constexpr int wg_min_waves(int dt, int nw, int ept, int nq, bool asym)
 {
     const int row_regs = dt == 0 ? ept : ept / 2;
