@@ -423,11 +423,11 @@ static int encode_impl(const void* x, slicer_dtype dt, int64_t rows, int64_t row
 
     // asymmetric thresholds need a second selection over a subset of the row: the row-resident kernels have it for every row that
     // they hold, the generic kernel for every shape.  One wavefront takes long for two selections over a row of more than 4096 elements, so
-    // the workgroup has all of these but the narrower ones, and those whose list one wavefront has in registers, of large batches.  Encode
-    // us, wavefront / workgroup, lambda = 0.1, 8 + 8 blocks: bf16 [1 x 8192] 42 / 23, [256 x 8192] 49 / 29, [300 x 4160] 39 / 27, [4000 x 8192]
-    // 101 / 88 (409 kept), [8000 x 8192] 275 / 194 (1228 kept), [8903 x 6144] 169 / 167; but [13000 x 4160] 195 / 210, and [8000 x 8192] 156 / 156
-    // (409 kept), 239 / 270 where the values are multiples of 1/8.
-    const bool one_wave = asym ? p.small_epl && rows > 4096 && (row_len <= 6144 || p.small_maxs) : p.one_wave;
+    // the workgroup has all of these but, of large batches, the narrower ones with short lists and the longer ones whose list one wavefront has in
+    // registers.  Encode us, wavefront / workgroup, lambda = 0.1, 8 + 8 blocks: bf16 [1 x 8192] 42 / 23, [256 x 8192] 49 / 29, [300 x 4160] 39 / 27,
+    // [4000 x 8192] 101 / 88 (409 kept), [8000 x 8192] 275 / 194 (1228 kept), [5040 x 5952] 118 / 115 (595 kept); but [13000 x 4160] 195 / 210, and
+    // [8000 x 8192] 156 / 156 (409 kept), 239 / 270 where the values are multiples of 1/8.
+    const bool one_wave = asym ? rows > 4096 && (row_len <= 6144 ? p.one_wave : p.small_epl && p.small_maxs) : p.one_wave;
     const bool use_wg = p.wg_ept && on_elements && !one_wave;
     if (use_wg) {
         // one workgroup per row; rows it cannot hold are flagged and redone by the generic kernel
